@@ -1094,7 +1094,123 @@ __device__ __forceinline__ bool gather_fast(const MergeArgs& a, const Cand* part
     return true;
 }
 
-// General path: radix select over all entries of all lists (candidates are distinct, so the
+// Wide path (kprime above 64: every list holds 128 entries, best first).  A first cut is taken from
+// the heads (block_bucket_cut: at least kprime of them pass, so at least kprime candidates do), the
+// lists whose head passes are walked 16 entries at a time while their last entry read still passes,
+// and what passes is pooled.  When the best rows sit in few lists the kprime-th largest head is a
+// loose cut and the pool overflows; any kPoolCap entries that were pooled then give a tighter cut
+// and the walk starts over.  A pool of more than 512 is narrowed once more, and every pooled
+// candidate counts those ahead of it: the first kprime take their places.
+// What bounds it: one workgroup, a handful of dependent L2 reads and barriers.  (The radix select
+// over all entries reads 2 MB up to ten times from one compute unit: 494 us at 2048 lists against
+// 29 us here, k 100 on 4 M x 768 fp16 rows.)
+// Returns false (for the whole workgroup) when the lists do not fit or masses of equal keys keep
+// overflowing the pool.
+constexpr int kWideLists = 2048;           // lists the wide path can visit: all of one query's scan wavefronts
+constexpr int kWideRounds = 4;             // cuts tried before the radix select takes over
+__device__ __forceinline__ bool gather_wide(const MergeArgs& a, const Cand* part, const Cand* heads, MergeLds& L,
+                                            Cand* pool, uint16_t* alive) {
+    const int tid = threadIdx.x, nt = blockDim.x, lane = lane_id();
+    const int np = a.nparts, slots = a.list_len;
+    const uint32_t kp = (uint32_t)a.kprime;
+    if (np > kWideLists) return false;
+    const Cand h0 = tid < np ? heads[tid] : (Cand)0;
+    const Cand h1 = tid + nt < np ? heads[tid + nt] : (Cand)0;
+    auto head_key = [&](uint32_t l) -> uint32_t { return (uint32_t)((l == (uint32_t)tid ? h0 : l == (uint32_t)(tid + nt) ? h1 : heads[l]) >> 32); };
+    auto pool_key = [&](uint32_t i) -> uint32_t { return (uint32_t)(pool[i] >> 32); };
+    // appends c of every lane with ok to the pool; entries past the end are counted, not stored
+    auto append = [&](Cand c, bool ok) {
+        const uint64_t b = __ballot(ok);
+        if (!b) return;
+        uint32_t base = 0;
+        if (lane == 0) base = atomicAdd(&L.sh[4], (uint32_t)__popcll(b));
+        base = read_lane(base, 0);
+        const uint32_t pos = base + __popcll(b & ((1ull << lane) - 1ull));
+        if (ok && pos < (uint32_t)kMergeCandCap) pool[pos] = c;
+    };
+    BucketCut bc = block_bucket_cut(head_key, (uint32_t)np, kp, L.hist, L.gmax);
+    uint32_t cnt = 0;
+#pragma unroll 1
+    for (int round = 0;; ++round) {
+        __syncthreads();                       // the cut has been read by everyone
+        if (tid == 0) { L.sh[4] = 0; L.sh[5] = 0; }
+        __syncthreads();
+#pragma unroll 1
+        for (int l = tid; l < np; l += nt) {
+            const uint32_t key = head_key((uint32_t)l);
+            if (key != 0 && bc.pass(key)) alive[atomicAdd(&L.sh[5], 1u)] = (uint16_t)l;
+        }
+        __syncthreads();
+        uint32_t na = L.sh[5];
+        uint16_t* cur = alive;
+        uint16_t* nxt = alive + kWideLists;
+#pragma unroll 1
+        for (int lvl = 0; lvl < slots && na; lvl += 16) {
+            __syncthreads();                   // the count of this level has been read
+            if (tid == 0) L.sh[5] = 0;
+            __syncthreads();
+            const uint32_t total = na * 16;
+#pragma unroll 1
+            for (uint32_t e0 = 0; e0 < total; e0 += 2 * nt) {
+                Cand c[2]; uint32_t l[2];
+#pragma unroll
+                for (int u = 0; u < 2; ++u) {
+                    const uint32_t e = e0 + u * nt + tid;
+                    l[u] = cur[min(e, total - 1) / 16];
+                    c[u] = e < total ? part[(size_t)l[u] * slots + lvl + e % 16] : (Cand)0;
+                }
+#pragma unroll
+                for (int u = 0; u < 2; ++u) {
+                    const bool ok = c[u] != 0 && bc.pass((uint32_t)(c[u] >> 32));
+                    if (ok && (tid & 15) == 15) nxt[atomicAdd(&L.sh[5], 1u)] = (uint16_t)l[u];
+                    append(c[u], ok);
+                }
+            }
+            __syncthreads();
+            na = L.sh[5];
+            uint16_t* t = cur; cur = nxt; nxt = t;
+        }
+        __syncthreads();
+        cnt = L.sh[4];
+        if (cnt <= (uint32_t)kMergeCandCap) break;
+        if (round == kWideRounds - 1) return false;
+        bc = block_bucket_cut(pool_key, (uint32_t)kMergeCandCap, kp, L.hist, L.gmax);
+    }
+    if (cnt > 512) {
+        // kMergeCandCap / kMergeFastThreads entries per thread stay in registers while the pool is rebuilt
+        bc = block_bucket_cut(pool_key, cnt, kp, L.hist, L.gmax);
+        Cand mine[kMergeCandCap / kMergeFastThreads];
+#pragma unroll
+        for (int u = 0; u < kMergeCandCap / kMergeFastThreads; ++u) mine[u] = (uint32_t)(tid + u * nt) < cnt ? pool[tid + u * nt] : (Cand)0;
+        __syncthreads();
+        if (tid == 0) L.sh[4] = 0;
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < kMergeCandCap / kMergeFastThreads; ++u) append(mine[u], mine[u] != 0 && bc.pass((uint32_t)(mine[u] >> 32)));
+        __syncthreads();
+        cnt = L.sh[4];
+    }
+#pragma unroll 1
+    for (uint32_t t = tid; t < cnt; t += nt) {
+        const Cand me = pool[t];
+        uint32_t rank = 0;
+#pragma unroll 1
+        for (uint32_t j0 = 0; j0 < cnt; j0 += 8) {
+            Cand o[8];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) o[u] = pool[min(j0 + u, cnt - 1)];
+#pragma unroll
+            for (int u = 0; u < 8; ++u) rank += (uint32_t)((o[u] > me) & (j0 + u < cnt));
+        }
+        if (rank < kp) L.c_cand[rank] = me;
+    }
+    __syncthreads();
+    if (tid == 0) L.sh[4] = min(cnt, kp);
+    __syncthreads();
+    return true;
+}
+
+// Last resort: radix select over all entries of all lists (candidates are distinct, so the
 // selection ends with exactly kprime of them).
 __device__ __forceinline__ void gather_radix(const MergeArgs& a, const Cand* part, MergeLds& L) {
     const int tid = threadIdx.x, nt = blockDim.x, lane = lane_id();
@@ -1142,7 +1258,10 @@ __device__ __forceinline__ bool result_is_safe(double s_k, float f_last, const M
     return s_k > (double)f_last + (double)e;
 }
 
-__global__ __launch_bounds__(kSelectThreads) void merge_kernel(MergeArgs a, int fast) {
+// WIDE: kprime above 64 (see gather_wide), else gather_fast; two kernels, so that neither carries
+// the code of the other (a workgroup that runs alone pays for the code it fetches).
+template <bool WIDE>
+__global__ __launch_bounds__(kMergeFastThreads) void merge_kernel(MergeArgs a) {
     extern __shared__ __align__(16) unsigned char m_dyn[];
     __shared__ MergeLds L;
     __shared__ double q_part[kSelectThreads / 64];
@@ -1165,11 +1284,10 @@ __global__ __launch_bounds__(kSelectThreads) void merge_kernel(MergeArgs a, int 
     }
 
     // 1. the kprime best fp32 candidates
-    bool gathered = false;
-    if (fast) {
-        Cand* pool = (Cand*)m_dyn;
-        gathered = gather_fast(a, part, a.heads + (size_t)qi * a.nparts, L, pool, (uint32_t*)(pool + kMergeCandCap));
-    }
+    Cand* pool = (Cand*)m_dyn;
+    const Cand* heads = a.heads + (size_t)qi * a.nparts;
+    const bool gathered = WIDE ? gather_wide(a, part, heads, L, pool, (uint16_t*)(pool + kMergeCandCap))
+                               : gather_fast(a, part, heads, L, pool, (uint32_t*)(pool + kMergeCandCap));
     if (__builtin_expect(!gathered, 0)) {
         __syncthreads();
         gather_radix(a, part, L);
@@ -1429,11 +1547,9 @@ hipError_t launch_redo(const RedoArgs& a, int grid, hipStream_t s) {
 
 hipError_t launch_merge(const MergeArgs& a, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
     if (a.done && a.nq != 1) return hipErrorInvalidValue;
-    const size_t n = (size_t)a.nparts * a.list_len;
-    const int fast = a.kprime <= 64;
-    const int threads = fast ? kMergeFastThreads : (n <= 8192 ? 256 : kSelectThreads);
-    const size_t lds = fast ? (size_t)kMergeCandCap * 8 + (size_t)kMergeQlistCap * 4 : 0;
-    IVF_LAUNCH(merge_kernel, dim3(a.nq), dim3(threads), lds, s, e0, e1, a, fast);
+    const size_t pool = (size_t)kMergeCandCap * sizeof(uint64_t);
+    if (a.kprime > 64) IVF_LAUNCH(merge_kernel<true>, dim3(a.nq), dim3(kMergeFastThreads), pool + 2 * kWideLists * sizeof(uint16_t), s, e0, e1, a);
+    else IVF_LAUNCH(merge_kernel<false>, dim3(a.nq), dim3(kMergeFastThreads), pool + kMergeQlistCap * sizeof(uint32_t), s, e0, e1, a);
     return hipGetLastError();
 }
 

@@ -1,0 +1,48 @@
+"""Kernel variants that a rule on sizes selects, at the sizes where they can go wrong."""
+import numpy as np
+import pytest
+import torch
+
+import oracle as O
+import paper_2502_20969_amd as P
+from parity import check_topk, stored
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def streams():
+    assert torch.cuda.is_available()
+    return torch.cuda.Stream(), torch.cuda.Stream()
+
+
+@pytest.mark.parametrize("k", [57, 64, 112])
+@pytest.mark.parametrize("n,layout", [(130, "random"), (9000, "random"), (60000, "random"), (60000, "best_first"),
+                                      (60000, "best_in_two_lists"), (60000, "equal")])
+def test_merge_of_wide_lists(streams, k, n, layout):
+    """More than 56 results: the merge cuts by the heads of the wavefronts' lists.  best_first and
+    best_in_two_lists put all good rows into few lists, so that the first cut lets more pass than
+    the pool holds; with masses of equal scores no cut helps and the radix select takes over."""
+    rng = np.random.default_rng(k + n)
+    d, nlist = 16, 70                       # more than 64 lists: contiguous shares per wavefront
+    score = rng.permutation(n).astype(np.float32) / n
+    if layout == "best_first":
+        score = -np.sort(-score)
+    elif layout == "best_in_two_lists":
+        score[n // 2:n // 2 + 6000] += 2.0
+    elif layout == "equal":
+        score[rng.permutation(n)[:30000]] = 2.0
+    rows = np.zeros((n, d), np.float32)
+    rows[:, 0] = score
+    assign = (np.arange(n) * nlist // n).astype(np.int32)
+    cent = 0.01 * rng.standard_normal((nlist, d)).astype(np.float32)
+    ids = rng.permutation(n).astype(np.int64) * 3
+    index = P.ivf_build_layout(rows, "f32", cent, assign, ids=ids, compute_stream=streams[0], copy_stream=streams[1])
+    off, perm = O.build_layout(assign, nlist)
+    q = np.zeros((1, d), np.float32)
+    q[0, 0] = 1.0
+    gi, gd = index.ivf_search(q, nlist, k)
+    oi, osc = O.search(rows[perm], O.F32, off, ids[perm], cent, q[0], nlist, k, O.IP)
+    assert list(gi[0]) == list(oi)
+    np.testing.assert_array_equal(gd[0], osc.astype(np.float32))
+    index.close()
