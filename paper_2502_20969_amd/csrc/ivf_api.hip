@@ -1264,22 +1264,23 @@ extern "C" int ivf_schedule(ivf_index* ix, const float* q, int32_t nq, int32_t m
     if (nq > kScheduleMaxQueries) return fail(IVF_ELIMIT, "at most %d queries per global batch", kScheduleMaxQueries);
     int rc = settle_on_lane0(ix);
     if (rc) return rc;
-    float* d_q = nullptr; double* d_dist = nullptr; int32_t* d_order = nullptr;
+    float* d_q = nullptr; double* d_dist = nullptr; uint16_t* d_near = nullptr; int32_t* d_order = nullptr;
     hipEvent_t e0 = nullptr, e1 = nullptr;
     auto cleanup = [&]() {
-        dfree(d_q); dfree(d_dist); dfree(d_order);
+        dfree(d_q); dfree(d_dist); dfree(d_near); dfree(d_order);
         if (e0) (void)hipEventDestroy(e0);
         if (e1) (void)hipEventDestroy(e1);
     };
 #define SCHED_TRY(call) do { hipError_t e_ = (call); if (e_ != hipSuccess) { cleanup(); return fail(IVF_EHIP, "%s: %s", #call, hipGetErrorString(e_)); } } while (0)
     SCHED_TRY(hipMalloc(&d_q, (size_t)nq * ix->d * sizeof(float)));
     SCHED_TRY(hipMalloc(&d_dist, (size_t)nq * nq * sizeof(double)));
+    SCHED_TRY(hipMalloc(&d_near, (size_t)nq * schedule_near_stride(nq) * sizeof(uint16_t)));
     SCHED_TRY(hipMalloc(&d_order, (size_t)nq * sizeof(int32_t)));
     SCHED_TRY(hipEventCreate(&e0));
     SCHED_TRY(hipEventCreate(&e1));
     SCHED_TRY(hipMemcpyAsync(d_q, q, (size_t)nq * ix->d * sizeof(float), hipMemcpyHostToDevice, ix->cs));
     SCHED_TRY(hipEventRecord(e0, ix->cs));
-    SCHED_TRY(launch_schedule(d_q, nq, ix->d, micro, d_dist, d_order, ix->cs));
+    SCHED_TRY(launch_schedule(d_q, nq, ix->d, micro, d_dist, d_near, d_order, ix->cs));
     SCHED_TRY(hipEventRecord(e1, ix->cs));
     SCHED_TRY(hipMemcpyAsync(order, d_order, (size_t)nq * sizeof(int32_t), hipMemcpyDeviceToHost, ix->cs));
     SCHED_TRY(hipStreamSynchronize(ix->cs));

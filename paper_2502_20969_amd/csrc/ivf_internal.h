@@ -152,8 +152,10 @@ hipError_t launch_cache_admit(float* hot, uint32_t* used, const int64_t* res_off
                               hipStream_t s);
 hipError_t launch_cache_round(float* hot, uint32_t* used, int nlist, float decay, float h_inc, hipStream_t s);
 
-// prefetching scheduler (ivf_sched.hip): pairwise squared L2 distances [B x B] and the greedy grouping
-hipError_t launch_schedule(const float* q_dev, int B, int d, int m, double* dist, int32_t* order, hipStream_t s);
+// prefetching scheduler (ivf_sched.hip): pairwise squared L2 distances [B x B], every query's others in
+// order of distance [B x schedule_near_stride(B)] and the greedy grouping
+size_t schedule_near_stride(int B);
+hipError_t launch_schedule(const float* q_dev, int B, int d, int m, double* dist, uint16_t* near, int32_t* order, hipStream_t s);
 constexpr int kScheduleMaxQueries = 4096;
 
 // ---- batched (list-major) search: ivf_batched.hip ------------------------------------------------

@@ -1,111 +1,207 @@
 // Prefetching scheduler (TeleRAG, arxiv 2502.20969, Sec. 4.2 "Scheduling optimization for
 // prefetching"): the queries of a global batch are grouped into micro-batches by a greedy search on
 // squared L2 distance, so that the queries of one micro-batch want largely the same clusters.
-// Two kernels: all pairwise distances, then the greedy pick.
+// Three kernels: all pairwise distances, every query's others in order of distance, then the greedy pick.
 #include "ivf_device.h"
+#include <algorithm>
 
 namespace ivf {
 using namespace dev;
 
-// D[i][j] = sum over t of (q[i][t] - q[j][t])^2 in fp64, added term by term in index order with
-// separately rounded multiply and add: the greedy pick compares these values, and a fixed order
-// of operations makes its decisions reproducible down to exact ties.
-// One workgroup per 16 x 16 tile of pairs; slabs of 64 components go through LDS.
+// D[i][j] = sum over t of (q[i][t] - q[j][t])^2 in fp64, added term by term in index order: the
+// greedy pick compares these values, and a fixed order of operations makes its decisions
+// reproducible down to exact ties.  (x - y)^2 and (y - x)^2 are
+// the same value, so only the tiles on and above the diagonal are computed and stored twice.
+// One workgroup per 16 x 16 tile of pairs; slabs of 64 components go through LDS, widened to
+// double on the way in (once per tile instead of once per pair), the next slab requested while one
+// is worked on.  Bound by LDS latency and fp64 issue: 55 -> 35 us for 512 queries x 768 (without
+// the reads ahead inside a slab 54 us).
 constexpr int kPairTile = 16, kPairSlab = 64;
 
 __global__ __launch_bounds__(256) void pair_dist_kernel(const float* q, int B, int d, double* D) {
-    __shared__ float sa[kPairTile][kPairSlab + 1];
-    __shared__ float sb[kPairTile][kPairSlab + 1];
+    __shared__ __align__(16) double sa[kPairTile][kPairSlab + 2];
+    __shared__ __align__(16) double sb[kPairTile][kPairSlab + 2];
+    if (blockIdx.x < blockIdx.y) return;                   // below the diagonal: stored by the mirrored tile
     const int tid = threadIdx.x;
     const int ti = tid / kPairTile, tj = tid % kPairTile;
     const int i0 = blockIdx.y * kPairTile, j0 = blockIdx.x * kPairTile;
     double acc = 0.0;
-    for (int k0 = 0; k0 < d; k0 += kPairSlab) {
-        for (int e = tid; e < kPairTile * kPairSlab; e += 256) {
-            const int r = e / kPairSlab, t = e % kPairSlab;
+    float va[4], vb[4];                                    // the next slab: on its way while one is worked on
+    auto request = [&](int k0) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int e = tid + u * 256, r = e / kPairSlab, t = e % kPairSlab;
             const bool in_k = k0 + t < d;
-            sa[r][t] = (in_k && i0 + r < B) ? q[(size_t)(i0 + r) * d + k0 + t] : 0.f;
-            sb[r][t] = (in_k && j0 + r < B) ? q[(size_t)(j0 + r) * d + k0 + t] : 0.f;
+            va[u] = (in_k && i0 + r < B) ? q[(size_t)(i0 + r) * d + k0 + t] : 0.f;
+            vb[u] = (in_k && j0 + r < B) ? q[(size_t)(j0 + r) * d + k0 + t] : 0.f;
+        }
+    };
+    request(0);
+    for (int k0 = 0; k0 < d; k0 += kPairSlab) {
+        __syncthreads();                                   // the previous slab has been read
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int e = tid + u * 256;
+            sa[e / kPairSlab][e % kPairSlab] = (double)va[u];
+            sb[e / kPairSlab][e % kPairSlab] = (double)vb[u];
         }
         __syncthreads();
+        if (k0 + kPairSlab < d) request(k0 + kPairSlab);
         const int kn = min(kPairSlab, d - k0);
-        for (int t = 0; t < kn; ++t) {
-            const double df = (double)sa[ti][t] - (double)sb[tj][t];
-            acc = __dadd_rn(acc, __dmul_rn(df, df));
+        if (kn == kPairSlab) {
+            // eight terms are read while the eight before them are added: with two wavefronts per
+            // SIMD nothing else hides the LDS latency
+            double2 xa[2][4], xb[2][4];
+            auto read8 = [&](int t0, double2 (&x)[4], double2 (&y)[4]) {
+#pragma unroll
+                for (int u = 0; u < 4; ++u) { x[u] = *(const double2*)&sa[ti][t0 + 2 * u]; y[u] = *(const double2*)&sb[tj][t0 + 2 * u]; }
+            };
+            read8(0, xa[0], xb[0]);
+#pragma unroll
+            for (int c = 0; c < kPairSlab / 8; ++c) {
+                if (c + 1 < kPairSlab / 8) read8(c * 8 + 8, xa[(c + 1) & 1], xb[(c + 1) & 1]);
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const double d0 = xa[c & 1][u].x - xb[c & 1][u].x, d1 = xa[c & 1][u].y - xb[c & 1][u].y;
+                    acc = __dadd_rn(acc, __dmul_rn(d0, d0));
+                    acc = __dadd_rn(acc, __dmul_rn(d1, d1));
+                }
+            }
+        } else {
+            for (int t = 0; t < kn; ++t) {
+                const double df = sa[ti][t] - sb[tj][t];
+                acc = __dadd_rn(acc, __dmul_rn(df, df));
+            }
         }
-        __syncthreads();
     }
     if (i0 + ti < B && j0 + tj < B) D[(size_t)(i0 + ti) * B + j0 + tj] = acc;
-}
-
-// Greedy pick, one workgroup.  While queries remain: the remaining query of lowest index seeds a
-// micro-batch; the m - 1 remaining queries nearest to it follow, nearest first, equal distances by
-// lower index.  A distance is non-negative, so its bit pattern orders like its value.
-constexpr int kSchedThreads = 1024, kSchedPerThread = 4;      // up to 4096 queries
-
-struct Pick { unsigned long long key; uint32_t idx; };
-__device__ __forceinline__ Pick better(const Pick& a, const Pick& b) {
-    return (b.key < a.key || (b.key == a.key && b.idx < a.idx)) ? b : a;
-}
-
-__global__ __launch_bounds__(kSchedThreads) void greedy_groups_kernel(const double* D, int B, int m, int32_t* order) {
-    __shared__ unsigned char taken[kSchedThreads * kSchedPerThread];
-    __shared__ unsigned long long w_key[kSchedThreads / 64];
-    __shared__ uint32_t w_idx[kSchedThreads / 64];
-    const int tid = threadIdx.x, lane = lane_id(), wave = wave_id();
-    for (int i = tid; i < kSchedThreads * kSchedPerThread; i += kSchedThreads) taken[i] = i < B ? 0 : 1;
+    if (blockIdx.x == blockIdx.y) return;
     __syncthreads();
-    int pos = 0, cursor = 0;
-    while (pos < B) {
-        // the seed: seeds only ever move up, so the search resumes where the last one stopped
-        while (taken[cursor]) ++cursor;            // uniform: every thread walks the same flags
-        const int seed = cursor;
-        __syncthreads();                           // everyone has read the flags
-        if (tid == 0) { taken[seed] = 1; order[pos] = seed; }
-        ++pos;
-        unsigned long long mine[kSchedPerThread];
-#pragma unroll
-        for (int r = 0; r < kSchedPerThread; ++r) {
-            const int j = tid + r * kSchedThreads;
-            mine[r] = j < B ? (unsigned long long)__double_as_longlong(D[(size_t)seed * B + j]) : ~0ull;
-        }
-        __syncthreads();
-        for (int slot = 1; slot < m && pos < B; ++slot) {
-            Pick p{~0ull, 0xFFFFFFFFu};
-#pragma unroll
-            for (int r = 0; r < kSchedPerThread; ++r) {
-                const int j = tid + r * kSchedThreads;
-                if (j < B && !taken[j]) p = better(p, Pick{mine[r], (uint32_t)j});
+    sa[tj][ti] = acc;
+    __syncthreads();
+    if (j0 + ti < B && i0 + tj < B) D[(size_t)(j0 + ti) * B + i0 + tj] = sa[ti][tj];
+}
+
+constexpr int kNearStep = 512;
+
+// near[i] = all queries in the order in which seed i would take them: ascending (distance, index).
+// A distance is non-negative, so its bit pattern orders like its value.  One workgroup per query,
+// a bitonic sort of (bits, index) pairs in LDS over the next power of two.  The sorts of all rows
+// run side by side, so that the greedy pick, which is sequential, only walks lists.
+// A row of near is a multiple of kNearStep entries, so that one wavefront reads kNearStep of them
+// with one 16-byte load per lane; entries past B are 0xFFFF.
+__global__ void sort_near_kernel(const double* D, int B, uint32_t pad, int stride, uint16_t* near) {
+    extern __shared__ __align__(16) unsigned char s_raw[];
+    unsigned long long* key = (unsigned long long*)s_raw;
+    uint16_t* idx = (uint16_t*)(key + pad);
+    const uint32_t tid = threadIdx.x, nt = blockDim.x;
+    const int row = blockIdx.x;
+    for (uint32_t i = tid; i < pad; i += nt) {
+        key[i] = (int)i < B ? (unsigned long long)__double_as_longlong(D[(size_t)row * B + i]) : ~0ull;
+        idx[i] = (int)i < B ? (uint16_t)i : (uint16_t)0xFFFFu;
+    }
+    __syncthreads();
+    for (uint32_t size = 2; size <= pad; size <<= 1) {
+        for (uint32_t st = size >> 1; st > 0; st >>= 1) {
+            for (uint32_t p = tid; p < pad / 2; p += nt) {
+                const uint32_t i = 2 * p - (p & (st - 1)), j = i + st;      // i has bit st clear
+                const unsigned long long ki = key[i], kj = key[j];
+                const uint16_t xi = idx[i], xj = idx[j];
+                const bool i_after_j = ki > kj || (ki == kj && xi > xj);
+                if (i_after_j == ((i & size) == 0)) {
+                    key[i] = kj; key[j] = ki;
+                    idx[i] = xj; idx[j] = xi;
+                }
             }
-#pragma unroll
-            for (int o = 32; o >= 1; o >>= 1) {
-                Pick other;
-                other.key = ((unsigned long long)(uint32_t)__shfl_xor((int)(uint32_t)(p.key >> 32), o) << 32) |
-                            (uint32_t)__shfl_xor((int)(uint32_t)p.key, o);
-                other.idx = (uint32_t)__shfl_xor((int)p.idx, o);
-                p = better(p, other);
-            }
-            if (lane == 0) { w_key[wave] = p.key; w_idx[wave] = p.idx; }
-            __syncthreads();
-            if (tid == 0) {
-                Pick best{w_key[0], w_idx[0]};
-                for (int w = 1; w < kSchedThreads / 64; ++w) best = better(best, Pick{w_key[w], w_idx[w]});
-                taken[best.idx] = 1;
-                order[pos] = (int32_t)best.idx;
-            }
-            ++pos;
             __syncthreads();
         }
     }
+    for (int i = (int)tid; i < stride; i += (int)nt) near[(size_t)row * stride + i] = i < (int)pad ? idx[i] : (uint16_t)0xFFFFu;
 }
 
-hipError_t launch_schedule(const float* q_dev, int B, int d, int m, double* dist, int32_t* order, hipStream_t s) {
-    if (B < 1 || B > kSchedThreads * kSchedPerThread || d < 1 || m < 1) return hipErrorInvalidValue;
+// Greedy pick by one wavefront.  While queries remain: the remaining query of lowest index seeds a
+// micro-batch; the m - 1 remaining queries nearest to it follow, nearest first, equal distances by
+// lower index: the first m - 1 entries of its sorted list that are not taken.  512 entries of the
+// list are looked at per step (eight per lane: free ones counted, a prefix over the lanes gives
+// their places).  A chain of LDS reads per micro-batch bounds it; the list of the query that will
+// most likely seed next is requested one micro-batch ahead, so that memory is not part of the
+// chain.  (Picking one query at a time with a workgroup-wide minimum: 892 us for 512 queries in
+// groups of 8; sort_near_kernel + this: 15 + 67 us.  4096 queries: 8.8 -> 1.3 ms for all three kernels.)
+__global__ __launch_bounds__(64) void greedy_groups_kernel(const uint16_t* near, int B, int stride, int m, int32_t* order) {
+    __shared__ unsigned char taken[kScheduleMaxQueries + 64];
+    const int lane = threadIdx.x;
+    for (int i = lane; i < kScheduleMaxQueries + 64; i += 64) taken[i] = i < B ? 0 : 1;
+    __syncthreads();
+    // lowest remaining query at or above `from`, B when there is none
+    auto lowest_free = [&](int from) -> int {
+        for (; from < B; from += 64) {
+            const uint64_t free_lanes = __ballot(taken[from + lane] == 0);       // past B: taken
+            if (free_lanes) return from + __ffsll((long long)free_lanes) - 1;
+        }
+        return B;
+    };
+    auto fetch = [&](int row, int at) { return *(const uint4*)(near + (size_t)row * stride + at + lane * 8); };
+    int pos = 0, seed = 0;
+    uint4 cur = fetch(0, 0);
+    while (seed < B) {
+        if (lane == 0) { taken[seed] = 1; order[pos] = seed; }
+        __syncthreads();
+        ++pos;
+        const int guess = lowest_free(seed + 1);
+        uint4 ahead = cur;
+        if (guess < B) ahead = fetch(guess, 0);
+        int need = min(m - 1, B - pos);
+        for (int at = 0; need > 0 && at < stride; at += kNearStep) {
+            const uint4 v = at == 0 ? cur : fetch(seed, at);
+            const uint32_t w[4] = {v.x, v.y, v.z, v.w};
+            uint32_t x[8], is_free = 0;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) x[e] = (w[e >> 1] >> (16 * (e & 1))) & 0xFFFFu;
+            unsigned char t[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) t[e] = taken[min(x[e], (uint32_t)kScheduleMaxQueries)];      // 0xFFFF: reads as taken
+#pragma unroll
+            for (int e = 0; e < 8; ++e) is_free |= (uint32_t)(t[e] == 0) << e;
+            const int mine = __popc(is_free);
+            int before = mine;                              // free entries in this lane and all lower ones
+#pragma unroll
+            for (int o = 1; o < 64; o <<= 1) {
+                const int up = __shfl_up(before, o);
+                if (lane >= o) before += up;
+            }
+            const int total = __builtin_amdgcn_readlane(before, 63);
+            int rank = before - mine;
+#pragma unroll
+            for (int e = 0; e < 8; ++e) {
+                if ((is_free >> e) & 1u) {
+                    if (rank < need) { taken[x[e]] = 1; order[pos + rank] = (int32_t)x[e]; }
+                    ++rank;
+                }
+            }
+            const int got = min(total, need);
+            pos += got;
+            need -= got;
+            __syncthreads();
+        }
+        const int next = lowest_free(seed + 1);
+        cur = next == guess || next >= B ? ahead : fetch(next, 0);
+        seed = next;
+    }
+}
+
+size_t schedule_near_stride(int B) { return (size_t)((B + kNearStep - 1) / kNearStep) * kNearStep; }
+
+hipError_t launch_schedule(const float* q_dev, int B, int d, int m, double* dist, uint16_t* near, int32_t* order, hipStream_t s) {
+    if (B < 1 || B > kScheduleMaxQueries || d < 1 || m < 1) return hipErrorInvalidValue;
     const int tiles = (B + kPairTile - 1) / kPairTile;
     hipLaunchKernelGGL(pair_dist_kernel, dim3(tiles, tiles), dim3(256), 0, s, q_dev, B, d, dist);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(greedy_groups_kernel, dim3(1), dim3(kSchedThreads), 0, s, dist, B, m, order);
+    uint32_t pad = 64;
+    while (pad < (uint32_t)B) pad <<= 1;
+    const unsigned threads = std::min<uint32_t>(1024, std::max<uint32_t>(64, pad / 2));
+    const int stride = (int)schedule_near_stride(B);
+    hipLaunchKernelGGL(sort_near_kernel, dim3(B), dim3(threads), (size_t)pad * 10, s, dist, B, pad, stride, near);
+    hipLaunchKernelGGL(greedy_groups_kernel, dim3(1), dim3(64), 0, s, near, B, stride, m, order);
     return hipGetLastError();
 }
 

@@ -46,3 +46,19 @@ def test_merge_of_wide_lists(streams, k, n, layout):
     assert list(gi[0]) == list(oi)
     np.testing.assert_array_equal(gd[0], osc.astype(np.float32))
     index.close()
+
+
+@pytest.mark.parametrize("B,d,micro", [(2, 64, 2), (16, 65, 3), (17, 128, 16), (511, 64, 9), (512, 3, 512), (513, 130, 8),
+                                       (1025, 64, 600), (4096, 4, 17)])
+def test_scheduler_walks_sorted_lists(streams, B, d, micro):
+    """Edges of the scheduler's tiles (16 queries, 64 components), of its sorted lists (a power of
+    two, steps of 512 entries) and groups that need more than one step; half the queries are
+    duplicates of others, so that equal distances are common."""
+    rng = np.random.default_rng(B + d)
+    q = rng.standard_normal((B, d)).astype(np.float32)
+    q[rng.permutation(B)[:B // 2]] = q[rng.integers(0, B, B // 2)]
+    rows = torch.zeros(1, d, device="cuda")
+    index = P.ivf_adopt_layout(rows, "f32", np.array([0, 1]), np.zeros((1, d), np.float32), compute_stream=streams[0],
+                               copy_stream=streams[1])
+    assert list(index.ivf_schedule(q, micro)) == list(O.schedule(q, micro))
+    index.close()
