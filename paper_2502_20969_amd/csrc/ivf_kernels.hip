@@ -19,7 +19,10 @@ using namespace dev;
 // at once; HBM-bound on the nlist*d*4 bytes of the centroid matrix, in practice one memory
 // latency.  A batch of queries: a dense contraction Q x C^T on the fp64 matrix cores.
 // =============================================================================================
-constexpr int kCoarseRowMax = 16;          // batches below this use the row kernel
+// Batches below this use the row kernel, which walks the queries one after the other: with 8
+// queries x 4096 x 768 17.7 us against 8.4 on the matrix cores, with 2 7.9 (and with 3 9.9).  Squared
+// L2 keeps the direct sum of squared differences up to 15 queries (the matrix cores need the three norms form).
+constexpr int kCoarseRowMaxIp = 3, kCoarseRowMaxL2 = 16;
 constexpr int kSelectWaveSortMax = 4096;   // select: register sorting path up to this many clusters
 
 __global__ __launch_bounds__(256) void coarse_rows_kernel(CoarseArgs a) {
@@ -69,94 +72,152 @@ __global__ __launch_bounds__(256) void coarse_rows_kernel(CoarseArgs a) {
 
 // Q x C^T with v_mfma_f64_16x16x4_f64.  Operand layout of the instruction: lane l supplies
 // A[i = l % 16][k = l / 16] and B[k = l / 16][j = l % 16]; result register r of lane l is
-// C[i = 4 r + l / 16][j = l % 16].  A workgroup of four wavefronts covers (WQ * 32) queries by
-// ((4 / WQ) * 32) centroids, each wavefront 32 x 32 as 2 x 2 instruction tiles; fp32 operand
-// slabs of 32 k-values go through LDS (rows padded by 4 floats: the 64 lanes of a fragment
-// read then fall on 64 different (bank, half) positions) and are widened on use.  For the
-// squared distance the norms are accumulated beside the products: |q - c|^2 = |q|^2 + |c|^2 - 2 q.c.
+// C[i = 4 r + l / 16][j = l % 16].  The order of the elements inside a dot product is free, so lane
+// (row i, part p) loads the 16 bytes p of each 16-element block of its row straight from memory
+// and the four values feed four instructions: no LDS on the way in.  A workgroup covers QT * 16
+// queries by CT * 16 centroids; its W wavefronts take every W-th 32-element block of the rows (the
+// next block in flight while one is multiplied) and their sums are added through LDS, in order.
+// Why this split: batches are tens of queries, and what bounds them is the length of the chain
+// through the elements, not the matrix cores.  (Tiles of 32 x 128 that walked all elements through
+// LDS slabs, a barrier pair per 32: 52.7, 55.5 and 117 us for 16 queries x 1024 x 768, 32 x 4096 x 768
+// and 256 x 8192 x 1024; this: 8.2, 12.6 and 94; the fp64 matrix peak for the last is 55 us.)
+// Workgroups that follow each other on one XCD share their centroids (blockIdx % 8 is the XCD):
+// each L2 then holds one eighth of the centroids instead of all of them.
+// For the squared distance the norms are accumulated beside the products: |q - c|^2 = |q|^2 + |c|^2 - 2 q.c.
 typedef double double4_t __attribute__((ext_vector_type(4)));
-constexpr int kCoarseKT = 32, kCoarseLd = kCoarseKT + 4;
-
-template <int WQ>
-__global__ __launch_bounds__(256) void coarse_mfma_kernel(CoarseArgs a) {
-    constexpr int WC = 4 / WQ, TQ = WQ * 32, TC = WC * 32;
-    __shared__ float sq[TQ * kCoarseLd];
-    __shared__ float sc[TC * kCoarseLd];
-    const int tid = threadIdx.x, lane = lane_id(), wave = wave_id();
-    const int q0 = blockIdx.y * TQ, c0 = blockIdx.x * TC;
-    const int wq = (wave % WQ) * 32, wc = (wave / WQ) * 32;      // this wavefront's corner in the tile
+template <int QT, int CT, int W>
+__global__ __launch_bounds__(W * 64) void coarse_mfma_kernel(CoarseArgs a, int q_tiles) {
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    typedef double SumTile[QT * CT][4][64];
+    SumTile* s_acc = (SumTile*)smem_raw;               // [W]
+    double (*s_nq)[QT * 16] = (double (*)[QT * 16])(s_acc + W);
+    double (*s_nc)[CT * 16] = (double (*)[CT * 16])(s_nq + W);
+    const int lane = lane_id(), wave = wave_id();
+    const int xcd = blockIdx.x & 7, in_xcd = blockIdx.x >> 3;
+    const int c0 = ((in_xcd / q_tiles) * 8 + xcd) * (CT * 16), q0 = (in_xcd % q_tiles) * (QT * 16);
+    if (c0 >= a.nlist) return;
     const int fi = lane & 15, fk = lane >> 4;
-    double4_t acc[2][2];
+    const float* qrow[QT];
+    const float* crow[CT];
 #pragma unroll
-    for (int x = 0; x < 2; ++x)
+    for (int x = 0; x < QT; ++x) qrow[x] = a.q + (size_t)min(q0 + x * 16 + fi, a.nq - 1) * a.d + fk * 4;
 #pragma unroll
-        for (int y = 0; y < 2; ++y) acc[x][y] = double4_t{0.0, 0.0, 0.0, 0.0};
-    double nq2[2] = {0.0, 0.0}, nc2[2] = {0.0, 0.0};
+    for (int y = 0; y < CT; ++y) crow[y] = a.centroids + (size_t)min(c0 + y * 16 + fi, a.nlist - 1) * a.d + fk * 4;
+    double4_t acc[QT][CT];
+    double nq2[QT], nc2[CT];
+#pragma unroll
+    for (int x = 0; x < QT; ++x) {
+        nq2[x] = 0.0;
+#pragma unroll
+        for (int y = 0; y < CT; ++y) acc[x][y] = double4_t{0.0, 0.0, 0.0, 0.0};
+    }
+#pragma unroll
+    for (int y = 0; y < CT; ++y) nc2[y] = 0.0;
+    struct Stage { float4 q[2][QT], c[2][CT]; };       // a 32-element block: two 16-element halves
+    auto request = [&](int k0, Stage& s) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+            const int k = k0 + h * 16;
+            const bool in = k + fk * 4 < a.d;          // d is a multiple of 4
+#pragma unroll
+            for (int x = 0; x < QT; ++x) s.q[h][x] = in ? *(const float4*)(qrow[x] + k) : make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+            for (int y = 0; y < CT; ++y) s.c[h][y] = in ? *(const float4*)(crow[y] + k) : make_float4(0.f, 0.f, 0.f, 0.f);
+        }
+    };
+    auto multiply = [&](const Stage& s) {
+#pragma unroll
+        for (int h = 0; h < 2; ++h) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                double fa[QT], fb[CT];
+#pragma unroll
+                for (int x = 0; x < QT; ++x) {
+                    fa[x] = (double)(e == 0 ? s.q[h][x].x : e == 1 ? s.q[h][x].y : e == 2 ? s.q[h][x].z : s.q[h][x].w);
+                    if (a.metric != 0) nq2[x] = fma(fa[x], fa[x], nq2[x]);
+                }
+#pragma unroll
+                for (int y = 0; y < CT; ++y) {
+                    fb[y] = (double)(e == 0 ? s.c[h][y].x : e == 1 ? s.c[h][y].y : e == 2 ? s.c[h][y].z : s.c[h][y].w);
+                    if (a.metric != 0) nc2[y] = fma(fb[y], fb[y], nc2[y]);
+                }
+#pragma unroll
+                for (int x = 0; x < QT; ++x)
+#pragma unroll
+                    for (int y = 0; y < CT; ++y)
+                        acc[x][y] = __builtin_amdgcn_mfma_f64_16x16x4f64(fa[x], fb[y], acc[x][y], 0, 0, 0);
+            }
+        }
+    };
+    Stage st[2];
+    const int step = W * 32;
+    int k = wave * 32;
+    if (k < a.d) request(k, st[0]);
 #pragma unroll 1
-    for (int k0 = 0; k0 < a.d; k0 += kCoarseKT) {
-        // slabs: 8 float4 per row
-        for (int i = tid; i < TQ * 8; i += 256) {
-            const int r = i >> 3, k4 = (i & 7) * 4;
-            float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-            if (q0 + r < a.nq && k0 + k4 < a.d) v = *(const float4*)(a.q + (size_t)(q0 + r) * a.d + k0 + k4);
-            *(float4*)&sq[r * kCoarseLd + k4] = v;
-        }
-        for (int i = tid; i < TC * 8; i += 256) {
-            const int r = i >> 3, k4 = (i & 7) * 4;
-            float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
-            if (c0 + r < a.nlist && k0 + k4 < a.d) v = *(const float4*)(a.centroids + (size_t)(c0 + r) * a.d + k0 + k4);
-            *(float4*)&sc[r * kCoarseLd + k4] = v;
-        }
-        __syncthreads();
-#pragma unroll
-        for (int ks = 0; ks < kCoarseKT; ks += 4) {
-            double fa[2], fb[2];
-#pragma unroll
-            for (int x = 0; x < 2; ++x) {
-                fa[x] = (double)sq[(wq + x * 16 + fi) * kCoarseLd + ks + fk];
-                fb[x] = (double)sc[(wc + x * 16 + fi) * kCoarseLd + ks + fk];
-                nq2[x] = fma(fa[x], fa[x], nq2[x]);
-                nc2[x] = fma(fb[x], fb[x], nc2[x]);
-            }
-#pragma unroll
-            for (int x = 0; x < 2; ++x)
-#pragma unroll
-                for (int y = 0; y < 2; ++y)
-                    acc[x][y] = __builtin_amdgcn_mfma_f64_16x16x4f64(fa[x], fb[y], acc[x][y], 0, 0, 0);
-        }
-        __syncthreads();
+    for (; k < a.d; k += 2 * step) {
+        if (k + step < a.d) request(k + step, st[1]);
+        multiply(st[0]);
+        if (k + step >= a.d) break;
+        if (k + 2 * step < a.d) request(k + 2 * step, st[0]);
+        multiply(st[1]);
     }
-    // norms: sum over the four k-groups of lanes; then lane l holds the norm of row l % 16
+    // the four wavefronts' sums, added in order
 #pragma unroll
-    for (int x = 0; x < 2; ++x) {
-        nq2[x] += __shfl_xor(nq2[x], 16); nq2[x] += __shfl_xor(nq2[x], 32);
-        nc2[x] += __shfl_xor(nc2[x], 16); nc2[x] += __shfl_xor(nc2[x], 32);
-    }
+    for (int x = 0; x < QT; ++x)
 #pragma unroll
-    for (int x = 0; x < 2; ++x) {
+        for (int y = 0; y < CT; ++y)
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-            const int i = 4 * r + fk;                      // row of result register r inside the 16 x 16 tile
-            const double qn = __shfl(nq2[x], i);
-            const int qi = q0 + wq + x * 16 + i;
+            for (int r = 0; r < 4; ++r) s_acc[wave][x * CT + y][r][lane] = acc[x][y][r];
+    if (a.metric != 0) {
+        // over the four parts of a row; then lane l < 16 holds the norm of row l
 #pragma unroll
-            for (int y = 0; y < 2; ++y) {
-                const int cj = c0 + wc + y * 16 + fi;
-                const double dot = acc[x][y][r];
-                const double s = a.metric == 0 ? dot : fma(-2.0, dot, qn + nc2[y]);
-                if (qi < a.nq && cj < a.nlist) a.scores[(size_t)qi * a.nlist + cj] = s;
-            }
+        for (int x = 0; x < QT; ++x) {
+            nq2[x] += __shfl_xor(nq2[x], 16); nq2[x] += __shfl_xor(nq2[x], 32);
+            if (lane < 16) s_nq[wave][x * 16 + lane] = nq2[x];
         }
+#pragma unroll
+        for (int y = 0; y < CT; ++y) {
+            nc2[y] += __shfl_xor(nc2[y], 16); nc2[y] += __shfl_xor(nc2[y], 32);
+            if (lane < 16) s_nc[wave][y * 16 + lane] = nc2[y];
+        }
+    }
+    __syncthreads();
+    // result registers (tile, r) of the workgroup, dealt to the wavefronts
+#pragma unroll
+    for (int n0 = 0; n0 < QT * CT * 4; n0 += W) {
+        const int n = n0 + wave, t = n >> 2, r = n & 3, x = t / CT, y = t % CT;
+        if (n >= QT * CT * 4) break;
+        double s = s_acc[0][t][r][lane];
+#pragma unroll
+        for (int w = 1; w < W; ++w) s += s_acc[w][t][r][lane];
+        const int i = x * 16 + 4 * r + fk, j = y * 16 + fi;
+        if (a.metric != 0) {
+            double qn = s_nq[0][i], cn = s_nc[0][j];
+#pragma unroll
+            for (int w = 1; w < W; ++w) { qn += s_nq[w][i]; cn += s_nc[w][j]; }
+            s = fma(-2.0, s, qn + cn);
+        }
+        if (q0 + i < a.nq && c0 + j < a.nlist) a.scores[(size_t)(q0 + i) * a.nlist + c0 + j] = s;
     }
 }
 
+template <int QT, int CT, int W>
+static void launch_coarse_mfma(const CoarseArgs& a, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
+    const int q_tiles = (a.nq + QT * 16 - 1) / (QT * 16), c_tiles = (a.nlist + CT * 16 - 1) / (CT * 16);
+    const size_t lds = (size_t)W * (QT * CT * 4 * 64 + QT * 16 + CT * 16) * sizeof(double);
+    IVF_LAUNCH((coarse_mfma_kernel<QT, CT, W>), dim3((unsigned)((c_tiles + 7) / 8 * 8 * q_tiles)), dim3(W * 64), lds, s, e0, e1, a, q_tiles);
+}
+
 hipError_t launch_coarse(const CoarseArgs& a, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
-    if (a.nq < kCoarseRowMax || (a.d & 3) != 0) {
+    if (a.nq < (a.metric == 0 ? kCoarseRowMaxIp : kCoarseRowMaxL2) || (a.d & 3) != 0) {
         IVF_LAUNCH(coarse_rows_kernel, dim3((a.nlist + 3) / 4), dim3(256), 0, s, e0, e1, a);
-    } else if (a.nq < 48) {
-        IVF_LAUNCH(coarse_mfma_kernel<1>, dim3((a.nlist + 127) / 128, (a.nq + 31) / 32), dim3(256), 0, s, e0, e1, a);
     } else {
-        IVF_LAUNCH(coarse_mfma_kernel<2>, dim3((a.nlist + 63) / 64, (a.nq + 63) / 64), dim3(256), 0, s, e0, e1, a);
+        // Small tiles while they leave the chip short of work, measured with 1024, 4096 and 8192 lists:
+        // 512 of them 12.9, 12.6, 14.3 us against 15.7, 16.1, 19.1 of the large ones; 768: 16.0 against
+        // 17.0; 1024: 19.3, 19.2, 22.5 against 17.0, 17.0, 19.5; 8192: 123 against 94.
+        const size_t small_tiles = (size_t)((a.nlist + 15) / 16) * ((a.nq + 15) / 16);
+        if (small_tiles <= 768) launch_coarse_mfma<1, 1, 8>(a, s, e0, e1);
+        else launch_coarse_mfma<2, 2, 4>(a, s, e0, e1);
     }
     return hipGetLastError();
 }
