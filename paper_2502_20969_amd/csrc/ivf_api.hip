@@ -104,7 +104,7 @@ struct Workspace {
     int b_nq = 0, b_nprobe = 0;
     void* d_q_store = nullptr;
     float* d_thr = nullptr;
-    float* d_thr_part = nullptr;
+    uint32_t* d_thr_part = nullptr;
     float *d_cand_score = nullptr, *d_eps = nullptr, *d_qq = nullptr;
     uint32_t* d_surv_row = nullptr;
     uint32_t *d_list_count = nullptr, *d_cursor = nullptr, *d_qstart = nullptr, *d_tstart = nullptr, *d_qidx = nullptr;
@@ -542,8 +542,8 @@ int ensure_batched_workspace(ivf_index* ix, int nq, int nprobe) {
     HIP_TRY(hipMalloc(&w.d_q_store, nqz * ix->d * 2));
     HIP_TRY(hipMalloc(&w.d_qq, nqz * sizeof(float)));
     HIP_TRY(hipMalloc(&w.d_thr, nqz * sizeof(float)));
-    HIP_TRY(hipMalloc(&w.d_thr_part, batched_thr_part_floats(nq2) * sizeof(float)));
-    HIP_TRY(hipMalloc(&w.d_list_count, (nl + 1) * sizeof(uint32_t)));      // + the scan's task counter
+    HIP_TRY(hipMalloc(&w.d_thr_part, batched_sample_words(nq2) * sizeof(uint32_t)));
+    HIP_TRY(hipMalloc(&w.d_list_count, (nl + 2) * sizeof(uint32_t)));      // + a place past the end and the scan's task counter
     HIP_TRY(hipMalloc(&w.d_cursor, nl * sizeof(uint32_t)));
     HIP_TRY(hipMalloc(&w.d_qstart, (nl + 1) * sizeof(uint32_t)));
     HIP_TRY(hipMalloc(&w.d_tstart, (nl + 1) * sizeof(uint32_t)));
@@ -566,7 +566,7 @@ static void fill_batched_args(const ivf_index* ix, const Workspace& w, BatchedAr
     b.lists = ix->d_buf; b.off = ix->d_off; b.ids = ix->d_ids; b.probe = w.d_probe;
     b.q_store = w.d_q_store; b.thr = w.d_thr; b.thr_part = w.d_thr_part; b.row_norm_max_bits = ix->d_row_norm_max;
     b.list_count = w.d_list_count; b.cursor = w.d_cursor; b.qstart = w.d_qstart; b.tstart = w.d_tstart;
-    b.ticket = w.d_list_count + ix->nlist;
+    b.ticket = w.d_list_count + ix->nlist + 1;
     b.qidx = w.d_qidx; b.tasks = w.d_tasks; b.cand_count = w.d_cand_count; b.cand_row = w.d_cand_row;
     b.cand_key = w.d_cand_key; b.cand_score = w.d_cand_score; b.eps = w.d_eps; b.qq = w.d_qq; b.row_norm = ix->d_row_norm;
     b.surv_row = w.d_surv_row; b.overflow = w.d_overflow;

@@ -16,6 +16,7 @@
 // Every true top-k row passes this filter.
 #include "ivf_device.h"
 #include <hip/hip_ext.h>
+#include <algorithm>
 
 namespace ivf {
 using namespace dev;
@@ -61,24 +62,169 @@ hipError_t launch_row_norms(const void* lists, int dtype, int64_t n, int d, unsi
     return hipGetLastError();
 }
 
-// ---- threshold sample --------------------------------------------------------------------------------------
-// fp32 scores (fp32 query; <q, y>, or -sum (q - y)^2 for L2) of the first 2048 rows of each query's (at most 64 nearest) selected
-// clusters, taken in probe order (usually all from the nearest cluster; more clusters when those
-// are small), reduced to the k-th best.  Any subset of the selected rows gives a valid lower bound of the k-th best
-// score over all of them.  The sample of a query is split over kSampleParts workgroups of 128 rows;
-// each writes its k best keys, and prep_queries_kernel merges the parts.
-constexpr int kSampleParts = 16;
-constexpr int kSamplePartRows = 128;
+// ---- in front of the scan: threshold sample, queries in the storage type, cluster -> queries map ---------
+// One launch for everything that needs only the selected clusters: its workgroups differ in what
+// they do (the steps are short, and as launches of their own they cost more than they computed:
+// sample, queries, map and task list in seven launches 65, 72 and 260 us for 8 and 32 queries x 768
+// fp32 and 256 x 1024 bf16 with 128, 32 and 512 clusters each; the two launches here 16, 20 and 119).
+//
+// Workgroup 0 builds the map from clusters to the queries that probe them.  Each of the others
+// scores one part of a query's threshold sample: fp32 scores (fp32 query; <q, y>, or -sum (q - y)^2
+// for L2) of the first rows of the query's (at most 64 nearest) selected clusters, taken in probe order
+// (usually all from the nearest cluster; more clusters when those are small).  Any subset of the
+// selected rows gives a valid lower bound of the k-th best score over all of them.  How many: half
+// the mean size of the eight nearest clusters, but at least 512 and 8 k, at most 2048.  The k-th
+// best of S rows out of n alike ones lets about k n / S of them pass, so S may be small where the
+// clusters are; the bytes of the sample are what this launch costs (32 queries x 768 fp32: 2048
+// rows 37 us, 512 13; 256 queries x 1024 bf16 with k 100: 2048 rows 190 us, 800 104).
+// A wavefront scores four rows, all of them in flight: the sample is bound by the bytes of its
+// rows when there are many queries and by the memory round trips in front of them when there are
+// few.  One more workgroup per query rounds the query to the storage type.
+constexpr int kFrontThreads = 512;
+constexpr int kSampleRows = 2048;
+constexpr int kSampleStep = kFrontThreads / 64 * 4;          // rows a workgroup scores at a time
+// Workgroups per query: one step each for small batches, more steps once the workgroups of the
+// batch fill the chip (four resident per compute unit): with 32 per query the starts of 8192
+// workgroups took 150 us of a 256-query batch.
+static int sample_parts(int nq) { return std::max(4, std::min(kSampleRows / kSampleStep, 1024 / nq)); }
+constexpr int kMapLdsLists = 8192;          // up to this many clusters the map is counted in LDS
+
+// Map: queries per cluster, and their prefix sums qstart (= cursor) and tstart (tasks per cluster).
+// One workgroup: LDS atomics and a few rounds of prefix sums, beside the sample.  (The places of the
+// queries are filled in by the next launch: 131,072 scattered stores from one compute unit took
+// 140 us, from all of them 6.)
+template <bool LDS>
+__device__ __forceinline__ void build_map(const BatchedArgs& a, uint32_t* cnt) {
+    __shared__ uint32_t wsum_q[kFrontThreads / 64], wsum_t[kFrontThreads / 64];
+    const int tid = threadIdx.x, lane = lane_id(), wave = wave_id();
+    const uint32_t pairs = (uint32_t)a.nq * (uint32_t)a.nprobe;
+    // counters in global memory are read past the L1 and ordered by device-wide fences
+    auto meet = [&]() { if (!LDS) __threadfence(); __syncthreads(); };
+    auto count_of = [&](int c) -> uint32_t { return LDS ? cnt[c] : __hip_atomic_load(&cnt[c], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
+    for (int c = tid; c <= a.nlist; c += kFrontThreads) {              // one more: pairs past the end count there
+        if (LDS) cnt[c] = 0u;
+        else __hip_atomic_store(&cnt[c], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
+    if (tid == 0) *a.ticket = 0u;
+    meet();
+    // sixteen pairs per thread and pass: all requested before the first is used, and no branches that
+    // differ between lanes, so that neither the reads nor the atomics wait for each other
+#pragma unroll 1
+    for (uint32_t i0 = 0; i0 < pairs; i0 += kFrontThreads * 16) {
+        int32_t c[16];
+#pragma unroll
+        for (int u = 0; u < 16; ++u) c[u] = a.probe[min(i0 + (uint32_t)(u * kFrontThreads + tid), pairs - 1)];
+#pragma unroll
+        for (int u = 0; u < 16; ++u) {
+            const uint32_t i = i0 + (uint32_t)(u * kFrontThreads + tid);
+            if (i0 + (uint32_t)(u * kFrontThreads) < pairs) atomicAdd(&cnt[i < pairs ? c[u] : a.nlist], 1u);
+        }
+    }
+    meet();
+    // prefix sums over all clusters of (queries per cluster) and (tasks per cluster), four clusters per thread
+    uint32_t carry_q = 0, carry_t = 0;
+    unsigned long long rows = 0;
+#pragma unroll 1
+    for (int base = 0; base < a.nlist; base += kFrontThreads * 4) {
+        uint32_t cq[4], ct[4], sq = 0, st = 0;
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int c = base + tid * 4 + u;
+            cq[u] = 0; ct[u] = 0;
+            if (c < a.nlist) {
+                const uint32_t n = (uint32_t)(a.off[c + 1] - a.off[c]);
+                cq[u] = count_of(c);
+                ct[u] = cq[u] ? ((n + kTileRows - 1) / kTileRows) * ((cq[u] + a.group_q - 1) / a.group_q) : 0u;
+                if (cq[u]) rows += n;
+            }
+            sq += cq[u]; st += ct[u];
+        }
+        uint32_t iq = sq, it = st;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const uint32_t uq = __shfl_up(iq, o), ut = __shfl_up(it, o);
+            if (lane >= o) { iq += uq; it += ut; }
+        }
+        if (lane == 63) { wsum_q[wave] = iq; wsum_t[wave] = it; }
+        __syncthreads();
+        uint32_t oq = carry_q + iq - sq, ot = carry_t + it - st;
+#pragma unroll
+        for (int w = 0; w < kFrontThreads / 64; ++w) {
+            if (w < wave) { oq += wsum_q[w]; ot += wsum_t[w]; }
+            carry_q += wsum_q[w]; carry_t += wsum_t[w];
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int c = base + tid * 4 + u;
+            if (c < a.nlist) { a.qstart[c] = oq; a.tstart[c] = ot; a.cursor[c] = oq; }
+            oq += cq[u]; ot += ct[u];
+        }
+        __syncthreads();
+    }
+    if (tid == 0) { a.qstart[a.nlist] = carry_q; a.tstart[a.nlist] = carry_t; }
+    // rows the scan covers once per cluster (for the roofline accounting)
+    if (a.rows_counter) {
+        for (int m = 32; m >= 1; m >>= 1) rows += __shfl_xor(rows, m);
+        if (lane == 0 && rows) atomicAdd(a.rows_counter, rows);
+    }
+}
+
+// Query `qi` rounded to the storage type, its norm and the bound of |filter score - exact score|
+// for any row y.  Inner product from the MFMA: the query rounding contributes |<q~ - q, y>| <=
+// |q~ - q| |y| (Cauchy-Schwarz, with the residual norm measured here), the fp32 accumulation at
+// most acc_coef |q~| |y|.  The fp32 sample score behind the threshold is off by at most samp_coef
+// |q| |y| (inner product) or samp_coef |q - y|^2 (L2: every term of the sum is positive).  The L2
+// filter score 2 <q, y> - |y|^2 - |q|^2 doubles the inner-product error and adds the rounding of
+// the two norms and of its two operations, each at most 2^-24 (|q| + |y|)^2.  A little slack
+// absorbs the rounding of this arithmetic itself.
+__device__ __forceinline__ void prepare_query(const BatchedArgs& a, int qi) {
+    __shared__ float p_s[kFrontThreads / 64], p_res[kFrontThreads / 64];
+    __shared__ double p_qq[kFrontThreads / 64];
+    float s = 0.f, res = 0.f;          // |q~|^2 of the rounded query and |q~ - q|^2 of the rounding
+    double qq = 0.0;                   // |q|^2
+    for (int t = threadIdx.x; t < a.d; t += kFrontThreads) {
+        const float x = a.q[(size_t)qi * a.d + t];
+        float xr = x;
+        if (a.dtype == 1) { _Float16 h = (_Float16)x; ((_Float16*)a.q_store)[(size_t)qi * a.d + t] = h; xr = (float)h; }
+        else if (a.dtype == 2) { __bf16 h = (__bf16)x; ((__bf16*)a.q_store)[(size_t)qi * a.d + t] = h; xr = (float)h; }
+        s = fmaf(xr, xr, s);
+        res = fmaf(xr - x, xr - x, res);
+        qq = fma((double)x, (double)x, qq);
+    }
+    s = group_sum<64>(s);
+    res = group_sum<64>(res);
+    qq = wave_sum(qq);
+    if (lane_id() == 0) { p_s[wave_id()] = s; p_res[wave_id()] = res; p_qq[wave_id()] = qq; }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        s = 0.f; res = 0.f; qq = 0.0;
+        for (int w = 0; w < kFrontThreads / 64; ++w) { s += p_s[w]; res += p_res[w]; qq += p_qq[w]; }
+        const float ymax = sqrtf(__uint_as_float(*a.row_norm_max_bits));
+        const float qn = sqrtf((float)qq);
+        const float ip_err = (sqrtf(res) + a.acc_coef * sqrtf(s)) * ymax;
+        a.eps[qi] = a.metric == 0 ? 1.01f * (ip_err + a.samp_coef * qn * ymax)
+                                  : 1.01f * (2.f * ip_err + (a.samp_coef + 0x1p-21f) * (qn + ymax) * (qn + ymax));
+        a.qq[qi] = (float)qq;
+        a.cand_count[qi] = 0;
+    }
+}
 
 template <typename T>
-__global__ __launch_bounds__(256) void thr_sample_kernel(BatchedArgs a) {
+__global__ __launch_bounds__(kFrontThreads) void batch_front_kernel(BatchedArgs a, int parts) {
     extern __shared__ __align__(16) unsigned char smem[];
-    __shared__ Cand m_cand[3 * kMaxKPrime];
-    constexpr int EPL = T::kPerLoad;
-    const int qi = blockIdx.x, part = blockIdx.y, lane = lane_id(), wave = wave_id();
+    if (blockIdx.x == 0) {
+        if (a.nlist <= kMapLdsLists) build_map<true>(a, (uint32_t*)smem);
+        else build_map<false>(a, a.list_count);
+        return;
+    }
+    constexpr int EPL = T::kPerLoad, U = kSampleStep / (kFrontThreads / 64), V = 4;      // rows of a wavefront, 16-byte loads per lane and row in flight
+    const int qi = (int)(blockIdx.x - 1) / (parts + 1), part = (int)(blockIdx.x - 1) % (parts + 1) - 1;
+    const int lane = lane_id(), wave = wave_id();
     float* ql = (float*)smem;
-    for (int i = threadIdx.x; i < a.d; i += blockDim.x) ql[i] = a.q[(size_t)qi * a.d + i];
-    __syncthreads();
+    if (part < 0) {
+        prepare_query(a, qi);
+        return;
+    }
     // The rows of the first 64 selected clusters laid end to end: lane i holds cluster i's first
     // row and the running total of rows up to and including it (one parallel prefix, so that
     // finding the cluster of a sample row is a ballot instead of a walk through dependent loads).
@@ -90,6 +236,7 @@ __global__ __launch_bounds__(256) void thr_sample_kernel(BatchedArgs a) {
         my_lo = a.off[c];
         my_n = (uint32_t)(a.off[c + 1] - my_lo);
     }
+    for (int i = threadIdx.x; i < a.d; i += kFrontThreads) ql[i] = a.q[(size_t)qi * a.d + i];
     uint32_t my_end = my_n;
 #pragma unroll
     for (int o = 1; o < 64; o <<= 1) {
@@ -104,194 +251,123 @@ __global__ __launch_bounds__(256) void thr_sample_kernel(BatchedArgs a) {
         const int64_t lo_i = ((int64_t)read_lane((uint32_t)((uint64_t)my_lo >> 32), i) << 32) | read_lane((uint32_t)my_lo, i);
         return lo_i + (int64_t)(r - (end_i - n_i));
     };
-    const uint32_t r_begin = part * kSamplePartRows + wave * 32;
-    const uint32_t r_end = r_begin + 32;
+    __syncthreads();
+    const uint32_t want = min(max(read_lane(my_end, min(7, a.nprobe - 1)) / 16, max(512u, 8u * (uint32_t)a.k)), (uint32_t)kSampleRows);
     const int chunks = a.d / EPL;
-    WaveTopK<2, false> top;                     // ties inside the sample do not matter for a bound
-    top.init();
-    for (uint32_t r0 = r_begin; r0 < r_end; r0 += 4) {
-        int64_t g[4];
+#pragma unroll 1
+    for (uint32_t r0 = (uint32_t)(part * kSampleStep + wave * U); r0 < (uint32_t)kSampleRows; r0 += (uint32_t)(parts * kSampleStep)) {
+        uint32_t key = 0;                                 // lane u < U: the ordered score of sample row r0 + u, 0 = none
+        int64_t g[U];
 #pragma unroll
-        for (int u = 0; u < 4; ++u) g[u] = locate(r0 + u);
-        if (g[0] < 0) break;                              // the selected clusters hold no more rows
-        float s[4] = {0.f, 0.f, 0.f, 0.f};
-        for (int ch = lane; ch < chunks; ch += 64) {
-            uint4 v[4];
+        for (int u = 0; u < U; ++u) g[u] = locate(r0 + u);
+        if (g[0] >= 0 && r0 < want) {
+            const unsigned char* rp[U];
+            float s[U];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                const int64_t row = g[u] >= 0 ? g[u] : g[0];      // past the end: re-read a valid row
-                v[u] = *(const uint4*)((const unsigned char*)a.lists + (size_t)row * a.d * T::kBytes + (size_t)ch * 16);
+            for (int u = 0; u < U; ++u) {
+                rp[u] = (const unsigned char*)a.lists + (size_t)(g[u] >= 0 ? g[u] : g[0]) * a.d * T::kBytes;      // past the end: a valid row again
+                s[u] = 0.f;
             }
+#pragma unroll 1
+            for (int c0 = lane; c0 < chunks; c0 += 64 * V) {
+                uint4 v[V][U];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                float x[EPL];
-                Unpack<T>::run(v[u], x);
+                for (int w = 0; w < V; ++w) {
+                    const int ch = min(c0 + 64 * w, chunks - 1);
 #pragma unroll
-                for (int e = 0; e < EPL; ++e) {
-                    if (a.metric == 0) s[u] = fmaf(ql[ch * EPL + e], x[e], s[u]);
-                    else { const float df = ql[ch * EPL + e] - x[e]; s[u] = fmaf(df, df, s[u]); }
+                    for (int u = 0; u < U; ++u) v[w][u] = *(const uint4*)(rp[u] + (size_t)ch * 16);
+                }
+#pragma unroll
+                for (int w = 0; w < V; ++w) {
+                    const int ch = c0 + 64 * w;
+                    if (ch >= chunks) break;
+#pragma unroll
+                    for (int u = 0; u < U; ++u) {
+                        float x[EPL];
+                        Unpack<T>::run(v[w][u], x);
+#pragma unroll
+                        for (int e = 0; e < EPL; ++e) {
+                            if (a.metric == 0) s[u] = fmaf(ql[ch * EPL + e], x[e], s[u]);
+                            else { const float df = ql[ch * EPL + e] - x[e]; s[u] = fmaf(df, df, s[u]); }
+                        }
+                    }
                 }
             }
-        }
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            float ck = read_lane(group_total_last_lane<64>(s[u]), 63);
-            if (a.metric != 0) ck = -ck;
-            if (g[u] >= 0 && ck >= top.thr) top.push(ck, r0 + u);
+            for (int u = 0; u < U; ++u) {
+                float ck = read_lane(group_total_last_lane<64>(s[u]), 63);
+                if (a.metric != 0) ck = -ck;
+                if (lane == u && g[u] >= 0 && ck > -INFINITY) key = ordered(ck);      // not a number: no bound from this row
+            }
         }
-        if (top.pcount > 60) top.flush(a.k);
+        if (lane < U) a.thr_part[(size_t)qi * kSampleRows + r0 + lane] = key;
     }
-    top.flush(a.k);
-    if (wave > 0) {
+}
+
+// Workgroups 0 .. nq - 1: the threshold of a query, the k-th best score of its sample less eps (a
+// bucket cut leaves a few more than k, which are ranked by counting).  The others fill the map
+// (qidx: the queries grouped by cluster) and write the task list, one wavefront per cluster: tasks
+// of a cluster are ordered (query group, row tile), so that tiles of one group are consecutive.
+__global__ __launch_bounds__(256) void batch_tasks_kernel(BatchedArgs a) {
+    __shared__ uint32_t pool[kSampleRows];
+    __shared__ uint32_t hist[256], red[96];
+    __shared__ uint32_t s_cnt;
+    const int tid = threadIdx.x, lane = lane_id();
+    if ((int)blockIdx.x >= a.nq) {
+        const uint32_t pairs = (uint32_t)a.nq * (uint32_t)a.nprobe, stride = (gridDim.x - (uint32_t)a.nq) * 256u;
+        for (uint32_t i = (blockIdx.x - (uint32_t)a.nq) * 256u + (uint32_t)tid; i < pairs; i += stride)
+            a.qidx[atomicAdd(&a.cursor[a.probe[i]], 1u)] = i / (uint32_t)a.nprobe;
+        const int step = ((int)gridDim.x - a.nq) * 4;
+        for (int c = ((int)blockIdx.x - a.nq) * 4 + wave_id(); c < a.nlist; c += step) {
+            const uint32_t t0 = a.tstart[c], t1 = a.tstart[c + 1];
+            if (t0 == t1) continue;
+            const uint32_t n = (uint32_t)(a.off[c + 1] - a.off[c]);
+            const uint32_t tiles = (n + kTileRows - 1) / kTileRows;
+            for (uint32_t i = lane; i < t1 - t0; i += 64) a.tasks[t0 + i] = BatchTask{(uint32_t)c, i / tiles, i % tiles};
+        }
+        return;
+    }
+    const int qi = blockIdx.x;
+    const uint32_t k = (uint32_t)a.k;
+    uint32_t v[kSampleRows / 256];
 #pragma unroll
-        for (int j = 0; j < 2; ++j) {
-            int e = j * 64 + lane;
-            if (e < a.k) m_cand[(wave - 1) * a.k + e] = top.top[j];
+    for (int u = 0; u < kSampleRows / 256; ++u) v[u] = a.thr_part[(size_t)qi * kSampleRows + u * 256 + tid];
+#pragma unroll
+    for (int u = 0; u < kSampleRows / 256; ++u) pool[u * 256 + tid] = v[u];
+    if (tid == 0) s_cnt = 0;
+    __syncthreads();
+    const BucketCut bc = block_bucket_cut([&](uint32_t i) { return pool[i]; }, kSampleRows, k, hist, red);
+    __syncthreads();
+#pragma unroll
+    for (int u = 0; u < kSampleRows / 256; ++u) {
+        const bool ok = v[u] != 0 && bc.pass(v[u]);
+        const uint64_t b = __ballot(ok);
+        if (b) {
+            uint32_t base = 0;
+            if (lane == 0) base = atomicAdd(&s_cnt, (uint32_t)__popcll(b));
+            base = read_lane(base, 0);
+            if (ok) pool[base + __popcll(b & ((1ull << lane) - 1ull))] = v[u];
         }
     }
     __syncthreads();
-    if (wave == 0) {
-        for (int w = 0; w < 3; ++w) {
+    const uint32_t cnt = s_cnt;
+    if (cnt < k || a.keep_all) {                               // fewer than k rows sampled: everything passes
+        if (tid == 0) a.thr[qi] = -INFINITY;
+        return;
+    }
+#pragma unroll 1
+    for (uint32_t t = tid; t < cnt; t += 256) {
+        const uint32_t me = pool[t];
+        uint32_t above = 0, equal = 0;
+#pragma unroll 1
+        for (uint32_t j0 = 0; j0 < cnt; j0 += 8) {
+            uint32_t o[8];
 #pragma unroll
-            for (int j = 0; j < 2; ++j) {
-                int e = j * 64 + lane;
-                top.merge_run_if_useful(e < a.k ? m_cand[w * a.k + e] : (Cand)0, a.k);
-            }
-        }
-        float* out = a.thr_part + ((size_t)qi * kSampleParts + part) * kMaxKPrime;
+            for (int u = 0; u < 8; ++u) o[u] = pool[min(j0 + u, cnt - 1)];
 #pragma unroll
-        for (int j = 0; j < 2; ++j) {
-            int e = j * 64 + lane;
-            if (e < a.k) out[e] = top.top[j] == 0 ? -INFINITY : cand_key(top.top[j]);
+            for (int u = 0; u < 8; ++u) { above += (uint32_t)((o[u] > me) & (j0 + u < cnt)); equal += (uint32_t)((o[u] == me) & (j0 + u < cnt)); }
         }
-    }
-}
-
-// ---- queries in the storage type, thresholds ---------------------------------------------------------
-__global__ void prep_queries_kernel(BatchedArgs a) {
-    const int qi = blockIdx.x, lane = threadIdx.x & 63;
-    const float* q = a.q + (size_t)qi * a.d;
-    float s = 0.f, res = 0.f;          // |q~|^2 of the rounded query and |q~ - q|^2 of the rounding
-    double qq = 0.0;                   // |q|^2
-    for (int t = threadIdx.x; t < a.d; t += 64) {
-        float x = q[t], xr = x;
-        if (a.dtype == 1) { _Float16 h = (_Float16)x; ((_Float16*)a.q_store)[(size_t)qi * a.d + t] = h; xr = (float)h; }
-        else if (a.dtype == 2) { __bf16 h = (__bf16)x; ((__bf16*)a.q_store)[(size_t)qi * a.d + t] = h; xr = (float)h; }
-        s = fmaf(xr, xr, s);
-        res = fmaf(xr - x, xr - x, res);
-        qq = fma((double)x, (double)x, qq);
-    }
-    s = group_sum<64>(s);
-    res = group_sum<64>(res);
-    qq = wave_sum(qq);
-    // k-th best key over the sample parts
-    WaveTopK<2, false> top;
-    top.init();
-    for (int part = 0; part < kSampleParts; ++part) {
-        const float* in = a.thr_part + ((size_t)qi * kSampleParts + part) * kMaxKPrime;
-#pragma unroll
-        for (int j = 0; j < 2; ++j) {
-            int e = j * 64 + lane;
-            float key = e < a.k ? in[e] : -INFINITY;
-            top.merge_run_if_useful(key == -INFINITY ? (Cand)0 : pack_cand(key, (uint32_t)(part * kMaxKPrime + e)), a.k);
-        }
-    }
-    if (lane == 0) {
-        // Bound of |filter score - exact score| for any row y.  Inner product from the MFMA: the
-        // query rounding contributes |<q~ - q, y>| <= |q~ - q| |y| (Cauchy-Schwarz, with the
-        // residual norm measured above), the fp32 accumulation at most acc_coef |q~| |y|.  The
-        // fp32 sample score behind the threshold is off by at most samp_coef |q| |y| (inner
-        // product) or samp_coef |q - y|^2 (L2: every term of the sum is positive).  The L2
-        // filter score 2 <q, y> - |y|^2 - |q|^2 doubles the inner-product error and adds the
-        // rounding of the two norms and of its two operations, each at most 2^-24 (|q| + |y|)^2.
-        // A little slack absorbs the rounding of this arithmetic itself.
-        const float ymax = sqrtf(__uint_as_float(*a.row_norm_max_bits));
-        const float qn = sqrtf((float)qq);
-        const float ip_err = (sqrtf(res) + a.acc_coef * sqrtf(s)) * ymax;
-        float eps;
-        if (a.metric == 0) eps = 1.01f * (ip_err + a.samp_coef * qn * ymax);
-        else eps = 1.01f * (2.f * ip_err + (a.samp_coef + 0x1p-21f) * (qn + ymax) * (qn + ymax));
-        a.thr[qi] = a.keep_all ? -INFINITY : top.thr - eps;        // -inf (fewer than k sampled rows) stays -inf
-        a.eps[qi] = eps;
-        a.qq[qi] = (float)qq;
-        a.cand_count[qi] = 0;
-    }
-}
-
-// ---- cluster -> queries map and the task list ------------------------------------------------------------
-__global__ void zero_u32_kernel(uint32_t* p, int n) {
-    int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < n) p[i] = 0;
-}
-
-__global__ void count_pairs_kernel(BatchedArgs a) {
-    int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i < a.nq * a.nprobe) atomicAdd(&a.list_count[a.probe[i]], 1u);
-}
-
-// one workgroup: prefix sums over all clusters of (queries per cluster) and (tasks per cluster)
-__global__ __launch_bounds__(1024) void scan_lists_kernel(BatchedArgs a) {
-    __shared__ uint32_t wsum_q[17], wsum_t[17];
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    uint32_t carry_q = 0, carry_t = 0;
-    for (int base = 0; base < a.nlist; base += 1024) {
-        int c = base + tid;
-        uint32_t cq = 0, ct = 0;
-        if (c < a.nlist) {
-            cq = a.list_count[c];
-            uint32_t n = (uint32_t)(a.off[c + 1] - a.off[c]);
-            ct = cq ? ((n + kTileRows - 1) / kTileRows) * ((cq + a.group_q - 1) / a.group_q) : 0;
-            a.cursor[c] = 0;
-        }
-        uint32_t iq = cq, it = ct;
-#pragma unroll
-        for (int o = 1; o < 64; o <<= 1) {
-            uint32_t uq = __shfl_up(iq, o), ut = __shfl_up(it, o);
-            if (lane >= o) { iq += uq; it += ut; }
-        }
-        if (lane == 63) { wsum_q[wave] = iq; wsum_t[wave] = it; }
-        __syncthreads();
-        uint32_t oq = 0, ot = 0, tq = 0, tt = 0;
-        for (int w = 0; w < 16; ++w) {
-            if (w < wave) { oq += wsum_q[w]; ot += wsum_t[w]; }
-            tq += wsum_q[w]; tt += wsum_t[w];
-        }
-        if (c < a.nlist) { a.qstart[c] = carry_q + oq + iq - cq; a.tstart[c] = carry_t + ot + it - ct; }
-        carry_q += tq; carry_t += tt;
-        __syncthreads();
-    }
-    if (tid == 0) { a.qstart[a.nlist] = carry_q; a.tstart[a.nlist] = carry_t; }
-    // rows the scan covers once per cluster (for the roofline accounting)
-    if (a.rows_counter) {
-        unsigned long long rows = 0;
-        for (int c = tid; c < a.nlist; c += 1024) if (a.list_count[c]) rows += (unsigned long long)(a.off[c + 1] - a.off[c]);
-        for (int m = 32; m >= 1; m >>= 1) rows += __shfl_xor(rows, m);
-        if (lane == 0 && rows) atomicAdd(a.rows_counter, rows);
-    }
-}
-
-__global__ void fill_pairs_kernel(BatchedArgs a) {
-    int i = blockIdx.x * blockDim.x + threadIdx.x;
-    if (i >= a.nq * a.nprobe) return;
-    int c = a.probe[i];
-    uint32_t pos = atomicAdd(&a.cursor[c], 1u);
-    a.qidx[a.qstart[c] + pos] = (uint32_t)(i / a.nprobe);
-}
-
-// tasks of cluster c, ordered (query group, row tile) so that tiles of one group are consecutive
-__global__ void make_tasks_kernel(BatchedArgs a) {
-    for (int c = blockIdx.x; c < a.nlist; c += gridDim.x) {
-        const uint32_t t0 = a.tstart[c], t1 = a.tstart[c + 1];
-        if (t0 == t1) continue;
-        const uint32_t n = (uint32_t)(a.off[c + 1] - a.off[c]);
-        const uint32_t tiles = (n + kTileRows - 1) / kTileRows;
-        for (uint32_t i = threadIdx.x; i < t1 - t0; i += blockDim.x) {
-            BatchTask t;
-            t.cluster = (uint32_t)c;
-            t.group = i / tiles;
-            t.tile = i % tiles;
-            a.tasks[t0 + i] = t;
-        }
+        if (above < k && k <= above + equal) a.thr[qi] = unordered(me) - a.eps[qi];      // every holder of the k-th value writes the same
     }
 }
 
@@ -826,7 +902,7 @@ uint64_t batched_task_bound(const int64_t* off_host, int nlist, int nq, int dtyp
     return tiles * (((uint64_t)nq + gq - 1) / gq) + 1;
 }
 
-size_t batched_thr_part_floats(int nq) { return (size_t)nq * kSampleParts * kMaxKPrime; }
+size_t batched_sample_words(int nq) { return (size_t)nq * kSampleRows; }
 
 typedef void (*BatchedScanFn)(BatchedArgs);
 static BatchedScanFn batched_scan_fn(int dtype, int metric) {
@@ -854,16 +930,13 @@ float batched_sample_coef(int d, int dtype, int metric) {
 }
 
 hipError_t launch_batched(const BatchedArgs& a, int grid, hipStream_t s, hipEvent_t scan_start, hipEvent_t scan_stop, bool with_merge) {
-    const int pairs = a.nq * a.nprobe;
-    if (a.dtype == 0) hipLaunchKernelGGL(thr_sample_kernel<F32>, dim3(a.nq, kSampleParts), dim3(256), (size_t)a.d * 4, s, a);
-    else if (a.dtype == 1) hipLaunchKernelGGL(thr_sample_kernel<F16>, dim3(a.nq, kSampleParts), dim3(256), (size_t)a.d * 4, s, a);
-    else hipLaunchKernelGGL(thr_sample_kernel<BF16>, dim3(a.nq, kSampleParts), dim3(256), (size_t)a.d * 4, s, a);
-    hipLaunchKernelGGL(prep_queries_kernel, dim3(a.nq), dim3(64), 0, s, a);
-    hipLaunchKernelGGL(zero_u32_kernel, dim3((a.nlist + 1 + 255) / 256), dim3(256), 0, s, a.list_count, a.nlist + 1);   // and the ticket behind them
-    hipLaunchKernelGGL(count_pairs_kernel, dim3((pairs + 255) / 256), dim3(256), 0, s, a);
-    hipLaunchKernelGGL(scan_lists_kernel, dim3(1), dim3(1024), 0, s, a);
-    hipLaunchKernelGGL(fill_pairs_kernel, dim3((pairs + 255) / 256), dim3(256), 0, s, a);
-    hipLaunchKernelGGL(make_tasks_kernel, dim3(min(a.nlist, 4096)), dim3(256), 0, s, a);
+    const size_t front_lds = std::max((size_t)a.d * 4, a.nlist <= kMapLdsLists ? ((size_t)a.nlist + 1) * 4 : (size_t)0);
+    const int parts = sample_parts(a.nq);
+    const dim3 front(1 + (unsigned)a.nq * (unsigned)(parts + 1)), tasks((unsigned)a.nq + (unsigned)std::min((a.nlist + 3) / 4, 1024));
+    if (a.dtype == 0) hipLaunchKernelGGL(batch_front_kernel<F32>, front, dim3(kFrontThreads), front_lds, s, a, parts);
+    else if (a.dtype == 1) hipLaunchKernelGGL(batch_front_kernel<F16>, front, dim3(kFrontThreads), front_lds, s, a, parts);
+    else hipLaunchKernelGGL(batch_front_kernel<BF16>, front, dim3(kFrontThreads), front_lds, s, a, parts);
+    hipLaunchKernelGGL(batch_tasks_kernel, tasks, dim3(256), 0, s, a);
     const BatchedScanFn scan = batched_scan_fn(a.dtype, a.metric);
     IVF_LAUNCH(scan, dim3(grid), dim3(kBatchThreads), batched_scan_lds(a.d, a.dtype), s, scan_start, scan_stop, a);
     if (with_merge) hipLaunchKernelGGL(batched_merge_kernel, dim3(a.nq), dim3(kSelectThreads), 0, s, a);

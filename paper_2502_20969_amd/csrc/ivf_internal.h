@@ -169,10 +169,10 @@ struct BatchedArgs {
     const int32_t* probe;        // [nq x nprobe] selected clusters
     void* q_store;               // [nq x d] queries rounded to the storage type (out)
     float* thr;                  // [nq] out: filter threshold
-    float* thr_part;             // [batched_thr_part_floats(nq)] best sample keys per (query, part)
+    uint32_t* thr_part;          // [batched_sample_words(nq)] ordered scores of the threshold sample, 0 = none
     const unsigned int* row_norm_max_bits;   // largest squared row norm of the lists, as float bits
-    uint32_t* list_count;        // [nlist] queries probing each cluster
-    uint32_t* cursor;            // [nlist]
+    uint32_t* list_count;        // [nlist+1] queries probing each cluster (counted here when that does not fit LDS)
+    uint32_t* cursor;            // [nlist] next free place of a cluster in qidx
     uint32_t* qstart;            // [nlist+1] prefix of list_count
     uint32_t* tstart;            // [nlist+1] prefix of tasks per cluster
     uint32_t* qidx;              // [nq x nprobe] queries grouped by cluster
@@ -205,7 +205,7 @@ float batched_sample_coef(int d, int dtype, int metric);
 hipError_t launch_batched(const BatchedArgs& a, int grid, hipStream_t s, hipEvent_t scan_start = nullptr,
                           hipEvent_t scan_stop = nullptr, bool with_merge = true);
 int batched_resident_grid(int dtype, int metric, int d, int n_cu);
-size_t batched_thr_part_floats(int nq);
+size_t batched_sample_words(int nq);
 size_t batched_scan_lds(int d, int dtype);      // LDS bytes of the batched scan kernel (one group of queries)
 
 // scatters n rows to their cluster-major positions: dst[pos[i]] = src[i] (row_bytes each)

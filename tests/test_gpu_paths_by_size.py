@@ -83,3 +83,25 @@ def test_coarse_scores_by_batch_size(streams, nq, nlist, d, metric):
     bound = 8 * d * 2.0 ** -53 * (np.abs(x) @ np.abs(y).T + (x * x).sum(1)[:, None] + (y * y).sum(1)[None])
     assert (np.abs(got - want) <= bound).all()
     index.close()
+
+
+@pytest.mark.parametrize("nlist,nq,nprobe,k,d", [(8192, 5, 40, 3, 64), (8193, 5, 40, 3, 64), (9000, 70, 33, 100, 64), (3, 2, 3, 1, 128),
+                                                 (40, 300, 7, 20, 64), (700, 33, 512, 112, 128)])
+def test_front_of_a_list_major_batch(streams, nlist, nq, nprobe, k, d):
+    """The map from clusters to queries in LDS and in global memory, samples of fewer rows than k, one
+    and several steps of the sample per workgroup: list-major equals query by query bit for bit."""
+    rng = np.random.default_rng(nlist + nq)
+    n = nlist * 9
+    assign = rng.integers(0, nlist, n).astype(np.int32)
+    assign[:n // 3] = 0                              # one large cluster, some empty ones
+    cent = rng.standard_normal((nlist, d)).astype(np.float32)
+    rows = (cent[assign] + 0.5 * rng.standard_normal((n, d))).astype(np.float16)
+    index = P.ivf_build_layout(rows, "f16", cent, assign, compute_stream=streams[0], copy_stream=streams[1])
+    q = (cent[rng.integers(0, nlist, nq)] + 0.3 * rng.standard_normal((nq, d))).astype(np.float32)
+    q[0] = cent[0]
+    index.ivf_set_batch_mode(2)
+    bi, bd = index.ivf_search(q, nprobe, k)
+    index.ivf_set_batch_mode(1)
+    pi, pd = index.ivf_search(q, nprobe, k)
+    assert np.array_equal(bi, pi) and np.array_equal(bd, pd)
+    index.close()
