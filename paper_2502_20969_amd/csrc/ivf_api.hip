@@ -106,12 +106,10 @@ struct Workspace {
     float* d_thr = nullptr;
     uint32_t* d_thr_part = nullptr;
     float *d_cand_score = nullptr, *d_eps = nullptr, *d_qq = nullptr;
-    uint32_t* d_surv_row = nullptr;
     uint32_t *d_list_count = nullptr, *d_cursor = nullptr, *d_qstart = nullptr, *d_tstart = nullptr, *d_qidx = nullptr;
     BatchTask* d_tasks = nullptr;
     uint32_t *d_cand_count = nullptr, *d_cand_row = nullptr;
-    uint64_t* d_cand_key = nullptr;
-    int32_t *d_overflow = nullptr, *h_overflow = nullptr;
+    int32_t *h_overflow = nullptr, *hd_overflow = nullptr;     // pinned, written by the batched merge kernel; as the device addresses it
 };
 
 struct ProfSet { hipEvent_t e[8]; };   // begin/end of the coarse, select, scan and merge kernels
@@ -230,10 +228,10 @@ void free_workspace(Workspace& w) {
     dfree(w.d_redo_id); dfree(w.d_redo_key); hfree(w.h_flag);
     hfree(w.h_q); hfree(w.h_done); hfree(w.h_probe); hfree(w.h_out_ids); hfree(w.h_out_dists);
     hfree(w.h_cand); hfree(w.h_cand_count); hfree(w.h_scores);
-    dfree(w.d_thr_part); dfree(w.d_cand_score); dfree(w.d_eps); dfree(w.d_surv_row); dfree(w.d_qq);
+    dfree(w.d_thr_part); dfree(w.d_cand_score); dfree(w.d_eps); dfree(w.d_qq);
     dfree(w.d_q_store); dfree(w.d_thr); dfree(w.d_list_count); dfree(w.d_cursor); dfree(w.d_qstart);
     dfree(w.d_tstart); dfree(w.d_qidx); dfree(w.d_tasks); dfree(w.d_cand_count); dfree(w.d_cand_row);
-    dfree(w.d_cand_key); dfree(w.d_overflow); hfree(w.h_overflow);
+    hfree(w.h_overflow);
     w = Workspace{};
 }
 
@@ -513,7 +511,6 @@ int enqueue_redo(ivf_index* ix, const float* q_dev, int nq, int nprobe, int k, i
 
 // ---- batched (list-major) search ----------------------------------------------------------------
 constexpr int kCandCap = 65536;          // candidates a query may collect in the batched scan
-constexpr int kSurvCap = 4096;           // of those, rows re-scored in fp64
 
 bool batched_eligible(const ivf_index* ix, int nq) {
     if (ix->batch_mode == 1 || nq < 2) return false;
@@ -529,13 +526,13 @@ int ensure_batched_workspace(ivf_index* ix, int nq, int nprobe) {
     if (nq <= w.b_nq && nprobe <= w.b_nprobe) return IVF_OK;
     const int nq2 = std::max(nq, w.b_nq), np2 = std::max(nprobe, w.b_nprobe);
     HIP_TRY(hipDeviceSynchronize());
-    dfree(w.d_thr_part); dfree(w.d_cand_score); dfree(w.d_eps); dfree(w.d_surv_row); dfree(w.d_qq);
+    dfree(w.d_thr_part); dfree(w.d_cand_score); dfree(w.d_eps); dfree(w.d_qq);
     dfree(w.d_q_store); dfree(w.d_thr); dfree(w.d_list_count); dfree(w.d_cursor); dfree(w.d_qstart);
     dfree(w.d_tstart); dfree(w.d_qidx); dfree(w.d_tasks); dfree(w.d_cand_count); dfree(w.d_cand_row);
-    dfree(w.d_cand_key); dfree(w.d_overflow); hfree(w.h_overflow);
-    w.d_thr_part = nullptr; w.d_cand_score = nullptr; w.d_eps = nullptr; w.d_surv_row = nullptr; w.d_qq = nullptr;
+    hfree(w.h_overflow);
+    w.d_thr_part = nullptr; w.d_cand_score = nullptr; w.d_eps = nullptr; w.d_qq = nullptr;
     w.d_q_store = nullptr; w.d_thr = nullptr; w.d_list_count = w.d_cursor = w.d_qstart = w.d_tstart = w.d_qidx = nullptr;
-    w.d_tasks = nullptr; w.d_cand_count = w.d_cand_row = nullptr; w.d_cand_key = nullptr; w.d_overflow = w.h_overflow = nullptr;
+    w.d_tasks = nullptr; w.d_cand_count = w.d_cand_row = nullptr; w.h_overflow = w.hd_overflow = nullptr;
     w.b_nq = w.b_nprobe = 0;
     const size_t nqz = nq2, nl = ix->nlist;
     const uint64_t task_cap = batched_task_bound(ix->h_off.data(), ix->nlist, nq2, ix->dtype);
@@ -553,32 +550,30 @@ int ensure_batched_workspace(ivf_index* ix, int nq, int nprobe) {
     HIP_TRY(hipMalloc(&w.d_cand_row, nqz * kCandCap * sizeof(uint32_t)));
     HIP_TRY(hipMalloc(&w.d_cand_score, nqz * kCandCap * sizeof(float)));
     HIP_TRY(hipMalloc(&w.d_eps, nqz * sizeof(float)));
-    HIP_TRY(hipMalloc(&w.d_surv_row, nqz * kSurvCap * sizeof(uint32_t)));
-    HIP_TRY(hipMalloc(&w.d_cand_key, nqz * kSurvCap * sizeof(uint64_t)));
-    HIP_TRY(hipMalloc(&w.d_overflow, nqz * sizeof(int32_t)));
     HIP_TRY(hipHostMalloc(&w.h_overflow, nqz * sizeof(int32_t)));
+    HIP_TRY(hipHostGetDevicePointer((void**)&w.hd_overflow, w.h_overflow, 0));
     w.b_nq = nq2; w.b_nprobe = np2;
     return IVF_OK;
 }
 
 // the parts of the batched scan's arguments that do not depend on the call
 static void fill_batched_args(const ivf_index* ix, const Workspace& w, BatchedArgs& b) {
-    b.lists = ix->d_buf; b.off = ix->d_off; b.ids = ix->d_ids; b.probe = w.d_probe;
+    b.lists = ix->d_buf; b.off = ix->d_off; b.ids = ix->d_ids; b.probe = w.d_probe; b.rprefix = w.slots.rprefix;
     b.q_store = w.d_q_store; b.thr = w.d_thr; b.thr_part = w.d_thr_part; b.row_norm_max_bits = ix->d_row_norm_max;
     b.list_count = w.d_list_count; b.cursor = w.d_cursor; b.qstart = w.d_qstart; b.tstart = w.d_tstart;
     b.ticket = w.d_list_count + ix->nlist + 1;
     b.qidx = w.d_qidx; b.tasks = w.d_tasks; b.cand_count = w.d_cand_count; b.cand_row = w.d_cand_row;
-    b.cand_key = w.d_cand_key; b.cand_score = w.d_cand_score; b.eps = w.d_eps; b.qq = w.d_qq; b.row_norm = ix->d_row_norm;
-    b.surv_row = w.d_surv_row; b.overflow = w.d_overflow;
+    b.cand_score = w.d_cand_score; b.eps = w.d_eps; b.qq = w.d_qq; b.row_norm = ix->d_row_norm;
+    b.overflow = w.hd_overflow;
     b.nlist = ix->nlist; b.d = ix->d; b.dtype = ix->dtype; b.metric = ix->metric;
-    b.cand_cap = kCandCap; b.surv_cap = kSurvCap;
+    b.cand_cap = kCandCap;
     b.group_q = batched_group_q(ix->dtype);
     b.acc_coef = (float)ix->d * 0x1p-23f;            // d products accumulated in fp32, in an order the hardware chooses
     b.samp_coef = batched_sample_coef(ix->d, ix->dtype, ix->metric);
 }
 
 // coarse + select for the batch, then the list-major scan and the final ranking into (out_ids,
-// out_dists) (device pointers); the overflow flags land in the workspace
+// out_dists) (as the device addresses them); the overflow flags land in the workspace's pinned array
 int enqueue_batched(ivf_index* ix, const float* q_dev, int nq, int nprobe, int k, int64_t* out_ids, float* out_dists) {
     Workspace& w = *ix->cw;
     int rc;
@@ -594,7 +589,6 @@ int enqueue_batched(ivf_index* ix, const float* q_dev, int nq, int nprobe, int k
     if ((rc = prof_events(ix, 3, &m0, &m1))) return rc;
     HIP_TRY(launch_batched(b, ix->batched_grid, ix->cs, e0, e1));
     if (m0) { HIP_TRY(hipEventRecord(m0, ix->cs)); HIP_TRY(hipEventRecord(m1, ix->cs)); }
-    HIP_TRY(hipMemcpyAsync(w.h_overflow, w.d_overflow, (size_t)nq * sizeof(int32_t), hipMemcpyDeviceToHost, ix->cs));
     return IVF_OK;
 }
 
@@ -1072,9 +1066,10 @@ extern "C" int ivf_search(ivf_index* ix, const float* q_out, int32_t nq, int32_t
     if ((rc = stage_queries(ix, q_out, nq))) return rc;
     if (batched_eligible(ix, nq)) {
         // list-major batched search: every selected cluster is read once per group of 32 queries
-        if ((rc = run_batched(ix, 0, w.d_q, nq, nprobe, k, w.d_out_ids, w.d_out_dists, false))) return rc;
-        HIP_TRY(hipMemcpy(ids, w.d_out_ids, (size_t)nq * k * sizeof(int64_t), hipMemcpyDeviceToHost));
-        HIP_TRY(hipMemcpy(dists, w.d_out_dists, (size_t)nq * k * sizeof(float), hipMemcpyDeviceToHost));
+        // (the merge kernel stores the results in the pinned buffers itself: no copies to wait for)
+        if ((rc = run_batched(ix, 0, w.d_q, nq, nprobe, k, w.hd_out_ids, w.hd_out_dists, false))) return rc;
+        memcpy(ids, w.h_out_ids, (size_t)nq * k * sizeof(int64_t));
+        memcpy(dists, w.h_out_dists, (size_t)nq * k * sizeof(float));
         if (stats) {
             HIP_TRY(hipMemcpy(w.h_probe, w.d_probe, (size_t)nq * nprobe * sizeof(int32_t), hipMemcpyDeviceToHost));
             std::vector<uint8_t> seen(ix->nlist, 0);

@@ -15,6 +15,7 @@
 // of the filter score (query rounded to the storage type, fp32 accumulation, rounded norms).
 // Every true top-k row passes this filter.
 #include "ivf_device.h"
+#include "../../include/ivf.h"
 #include <hip/hip_ext.h>
 #include <algorithm>
 
@@ -72,11 +73,12 @@ hipError_t launch_row_norms(const void* lists, int dtype, int64_t n, int d, unsi
 // scores one part of a query's threshold sample: fp32 scores (fp32 query; <q, y>, or -sum (q - y)^2
 // for L2) of the first rows of the query's (at most 64 nearest) selected clusters, taken in probe order
 // (usually all from the nearest cluster; more clusters when those are small).  Any subset of the
-// selected rows gives a valid lower bound of the k-th best score over all of them.  How many: half
-// the mean size of the eight nearest clusters, but at least 512 and 8 k, at most 2048.  The k-th
-// best of S rows out of n alike ones lets about k n / S of them pass, so S may be small where the
-// clusters are; the bytes of the sample are what this launch costs (32 queries x 768 fp32: 2048
-// rows 37 us, 512 13; 256 queries x 1024 bf16 with k 100: 2048 rows 190 us, 800 104).
+// selected rows gives a valid lower bound of the k-th best score over all of them.  How many: the
+// k-th best of S rows out of n alike ones lets about k n / S of them pass, so S may be small where
+// the clusters are: half the mean size of the eight nearest, but at least 512 and 8 k, and so many
+// that a query whose selected rows are all alike fills half of its candidate list; at most 2048.
+// The bytes of the sample are what this launch costs (32 queries x 768 fp32: 2048 rows 37 us, 512
+// 13; 256 queries x 1024 bf16 with k 100: 2048 rows 190 us, 800 104).
 // A wavefront scores four rows, all of them in flight: the sample is bound by the bytes of its
 // rows when there are many queries and by the memory round trips in front of them when there are
 // few.  One more workgroup per query rounds the query to the storage type.
@@ -252,7 +254,9 @@ __global__ __launch_bounds__(kFrontThreads) void batch_front_kernel(BatchedArgs 
         return lo_i + (int64_t)(r - (end_i - n_i));
     };
     __syncthreads();
-    const uint32_t want = min(max(read_lane(my_end, min(7, a.nprobe - 1)) / 16, max(512u, 8u * (uint32_t)a.k)), (uint32_t)kSampleRows);
+    const uint32_t rows = a.rprefix[(size_t)qi * (a.nprobe + 1) + a.nprobe];
+    const uint32_t at_least = (uint32_t)((uint64_t)rows * (uint64_t)a.k * 2u / (uint64_t)a.cand_cap);
+    const uint32_t want = min(max(max(read_lane(my_end, min(7, a.nprobe - 1)) / 16, at_least), max(512u, 8u * (uint32_t)a.k)), (uint32_t)kSampleRows);
     const int chunks = a.d / EPL;
 #pragma unroll 1
     for (uint32_t r0 = (uint32_t)(part * kSampleStep + wave * U); r0 < (uint32_t)kSampleRows; r0 += (uint32_t)(parts * kSampleStep)) {
@@ -746,143 +750,233 @@ __global__ __launch_bounds__(kBatchThreads) void batched_scan_f32_kernel(Batched
 }
 
 // ---- final ranking of a query's candidates ------------------------------------------------------------------
-// One workgroup per query: candidates are first pruned by their approximate scores, the survivors
-// are re-scored in fp64 (fp32 query), and the k best by (score, id) come from a radix select on
-// the 64-bit keys and a rank-by-counting.
+// One workgroup per query.  Candidates are pruned by their approximate scores, each within eps of the
+// exact one: with t = the k-th best of them, a row of the true top k has an approximate score of at
+// least t - 2 eps.  The survivors are re-scored in fp64 (fp32 query), in the order of operations of
+// the query-by-query merge, and the k best by (score, id) are ranked by counting.  When there are
+// many survivors those that reach t go first: with s = the smallest of their exact scores the true
+// k-th best is at least s, and of the others only the rows that reach s - eps can matter (about half
+// of them).  Everything lives in LDS and nothing is sorted: bucket cuts leave a few more than k.
+// What bounds it: the re-scores' trips to memory (two rows per group of lanes in flight), and in a
+// batch the query with the most survivors.  (Radix selects over candidates and re-scores in global
+// memory, one row in flight per group: 13, 17 and 140 us for 8, 32 and 256 queries with k 3, 10 and
+// 100; this: 10, 12 and 61.)
+// A query whose candidates or survivors do not fit sets its overflow flag and is searched again.
+constexpr int kRescoreInFlight = 2;
+constexpr uint32_t kSurvivorsAtOnce = kSelectThreads / kRescoreLanes * kRescoreInFlight * 2;     // up to here: no second look
+
+// How many of the n values of an LDS array are above `me` and how many equal it: eight lanes per
+// value, `sub` is the lane's number in its group; every lane of the group gets the counts.
+template <typename V>
+__device__ __forceinline__ void count_above(const V* a, uint32_t n, V me, uint32_t sub, uint32_t& above, uint32_t& equal) {
+    uint32_t ab = 0, eq = 0;
+#pragma unroll 1
+    for (uint32_t j0 = sub; j0 < n; j0 += 32) {
+        V o[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) o[u] = a[min(j0 + 8u * u, n - 1)];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            ab += (uint32_t)((o[u] > me) & (j0 + 8u * u < n));
+            eq += (uint32_t)((o[u] == me) & (j0 + 8u * u < n));
+        }
+    }
+    ab += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)ab, 0xB1, 0xF, 0xF, true);
+    eq += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)eq, 0xB1, 0xF, 0xF, true);
+    ab += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)ab, 0x4E, 0xF, 0xF, true);
+    eq += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)eq, 0x4E, 0xF, 0xF, true);
+    ab += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)ab, 0x141, 0xF, 0xF, true);
+    eq += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)eq, 0x141, 0xF, 0xF, true);
+    above = ab; equal = eq;
+}
+
 __global__ __launch_bounds__(kSelectThreads) void batched_merge_kernel(BatchedArgs a) {
-    __shared__ uint32_t hist[256];
-    __shared__ uint32_t sh[8];
-    __shared__ double f_key[2 * kMaxKPrime];
-    __shared__ int64_t f_id[2 * kMaxKPrime];
-    __shared__ unsigned long long best;
-    const int tid = threadIdx.x, nt = blockDim.x, lane = lane_id();
-    const int qi = blockIdx.x, k = a.k;
-    const uint32_t raw = a.cand_count[qi];
-    if (raw > (uint32_t)a.cand_cap) {                  // too many candidates: the host redoes this query
+    __shared__ uint64_t s_key[kBatchSurvivors];     // ordered(fp64 score): larger is nearer
+    __shared__ uint32_t s_row[kBatchSurvivors];
+    __shared__ uint32_t hist[256], red[96];
+    __shared__ uint32_t s_n, s_m, s_kth;
+    __shared__ unsigned long long s_low;
+    __shared__ int64_t o_id[IVF_MAX_K];
+    __shared__ float o_dist[IVF_MAX_K];
+    const int tid = threadIdx.x, lane = lane_id();
+    constexpr int nt = kSelectThreads;
+    const int qi = blockIdx.x;
+    const uint32_t k = (uint32_t)a.k;
+    const uint32_t n0 = a.cand_count[qi];
+    if (n0 > (uint32_t)a.cand_cap) {                   // too many candidates: the host redoes this query
         if (tid == 0) a.overflow[qi] = 1;
         return;
     }
-    // 1. prune by the approximate scores: with t = the k-th best approximate score, a row of the
-    //    true top k has an approximate score of at least t - 2 eps (each score is within eps of
-    //    the exact one), so only those rows are re-scored.
-    const uint32_t n0 = raw;
     const float* sc = a.cand_score + (size_t)qi * a.cand_cap;
     const uint32_t* rows0 = a.cand_row + (size_t)qi * a.cand_cap;
-    uint32_t* rows = a.surv_row + (size_t)qi * a.surv_cap;
-    auto skey = [&](uint32_t i) { return ~ordered(sc[i]); };      // ascending key = best first
-    if (tid == 0) { sh[4] = 0; sh[5] = 0; sh[6] = 0; }
-    __syncthreads();
-    float cut = -INFINITY;
-    if (n0 > (uint32_t)k) {
-        uint32_t mask, prefix, need, group;
-        block_radix_select<uint32_t>(skey, n0, (uint32_t)k, hist, sh, mask, prefix, need, group);
-        // key of the k-th best: the largest kept key
-        uint32_t worst = 0;
-        for (uint32_t i = tid; i < n0; i += nt) {
-            uint32_t ky = skey(i), hi = ky & mask;
-            if (hi < prefix || hi == prefix) worst = max(worst, (need == group || hi < prefix) ? ky : prefix);
-        }
-#pragma unroll
-        for (int m2 = 32; m2 >= 1; m2 >>= 1) worst = max(worst, (uint32_t)__shfl_xor((int)worst, m2));
-        if (lane == 0) atomicMax(&sh[6], worst);
-        __syncthreads();
-        const uint32_t o = ~sh[6];                        // ordered(float) of the k-th best approximate score
-        const float kth = __uint_as_float((o & 0x80000000u) ? (o & 0x7FFFFFFFu) : ~o);
-        cut = kth - 2.f * a.eps[qi];
-    }
-    for (uint32_t i0 = 0; i0 < n0; i0 += nt) {
-        uint32_t i = i0 + tid;
-        bool ok = i < n0 && sc[i] >= cut;
-        uint64_t bal = __ballot(ok);
+    // reserves a place behind counter `n` for every lane with ok
+    auto place = [&](uint32_t& n, bool ok) -> uint32_t {
+        const uint64_t b = __ballot(ok);
+        if (!b) return 0;
         uint32_t base = 0;
-        if (lane == 0 && bal) base = atomicAdd(&sh[5], (uint32_t)__popcll(bal));
-        base = read_lane(base, 0);
-        uint32_t p = base + __popcll(bal & ((1ull << lane) - 1ull));
-        if (ok && p < (uint32_t)a.surv_cap) rows[p] = rows0[i];
+        if (lane == 0) base = atomicAdd(&n, (uint32_t)__popcll(b));
+        return read_lane(base, 0) + __popcll(b & ((1ull << lane) - 1ull));
+    };
+    // four candidates per thread are requested together; the first four stay in registers
+    constexpr int C = 4;
+    auto read_scores = [&](uint32_t i0, float (&v)[C]) {
+#pragma unroll
+        for (int u = 0; u < C; ++u)
+            if (i0 + (uint32_t)(u * nt) < n0) v[u] = sc[min(i0 + (uint32_t)(u * nt + tid), n0 - 1)];
+    };
+    float first[C];
+    read_scores(0, first);
+    const uint32_t row_first = n0 ? rows0[min((uint32_t)tid, n0 - 1)] : 0u;
+    auto for_scores = [&](auto&& use) {
+#pragma unroll
+        for (int u = 0; u < C; ++u)
+            if ((uint32_t)(u * nt) < n0) use((uint32_t)(u * nt + tid), first[u]);
+#pragma unroll 1
+        for (uint32_t i0 = C * nt; i0 < n0; i0 += C * nt) {
+            float v[C];
+            read_scores(i0, v);
+#pragma unroll
+            for (int u = 0; u < C; ++u)
+                if (i0 + (uint32_t)(u * nt) < n0) use(i0 + (uint32_t)(u * nt + tid), v[u]);
+        }
+    };
+    const float eps = a.eps[qi];
+    const uint32_t sub8 = (uint32_t)tid & 7u;
+    // 1. the k-th best approximate score
+    float kth = -INFINITY;
+    if (tid == 0) { s_n = 0; s_m = 0; s_kth = 0xFFFFFFFFu; s_low = ~0ull; }
+    if (n0 > k) {
+        // the candidates are dealt to the threads: as many threads' best reach the cut of those as
+        // were asked for, so at least k candidates do, and not many more
+        uint32_t mine = 0;
+        for_scores([&](uint32_t i, float v) { mine = max(mine, i < n0 ? ordered(v) : 0u); });
+        const BucketCut bc = block_bucket_cut([&](uint32_t) { return mine; }, (uint32_t)nt, k, hist, red);
+        __syncthreads();
+        uint32_t* pool = s_row;                        // ordered scores that pass the cut
+        for_scores([&](uint32_t i, float v) {
+            const bool ok = i < n0 && bc.pass(ordered(v));
+            const uint32_t pos = place(s_n, ok);
+            if (ok && pos < (uint32_t)kBatchSurvivors) pool[pos] = ordered(v);
+        });
+        __syncthreads();
+        // masses of equal scores may let more pass than the pool holds: the smallest of those stored
+        // that has fewer than k above it is then still a lower bound of the k-th best
+        const uint32_t m = min(s_n, (uint32_t)kBatchSurvivors);
+        for (uint32_t t = (uint32_t)tid / 8; t < m; t += nt / 8) {
+            const uint32_t me = pool[t];
+            uint32_t above, equal;
+            count_above(pool, m, me, sub8, above, equal);
+            if (sub8 == 0 && above < k) atomicMin(&s_kth, me);
+        }
+        __syncthreads();
+        kth = unordered(s_kth);
+        if (tid == 0) s_n = 0;
     }
     __syncthreads();
-    const uint32_t n = sh[5];
-    if (n > (uint32_t)a.surv_cap) {                    // cannot happen unless scores are massively tied
+    // 2. survivors: those that reach the k-th best from the front, the others from the back, these
+    //    with their approximate score in the place of the exact one
+    const float cut = kth - 2.f * eps;
+    for_scores([&](uint32_t i, float v) {
+        const bool ok = i < n0 && v >= cut, top = ok && v >= kth;
+        const uint32_t row = i < (uint32_t)nt ? row_first : ok ? rows0[i] : 0u;
+        const uint32_t front = place(s_n, top), back = place(s_m, ok && !top);
+        if (top && front < (uint32_t)kBatchSurvivors) s_row[front] = row;
+        if (ok && !top && back < (uint32_t)kBatchSurvivors) {
+            s_row[kBatchSurvivors - 1 - back] = row;
+            s_key[kBatchSurvivors - 1 - back] = ordered(v);
+        }
+    });
+    __syncthreads();
+    const uint32_t n_top = s_n, n_back = s_m;
+    if (n_top + n_back > (uint32_t)kBatchSurvivors) {  // cannot happen unless scores are massively tied
         if (tid == 0) a.overflow[qi] = 1;
         return;
     }
-    if (tid == 0) a.overflow[qi] = 0;
-    // 2. fp64 re-score of the survivors
-    uint64_t* keys = a.cand_key + (size_t)qi * a.surv_cap;
+    // 3. fp64 re-scores of survivors c0 .. c1 - 1: a group of lanes per survivor, two rows in flight
     const float* q = a.q + (size_t)qi * a.d;
-    // a group of lanes per survivor, so that their row loads overlap; the same order of operations
-    // as the query-by-query merge
-    constexpr int kLpc = kRescoreLanes;
-    const int sub = tid % kLpc;
+    const bool whole = ((size_t)a.d * (a.dtype == 0 ? 4 : 2)) % 16 == 0;
+    const int sub = tid % kRescoreLanes;
+    auto rescore = [&](uint32_t c0, uint32_t c1) {
+        constexpr uint32_t groups = nt / kRescoreLanes;
 #pragma unroll 1
-    for (uint32_t c = (uint32_t)(tid / kLpc); c < n; c += (uint32_t)(nt / kLpc)) {
-        const double s = rescore_row(a.lists, q, a.d, a.dtype, a.metric, rows[c], sub);
-        if (sub == 0) keys[c] = ~ordered(a.metric == 0 ? s : -s);            // ascending key = best first
-    }
-    __syncthreads();
-    const uint32_t want = min((uint32_t)k, n);
-    if (tid == 0) sh[4] = 0;
-    __syncthreads();
-    auto key_at = [&](uint32_t i) { return keys[i]; };
-    auto id_at = [&](uint32_t i) { return a.ids ? a.ids[rows[i]] : (int64_t)rows[i]; };
-    auto emit = [&](uint32_t i) {
-        uint32_t p = atomicAdd(&sh[4], 1u);
-        if (p < 2 * kMaxKPrime) { f_key[p] = unordered(~keys[i]); f_id[p] = id_at(i); }
+        for (uint32_t c = c0 + (uint32_t)(tid / kRescoreLanes); c < c1; c += groups * kRescoreInFlight) {
+            double s[kRescoreInFlight];
+            uint32_t row[kRescoreInFlight];
+#pragma unroll
+            for (int r = 0; r < kRescoreInFlight; ++r) row[r] = s_row[min(c + groups * r, c1 - 1)];
+            if (whole) rescore_rows<kRescoreInFlight>(a.lists, q, a.d, a.dtype, a.metric, row, sub, s);
+            else {
+#pragma unroll
+                for (int r = 0; r < kRescoreInFlight; ++r) s[r] = rescore_row(a.lists, q, a.d, a.dtype, a.metric, row[r], sub);
+            }
+#pragma unroll
+            for (int r = 0; r < kRescoreInFlight; ++r)
+                if (sub == 0 && c + groups * r < c1) s_key[c + groups * r] = ordered(a.metric == 0 ? s[r] : -s[r]);
+        }
     };
-    if (want > 0) {
-        uint64_t mask, prefix; uint32_t need, group;
-        block_radix_select<uint64_t>(key_at, n, want, hist, sh, mask, prefix, need, group);
-        const bool take_group = need == group;
-        for (uint32_t i = tid; i < n; i += nt) {
-            uint64_t hi = keys[i] & mask;
-            if (hi < prefix || (take_group && hi == prefix)) emit(i);
+    // the others come to the front, all of them or those that reach `low`
+    auto gather_back = [&](float low) -> uint32_t {
+        uint32_t row[kBatchSurvivors / nt];
+        bool ok[kBatchSurvivors / nt];
+#pragma unroll
+        for (int u = 0; u < kBatchSurvivors / nt; ++u) {
+            const uint32_t i = (uint32_t)(u * nt + tid);
+            ok[u] = i < n_back && unordered((uint32_t)s_key[kBatchSurvivors - 1 - min(i, (uint32_t)kBatchSurvivors - 1)]) >= low;
+            row[u] = s_row[kBatchSurvivors - 1 - min(i, (uint32_t)kBatchSurvivors - 1)];
         }
         __syncthreads();
-        if (!take_group) {
-            long long last = -1;
-            for (uint32_t it = 0; it < need; ++it) {
-                if (tid == 0) best = ~0ull;
-                __syncthreads();
-                for (uint32_t i = tid; i < n; i += nt)
-                    if ((keys[i] & mask) == prefix) { long long id = id_at(i); if (id > last) atomicMin(&best, (unsigned long long)id); }
-                __syncthreads();
-                unsigned long long b = best;
-                if (b == ~0ull) break;
-                last = (long long)b;
-                for (uint32_t i = tid; i < n; i += nt)
-                    if ((keys[i] & mask) == prefix && id_at(i) == last) emit(i);
-                __syncthreads();
-            }
+#pragma unroll
+        for (int u = 0; u < kBatchSurvivors / nt; ++u) {
+            const uint32_t pos = place(s_n, ok[u]);
+            if (ok[u]) s_row[pos] = row[u];
         }
-    }
-    __syncthreads();
-    const uint32_t tot = min(sh[4], (uint32_t)(2 * kMaxKPrime));
-    if ((uint32_t)tid < tot) {
-        double mk = f_key[tid]; int64_t mi = f_id[tid];
-        uint32_t rank = 0;
-        // eight others per pass, all read before any is compared, and no branches
+        __syncthreads();
+        return s_n;
+    };
+    const bool at_once = n_top + n_back <= kSurvivorsAtOnce;
+    uint32_t done = 0, n = n_top;
 #pragma unroll 1
-        for (uint32_t j0 = 0; j0 < tot; j0 += 8) {
-            double ok[8]; int64_t oi[8];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const uint32_t j = min(j0 + u, tot - 1);
-                ok[u] = f_key[j]; oi[u] = f_id[j];
+    for (int look = at_once ? 1 : 0; look < 2; ++look) {
+        if (look == 1) {
+            float low = -INFINITY;
+            if (!at_once) {
+                for (uint32_t t = tid; t < n_top; t += nt) atomicMin(&s_low, (unsigned long long)s_key[t]);
+                __syncthreads();
+                low = nextafterf((float)(unordered((uint64_t)s_low) - 1.0001 * (double)eps), -INFINITY);
             }
-#pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const bool ahead = (ok[u] > mk) | ((ok[u] == mk) & (oi[u] < mi));
-                rank += (uint32_t)(ahead & (j0 + u < tot));
-            }
+            n = gather_back(low);
         }
-        if (rank < (uint32_t)k) {
-            a.out_ids[(size_t)qi * k + rank] = mi;
-            a.out_dists[(size_t)qi * k + rank] = (float)(a.metric == 0 ? mk : -mk);
-        }
+        rescore(done, n);
+        done = n;
+        __syncthreads();
     }
-    for (uint32_t i = tot + tid; i < (uint32_t)k; i += nt) {
-        a.out_ids[(size_t)qi * k + i] = -1;
-        a.out_dists[(size_t)qi * k + i] = a.metric == 0 ? -INFINITY : INFINITY;
+    // 4. many: only those that pass a bucket cut over the high halves can be among the k best
+    BucketCut bc;
+    bc.lo = 0u; bc.scale = 0.f; bc.cut = 0u; bc.passing = n;
+    if (n > 512) bc = block_bucket_cut([&](uint32_t i) { return (uint32_t)(s_key[i] >> 32); }, n, k, hist, red);
+    // 5. rank by counting, nearest first, ties by smaller id (the ids are looked at only on a tie)
+    auto id_at = [&](uint32_t i) { return a.ids ? a.ids[s_row[i]] : (int64_t)s_row[i]; };
+    for (uint32_t t = (uint32_t)tid / 8; t < n; t += nt / 8) {
+        const uint64_t me = s_key[t];
+        if (!bc.pass((uint32_t)(me >> 32))) continue;
+        uint32_t rank, equal;
+        count_above(s_key, n, me, sub8, rank, equal);
+        if (sub8 != 0 || rank >= k) continue;
+        const int64_t id = id_at(t);
+        if (__builtin_expect(equal > 1, 0)) {
+            for (uint32_t j = 0; j < n; ++j) rank += (uint32_t)(s_key[j] == me && id_at(j) < id);
+            if (rank >= k) continue;
+        }
+        const double key = unordered(me);
+        o_id[rank] = id;
+        o_dist[rank] = (float)(a.metric == 0 ? key : -key);
+    }
+    if (tid == 0) a.overflow[qi] = 0;
+    __syncthreads();
+    // in order: the outputs may be host memory
+    for (uint32_t i = tid; i < k; i += nt) {
+        a.out_ids[(size_t)qi * k + i] = i < n ? o_id[i] : -1;
+        a.out_dists[(size_t)qi * k + i] = i < n ? o_dist[i] : (a.metric == 0 ? -INFINITY : INFINITY);
     }
 }
 

@@ -139,41 +139,45 @@ __device__ __forceinline__ double widen(const void* base, int dtype, size_t idx)
 // the same scheme over single elements.
 constexpr int kRescoreLanes = 32;
 
-// Partial fp64 score of one stored row over the 16-byte chunks sub, sub + lpc, ... (lane `sub`
-// of a group of `lpc` lanes); several loads are in flight at a time.
-template <typename T>
-__device__ __forceinline__ double rescore_partial(const unsigned char* row, const float* q, int d, int metric,
-                                                  int sub, int lpc) {
+// Partial fp64 scores of R stored rows over the 16-byte chunks sub, sub + lpc, ... (lane `sub`
+// of a group of `lpc` lanes); several loads are in flight at a time, those of all rows together.
+template <typename T, int R>
+__device__ __forceinline__ void rescore_partial(const unsigned char* const (&row)[R], const float* q, int d, int metric,
+                                                int sub, int lpc, double (&acc)[R]) {
     constexpr int EPL = T::kPerLoad;
     constexpr int U = EPL == 4 ? 6 : 4;        // 768 fp32 values over 32 lanes: one pass
     const int chunks = d / EPL;
-    double acc = 0.0;
+#pragma unroll
+    for (int r = 0; r < R; ++r) acc[r] = 0.0;
 #pragma unroll 1
     for (int c0 = sub; c0 < chunks; c0 += lpc * U) {
-        uint4 v[U];
+        uint4 v[R][U];
         float qv[U][EPL];
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const int c = min(c0 + u * lpc, chunks - 1);
-            v[u] = *(const uint4*)(row + (size_t)c * 16);
+#pragma unroll
+            for (int r = 0; r < R; ++r) v[r][u] = *(const uint4*)(row[r] + (size_t)c * 16);
 #pragma unroll
             for (int e = 0; e < EPL; e += 4) *(float4*)&qv[u][e] = *(const float4*)(q + (size_t)c * EPL + e);
         }
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             if (c0 + u * lpc < chunks) {
-                float x[EPL];
-                Unpack<T>::run(v[u], x);
 #pragma unroll
-                for (int e = 0; e < EPL; ++e) {
-                    const double qd = (double)qv[u][e], y = (double)x[e];
-                    if (metric == 0) acc = fma(qd, y, acc);
-                    else { const double df = qd - y; acc = fma(df, df, acc); }
+                for (int r = 0; r < R; ++r) {
+                    float x[EPL];
+                    Unpack<T>::run(v[r][u], x);
+#pragma unroll
+                    for (int e = 0; e < EPL; ++e) {
+                        const double qd = (double)qv[u][e], y = (double)x[e];
+                        if (metric == 0) acc[r] = fma(qd, y, acc[r]);
+                        else { const double df = qd - y; acc[r] = fma(df, df, acc[r]); }
+                    }
                 }
             }
         }
     }
-    return acc;
 }
 
 // fp64 score of the stored row `brow` of the buffer for the query q, computed by a group of
@@ -186,9 +190,12 @@ __device__ __forceinline__ double rescore_row(const void* buf, const float* q, i
     const unsigned char* rp = (const unsigned char*)buf + brow * row_bytes;
     double s = 0.0;
     if (row_bytes % 16 == 0) {
-        if (dtype == 0) s = rescore_partial<F32>(rp, q, d, metric, sub, lpc);
-        else if (dtype == 1) s = rescore_partial<F16>(rp, q, d, metric, sub, lpc);
-        else s = rescore_partial<BF16>(rp, q, d, metric, sub, lpc);
+        const unsigned char* const one[1] = {rp};
+        double acc[1];
+        if (dtype == 0) rescore_partial<F32, 1>(one, q, d, metric, sub, lpc, acc);
+        else if (dtype == 1) rescore_partial<F16, 1>(one, q, d, metric, sub, lpc, acc);
+        else rescore_partial<BF16, 1>(one, q, d, metric, sub, lpc, acc);
+        s = acc[0];
     } else {
         const size_t e0 = brow * (size_t)d;
 #pragma unroll 1
@@ -201,6 +208,26 @@ __device__ __forceinline__ double rescore_row(const void* buf, const float* q, i
 #pragma unroll 1
     for (int o = 1; o < lpc; o <<= 1) s += __shfl_xor(s, o);
     return s;
+}
+
+// The same for R rows at once, whole 16-byte chunks only: their loads overlap, every row's order of
+// operations is that of rescore_row.
+template <int R>
+__device__ __forceinline__ void rescore_rows(const void* buf, const float* q, int d, int dtype, int metric,
+                                             const uint32_t (&brow)[R], int sub, double (&s)[R]) {
+    constexpr int lpc = kRescoreLanes;
+    const size_t row_bytes = (size_t)d * (dtype == 0 ? 4 : 2);
+    const unsigned char* rp[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) rp[r] = (const unsigned char*)buf + brow[r] * row_bytes;
+    if (dtype == 0) rescore_partial<F32, R>(rp, q, d, metric, sub, lpc, s);
+    else if (dtype == 1) rescore_partial<F16, R>(rp, q, d, metric, sub, lpc, s);
+    else rescore_partial<BF16, R>(rp, q, d, metric, sub, lpc, s);
+#pragma unroll 1
+    for (int o = 1; o < lpc; o <<= 1) {
+#pragma unroll
+        for (int r = 0; r < R; ++r) s[r] += __shfl_xor(s[r], o);
+    }
 }
 
 // ---- order-preserving integer keys ------------------------------------------------------------

@@ -159,6 +159,7 @@ hipError_t launch_schedule(const float* q_dev, int B, int d, int m, double* dist
 constexpr int kScheduleMaxQueries = 4096;
 
 // ---- batched (list-major) search: ivf_batched.hip ------------------------------------------------
+constexpr int kBatchSurvivors = 4096;      // candidates of a query that are re-scored in fp64
 struct BatchTask { uint32_t cluster, group, tile; };    // tile: 256 rows of the cluster; group: up to 32 (fp32 rows: 16) of the queries probing it
 
 struct BatchedArgs {
@@ -167,6 +168,7 @@ struct BatchedArgs {
     const int64_t* ids;          // [n] or nullptr
     const float* q;              // [nq x d] fp32 queries
     const int32_t* probe;        // [nq x nprobe] selected clusters
+    const uint32_t* rprefix;     // [nq x (nprobe+1)] SlotTables::rprefix: the last entry is a query's selected rows
     void* q_store;               // [nq x d] queries rounded to the storage type (out)
     float* thr;                  // [nq] out: filter threshold
     uint32_t* thr_part;          // [batched_sample_words(nq)] ordered scores of the threshold sample, 0 = none
@@ -184,12 +186,11 @@ struct BatchedArgs {
     float* eps;                  // [nq] bound of |approximate - exact| score
     float* qq;                   // [nq] squared norms of the queries
     const float* row_norm;       // [n] squared norms of the rows (L2 only)
-    uint32_t* surv_row;          // [nq x surv_cap] rows that survive the pruning by approximate score
-    uint64_t* cand_key;          // [nq x surv_cap] fp64 re-scores as ascending keys
-    int32_t* overflow;           // [nq] 1 when a query had more candidates than cand_cap
+    int32_t* overflow;           // [nq] 1 when a query had more candidates than cand_cap or more survivors than
+                                 // kBatchSurvivors (host memory, read once the stream has passed the merge)
     int64_t* out_ids; float* out_dists;      // [nq x k]
     unsigned long long* rows_counter;        // nullable: rows covered by the scan tasks (profiling)
-    int nlist, d, dtype, metric, nq, nprobe, k, kprime, cand_cap, surv_cap;
+    int nlist, d, dtype, metric, nq, nprobe, k, kprime, cand_cap;
     int group_q;                 // queries per task: batched_group_q(dtype)
     float acc_coef;              // fp32 accumulation of the MFMA: |error| <= acc_coef |q| |y|
     float samp_coef;             // batched_sample_coef(d, dtype, metric)

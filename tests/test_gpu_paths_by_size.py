@@ -105,3 +105,30 @@ def test_front_of_a_list_major_batch(streams, nlist, nq, nprobe, k, d):
     pi, pd = index.ivf_search(q, nprobe, k)
     assert np.array_equal(bi, pi) and np.array_equal(bd, pd)
     index.close()
+
+
+@pytest.mark.parametrize("dtype,metric,k", [("bf16", "ip", 112), ("f16", "l2", 10), ("f32", "ip", 100)])
+@pytest.mark.parametrize("band", [3, 120, 700, 4500])
+def test_survivors_of_a_list_major_batch(streams, dtype, metric, k, band):
+    """`band` rows per query score within the filter's error of each other, a third of them exact
+    copies: fewer survivors than k, one look, two looks, and more than the merge holds (the query is
+    searched again).  List-major equals query by query bit for bit."""
+    rng = np.random.default_rng(band + k)
+    d, nlist, nq = 128, 6, 9
+    cent = rng.standard_normal((nlist, d)).astype(np.float32)
+    rows = 0.2 * rng.standard_normal((nlist * 5000, d)).astype(np.float32)
+    assign = (np.arange(rows.shape[0]) % nlist).astype(np.int32)
+    for c in range(nlist):
+        at = np.nonzero(assign == c)[0][rng.permutation(5000)[:band]]
+        rows[at] = cent[c] + 1e-4 * rng.standard_normal((band, d)).astype(np.float32)
+        rows[at[:band // 3]] = rows[at[0]]
+    st, _ = stored(rows, dtype)
+    index = P.ivf_build_layout(st, dtype, cent, assign, metric=P.IVF_IP if metric == "ip" else P.IVF_L2,
+                               compute_stream=streams[0], copy_stream=streams[1])
+    q = (cent[np.arange(nq) % nlist] + 1e-3 * rng.standard_normal((nq, d))).astype(np.float32)
+    index.ivf_set_batch_mode(2)
+    bi, bd = index.ivf_search(q, 4, k)
+    index.ivf_set_batch_mode(1)
+    pi, pd = index.ivf_search(q, 4, k)
+    assert np.array_equal(bi, pi) and np.array_equal(bd, pd)
+    index.close()
