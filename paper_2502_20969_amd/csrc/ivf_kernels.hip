@@ -286,53 +286,113 @@ __device__ __forceinline__ void select_sorted(const SelectArgs& a, const double*
     block_bitonic_sort(keys, idx, pad);
 }
 
-// The nprobe nearest by a bucket cut (see block_bucket_cut) over the high halves of the keys: the
-// clusters that pass the cut (the nprobe nearest and a few more) are pooled with their full keys
-// and each counts the pooled clusters ahead of it by (key, index); the first nprobe take their
-// places in idx.  Exact, with no sorting network.  Returns false (for the whole workgroup) when
-// more clusters pass than the pool holds (masses of equal scores); idx is then untouched.
-constexpr int kSelectPoolCap = 1024;
-constexpr int kSelectCutMax = 512;          // largest nprobe this path takes
-__device__ __forceinline__ bool select_by_cut(const SelectArgs& a, const double* sc, uint32_t* idx, uint64_t* pool_key,
-                                              uint32_t* pool_idx, uint32_t* hist, uint32_t* red, uint32_t* sh) {
-    const int tid = threadIdx.x, nt = blockDim.x;
-    const uint32_t nlist = a.nlist, nprobe = a.nprobe;
-    auto key_at = [&](uint32_t i) { return coarse_key(sc[i], a.metric); };
-    // larger = nearer; never 0, so that every cluster counts
-    auto near_at = [&](uint32_t i) -> uint32_t { const uint32_t v = (uint32_t)(~key_at(i) >> 32); return v ? v : 1u; };
-    if (tid == 0) sh[4] = 0;
-    const BucketCut bc = block_bucket_cut(near_at, nlist, nprobe, hist, red);
-    if (bc.passing > (uint32_t)kSelectPoolCap) return false;
-    for (uint32_t i = tid; i < nlist; i += nt) {
-        if (bc.pass(near_at(i))) {
-            const uint32_t p = atomicAdd(&sh[4], 1u);
-            pool_key[p] = key_at(i); pool_idx[p] = i;
-        }
-    }
+// The nprobe nearest by packed candidates (top 40 bits of the descending key image, complement of
+// the cluster index: larger = nearer).  The candidates are dealt to the threads; a bucket cut over
+// the threads' best lets at least nprobe of those pass, so at least nprobe candidates do, and, with
+// 8 candidates per thread and half the threads' best wanted, about a third more than that.  Those are
+// pooled, sorted in runs of 64 by the wavefronts (registers only), and each finds its place by a
+// binary search in every run.  The order of the prefixes is the order of the scores wherever
+// prefixes differ: on a tie among the selected clusters or across the cut, and when more pass than
+// the pool holds, the result is not used: returns false (for the whole workgroup), idx is then
+// undefined.  Bound by barriers and dependent LDS reads of one workgroup.  (Ranking the pool by
+// counting on 64-bit keys, with the histogram taken over all scores: 18, 31 and 95 us for 8 queries
+// of 2048 lists with nprobe 128, 32 of 4096 with 128 and 256 of 8192 with 512; this: 11, 12 and 24.)
+constexpr int kSelectPoolCap = 2048;
+__device__ __forceinline__ bool select_pooled(const SelectArgs& a, const double* sc, uint32_t* idx, Cand* pool, Cand* sel,
+                                              uint32_t* hist, uint32_t* red, uint32_t* sh) {
+    const int tid = threadIdx.x, nt = blockDim.x, lane = lane_id(), wave = wave_id();
+    const uint32_t nprobe = a.nprobe;
+    auto packed = [&](int i, double s) {
+        return (~coarse_key(s, a.metric) & ~0xFFFFFFull) | (uint64_t)(0xFFFFFFu - (uint32_t)i);
+    };
+    // the first eight scores of a thread are requested together and stay in registers
+    constexpr int C = 8;
+    double s8[C];
+#pragma unroll
+    for (int j = 0; j < C; ++j) s8[j] = sc[min(tid + j * nt, a.nlist - 1)];
+    if (tid == 0) { sh[4] = 0; sh[6] = 0; }
+    auto nearness = [&](double s) { return (float)(a.metric == 0 ? s : -s); };
+    float best = -INFINITY;
+#pragma unroll
+    for (int j = 0; j < C; ++j) if (tid + j * nt < a.nlist) best = fmaxf(best, nearness(s8[j]));
+#pragma unroll 1
+    for (int i = tid + C * nt; i < a.nlist; i += nt) best = fmaxf(best, nearness(sc[i]));
+    // the cut is taken on scores mapped linearly to integers: bit images of scores around zero leave
+    // all the exponents between them to one bucket
+    float lo = tid < a.nlist ? best : INFINITY, hi = best;
+#pragma unroll
+    for (int m = 32; m >= 1; m >>= 1) { lo = fminf(lo, __shfl_xor(lo, m)); hi = fmaxf(hi, __shfl_xor(hi, m)); }
+    float* ends = (float*)red;
+    if (lane == 0) { ends[wave] = lo; ends[16 + wave] = hi; }
+    __syncthreads();
+    for (int w = 0; w < nt >> 6; ++w) { lo = fminf(lo, ends[w]); hi = fmaxf(hi, ends[16 + w]); }
+    const float scale = hi > lo ? 4.0e9f / (hi - lo) : 0.f;
+    if (!(hi - lo < INFINITY) || !(scale < INFINITY)) return false;       // infinities, or all but equal scores
+    auto level = [&](float f) -> uint32_t { return f > lo ? 1u + (uint32_t)((f - lo) * scale) : 1u; };
+    __syncthreads();                                    // ends has been read
+    const BucketCut bc = block_bucket_cut([&](uint32_t) { return tid < a.nlist ? level(best) : 0u; }, (uint32_t)nt, nprobe, hist, red);
+    auto offer = [&](int i, double s) {
+        const bool ok = i < a.nlist && bc.pass(level(nearness(s)));
+        const uint64_t bal = __ballot(ok);
+        if (!bal) return;
+        uint32_t base = 0;
+        if (lane == 0) base = atomicAdd(&sh[4], (uint32_t)__popcll(bal));
+        base = read_lane(base, 0);
+        const uint32_t pos = base + __popcll(bal & ((1ull << lane) - 1ull));
+        if (ok && pos < (uint32_t)kSelectPoolCap) pool[pos] = packed(i, s);
+    };
+#pragma unroll
+    for (int j = 0; j < C; ++j) offer(tid + j * nt, s8[j]);
+#pragma unroll 1
+    for (int i0 = C * nt; i0 < a.nlist; i0 += nt) offer(i0 + tid, sc[min(i0 + tid, a.nlist - 1)]);
     __syncthreads();
     const uint32_t cnt = sh[4];
+    if (cnt > (uint32_t)kSelectPoolCap) return false;
+    const int runs = (int)((cnt + 63) / 64);
 #pragma unroll 1
-    for (uint32_t t = tid; t < cnt; t += nt) {
-        const uint64_t mk = pool_key[t];
-        const uint32_t mi = pool_idx[t];
-        uint32_t rank = 0;
-        // eight others per pass, all read before any is compared
+    for (int r = wave; r < runs; r += nt >> 6) {
+        const uint32_t e = (uint32_t)(r * 64 + lane);
+        pool[e] = bitonic_sort64<true>(e < cnt ? pool[e] : (Cand)0);
+    }
+    if (tid == 0) sel[nprobe] = 0;                      // fewer than nprobe + 1 pooled: nothing behind the last
+    __syncthreads();
 #pragma unroll 1
-        for (uint32_t j0 = 0; j0 < cnt; j0 += 8) {
-            uint64_t ok[8]; uint32_t oi[8];
+    for (uint32_t t = tid; t < (uint32_t)runs * 64; t += nt) {
+        const Cand me = pool[t];
+        uint32_t rank = 0;                              // candidates ahead of this one
+#pragma unroll 1
+        for (int r0 = 0; r0 < runs; r0 += 4) {
+            // four runs at a time: their reads overlap
+            uint32_t at[4] = {0, 0, 0, 0};
 #pragma unroll
-            for (int u = 0; u < 8; ++u) { const uint32_t j = min(j0 + u, cnt - 1); ok[u] = pool_key[j]; oi[u] = pool_idx[j]; }
+            for (int st = 32; st >= 1; st >>= 1) {
+                Cand o[4];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) rank += (uint32_t)(((ok[u] < mk) | ((ok[u] == mk) & (oi[u] < mi))) & (j0 + u < cnt));
+                for (int u = 0; u < 4; ++u) o[u] = pool[min(r0 + u, runs - 1) * 64 + at[u] + st - 1];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) at[u] += o[u] > me ? st : 0;
+            }
+            Cand o[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) o[u] = pool[min(r0 + u, runs - 1) * 64 + at[u]];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) rank += r0 + u < runs ? at[u] + (o[u] > me ? 1u : 0u) : 0u;
         }
-        if (rank < nprobe) idx[rank] = mi;
+        if (me != 0 && rank <= nprobe) sel[rank] = me;
     }
     __syncthreads();
-    return true;
+#pragma unroll 1
+    for (uint32_t i = tid; i < nprobe; i += nt) {
+        const Cand c = sel[i];
+        idx[i] = 0xFFFFFFu - (uint32_t)(c & 0xFFFFFFull);
+        if ((c >> 24) == (sel[i + 1] >> 24)) sh[6] = 1;
+    }
+    __syncthreads();
+    return sh[6] == 0;
 }
 
 __global__ __launch_bounds__(kSelectThreads) void select_kernel(SelectArgs a, uint32_t pad, int in_lds,
-                                                                int prefix_in_lds, int by_cut) {
+                                                                int prefix_in_lds, int pooled) {
     extern __shared__ __align__(16) unsigned char smem_raw[];
     __shared__ uint32_t hist[256];
     __shared__ uint32_t sh[8];
@@ -474,9 +534,9 @@ __global__ __launch_bounds__(kSelectThreads) void select_kernel(SelectArgs a, ui
         uint64_t* keys = (uint64_t*)smem_raw;
         idx = (uint32_t*)(smem_raw + sizeof(uint64_t) * pad);
         bool done = false;
-        if (by_cut) {
-            uint64_t* pool_key = (uint64_t*)(((uintptr_t)(smem_raw + sort_bytes + (size_t)(nprobe + 1) * 4) + 15) & ~(uintptr_t)15);
-            done = select_by_cut(a, sc, idx, pool_key, (uint32_t*)(pool_key + kSelectPoolCap), hist, red, sh);
+        if (pooled) {
+            Cand* pool = (Cand*)(((uintptr_t)(smem_raw + sort_bytes + (size_t)(nprobe + 1) * 4) + 15) & ~(uintptr_t)15);
+            done = select_pooled(a, sc, idx, pool, pool + kSelectPoolCap, hist, red, sh);
         }
         if (!done) {
             __syncthreads();
@@ -608,14 +668,17 @@ hipError_t launch_select(const SelectArgs& a, hipStream_t s, hipEvent_t e0, hipE
     uint32_t pad = select_sort_pad(a.nlist, a.nprobe);
     int in_lds = pad <= (uint32_t)kSortLdsCap;
     int prefix_in_lds = a.nprobe <= kPrefixLdsCap;
-    // a workgroup with one wavefront per SIMD issues fastest when there is little work per thread
-    const int threads = a.nlist <= 1024 && a.grid <= 1024 ? 256 : kSelectThreads;
+    // a workgroup with one wavefront per SIMD issues fastest when there is little work per thread (up
+    // to 64 clusters wanted; more are ranked by all wavefronts: 256 of 1000 lists 23 us with 4, 12 with 16)
+    const int threads = a.nlist <= 1024 && a.grid <= 1024 && a.nprobe <= 64 ? 256 : kSelectThreads;
     size_t lds = (in_lds ? (size_t)pad * 12 : 0) + (prefix_in_lds ? (size_t)(a.nprobe + 1) * 4 : 0);
     const bool wave_sort = in_lds && a.nprobe <= 64 && a.nlist <= kSelectWaveSortMax;
-    const int by_cut = in_lds && !wave_sort && a.nprobe <= kSelectCutMax;
+    // the pool holds what passes the cut for up to 512 of any number of clusters, and all of 1024 (for
+    // 1000 of 2048 lists it would rank 2048: 50 us against 32 of the sorting network below)
+    const int pooled = in_lds && !wave_sort && a.nlist <= 0xFFFFFF && (a.nprobe <= 512 || a.nlist <= 1024);
     if (wave_sort) lds += 16 + (size_t)threads * 8 + 66 * 8 + (size_t)threads * 8;      // pool, the ranked few, the threads' best
-    if (by_cut) lds += 16 + (size_t)kSelectPoolCap * 12;
-    IVF_LAUNCH(select_kernel, dim3(a.nq), dim3(threads), lds, s, e0, e1, a, pad, in_lds, prefix_in_lds, by_cut);
+    if (pooled) lds += 16 + ((size_t)kSelectPoolCap + a.nprobe + 1) * 8;
+    IVF_LAUNCH(select_kernel, dim3(a.nq), dim3(threads), lds, s, e0, e1, a, pad, in_lds, prefix_in_lds, pooled);
     return hipGetLastError();
 }
 

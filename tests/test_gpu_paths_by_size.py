@@ -132,3 +132,31 @@ def test_survivors_of_a_list_major_batch(streams, dtype, metric, k, band):
     pi, pd = index.ivf_search(q, 4, k)
     assert np.array_equal(bi, pi) and np.array_equal(bd, pd)
     index.close()
+
+
+@pytest.mark.parametrize("metric", ["ip", "l2"])
+@pytest.mark.parametrize("nlist,nprobe", [(65, 65), (1000, 257), (1024, 1024), (2049, 512), (8191, 65), (8193, 512), (16500, 300), (4097, 3)])
+@pytest.mark.parametrize("kind", ["random", "one_side", "ties", "infinite"])
+def test_select_of_many_clusters(streams, nlist, nprobe, kind, metric):
+    """Selections through the pooled path: scores around zero, scores far from zero, masses of equal
+    scores (the pool overflows or prefixes tie: the exact path) and infinite ones; order and content
+    are the oracle's."""
+    rng = np.random.default_rng(nlist + nprobe)
+    d = 8
+    cent = rng.standard_normal((nlist, d)).astype(np.float32)
+    q = rng.standard_normal((3, d)).astype(np.float32)
+    if kind == "one_side":
+        cent, q = np.abs(cent) + 3.0, np.abs(q) + 1.0
+    elif kind == "ties":
+        cent = np.round(cent)
+        cent[rng.permutation(nlist)[:nlist // 2]] = cent[0]
+    elif kind == "infinite":
+        cent[rng.permutation(nlist)[:nprobe // 2]] *= np.float32(1e30)
+        q *= np.float32(1e30)
+    rows = torch.zeros(nlist, d, device="cuda")
+    index = P.ivf_adopt_layout(rows, "f32", np.arange(nlist + 1), cent, metric=P.IVF_IP if metric == "ip" else P.IVF_L2,
+                               compute_stream=streams[0], copy_stream=streams[1])
+    pr = index.ivf_probe(q, nprobe)
+    for b in range(3):
+        assert list(pr[b]) == list(O.probe(cent, q[b], nprobe, O.IP if metric == "ip" else O.L2))
+    index.close()
