@@ -164,7 +164,7 @@ struct ivf_index {
     int batch_mode = 0;                       // 0 auto, 1 always query by query, 2 list-major when eligible
     unsigned int* d_row_norm_max = nullptr;   // largest squared row norm (float bits); device placement
     float* d_row_norm = nullptr;              // squared norm of every row; device placement with squared L2
-    ScanShape shape{0, 0, 0, 4};
+    ScanShape shape{0, 0, 0, 4, 0};
     // Searches through ivf_search_device rotate over `lanes` (stream + workspace each) so that
     // independent queries overlap; lane 0 runs on compute_stream.  cs / cw: lane in use.
     // What a lane still owes for its last call (settle_lane).  A list-major batch: the queries whose

@@ -67,6 +67,14 @@ __device__ __forceinline__ uint4 load_stream16(const void* p) {
     return make_uint4(t.x, t.y, t.z, t.w);
 }
 
+// The same from an address that is aligned to elements of 2 or 4 bytes only (the hardware takes
+// 16-byte loads at any address).
+typedef u4_t u4_any_t __attribute__((aligned(2)));
+__device__ __forceinline__ uint4 load_stream16_any(const void* p) {
+    u4_t t = __builtin_nontemporal_load((const u4_any_t*)p);
+    return make_uint4(t.x, t.y, t.z, t.w);
+}
+
 __device__ __forceinline__ void store_stream16(void* p, const uint4& v) {
     u4_t t = {v.x, v.y, v.z, v.w};
     __builtin_nontemporal_store(t, (u4_t*)p);
@@ -198,11 +206,22 @@ __device__ __forceinline__ double rescore_row(const void* buf, const float* q, i
         s = acc[0];
     } else {
         const size_t e0 = brow * (size_t)d;
+        // four elements of a lane are requested together and added in order
 #pragma unroll 1
-        for (int t = sub; t < d; t += lpc) {
-            const double x = (double)q[t], y = widen(buf, dtype, e0 + t);
-            if (metric == 0) s = fma(x, y, s);
-            else { const double df = x - y; s = fma(df, df, s); }
+        for (int t0 = sub; t0 < d; t0 += 4 * lpc) {
+            double x[4], y[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const int t = min(t0 + u * lpc, d - 1);
+                x[u] = (double)q[t]; y[u] = widen(buf, dtype, e0 + t);
+            }
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                if (t0 + u * lpc < d) {
+                    if (metric == 0) s = fma(x[u], y[u], s);
+                    else { const double df = x[u] - y[u]; s = fma(df, df, s); }
+                }
+            }
         }
     }
 #pragma unroll 1

@@ -38,6 +38,7 @@ struct ScanShape {
     int segments;        // 16-byte loads per lane per row
     int unroll;          // row groups per batch
     int rows_per_batch;
+    int tail;            // 1: rows are not whole 16-byte chunks
 };
 ScanShape pick_scan_shape(int d, int dtype);
 

@@ -828,7 +828,12 @@ __device__ __forceinline__ void write_wave_list(WaveTopK<KL, false>& top, const 
     if (lane == 0) p.heads[list] = head;
 }
 
-template <typename T, int LPR, int SEG, int U, int METRIC, int KL>
+// TAIL: rows that are not whole 16-byte chunks, and therefore start at any element.  The lane with
+// the last, partial chunk of a row loads the 16 bytes that END with the row and clears the elements
+// that the lane before it has already, in its slice of the query and in every chunk it loads: no
+// load leaves the row.  (One element per lane and row at a time, 34,500 rows of 300 fp16: 30.1 us;
+// this: 12.4.)
+template <typename T, int LPR, int SEG, int U, int METRIC, int KL, bool TAIL>
 __global__ __launch_bounds__(kScanThreads) void scan_kernel(ScanArgs p) {
     constexpr int EPL = T::kPerLoad;
     constexpr int RPI = 64 / LPR;
@@ -838,8 +843,19 @@ __global__ __launch_bounds__(kScanThreads) void scan_kernel(ScanArgs p) {
     const int qi = blockIdx.y;
     const size_t row_bytes = (size_t)p.d * T::kBytes;
 
-    // This lane's slice of the query (rows of this kernel are whole 16-byte chunks, so d is a
-    // multiple of EPL).  It is requested right AFTER the tables: loads return in order, and the
+    // first element of this lane's chunk `sg` in memory: the chunk's place, or for a partial one EPL
+    // elements before the end of the row (TAIL; d is at least EPL, else a multiple of it)
+    auto place = [&](int col) { return TAIL ? min(col, p.d - EPL) : col; };
+    const int tail_seg = TAIL ? ((p.d + EPL - 1) / EPL - 1) / LPR : 0;
+    uint32_t keep[4] = {~0u, ~0u, ~0u, ~0u};          // TAIL: the elements of the chunk in segment tail_seg that count
+    if (TAIL) {
+        const int col = (tail_seg * LPR + sub) * EPL, skip = col - place(col);       // above EPL: the lane has no chunk
+#pragma unroll
+        for (int e = 0; e < EPL; ++e)
+            if (e < skip) keep[e * T::kBytes / 4] &= T::kBytes == 4 ? 0u : (e & 1) ? 0x0000FFFFu : 0xFFFF0000u;
+    }
+
+    // This lane's slice of the query.  It is requested right AFTER the tables: loads return in order, and the
     // tables decide where the rows are, so nothing should arrive before them; the query is needed
     // only when the first rows are there.  (Measured: query first 16.8 us, tables first 16.5,
     // query after the first rows 16.6 - 16.9.)
@@ -849,11 +865,19 @@ __global__ __launch_bounds__(kScanThreads) void scan_kernel(ScanArgs p) {
 #pragma unroll
         for (int sg = 0; sg < SEG; ++sg) {
             const int col = (sg * LPR + sub) * EPL;
+            if (TAIL) {
 #pragma unroll
-            for (int e = 0; e < EPL; e += 4) {
-                float4 t = make_float4(0.f, 0.f, 0.f, 0.f);
-                if (col < p.d) t = *(const float4*)(q + col + e);
-                qv[sg][e] = t.x; qv[sg][e + 1] = t.y; qv[sg][e + 2] = t.z; qv[sg][e + 3] = t.w;
+                for (int e = 0; e < EPL; ++e) {
+                    const int c = place(col) + e;
+                    qv[sg][e] = col < p.d && c >= col ? q[c] : 0.f;
+                }
+            } else {
+#pragma unroll
+                for (int e = 0; e < EPL; e += 4) {
+                    float4 t = make_float4(0.f, 0.f, 0.f, 0.f);
+                    if (col < p.d) t = *(const float4*)(q + col + e);
+                    qv[sg][e] = t.x; qv[sg][e + 1] = t.y; qv[sg][e + 2] = t.z; qv[sg][e + 3] = t.w;
+                }
             }
         }
     };
@@ -876,7 +900,7 @@ __global__ __launch_bounds__(kScanThreads) void scan_kernel(ScanArgs p) {
 #pragma unroll
             for (int sg = 0; sg < SEG; ++sg) {
                 int col = (sg * LPR + sub) * EPL;
-                if (col < p.d) v[u][sg] = load_stream16(rp + (size_t)col * T::kBytes);
+                if (col < p.d) v[u][sg] = TAIL ? load_stream16_any(rp + (size_t)place(col) * T::kBytes) : load_stream16(rp + (size_t)col * T::kBytes);
                 else v[u][sg] = make_uint4(0, 0, 0, 0);
             }
         }
@@ -889,7 +913,9 @@ __global__ __launch_bounds__(kScanThreads) void scan_kernel(ScanArgs p) {
 #pragma unroll
             for (int sg = 0; sg < SEG; ++sg) {
                 float x[EPL];
-                Unpack<T>::run(v[u][sg], x);
+                uint4 w = v[u][sg];
+                if (TAIL && sg == tail_seg) { w.x &= keep[0]; w.y &= keep[1]; w.z &= keep[2]; w.w &= keep[3]; }
+                Unpack<T>::run(w, x);
 #pragma unroll
                 for (int e = 0; e < EPL; ++e) {
                     if (METRIC == 0) s = fmaf(qv[sg][e], x[e], s);
@@ -941,7 +967,7 @@ __global__ __launch_bounds__(kScanThreads) void scan_kernel(ScanArgs p) {
     write_wave_list<KL>(top, p, qi);
 }
 
-// Fallback for any d and any row alignment: element-wise loads, query in LDS, 4 rows per batch.
+// Fallback for rows of less than 16 bytes and of more than 8 KB: element-wise loads, query in LDS, 4 rows per batch.
 template <int METRIC, int KL>
 __global__ __launch_bounds__(kScanThreads) void scan_generic_kernel(ScanArgs p) {
     extern __shared__ __align__(16) unsigned char smem[];
@@ -995,8 +1021,8 @@ static const ShapeOpt kShapes[] = {{16, 1, 6}, {32, 1, 6}, {64, 1, 6}, {32, 3, 2
 ScanShape pick_scan_shape(int d, int dtype) {
     const int esz = dtype == 0 ? 4 : 2;
     const size_t row_bytes = (size_t)d * esz;
-    if (row_bytes % 16 != 0) return ScanShape{0, 0, 0, 4};
-    const int chunks = (int)(row_bytes / 16);
+    if (row_bytes < 16) return ScanShape{0, 0, 0, 4, 0};
+    const int chunks = (int)((row_bytes + 15) / 16);
     int best = -1, best_waste = 1 << 30;
     for (int i = 0; i < (int)(sizeof(kShapes) / sizeof(kShapes[0])); ++i) {
         int cap = kShapes[i].lpr * kShapes[i].seg;
@@ -1004,23 +1030,23 @@ ScanShape pick_scan_shape(int d, int dtype) {
         int waste = cap - chunks;
         if (waste < best_waste) { best = i; best_waste = waste; }
     }
-    if (best < 0) return ScanShape{0, 0, 0, 4};
+    if (best < 0) return ScanShape{0, 0, 0, 4, 0};
     return ScanShape{kShapes[best].lpr, kShapes[best].seg, kShapes[best].u,
-                     kShapes[best].u * (64 / kShapes[best].lpr)};
+                     kShapes[best].u * (64 / kShapes[best].lpr), row_bytes % 16 != 0};
 }
 
 typedef void (*ScanFn)(ScanArgs);
 
-template <typename T, int LPR, int SEG, int U>
+template <typename T, int LPR, int SEG, int U, bool TAIL>
 static ScanFn scan_fn_shape(int metric, bool big) {
-    if (metric == 0) return big ? (ScanFn)scan_kernel<T, LPR, SEG, U, 0, 2> : (ScanFn)scan_kernel<T, LPR, SEG, U, 0, 1>;
-    return big ? (ScanFn)scan_kernel<T, LPR, SEG, U, 1, 2> : (ScanFn)scan_kernel<T, LPR, SEG, U, 1, 1>;
+    if (metric == 0) return big ? (ScanFn)scan_kernel<T, LPR, SEG, U, 0, 2, TAIL> : (ScanFn)scan_kernel<T, LPR, SEG, U, 0, 1, TAIL>;
+    return big ? (ScanFn)scan_kernel<T, LPR, SEG, U, 1, 2, TAIL> : (ScanFn)scan_kernel<T, LPR, SEG, U, 1, 1, TAIL>;
 }
 
 template <typename T>
 static ScanFn scan_fn_dtype(const ScanShape& sh, int metric, bool big) {
     const int l = sh.lanes_per_row, g = sh.segments;
-#define IVF_SHAPE(L, G, UU) if (l == L && g == G) return scan_fn_shape<T, L, G, UU>(metric, big);
+#define IVF_SHAPE(L, G, UU) if (l == L && g == G) return sh.tail ? scan_fn_shape<T, L, G, UU, true>(metric, big) : scan_fn_shape<T, L, G, UU, false>(metric, big);
     IVF_SHAPE(16, 1, 6) IVF_SHAPE(32, 1, 6) IVF_SHAPE(64, 1, 6) IVF_SHAPE(32, 3, 2)
     IVF_SHAPE(64, 2, 3) IVF_SHAPE(64, 3, 2) IVF_SHAPE(64, 4, 2) IVF_SHAPE(64, 8, 1)
 #undef IVF_SHAPE

@@ -160,3 +160,28 @@ def test_select_of_many_clusters(streams, nlist, nprobe, kind, metric):
     for b in range(3):
         assert list(pr[b]) == list(O.probe(cent, q[b], nprobe, O.IP if metric == "ip" else O.L2))
     index.close()
+
+
+@pytest.mark.parametrize("metric", ["ip", "l2"])
+@pytest.mark.parametrize("dtype,d", [("f32", 3), ("f32", 5), ("f32", 63), ("f32", 65), ("f32", 129), ("f32", 333), ("f32", 770), ("f32", 2047),
+                                     ("f16", 7), ("f16", 9), ("f16", 127), ("f16", 129), ("f16", 300), ("f16", 513), ("bf16", 31),
+                                     ("bf16", 767), ("bf16", 1030), ("bf16", 4095)])
+def test_rows_that_are_not_whole_chunks(streams, dtype, d, metric):
+    """Every scan shape with a partial last chunk, rows at every alignment, an infinite element in
+    the part that two lanes load; the last row ends where the buffer does.  The oracle's results."""
+    rng = np.random.default_rng(d)
+    n, nlist, k = 331, 5, 12
+    om = O.IP if metric == "ip" else O.L2
+    cent = rng.standard_normal((nlist, d)).astype(np.float32)
+    assign = rng.integers(0, nlist, n).astype(np.int32)
+    rows = (cent[assign] + rng.standard_normal((n, d))).astype(np.float32)
+    rows[7, d - 2] = -np.inf if metric == "ip" else np.inf
+    st, odt = stored(rows, dtype)
+    index = P.ivf_build_layout(st, dtype, cent, assign, metric=P.IVF_IP if metric == "ip" else P.IVF_L2,
+                               compute_stream=streams[0], copy_stream=streams[1])
+    off, perm = O.build_layout(assign, nlist)
+    q = np.abs(rng.standard_normal((4, d))).astype(np.float32)
+    gi, gd = index.ivf_search(q, nlist, k)
+    for b in range(4):
+        assert check_topk(gi[b], gd[b], st[perm], odt, off, perm.astype(np.int64), cent, q[b], nlist, k, om) == 0
+    index.close()
