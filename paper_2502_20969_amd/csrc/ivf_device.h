@@ -75,6 +75,13 @@ __device__ __forceinline__ uint4 load_stream16_any(const void* p) {
     return make_uint4(t.x, t.y, t.z, t.w);
 }
 
+// Four floats from an address that is aligned to one float.
+typedef float f4_any_t __attribute__((ext_vector_type(4), aligned(4)));
+__device__ __forceinline__ float4 load_float4_any(const float* p) {
+    const f4_any_t t = *(const f4_any_t*)p;
+    return make_float4(t.x, t.y, t.z, t.w);
+}
+
 __device__ __forceinline__ void store_stream16(void* p, const uint4& v) {
     u4_t t = {v.x, v.y, v.z, v.w};
     __builtin_nontemporal_store(t, (u4_t*)p);
@@ -206,17 +213,17 @@ __device__ __forceinline__ double rescore_row(const void* buf, const float* q, i
         s = acc[0];
     } else {
         const size_t e0 = brow * (size_t)d;
-        // four elements of a lane are requested together and added in order
+        // eight elements of a lane are requested together and added in order
 #pragma unroll 1
-        for (int t0 = sub; t0 < d; t0 += 4 * lpc) {
-            double x[4], y[4];
+        for (int t0 = sub; t0 < d; t0 += 8 * lpc) {
+            double x[8], y[8];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
+            for (int u = 0; u < 8; ++u) {
                 const int t = min(t0 + u * lpc, d - 1);
                 x[u] = (double)q[t]; y[u] = widen(buf, dtype, e0 + t);
             }
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
+            for (int u = 0; u < 8; ++u) {
                 if (t0 + u * lpc < d) {
                     if (metric == 0) s = fma(x[u], y[u], s);
                     else { const double df = x[u] - y[u]; s = fma(df, df, s); }

@@ -25,6 +25,8 @@ using namespace dev;
 constexpr int kCoarseRowMaxIp = 3, kCoarseRowMaxL2 = 16;
 constexpr int kSelectWaveSortMax = 4096;   // select: register sorting path up to this many clusters
 
+// RAGGED: d is no multiple of 4, rows start at any element.
+template <bool RAGGED>
 __global__ __launch_bounds__(256) void coarse_rows_kernel(CoarseArgs a) {
     const int lane = lane_id(), wave = wave_id();
     const int row = blockIdx.x * 4 + wave;
@@ -34,24 +36,28 @@ __global__ __launch_bounds__(256) void coarse_rows_kernel(CoarseArgs a) {
     for (int qi = 0; qi < a.nq; ++qi) {
         const float* q = a.q + (size_t)qi * a.d;
         double acc = 0.0;
-        if ((a.d & 3) == 0) {
+        if (!RAGGED || a.d >= 4) {
+            // a chunk that the end of the row cuts short is taken from the four elements that end it,
+            // less those that the lane before has
 #pragma unroll 1
             for (int t0 = lane * 4; t0 < a.d; t0 += 1024) {
                 float4 cv[4], qv[4];
 #pragma unroll
                 for (int u = 0; u < 4; ++u) {
                     const int t = min(t0 + u * 256, a.d - 4);
-                    cv[u] = *(const float4*)(c + t);
-                    qv[u] = *(const float4*)(q + t);
+                    cv[u] = RAGGED ? load_float4_any(c + t) : *(const float4*)(c + t);
+                    qv[u] = RAGGED ? load_float4_any(q + t) : *(const float4*)(q + t);
                 }
 #pragma unroll
                 for (int u = 0; u < 4; ++u) {
                     if (t0 + u * 256 < a.d) {
+                        const int skip = RAGGED ? max(t0 + u * 256 - (a.d - 4), 0) : 0;
                         const float ce[4] = {cv[u].x, cv[u].y, cv[u].z, cv[u].w};
                         const float qe[4] = {qv[u].x, qv[u].y, qv[u].z, qv[u].w};
 #pragma unroll
                         for (int e = 0; e < 4; ++e) {
-                            const double x = (double)qe[e], y = (double)ce[e];
+                            const bool out = RAGGED && e < skip;
+                            const double x = out ? 0.0 : (double)qe[e], y = out ? 0.0 : (double)ce[e];
                             if (a.metric == 0) acc = fma(x, y, acc);
                             else { const double df = x - y; acc = fma(df, df, acc); }
                         }
@@ -81,11 +87,13 @@ __global__ __launch_bounds__(256) void coarse_rows_kernel(CoarseArgs a) {
 // through the elements, not the matrix cores.  (Tiles of 32 x 128 that walked all elements through
 // LDS slabs, a barrier pair per 32: 52.7, 55.5 and 117 us for 16 queries x 1024 x 768, 32 x 4096 x 768
 // and 256 x 8192 x 1024; this: 8.2, 12.6 and 94; the fp64 matrix peak for the last is 55 us.)
+// RAGGED: d is no multiple of 4, rows start at any element (the row kernel served such batches with
+// single elements: 272 and 1120 us for 256 queries x 2678 x 295 and x 8192 x 747; this: 20 and 75).
 // Workgroups that follow each other on one XCD share their centroids (blockIdx % 8 is the XCD):
 // each L2 then holds one eighth of the centroids instead of all of them.
 // For the squared distance the norms are accumulated beside the products: |q - c|^2 = |q|^2 + |c|^2 - 2 q.c.
 typedef double double4_t __attribute__((ext_vector_type(4)));
-template <int QT, int CT, int W>
+template <int QT, int CT, int W, bool RAGGED>
 __global__ __launch_bounds__(W * 64) void coarse_mfma_kernel(CoarseArgs a, int q_tiles) {
     extern __shared__ __align__(16) unsigned char smem_raw[];
     typedef double SumTile[QT * CT][4][64];
@@ -118,11 +126,17 @@ __global__ __launch_bounds__(W * 64) void coarse_mfma_kernel(CoarseArgs a, int q
 #pragma unroll
         for (int h = 0; h < 2; ++h) {
             const int k = k0 + h * 16;
-            const bool in = k + fk * 4 < a.d;          // d is a multiple of 4
+            const int left = a.d - (k + fk * 4);       // elements from this lane's first on
+            auto take = [&](const float* p) {
+                if (!RAGGED) return left > 0 ? *(const float4*)p : make_float4(0.f, 0.f, 0.f, 0.f);
+                if (left >= 4) return load_float4_any(p);
+                // the row ends inside the chunk or before it
+                return make_float4(left > 0 ? p[0] : 0.f, left > 1 ? p[1] : 0.f, left > 2 ? p[2] : 0.f, 0.f);
+            };
 #pragma unroll
-            for (int x = 0; x < QT; ++x) s.q[h][x] = in ? *(const float4*)(qrow[x] + k) : make_float4(0.f, 0.f, 0.f, 0.f);
+            for (int x = 0; x < QT; ++x) s.q[h][x] = take(qrow[x] + k);
 #pragma unroll
-            for (int y = 0; y < CT; ++y) s.c[h][y] = in ? *(const float4*)(crow[y] + k) : make_float4(0.f, 0.f, 0.f, 0.f);
+            for (int y = 0; y < CT; ++y) s.c[h][y] = take(crow[y] + k);
         }
     };
     auto multiply = [&](const Stage& s) {
@@ -205,12 +219,15 @@ template <int QT, int CT, int W>
 static void launch_coarse_mfma(const CoarseArgs& a, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
     const int q_tiles = (a.nq + QT * 16 - 1) / (QT * 16), c_tiles = (a.nlist + CT * 16 - 1) / (CT * 16);
     const size_t lds = (size_t)W * (QT * CT * 4 * 64 + QT * 16 + CT * 16) * sizeof(double);
-    IVF_LAUNCH((coarse_mfma_kernel<QT, CT, W>), dim3((unsigned)((c_tiles + 7) / 8 * 8 * q_tiles)), dim3(W * 64), lds, s, e0, e1, a, q_tiles);
+    const dim3 grid((unsigned)((c_tiles + 7) / 8 * 8 * q_tiles));
+    if (a.d & 3) IVF_LAUNCH((coarse_mfma_kernel<QT, CT, W, true>), grid, dim3(W * 64), lds, s, e0, e1, a, q_tiles);
+    else IVF_LAUNCH((coarse_mfma_kernel<QT, CT, W, false>), grid, dim3(W * 64), lds, s, e0, e1, a, q_tiles);
 }
 
 hipError_t launch_coarse(const CoarseArgs& a, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
-    if (a.nq < (a.metric == 0 ? kCoarseRowMaxIp : kCoarseRowMaxL2) || (a.d & 3) != 0) {
-        IVF_LAUNCH(coarse_rows_kernel, dim3((a.nlist + 3) / 4), dim3(256), 0, s, e0, e1, a);
+    if (a.nq < (a.metric == 0 ? kCoarseRowMaxIp : kCoarseRowMaxL2)) {
+        if (a.d & 3) IVF_LAUNCH(coarse_rows_kernel<true>, dim3((a.nlist + 3) / 4), dim3(256), 0, s, e0, e1, a);
+        else IVF_LAUNCH(coarse_rows_kernel<false>, dim3((a.nlist + 3) / 4), dim3(256), 0, s, e0, e1, a);
     } else {
         // Small tiles while they leave the chip short of work, measured with 1024, 4096 and 8192 lists:
         // 512 of them 12.9, 12.6, 14.3 us against 15.7, 16.1, 19.1 of the large ones; 768: 16.0 against

@@ -66,7 +66,8 @@ def test_scheduler_walks_sorted_lists(streams, B, d, micro):
 
 @pytest.mark.parametrize("metric", ["ip", "l2"])
 @pytest.mark.parametrize("nq,nlist,d", [(2, 40, 64), (3, 15, 4), (3, 129, 768), (15, 17, 36), (16, 1, 260), (17, 33, 1028),
-                                        (33, 6200, 20), (130, 1100, 96)])
+                                        (33, 6200, 20), (130, 1100, 96), (1, 9, 3), (2, 30, 257), (4, 33, 1), (5, 70, 2), (17, 40, 31),
+                                        (20, 300, 295), (40, 2000, 1023), (200, 50, 37)])
 def test_coarse_scores_by_batch_size(streams, nq, nlist, d, metric):
     """Row kernel, small and large matrix-core tiles: ragged in queries, centroids and elements (a
     row's blocks of 32 elements are dealt to 4 or 8 wavefronts), two XCD groups and more."""
