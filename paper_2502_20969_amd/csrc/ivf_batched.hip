@@ -765,31 +765,6 @@ __global__ __launch_bounds__(kBatchThreads) void batched_scan_f32_kernel(Batched
 constexpr int kRescoreInFlight = 2;
 constexpr uint32_t kSurvivorsAtOnce = kSelectThreads / kRescoreLanes * kRescoreInFlight * 2;     // up to here: no second look
 
-// How many of the n values of an LDS array are above `me` and how many equal it: eight lanes per
-// value, `sub` is the lane's number in its group; every lane of the group gets the counts.
-template <typename V>
-__device__ __forceinline__ void count_above(const V* a, uint32_t n, V me, uint32_t sub, uint32_t& above, uint32_t& equal) {
-    uint32_t ab = 0, eq = 0;
-#pragma unroll 1
-    for (uint32_t j0 = sub; j0 < n; j0 += 32) {
-        V o[4];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) o[u] = a[min(j0 + 8u * u, n - 1)];
-#pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            ab += (uint32_t)((o[u] > me) & (j0 + 8u * u < n));
-            eq += (uint32_t)((o[u] == me) & (j0 + 8u * u < n));
-        }
-    }
-    ab += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)ab, 0xB1, 0xF, 0xF, true);
-    eq += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)eq, 0xB1, 0xF, 0xF, true);
-    ab += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)ab, 0x4E, 0xF, 0xF, true);
-    eq += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)eq, 0x4E, 0xF, 0xF, true);
-    ab += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)ab, 0x141, 0xF, 0xF, true);
-    eq += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)eq, 0x141, 0xF, 0xF, true);
-    above = ab; equal = eq;
-}
-
 __global__ __launch_bounds__(kSelectThreads) void batched_merge_kernel(BatchedArgs a) {
     __shared__ uint64_t s_key[kBatchSurvivors];     // ordered(fp64 score): larger is nearer
     __shared__ uint32_t s_row[kBatchSurvivors];

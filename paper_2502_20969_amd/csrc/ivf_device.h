@@ -519,6 +519,31 @@ __device__ inline void block_bitonic_sort(uint64_t* keys, uint32_t* idx, uint32_
     }
 }
 
+// How many of the n values of an LDS array are above `me` and how many equal it: eight lanes per
+// value, `sub` is the lane's number in its group; every lane of the group gets the counts.
+template <typename V>
+__device__ __forceinline__ void count_above(const V* a, uint32_t n, V me, uint32_t sub, uint32_t& above, uint32_t& equal) {
+    uint32_t ab = 0, eq = 0;
+#pragma unroll 1
+    for (uint32_t j0 = sub; j0 < n; j0 += 32) {
+        V o[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) o[u] = a[min(j0 + 8u * u, n - 1)];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            ab += (uint32_t)((o[u] > me) & (j0 + 8u * u < n));
+            eq += (uint32_t)((o[u] == me) & (j0 + 8u * u < n));
+        }
+    }
+    ab += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)ab, 0xB1, 0xF, 0xF, true);
+    eq += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)eq, 0xB1, 0xF, 0xF, true);
+    ab += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)ab, 0x4E, 0xF, 0xF, true);
+    eq += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)eq, 0x4E, 0xF, 0xF, true);
+    ab += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)ab, 0x141, 0xF, 0xF, true);
+    eq += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)eq, 0x141, 0xF, 0xF, true);
+    above = ab; equal = eq;
+}
+
 // ---- packed candidates --------------------------------------------------------------------------
 // A candidate is one 64-bit word whose unsigned order is the result order: the order-preserving
 // image of an fp32 key in the high half and the complement of a tie-break rank in the low half

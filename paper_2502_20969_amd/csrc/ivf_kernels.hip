@@ -1270,7 +1270,7 @@ __device__ __forceinline__ bool gather_fast(const MergeArgs& a, const Cand* part
 // candidate counts those ahead of it: the first kprime take their places.
 // What bounds it: one workgroup, a handful of dependent L2 reads and barriers.  (The radix select
 // over all entries reads 2 MB up to ten times from one compute unit: 494 us at 2048 lists against
-// 29 us here, k 100 on 4 M x 768 fp16 rows.)
+// 27 us here, k 100 on 4 M x 768 fp16 rows.)
 // Returns false (for the whole workgroup) when the lists do not fit or masses of equal keys keep
 // overflowing the pool.
 constexpr int kWideLists = 2048;           // lists the wide path can visit: all of one query's scan wavefronts
@@ -1357,19 +1357,13 @@ __device__ __forceinline__ bool gather_wide(const MergeArgs& a, const Cand* part
         __syncthreads();
         cnt = L.sh[4];
     }
+    // eight lanes per candidate count those ahead of it
 #pragma unroll 1
-    for (uint32_t t = tid; t < cnt; t += nt) {
+    for (uint32_t t = (uint32_t)tid / 8; t < cnt; t += (uint32_t)nt / 8) {
         const Cand me = pool[t];
-        uint32_t rank = 0;
-#pragma unroll 1
-        for (uint32_t j0 = 0; j0 < cnt; j0 += 8) {
-            Cand o[8];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) o[u] = pool[min(j0 + u, cnt - 1)];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) rank += (uint32_t)((o[u] > me) & (j0 + u < cnt));
-        }
-        if (rank < kp) L.c_cand[rank] = me;
+        uint32_t rank, equal;
+        count_above(pool, cnt, me, (uint32_t)tid & 7u, rank, equal);
+        if ((tid & 7) == 0 && rank < kp) L.c_cand[rank] = me;
     }
     __syncthreads();
     if (tid == 0) L.sh[4] = min(cnt, kp);
@@ -1467,8 +1461,35 @@ __global__ __launch_bounds__(kMergeFastThreads) void merge_kernel(MergeArgs a) {
     const int np = a.nprobe;
     constexpr int lpc = kRescoreLanes;
     const int sub = tid % lpc;
+    // More than one round of them (WIDE), rows found without a search and whole 16-byte chunks: two
+    // candidates per group are in flight (112 of 1.5 KB: 29.4 -> 27.0 us for the whole kernel).
+    const bool paired = WIDE && a.identity && ((size_t)a.d * (a.dtype == 0 ? 4 : 2)) % 16 == 0;
+    if (paired) {
+        const uint32_t groups = (uint32_t)(nt / lpc);
 #pragma unroll 1
-    for (uint32_t c = (uint32_t)(tid / lpc); c < m; c += (uint32_t)(nt / lpc)) {
+        for (uint32_t c = (uint32_t)(tid / lpc); c < m; c += 2 * groups) {
+            uint32_t row[2];
+            int64_t id[2];
+            double s[2];
+#pragma unroll
+            for (int r = 0; r < 2; ++r) {
+                row[r] = cand_tie(L.c_cand[min(c + groups * r, m - 1)]);
+                id[r] = a.ids ? a.ids[row[r]] : (int64_t)row[r];
+            }
+            rescore_rows<2>(a.buf, q, a.d, a.dtype, a.metric, row, sub, s);
+#pragma unroll
+            for (int r = 0; r < 2; ++r) {
+                const uint32_t e = c + groups * r;
+                if (sub == 0 && e < m) {
+                    L.f_key[e] = a.metric == 0 ? s[r] : -s[r];
+                    L.f_id[e] = id[r];
+                    atomicMin(&f_min, (uint32_t)(L.c_cand[e] >> 32));
+                }
+            }
+        }
+    }
+#pragma unroll 1
+    for (uint32_t c = paired ? m : (uint32_t)(tid / lpc); c < m; c += (uint32_t)(nt / lpc)) {
         const Cand cand = L.c_cand[c];
         const uint32_t row = cand_tie(cand);
         const int64_t id = a.ids ? a.ids[row] : (int64_t)row;
