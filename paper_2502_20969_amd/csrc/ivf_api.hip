@@ -260,16 +260,20 @@ void free_workspace(Workspace& w) {
     w = Workspace{};
 }
 
+// rows of the nprobe largest lists: no query scans more
+uint64_t most_rows(const ivf_index* ix, int nprobe) { return ix->rows_desc_prefix[std::min<size_t>(nprobe, ix->rows_desc_prefix.size() - 1)]; }
+ScanShape shape_for(const ivf_index* ix, int nprobe, int kprime, int nq) {
+    return scan_shape_for_rows(ix->shape, most_rows(ix, nprobe) * (uint64_t)nq, kprime, ix->n_cu);
+}
 // Number of scan workgroups per query for a call of `nq` searches of `nprobe` clusters with
 // `kprime` candidates.  One query: as many as are resident at once (the rows are split statically),
 // and no more wavefronts than the largest possible scan has batches.  Several queries share the
 // GPU: together they get about four rounds of resident workgroups, at least one per query.
-int scan_grid_for(ivf_index* ix, int nprobe, int kprime, int nq) {
+int scan_grid_for(ivf_index* ix, int nprobe, int kprime, int nq, const ScanShape& shape) {
     const int cls = kprime > 64 ? 1 : 0;
     if (ix->resident_grid[cls] == 0)
         ix->resident_grid[cls] = scan_resident_grid(ix->shape, ix->dtype, ix->metric, cls ? 128 : 64, ix->d, ix->n_cu);
-    uint64_t rows = ix->rows_desc_prefix[std::min<size_t>(nprobe, ix->rows_desc_prefix.size() - 1)];
-    uint64_t batches = rows / ix->shape.rows_per_batch + (uint64_t)nprobe;
+    uint64_t batches = most_rows(ix, nprobe) / shape.rows_per_batch + (uint64_t)nprobe;
     uint64_t g = (batches + kScanWaves - 1) / kScanWaves;
     uint64_t cap = (uint64_t)ix->resident_grid[cls];
     if (g > cap) g = cap;
@@ -479,14 +483,14 @@ int enqueue_probe(ivf_index* ix, const float* q_dev, int nq, int nprobe, int gri
     return IVF_OK;
 }
 
-int enqueue_scan(ivf_index* ix, const float* q_dev, int nq, int nprobe, int kprime, int grid) {
+int enqueue_scan(ivf_index* ix, const float* q_dev, int nq, int nprobe, int kprime, int grid, const ScanShape& shape) {
     Workspace& w = *ix->cw;
     ScanArgs sc{};
     sc.buf = ix->d_buf; sc.q = q_dev; sc.slots = w.slots;
     sc.part = w.d_part; sc.heads = w.d_heads;
     sc.desc = w.d_desc;
     sc.d = ix->d; sc.dtype = ix->dtype; sc.metric = ix->metric; sc.nprobe = nprobe; sc.nq = nq;
-    sc.kprime = kprime; sc.grid = grid; sc.shape = ix->shape;
+    sc.kprime = kprime; sc.grid = grid; sc.shape = shape;
     hipEvent_t e0, e1;
     int rc = prof_events(ix, 2, &e0, &e1);
     if (rc) return rc;
@@ -941,9 +945,10 @@ static int enqueue_per_query(ivf_index* ix, const float* q_dev, int nq, int npro
     int r;
     if ((r = ensure_workspace(ix, nq, nprobe, k))) return r;
     const int kprime = kprime_for(k);
-    const int grid = scan_grid_for(ix, nprobe, kprime, nq);
+    const ScanShape shape = shape_for(ix, nprobe, kprime, nq);
+    const int grid = scan_grid_for(ix, nprobe, kprime, nq, shape);
     if ((r = enqueue_probe(ix, q_dev, nq, nprobe, grid, true, true))) return r;
-    if ((r = enqueue_scan(ix, q_dev, nq, nprobe, kprime, grid))) return r;
+    if ((r = enqueue_scan(ix, q_dev, nq, nprobe, kprime, grid, shape))) return r;
     if ((r = enqueue_merge(ix, q_dev, nq, nprobe, k, kprime, grid, false, ids_dev, dists_dev, lazy && nq == 1, lazy))) return r;
     if (lazy) return IVF_OK;
     return enqueue_redo(ix, q_dev, nq, nprobe, k, kprime, false, ids_dev, dists_dev);
@@ -1057,7 +1062,7 @@ extern "C" int ivf_search_device_noalloc(ivf_index* ix, const float* q_dev, int3
         if (l.pending.on) return fail(IVF_ESTATE, "a list-major batch is unfinished: call ivf_synchronize() first");
     nprobe = std::min(nprobe, ix->nlist);
     const int kprime = kprime_for(k);
-    const int grid = scan_grid_for(ix, nprobe, kprime, nq);
+    const int grid = scan_grid_for(ix, nprobe, kprime, nq, ix->shape);      // (not the finer one: the area is fixed)
     const uint32_t pad = select_sort_pad(ix->nlist, nprobe);
     Workspace w{};
     const size_t need = carve_search_buffers(w, nullptr, ix, nq, nprobe, k, kprime, grid, pad);
@@ -1073,7 +1078,7 @@ extern "C" int ivf_search_device_noalloc(ivf_index* ix, const float* q_dev, int3
     hipStream_t cs = ix->cs; Workspace* cw = ix->cw;
     ix->cs = ix->compute; ix->cw = &w;
     rc = enqueue_probe(ix, q_dev, nq, nprobe, grid, true, true);
-    if (!rc) rc = enqueue_scan(ix, q_dev, nq, nprobe, kprime, grid);
+    if (!rc) rc = enqueue_scan(ix, q_dev, nq, nprobe, kprime, grid, ix->shape);
     if (!rc) rc = enqueue_merge(ix, q_dev, nq, nprobe, k, kprime, grid, false, ids_dev, dists_dev);
     if (!rc) rc = enqueue_redo(ix, q_dev, nq, nprobe, k, kprime, false, ids_dev, dists_dev);
     ix->cs = cs; ix->cw = cw;
@@ -1094,7 +1099,8 @@ extern "C" int ivf_search(ivf_index* ix, const float* q_out, int32_t nq, int32_t
     if ((rc = ensure_workspace(ix, nq, nprobe, k))) return rc;
     Workspace& w = *ix->cw;
     const int kprime = kprime_for(k);
-    const int grid = scan_grid_for(ix, nprobe, kprime, nq);
+    const ScanShape shape = shape_for(ix, nprobe, kprime, nq);
+    const int grid = scan_grid_for(ix, nprobe, kprime, nq, shape);
     const bool hybrid = ix->placement == IVF_PLACE_HOST;
     ivf_search_stats st{};
 
@@ -1125,7 +1131,7 @@ extern "C" int ivf_search(ivf_index* ix, const float* q_out, int32_t nq, int32_t
         HIP_TRY(hipMemcpyAsync(w.h_probe, w.d_probe, (size_t)nq * nprobe * sizeof(int32_t), hipMemcpyDeviceToHost, ix->cs));
         HIP_TRY(hipEventRecord(ix->ev_probe, ix->cs));
     }
-    if ((rc = enqueue_scan(ix, w.d_q, nq, nprobe, kprime, grid))) return rc;
+    if ((rc = enqueue_scan(ix, w.d_q, nq, nprobe, kprime, grid, shape))) return rc;
 
     if (want_probe) {
         HIP_TRY(hipEventSynchronize(ix->ev_probe));

@@ -41,6 +41,8 @@ struct ScanShape {
     int tail;            // 1: rows are not whole 16-byte chunks
 };
 ScanShape pick_scan_shape(int d, int dtype);
+// the shape for a call whose queries scan at most `rows` rows together
+ScanShape scan_shape_for_rows(const ScanShape& shape, uint64_t rows, int kprime, int n_cu);
 
 // Per query and selected cluster ("slot", nearest first), written by the select kernel.
 struct SlotTables {

@@ -1052,6 +1052,21 @@ ScanShape pick_scan_shape(int d, int dtype) {
                      kShapes[best].u * (64 / kShapes[best].lpr), row_bytes % 16 != 0};
 }
 
+// The same shape with two row groups per batch: for scans whose rows would keep less than a quarter of
+// the wavefronts busy in batches of six groups, which then run long code for few rows.  Measured on
+// one query (us, two groups against six): 600 to 6000 rows of 128 fp32 4.2-4.5 / 5.0-5.6, 12000 5.0 /
+// 4.9; 2500 rows of 300 fp16 4.5 / 5.6, 6000 5.2 / 4.7; 2500 of 256 fp32 4.4 / 5.3, 6000 4.6 / 4.6.
+// (rows of several segments have two or three groups per batch as they are.)
+constexpr int kFewGroups = 2;
+ScanShape scan_shape_for_rows(const ScanShape& shape, uint64_t rows, int kprime, int n_cu) {
+    if (shape.lanes_per_row == 0 || shape.segments != 1 || kprime > 64) return shape;
+    if (rows / (uint64_t)shape.rows_per_batch > (uint64_t)(n_cu * kScanMaxWgPerCu * kScanWaves / 4)) return shape;
+    ScanShape few = shape;
+    few.unroll = kFewGroups;
+    few.rows_per_batch = kFewGroups * (64 / shape.lanes_per_row);
+    return few;
+}
+
 typedef void (*ScanFn)(ScanArgs);
 
 template <typename T, int LPR, int SEG, int U, bool TAIL>
@@ -1060,9 +1075,17 @@ static ScanFn scan_fn_shape(int metric, bool big) {
     return big ? (ScanFn)scan_kernel<T, LPR, SEG, U, 1, 2, TAIL> : (ScanFn)scan_kernel<T, LPR, SEG, U, 1, 1, TAIL>;
 }
 
+template <typename T, int LPR, bool TAIL>
+static ScanFn scan_fn_few(int metric) {
+    return metric == 0 ? (ScanFn)scan_kernel<T, LPR, 1, kFewGroups, 0, 1, TAIL> : (ScanFn)scan_kernel<T, LPR, 1, kFewGroups, 1, 1, TAIL>;
+}
+
 template <typename T>
 static ScanFn scan_fn_dtype(const ScanShape& sh, int metric, bool big) {
     const int l = sh.lanes_per_row, g = sh.segments;
+#define IVF_FEW(L) if (l == L && g == 1 && !big && sh.unroll == kFewGroups) return sh.tail ? scan_fn_few<T, L, true>(metric) : scan_fn_few<T, L, false>(metric);
+    IVF_FEW(16) IVF_FEW(32) IVF_FEW(64)
+#undef IVF_FEW
 #define IVF_SHAPE(L, G, UU) if (l == L && g == G) return sh.tail ? scan_fn_shape<T, L, G, UU, true>(metric, big) : scan_fn_shape<T, L, G, UU, false>(metric, big);
     IVF_SHAPE(16, 1, 6) IVF_SHAPE(32, 1, 6) IVF_SHAPE(64, 1, 6) IVF_SHAPE(32, 3, 2)
     IVF_SHAPE(64, 2, 3) IVF_SHAPE(64, 3, 2) IVF_SHAPE(64, 4, 2) IVF_SHAPE(64, 8, 1)

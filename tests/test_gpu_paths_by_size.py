@@ -186,3 +186,34 @@ def test_rows_that_are_not_whole_chunks(streams, dtype, d, metric):
     for b in range(4):
         assert check_topk(gi[b], gd[b], st[perm], odt, off, perm.astype(np.int64), cent, q[b], nlist, k, om) == 0
     index.close()
+
+
+@pytest.mark.parametrize("dtype,d,per_batch", [("f32", 64, 24), ("f16", 90, 24), ("f32", 128, 12), ("f32", 101, 12), ("bf16", 512, 6), ("f32", 255, 6)])
+@pytest.mark.parametrize("windows", [1, 511, 512, 513, 1100])
+def test_scan_of_few_rows(streams, dtype, d, per_batch, windows):
+    """Calls of few rows take smaller batches than the search on the fixed scratch area, which keeps
+    the usual ones: the results are the same bit for bit on both sides of the rule, and the oracle's
+    is found for the smallest."""
+    rng = np.random.default_rng(windows + d)
+    nlist, n = 7, windows * per_batch + 5
+    cent = rng.standard_normal((nlist, d)).astype(np.float32)
+    assign = rng.integers(0, nlist, n).astype(np.int32)
+    rows = (cent[assign] + 0.5 * rng.standard_normal((n, d))).astype(np.float32)
+    st, odt = stored(rows, dtype)
+    index = P.ivf_build_layout(st, dtype, cent, assign, compute_stream=streams[0], copy_stream=streams[1])
+    index.ivf_set_batch_mode(1)
+    for nq in (1, 3):
+        q = torch.from_numpy((cent[:nq] + 0.3 * rng.standard_normal((nq, d))).astype(np.float32)).cuda()
+        out = []
+        for call in (index.ivf_search_device, index.ivf_search_device_noalloc):
+            ids, dists = torch.empty(nq, 9, dtype=torch.int64, device="cuda"), torch.empty(nq, 9, device="cuda")
+            torch.cuda.synchronize()
+            call(q, nlist, 9, ids, dists)
+            torch.cuda.synchronize()
+            out.append((ids.cpu().numpy(), dists.cpu().numpy()))
+        assert np.array_equal(out[0][0], out[1][0]) and np.array_equal(out[0][1], out[1][1])
+    if windows == 1:
+        off, perm = O.build_layout(assign, nlist)
+        for b in range(3):
+            assert check_topk(out[0][0][b], out[0][1][b], st[perm], odt, off, perm.astype(np.int64), cent, q[b].cpu().numpy(), nlist, 9, O.IP) == 0
+    index.close()
