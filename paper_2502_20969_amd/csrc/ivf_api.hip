@@ -1062,7 +1062,11 @@ extern "C" int ivf_search_device_noalloc(ivf_index* ix, const float* q_dev, int3
         if (l.pending.on) return fail(IVF_ESTATE, "a list-major batch is unfinished: call ivf_synchronize() first");
     nprobe = std::min(nprobe, ix->nlist);
     const int kprime = kprime_for(k);
-    const int grid = scan_grid_for(ix, nprobe, kprime, nq, ix->shape);      // (not the finer one: the area is fixed)
+    // workgroups for batches of at least four rows where rows are not whole chunks, and never for the
+    // finer batches of few rows: more of them would not fit the area in every call that fits it now
+    ScanShape counted = ix->shape;
+    if (counted.tail) counted.rows_per_batch = std::max(counted.rows_per_batch, 4);
+    const int grid = scan_grid_for(ix, nprobe, kprime, nq, counted);
     const uint32_t pad = select_sort_pad(ix->nlist, nprobe);
     Workspace w{};
     const size_t need = carve_search_buffers(w, nullptr, ix, nq, nprobe, k, kprime, grid, pad);

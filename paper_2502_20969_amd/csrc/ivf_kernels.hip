@@ -21,7 +21,8 @@ using namespace dev;
 // =============================================================================================
 // Batches below this use the row kernel, which walks the queries one after the other: with 8
 // queries x 4096 x 768 17.7 us against 8.4 on the matrix cores, with 2 7.9 (and with 3 9.9).  Squared
-// L2 keeps the direct sum of squared differences up to 15 queries (the matrix cores need the three norms form).
+// L2 keeps the direct sum of squared differences up to 15 queries, and for any number when d is no multiple
+// of 4 (the matrix cores need the three norms form, which is less exact where distances are small).
 constexpr int kCoarseRowMaxIp = 3, kCoarseRowMaxL2 = 16;
 constexpr int kSelectWaveSortMax = 4096;   // select: register sorting path up to this many clusters
 
@@ -225,7 +226,7 @@ static void launch_coarse_mfma(const CoarseArgs& a, hipStream_t s, hipEvent_t e0
 }
 
 hipError_t launch_coarse(const CoarseArgs& a, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
-    if (a.nq < (a.metric == 0 ? kCoarseRowMaxIp : kCoarseRowMaxL2)) {
+    if (a.nq < (a.metric == 0 ? kCoarseRowMaxIp : kCoarseRowMaxL2) || (a.metric != 0 && (a.d & 3) != 0)) {
         if (a.d & 3) IVF_LAUNCH(coarse_rows_kernel<true>, dim3((a.nlist + 3) / 4), dim3(256), 0, s, e0, e1, a);
         else IVF_LAUNCH(coarse_rows_kernel<false>, dim3((a.nlist + 3) / 4), dim3(256), 0, s, e0, e1, a);
     } else {
@@ -329,11 +330,13 @@ __device__ __forceinline__ bool select_pooled(const SelectArgs& a, const double*
     for (int j = 0; j < C; ++j) s8[j] = sc[min(tid + j * nt, a.nlist - 1)];
     if (tid == 0) { sh[4] = 0; sh[6] = 0; }
     auto nearness = [&](double s) { return (float)(a.metric == 0 ? s : -s); };
+    // not a number: infinite here, which sends the selection to the exact path
+    auto better = [](float b, float f) { return f == f ? fmaxf(b, f) : INFINITY; };
     float best = -INFINITY;
 #pragma unroll
-    for (int j = 0; j < C; ++j) if (tid + j * nt < a.nlist) best = fmaxf(best, nearness(s8[j]));
+    for (int j = 0; j < C; ++j) if (tid + j * nt < a.nlist) best = better(best, nearness(s8[j]));
 #pragma unroll 1
-    for (int i = tid + C * nt; i < a.nlist; i += nt) best = fmaxf(best, nearness(sc[i]));
+    for (int i = tid + C * nt; i < a.nlist; i += nt) best = better(best, nearness(sc[i]));
     // the cut is taken on scores mapped linearly to integers: bit images of scores around zero leave
     // all the exponents between them to one bucket
     float lo = tid < a.nlist ? best : INFINITY, hi = best;

@@ -137,7 +137,7 @@ def test_survivors_of_a_list_major_batch(streams, dtype, metric, k, band):
 
 @pytest.mark.parametrize("metric", ["ip", "l2"])
 @pytest.mark.parametrize("nlist,nprobe", [(65, 65), (1000, 257), (1024, 1024), (2049, 512), (8191, 65), (8193, 512), (16500, 300), (4097, 3)])
-@pytest.mark.parametrize("kind", ["random", "one_side", "ties", "infinite"])
+@pytest.mark.parametrize("kind", ["random", "one_side", "ties", "infinite", "nan"])
 def test_select_of_many_clusters(streams, nlist, nprobe, kind, metric):
     """Selections through the pooled path: scores around zero, scores far from zero, masses of equal
     scores (the pool overflows or prefixes tie: the exact path) and infinite ones; order and content
@@ -154,12 +154,19 @@ def test_select_of_many_clusters(streams, nlist, nprobe, kind, metric):
     elif kind == "infinite":
         cent[rng.permutation(nlist)[:nprobe // 2]] *= np.float32(1e30)
         q *= np.float32(1e30)
+    elif kind == "nan":
+        cent[nlist // 2, 3] = np.nan            # one score that is none: the same choice in every path
     rows = torch.zeros(nlist, d, device="cuda")
     index = P.ivf_adopt_layout(rows, "f32", np.arange(nlist + 1), cent, metric=P.IVF_IP if metric == "ip" else P.IVF_L2,
                                compute_stream=streams[0], copy_stream=streams[1])
     pr = index.ivf_probe(q, nprobe)
-    for b in range(3):
-        assert list(pr[b]) == list(O.probe(cent, q[b], nprobe, O.IP if metric == "ip" else O.L2))
+    if kind == "nan":
+        # the oracle's sort has no place for it: the exact selection of all lists does
+        full = index.ivf_probe(q, nlist)
+        assert np.array_equal(pr, full[:, :nprobe])
+    else:
+        for b in range(3):
+            assert list(pr[b]) == list(O.probe(cent, q[b], nprobe, O.IP if metric == "ip" else O.L2))
     index.close()
 
 
