@@ -117,8 +117,7 @@ typedef struct ivf_profile {
  *   device_buffer_bytes  size of the prefetch buffer (IVF_PLACE_HOST only)
  *   compute_stream, copy_stream  hipStream_t values, or NULL for streams the
  *              library creates; kernels run on the first, prefetch copies on
- *              the second (and on streams of the library that start and end
- *              inside it); both must be of default priority
+ *              the second; both must be of default priority
  * Rows keep their input order inside a list.  The library owns all storage it
  * creates (device lists, or a pinned host region for IVF_PLACE_HOST).
  */

@@ -60,7 +60,6 @@ extern "C" const char* ivf_last_error(void) { return g_last_error.c_str(); }
 namespace {
 
 constexpr int kMaxD = 4096;             // coarse kernel stages 4 queries x d floats in 64 KB of LDS
-constexpr int kCopyStreams = 4;         // streams the copies of a prefetch are spread over
 constexpr int kProfileRing = 2048;      // searches whose events are kept before a drain
 
 struct Workspace {
@@ -168,9 +167,6 @@ struct ivf_index {
     int64_t* h_res_stage = nullptr; // pinned copy used as the source of the table upload
     size_t buf_used = 0;
     hipEvent_t ev_pf_begin = nullptr, ev_pf_done = nullptr, ev_probe = nullptr, ev_pf_table = nullptr;
-    // streams that share the copies of a prefetch with `copy`: their work begins and ends inside it
-    hipStream_t copy_more[kCopyStreams - 1] = {};
-    hipEvent_t ev_pf_join[kCopyStreams - 1] = {};
     bool pf_recorded = false;
 
     std::vector<uint64_t> rows_desc_prefix;   // prefix sums of list sizes, largest first
@@ -749,8 +745,6 @@ extern "C" void ivf_free(ivf_index* ix) {
     if (ix->ev_pf_done) (void)hipEventDestroy(ix->ev_pf_done);
     if (ix->ev_probe) (void)hipEventDestroy(ix->ev_probe);
     if (ix->ev_pf_table) (void)hipEventDestroy(ix->ev_pf_table);
-    for (auto& e : ix->ev_pf_join) if (e) (void)hipEventDestroy(e);
-    for (auto& m : ix->copy_more) if (m) (void)hipStreamDestroy(m);
     free_sched(ix->sched);
     if (ix->own_compute) (void)hipStreamDestroy(ix->compute);
     if (ix->own_copy) (void)hipStreamDestroy(ix->copy);
@@ -1257,29 +1251,16 @@ extern "C" int ivf_prefetch(ivf_index* ix, const float* q_in, int32_t nq, int32_
     std::vector<int32_t> taken;
     plan_prefetch(w.h_probe, nq, nprobe, ix->h_off.data(), rb, budget_bytes, ix->buf_bytes, buf_used, res_off.data(), taken, st);
     auto enqueue = [&]() -> int {
-        // Each copy goes to the stream with the fewest bytes so far: a copy of a few hundred KB costs
-        // about as much again in front of its first byte, which the other streams' copies cover (300
-        // clusters of 390 KB: 23 GB/s on one stream, 36, 46 and 49 on two, three and four, 44 on six).
-        const int ns = (int)std::min<size_t>(kCopyStreams, std::max<size_t>(taken.size(), 1));
-        for (int i = 0; i + 1 < ns; ++i) {
-            if (!ix->copy_more[i]) HIP_TRY(hipStreamCreateWithFlags(&ix->copy_more[i], hipStreamNonBlocking));
-            if (!ix->ev_pf_join[i]) HIP_TRY(hipEventCreateWithFlags(&ix->ev_pf_join[i], hipEventDisableTiming));
-        }
+        // One stream: spread over two to four streams the copies of a fresh process ran at 36 to 49 GB/s
+        // instead of 23, but after some thousand copies the runtime takes a slow path (4 GB/s per
+        // stream) for stretches of a thousand copies, with several streams most of the time.
         HIP_TRY(hipEventRecord(ix->ev_pf_begin, ix->copy));
-        for (int i = 0; i + 1 < ns; ++i) HIP_TRY(hipStreamWaitEvent(ix->copy_more[i], ix->ev_pf_begin, 0));
-        size_t given[kCopyStreams] = {};
         for (int32_t c : taken) {
             const size_t bytes = (size_t)(ix->h_off[c + 1] - ix->h_off[c]) * rb;
-            const int which = (int)(std::min_element(given, given + ns) - given);
-            given[which] += bytes;
             if (bytes > 0)
                 HIP_TRY(hipMemcpyAsync((char*)ix->d_buf + (size_t)res_off[c] * rb,
                                        (const char*)ix->h_lists + (size_t)ix->h_off[c] * rb, bytes,
-                                       hipMemcpyHostToDevice, which ? ix->copy_more[which - 1] : ix->copy));
-        }
-        for (int i = 0; i + 1 < ns; ++i) {
-            HIP_TRY(hipEventRecord(ix->ev_pf_join[i], ix->copy_more[i]));
-            HIP_TRY(hipStreamWaitEvent(ix->copy, ix->ev_pf_join[i], 0));
+                                       hipMemcpyHostToDevice, ix->copy));
         }
         // the residency table follows the data on the same stream; the pinned staging copy is reused,
         // so the previous upload from it must have finished
@@ -1299,7 +1280,6 @@ extern "C" int ivf_prefetch(ivf_index* ix, const float* q_in, int32_t nq, int32_
         // be stale: nothing is resident any more, on either side (best effort for the device side).
         const std::string why = g_last_error;
         (void)hipStreamSynchronize(ix->copy);
-        for (auto& m : ix->copy_more) if (m) (void)hipStreamSynchronize(m);
         std::fill(ix->h_res_off.begin(), ix->h_res_off.end(), (int64_t)-1);
         ix->buf_used = 0;
         (void)hipMemcpy(ix->d_res_off, ix->h_res_off.data(), (size_t)ix->nlist * sizeof(int64_t), hipMemcpyHostToDevice);
