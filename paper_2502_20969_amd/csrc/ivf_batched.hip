@@ -67,7 +67,7 @@ hipError_t launch_row_norms(const void* lists, int dtype, int64_t n, int d, unsi
 // One launch for everything that needs only the selected clusters: its workgroups differ in what
 // they do (the steps are short, and as launches of their own they cost more than they computed:
 // sample, queries, map and task list in seven launches 65, 72 and 260 us for 8 and 32 queries x 768
-// fp32 and 256 x 1024 bf16 with 128, 32 and 512 clusters each; the two launches here 16, 20 and 119).
+// fp32 and 256 x 1024 bf16 with 128, 32 and 512 clusters each; the two launches here 16, 20 and 151).
 //
 // Workgroup 0 builds the map from clusters to the queries that probe them.  Each of the others
 // scores one part of a query's threshold sample: fp32 scores (fp32 query; <q, y>, or -sum (q - y)^2
