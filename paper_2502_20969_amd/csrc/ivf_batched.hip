@@ -315,7 +315,7 @@ __global__ __launch_bounds__(kFrontThreads) void batch_front_kernel(BatchedArgs 
 __global__ __launch_bounds__(256) void batch_tasks_kernel(BatchedArgs a) {
     __shared__ uint32_t pool[kSampleRows];
     __shared__ uint32_t hist[256], red[96];
-    __shared__ uint32_t s_cnt;
+    __shared__ uint32_t s_cnt, s_kth;
     const int tid = threadIdx.x, lane = lane_id();
     if ((int)blockIdx.x >= a.nq) {
         const uint32_t pairs = (uint32_t)a.nq * (uint32_t)a.nprobe, stride = (gridDim.x - (uint32_t)a.nq) * 256u;
@@ -338,7 +338,7 @@ __global__ __launch_bounds__(256) void batch_tasks_kernel(BatchedArgs a) {
     for (int u = 0; u < kSampleRows / 256; ++u) v[u] = a.thr_part[(size_t)qi * kSampleRows + u * 256 + tid];
 #pragma unroll
     for (int u = 0; u < kSampleRows / 256; ++u) pool[u * 256 + tid] = v[u];
-    if (tid == 0) s_cnt = 0;
+    if (tid == 0) { s_cnt = 0; s_kth = 0xFFFFFFFFu; }
     __syncthreads();
     const BucketCut bc = block_bucket_cut([&](uint32_t i) { return pool[i]; }, kSampleRows, k, hist, red);
     __syncthreads();
@@ -359,20 +359,24 @@ __global__ __launch_bounds__(256) void batch_tasks_kernel(BatchedArgs a) {
         if (tid == 0) a.thr[qi] = -INFINITY;
         return;
     }
+    // the k-th best: the smallest with fewer than k above it (of a mass of equal ones few are counted)
 #pragma unroll 1
     for (uint32_t t = tid; t < cnt; t += 256) {
         const uint32_t me = pool[t];
-        uint32_t above = 0, equal = 0;
+        if (me >= __hip_atomic_load(&s_kth, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)) continue;
+        uint32_t above = 0;
 #pragma unroll 1
         for (uint32_t j0 = 0; j0 < cnt; j0 += 8) {
             uint32_t o[8];
 #pragma unroll
             for (int u = 0; u < 8; ++u) o[u] = pool[min(j0 + u, cnt - 1)];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) { above += (uint32_t)((o[u] > me) & (j0 + u < cnt)); equal += (uint32_t)((o[u] == me) & (j0 + u < cnt)); }
+            for (int u = 0; u < 8; ++u) above += (uint32_t)((o[u] > me) & (j0 + u < cnt));
         }
-        if (above < k && k <= above + equal) a.thr[qi] = unordered(me) - a.eps[qi];      // every holder of the k-th value writes the same
+        if (above < k) atomicMin(&s_kth, me);
     }
+    __syncthreads();
+    if (tid == 0) a.thr[qi] = unordered(s_kth) - a.eps[qi];
 }
 
 // ---- how the scan workgroups get their tasks ---------------------------------------------------------------
@@ -773,6 +777,12 @@ __global__ __launch_bounds__(kSelectThreads) void batched_merge_kernel(BatchedAr
     __shared__ unsigned long long s_low;
     __shared__ int64_t o_id[IVF_MAX_K];
     __shared__ float o_dist[IVF_MAX_K];
+    constexpr uint16_t kNoTie = 0xFFFFu;
+    __shared__ uint16_t s_tie[kBatchSurvivors];     // survivors that share their score: how many are above them
+    __shared__ uint64_t o_key[IVF_MAX_K];           // the score of those with this many above them
+    __shared__ uint32_t s_ties, s_edge_n, s_edge_above;     // any; those on the edge of the k best
+    __shared__ uint64_t s_edge_key;
+    __shared__ unsigned long long s_top_id;
     const int tid = threadIdx.x, lane = lane_id();
     constexpr int nt = kSelectThreads;
     const int qi = blockIdx.x;
@@ -819,7 +829,7 @@ __global__ __launch_bounds__(kSelectThreads) void batched_merge_kernel(BatchedAr
     const uint32_t sub8 = (uint32_t)tid & 7u;
     // 1. the k-th best approximate score
     float kth = -INFINITY;
-    if (tid == 0) { s_n = 0; s_m = 0; s_kth = 0xFFFFFFFFu; s_low = ~0ull; }
+    if (tid == 0) { s_n = 0; s_m = 0; s_kth = 0xFFFFFFFFu; s_low = ~0ull; s_ties = 0; s_edge_n = 0; s_top_id = 0; }
     if (n0 > k) {
         // the candidates are dealt to the threads: as many threads' best reach the cut of those as
         // were asked for, so at least k candidates do, and not many more
@@ -839,6 +849,8 @@ __global__ __launch_bounds__(kSelectThreads) void batched_merge_kernel(BatchedAr
         const uint32_t m = min(s_n, (uint32_t)kBatchSurvivors);
         for (uint32_t t = (uint32_t)tid / 8; t < m; t += nt / 8) {
             const uint32_t me = pool[t];
+            // only a smaller value can still lower the result: of a mass of equal ones few are counted
+            if (me >= __hip_atomic_load(&s_kth, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_WORKGROUP)) continue;
             uint32_t above, equal;
             count_above(pool, m, me, sub8, above, equal);
             if (sub8 == 0 && above < k) atomicMin(&s_kth, me);
@@ -929,22 +941,84 @@ __global__ __launch_bounds__(kSelectThreads) void batched_merge_kernel(BatchedAr
     BucketCut bc;
     bc.lo = 0u; bc.scale = 0.f; bc.cut = 0u; bc.passing = n;
     if (n > 512) bc = block_bucket_cut([&](uint32_t i) { return (uint32_t)(s_key[i] >> 32); }, n, k, hist, red);
-    // 5. rank by counting, nearest first, ties by smaller id (the ids are looked at only on a tie)
+    // 5. rank by counting, nearest first; a score that several survivors have is left to step 6
     auto id_at = [&](uint32_t i) { return a.ids ? a.ids[s_row[i]] : (int64_t)s_row[i]; };
-    for (uint32_t t = (uint32_t)tid / 8; t < n; t += nt / 8) {
-        const uint64_t me = s_key[t];
-        if (!bc.pass((uint32_t)(me >> 32))) continue;
-        uint32_t rank, equal;
-        count_above(s_key, n, me, sub8, rank, equal);
-        if (sub8 != 0 || rank >= k) continue;
-        const int64_t id = id_at(t);
-        if (__builtin_expect(equal > 1, 0)) {
-            for (uint32_t j = 0; j < n; ++j) rank += (uint32_t)(s_key[j] == me && id_at(j) < id);
-            if (rank >= k) continue;
+    auto put = [&](uint32_t rank, int64_t id, double key) { o_id[rank] = id; o_dist[rank] = (float)(a.metric == 0 ? key : -key); };
+    // masses of equal scores pass every cut: those that hold the k-th place are counted by the first
+    // of them only
+    const bool mass = n > 512 && bc.passing > 512;
+#pragma unroll 1
+    for (uint32_t t0 = 0; t0 < n; t0 += nt / 8) {
+        const uint32_t t = t0 + (uint32_t)tid / 8;
+        const uint32_t edge_n = s_edge_n, edge_above = s_edge_above;
+        const uint64_t edge_key = s_edge_key;
+        if (mass) __syncthreads();
+        if (t < n) {
+            const uint64_t me = s_key[t];
+            uint32_t above = k, equal = 0;
+            if (bc.pass((uint32_t)(me >> 32))) {
+                if (mass && edge_n != 0 && me == edge_key) { above = edge_above; equal = edge_n; }
+                else count_above(s_key, n, me, sub8, above, equal);
+            }
+            if (sub8 == 0) {
+                s_tie[t] = above < k && equal > 1 ? (uint16_t)above : kNoTie;
+                if (above < k && equal == 1) put(above, id_at(t), unordered(me));
+                if (above < k && equal > 1) {
+                    s_ties = 1;
+                    o_key[above] = me;
+                    if (above + equal > k) { s_edge_key = me; s_edge_above = above; s_edge_n = equal; }
+                }
+            }
         }
-        const double key = unordered(me);
-        o_id[rank] = id;
-        o_dist[rank] = (float)(a.metric == 0 ? key : -key);
+        if (mass) __syncthreads();
+    }
+    __syncthreads();
+    // 6. ties by smaller id.  Survivors of one score have the same number above them, which takes the
+    //    place of the score, so that the ids fit LDS in the place of the scores.  More than 512 on the
+    //    edge of the k best are cut by their ids first.  (32 queries with 1000 and 3500 copies of the
+    //    best row, the whole call with k 10: 0.21 and 0.47 ms; each of them asking every survivor of its
+    //    score for its id from memory took 1.6 and 15.9.)
+    if (__builtin_expect(s_ties != 0, 0)) {
+        const uint32_t edge_n = s_edge_n, edge_above = s_edge_above;
+#pragma unroll 1
+        for (uint32_t i0 = 0; i0 < n; i0 += 4 * nt) {
+            int64_t id[4];
+#pragma unroll
+            for (int u = 0; u < 4; ++u) id[u] = id_at(min(i0 + (uint32_t)(u * nt + tid), n - 1));
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+                const uint32_t i = i0 + (uint32_t)(u * nt + tid);
+                if (i < n && s_tie[i] != kNoTie) {
+                    s_key[i] = (uint64_t)id[u];
+                    if (edge_n > 512 && s_tie[i] == edge_above) atomicMax(&s_top_id, (unsigned long long)id[u]);
+                }
+            }
+        }
+        __syncthreads();
+        const int bits = 64 - __clzll((long long)s_top_id), shift = max(bits - 31, 0);
+        auto level = [&](uint32_t i) -> uint32_t { return s_tie[i] == edge_above ? 0x80000000u - (uint32_t)(s_key[i] >> shift) : 0u; };
+        if (edge_n > 512) bc = block_bucket_cut(level, n, k - edge_above, hist, red);
+#pragma unroll 1
+        for (uint32_t t = (uint32_t)tid / 8; t < n; t += nt / 8) {
+            const uint32_t tie = s_tie[t];
+            if (tie == kNoTie || (edge_n > 512 && tie == edge_above && !bc.pass(level(t)))) continue;
+            const uint64_t id = s_key[t];
+            uint32_t ahead = 0;
+#pragma unroll 1
+            for (uint32_t j0 = sub8; j0 < n; j0 += 32) {
+                uint64_t o[4];
+                uint32_t w[4];
+#pragma unroll
+                for (int u = 0; u < 4; ++u) { const uint32_t j = min(j0 + 8u * u, n - 1); o[u] = s_key[j]; w[u] = s_tie[j]; }
+#pragma unroll
+                for (int u = 0; u < 4; ++u) {
+                    const uint32_t j = j0 + 8u * u;
+                    ahead += (uint32_t)((j < n) & (w[u] == tie) & ((o[u] < id) | ((o[u] == id) & (j < t))));
+                }
+            }
+            const uint32_t rank = tie + sum_of_8(ahead);
+            if (sub8 == 0 && rank < k) put(rank, (int64_t)id, unordered(o_key[tie]));
+        }
     }
     if (tid == 0) a.overflow[qi] = 0;
     __syncthreads();

@@ -519,6 +519,14 @@ __device__ inline void block_bitonic_sort(uint64_t* keys, uint32_t* idx, uint32_
     }
 }
 
+// The sum over eight consecutive lanes, in each of them.
+__device__ __forceinline__ uint32_t sum_of_8(uint32_t v) {
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0xB1, 0xF, 0xF, true);
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x4E, 0xF, 0xF, true);
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x141, 0xF, 0xF, true);
+    return v;
+}
+
 // How many of the n values of an LDS array are above `me` and how many equal it: eight lanes per
 // value, `sub` is the lane's number in its group; every lane of the group gets the counts.
 template <typename V>
@@ -535,13 +543,7 @@ __device__ __forceinline__ void count_above(const V* a, uint32_t n, V me, uint32
             eq += (uint32_t)((o[u] == me) & (j0 + 8u * u < n));
         }
     }
-    ab += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)ab, 0xB1, 0xF, 0xF, true);
-    eq += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)eq, 0xB1, 0xF, 0xF, true);
-    ab += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)ab, 0x4E, 0xF, 0xF, true);
-    eq += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)eq, 0x4E, 0xF, 0xF, true);
-    ab += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)ab, 0x141, 0xF, 0xF, true);
-    eq += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)eq, 0x141, 0xF, 0xF, true);
-    above = ab; equal = eq;
+    above = sum_of_8(ab); equal = sum_of_8(eq);
 }
 
 // ---- packed candidates --------------------------------------------------------------------------

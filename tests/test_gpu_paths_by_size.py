@@ -1,4 +1,6 @@
 """Kernel variants that a rule on sizes selects, at the sizes where they can go wrong."""
+import time
+
 import numpy as np
 import pytest
 import torch
@@ -224,3 +226,49 @@ def test_scan_of_few_rows(streams, dtype, d, per_batch, windows):
         for b in range(3):
             assert check_topk(out[0][0][b], out[0][1][b], st[perm], odt, off, perm.astype(np.int64), cent, q[b].cpu().numpy(), nlist, 9, O.IP) == 0
     index.close()
+
+
+def _copies(streams, copies, ids, nq=4, d=64, per=5000, nlist=6):
+    """An index whose best rows for queries at the centres are `copies` equal ones per cluster."""
+    rng = np.random.default_rng(copies)
+    cent = rng.standard_normal((nlist, d)).astype(np.float32)
+    assign = np.repeat(np.arange(nlist, dtype=np.int32), per)
+    rows = (cent[assign] + 0.5 * rng.standard_normal((nlist * per, d))).astype(np.float32)
+    for c in range(nlist):
+        rows[c * per + rng.permutation(per)[:copies]] = 1.5 * cent[c]
+    index = P.ivf_build_layout(rows.astype(np.float16), "f16", cent, assign, ids=ids, compute_stream=streams[0], copy_stream=streams[1])
+    return index, (cent[np.arange(nq) % nlist] + 0.01 * rng.standard_normal((nq, d))).astype(np.float32)
+
+
+@pytest.mark.parametrize("copies", [2, 40, 600, 3500])
+@pytest.mark.parametrize("kind", ["none", "small", "large"])
+def test_equal_scores_in_a_list_major_batch(streams, copies, kind):
+    """Scores that several survivors share, fewer and more than k, around the 512 from which the
+    edge of the k best is cut by ids, with ids of 32 and 63 bits: equal to query by query."""
+    ids = None if kind == "none" else np.random.default_rng(1).permutation(30000).astype(np.int64) * (3 if kind == "small" else 1 << 48)
+    index, q = _copies(streams, copies, ids)
+    for k in (1, 39, 41, 112):
+        index.ivf_set_batch_mode(2)
+        bi, bd = index.ivf_search(q, 3, k)
+        index.ivf_set_batch_mode(1)
+        pi, pd = index.ivf_search(q, 3, k)
+        assert np.array_equal(bi, pi) and np.array_equal(bd, pd)
+    index.close()
+
+
+def test_equal_scores_do_not_stall_a_list_major_batch(streams):
+    """3500 copies of the best row cost a batch some hundred microseconds, no multiple of that: not
+    every survivor asks memory for the id of every other (which took over 100 times a plain batch)."""
+    took = []
+    for copies in (1, 3500):
+        index, q = _copies(streams, copies, None, nq=32)
+        index.ivf_set_batch_mode(2)
+        times = []
+        for _ in range(9):
+            t0 = time.perf_counter()
+            index.ivf_search(q, 3, 10)
+            times.append(time.perf_counter() - t0)
+        took.append(sorted(times)[4])
+        index.close()
+    # measured 5 to 8 times a plain batch; 25 leaves room for a busy host
+    assert took[1] < 25 * took[0], took
