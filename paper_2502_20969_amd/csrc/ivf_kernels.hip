@@ -310,13 +310,17 @@ __device__ __forceinline__ void select_sorted(const SelectArgs& a, const double*
 // 8 candidates per thread and half the threads' best wanted, about a third more than that.  Those are
 // pooled, sorted in runs of 64 by the wavefronts (registers only), and each finds its place by a
 // binary search in every run.  The order of the prefixes is the order of the scores wherever
-// prefixes differ: on a tie among the selected clusters or across the cut, and when more pass than
-// the pool holds, the result is not used: returns false (for the whole workgroup), idx is then
-// undefined.  Bound by barriers and dependent LDS reads of one workgroup.  (Ranking the pool by
-// counting on 64-bit keys, with the histogram taken over all scores: 18, 31 and 95 us for 8 queries
-// of 2048 lists with nprobe 128, 32 of 4096 with 128 and 256 of 8192 with 512; this: 11, 12 and 24.)
+// prefixes differ; where they tie among the selected clusters or across the cut, the pooled
+// candidates of one prefix are ordered by the low bits of their keys.  When more pass than the pool
+// holds, or a score is no number or infinite, the result is not used: returns false (for the
+// whole workgroup), idx is then undefined.  Bound by barriers and dependent LDS reads of one workgroup.
+// (Ranking the pool by counting on 64-bit keys, with the histogram taken over all scores: 18, 31 and
+// 95 us for 8 queries of 2048 lists with nprobe 128, 32 of 4096 with 128 and 256 of 8192 with 512;
+// this: 11, 12 and 24.  With two equal scores among the selected, one query of 1000, 4096 and 8192
+// lists with nprobe 100, 128 and 512: 13, 14 and 22 us, and 24, 31 and 54 when ties went to the exact
+// path.  256 queries of 65536 lists with nprobe 512: 63 us, 225 with their scores read one by one.)
 constexpr int kSelectPoolCap = 2048;
-__device__ __forceinline__ bool select_pooled(const SelectArgs& a, const double* sc, uint32_t* idx, Cand* pool, Cand* sel,
+__device__ __forceinline__ bool select_pooled(const SelectArgs& a, const double* sc, uint32_t* idx, Cand* pool, Cand* in_order,
                                               uint32_t* hist, uint32_t* red, uint32_t* sh) {
     const int tid = threadIdx.x, nt = blockDim.x, lane = lane_id(), wave = wave_id();
     const uint32_t nprobe = a.nprobe;
@@ -335,8 +339,19 @@ __device__ __forceinline__ bool select_pooled(const SelectArgs& a, const double*
     float best = -INFINITY;
 #pragma unroll
     for (int j = 0; j < C; ++j) if (tid + j * nt < a.nlist) best = better(best, nearness(s8[j]));
+    // the others four at a time
+    constexpr int M = 4;
+    auto request = [&](int i0, double (&v)[M]) {
+#pragma unroll
+        for (int j = 0; j < M; ++j) v[j] = sc[min(i0 + j * nt + tid, a.nlist - 1)];
+    };
 #pragma unroll 1
-    for (int i = tid + C * nt; i < a.nlist; i += nt) best = better(best, nearness(sc[i]));
+    for (int i0 = C * nt; i0 < a.nlist; i0 += M * nt) {
+        double v[M];
+        request(i0, v);
+#pragma unroll
+        for (int j = 0; j < M; ++j) if (i0 + j * nt + tid < a.nlist) best = better(best, nearness(v[j]));
+    }
     // the cut is taken on scores mapped linearly to integers: bit images of scores around zero leave
     // all the exponents between them to one bucket
     float lo = tid < a.nlist ? best : INFINITY, hi = best;
@@ -364,7 +379,12 @@ __device__ __forceinline__ bool select_pooled(const SelectArgs& a, const double*
 #pragma unroll
     for (int j = 0; j < C; ++j) offer(tid + j * nt, s8[j]);
 #pragma unroll 1
-    for (int i0 = C * nt; i0 < a.nlist; i0 += nt) offer(i0 + tid, sc[min(i0 + tid, a.nlist - 1)]);
+    for (int i0 = C * nt; i0 < a.nlist; i0 += M * nt) {
+        double v[M];
+        request(i0, v);
+#pragma unroll
+        for (int j = 0; j < M; ++j) offer(i0 + j * nt + tid, v[j]);
+    }
     __syncthreads();
     const uint32_t cnt = sh[4];
     if (cnt > (uint32_t)kSelectPoolCap) return false;
@@ -374,7 +394,6 @@ __device__ __forceinline__ bool select_pooled(const SelectArgs& a, const double*
         const uint32_t e = (uint32_t)(r * 64 + lane);
         pool[e] = bitonic_sort64<true>(e < cnt ? pool[e] : (Cand)0);
     }
-    if (tid == 0) sel[nprobe] = 0;                      // fewer than nprobe + 1 pooled: nothing behind the last
     __syncthreads();
 #pragma unroll 1
     for (uint32_t t = tid; t < (uint32_t)runs * 64; t += nt) {
@@ -398,17 +417,50 @@ __device__ __forceinline__ bool select_pooled(const SelectArgs& a, const double*
 #pragma unroll
             for (int u = 0; u < 4; ++u) rank += r0 + u < runs ? at[u] + (o[u] > me ? 1u : 0u) : 0u;
         }
-        if (me != 0 && rank <= nprobe) sel[rank] = me;
+        if (me != 0) in_order[rank] = me;
     }
     __syncthreads();
+    auto cluster_of = [](Cand c) { return 0xFFFFFFu - (uint32_t)(c & 0xFFFFFFull); };
 #pragma unroll 1
     for (uint32_t i = tid; i < nprobe; i += nt) {
-        const Cand c = sel[i];
-        idx[i] = 0xFFFFFFu - (uint32_t)(c & 0xFFFFFFull);
-        if ((c >> 24) == (sel[i + 1] >> 24)) sh[6] = 1;
+        const Cand c = in_order[i];
+        idx[i] = cluster_of(c);
+        if (i + 1 < cnt && (c >> 24) == (in_order[i + 1] >> 24)) sh[6] = 1;
     }
     __syncthreads();
-    return sh[6] == 0;
+    if (__builtin_expect(sh[6] != 0, 0)) {
+        uint32_t* low = (uint32_t*)pool;
+        // the low bits of the keys, larger = nearer; candidates of one prefix stand in order of their index
+#pragma unroll 1
+        for (uint32_t t = tid; t < cnt; t += nt) low[t] = (uint32_t)(~coarse_key(sc[cluster_of(in_order[t])], a.metric)) & 0xFFFFFFu;
+        __syncthreads();
+#pragma unroll 1
+        for (uint32_t t = tid; t < cnt; t += nt) {
+            const uint64_t prefix = in_order[t] >> 24;
+            if (!((t > 0 && (in_order[t - 1] >> 24) == prefix) || (t + 1 < cnt && (in_order[t + 1] >> 24) == prefix))) continue;
+            // first .. last - 1: those of this prefix
+            auto count_until = [&](auto&& before) {
+                uint32_t lo = 0, hi = cnt;
+                while (lo < hi) { const uint32_t m = (lo + hi) >> 1; if (before(in_order[m] >> 24)) lo = m + 1; else hi = m; }
+                return lo;
+            };
+            const uint32_t first = count_until([&](uint64_t p) { return p > prefix; });
+            const uint32_t last = count_until([&](uint64_t p) { return p >= prefix; });
+            const uint32_t me = low[t];
+            uint32_t at = first;
+#pragma unroll 1
+            for (uint32_t j0 = first; j0 < last; j0 += 8) {
+                uint32_t o[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) o[u] = low[min(j0 + u, last - 1)];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) at += (uint32_t)((j0 + u < last) & ((o[u] > me) | ((o[u] == me) & (j0 + u < t))));
+            }
+            if (at < nprobe) idx[at] = cluster_of(in_order[t]);
+        }
+        __syncthreads();
+    }
+    return true;
 }
 
 __global__ __launch_bounds__(kSelectThreads) void select_kernel(SelectArgs a, uint32_t pad, int in_lds,
@@ -697,7 +749,7 @@ hipError_t launch_select(const SelectArgs& a, hipStream_t s, hipEvent_t e0, hipE
     // 1000 of 2048 lists it would rank 2048: 50 us against 32 of the sorting network below)
     const int pooled = in_lds && !wave_sort && a.nlist <= 0xFFFFFF && (a.nprobe <= 512 || a.nlist <= 1024);
     if (wave_sort) lds += 16 + (size_t)threads * 8 + 66 * 8 + (size_t)threads * 8;      // pool, the ranked few, the threads' best
-    if (pooled) lds += 16 + ((size_t)kSelectPoolCap + a.nprobe + 1) * 8;
+    if (pooled) lds += 16 + (size_t)kSelectPoolCap * 16;           // the pool, as it came and in order
     IVF_LAUNCH(select_kernel, dim3(a.nq), dim3(threads), lds, s, e0, e1, a, pad, in_lds, prefix_in_lds, pooled);
     return hipGetLastError();
 }

@@ -139,11 +139,12 @@ def test_survivors_of_a_list_major_batch(streams, dtype, metric, k, band):
 
 @pytest.mark.parametrize("metric", ["ip", "l2"])
 @pytest.mark.parametrize("nlist,nprobe", [(65, 65), (1000, 257), (1024, 1024), (2049, 512), (8191, 65), (8193, 512), (16500, 300), (4097, 3)])
-@pytest.mark.parametrize("kind", ["random", "one_side", "ties", "infinite", "nan"])
+@pytest.mark.parametrize("kind", ["random", "one_side", "ties", "pairs", "near", "many_equal", "infinite", "nan"])
 def test_select_of_many_clusters(streams, nlist, nprobe, kind, metric):
     """Selections through the pooled path: scores around zero, scores far from zero, masses of equal
-    scores (the pool overflows or prefixes tie: the exact path) and infinite ones; order and content
-    are the oracle's."""
+    scores (the pool overflows: the exact path), scores that are equal in pairs, that differ in the low
+    bits of their keys only or that are equal by the hundred (prefixes tie inside the pool and across
+    the cut), and infinite ones; order and content are the oracle's."""
     rng = np.random.default_rng(nlist + nprobe)
     d = 8
     cent = rng.standard_normal((nlist, d)).astype(np.float32)
@@ -153,6 +154,19 @@ def test_select_of_many_clusters(streams, nlist, nprobe, kind, metric):
     elif kind == "ties":
         cent = np.round(cent)
         cent[rng.permutation(nlist)[:nlist // 2]] = cent[0]
+    elif kind == "pairs":
+        cent[nlist // 2:nlist // 2 * 2] = cent[:nlist // 2]
+    elif kind == "near":
+        # one large element of one value, the small one decides: relative differences of 1e-11 and less
+        cent[:, 1:] = 0.0
+        cent[:, 0] = 1.0
+        cent[:, 3] = 1e-10 * rng.permutation(nlist) / nlist
+        q[:, 0], q[:, 3] = 100.0, 1.0
+        if metric == "l2":
+            cent[:, 3] *= 1e2
+    elif kind == "many_equal":
+        best = rng.permutation(nlist)[:min(nprobe + 40, 700)]
+        cent[best] = 4.0 * np.sign(q[0])
     elif kind == "infinite":
         cent[rng.permutation(nlist)[:nprobe // 2]] *= np.float32(1e30)
         q *= np.float32(1e30)
