@@ -19,11 +19,17 @@ using namespace dev;
 // at once; HBM-bound on the nlist*d*4 bytes of the centroid matrix, in practice one memory
 // latency.  A batch of queries: a dense contraction Q x C^T on the fp64 matrix cores.
 // =============================================================================================
-// Batches below this use the row kernel, which walks the queries one after the other: with 8
-// queries x 4096 x 768 17.7 us against 8.4 on the matrix cores, with 2 7.9 (and with 3 9.9).  Squared
-// L2 keeps the direct sum of squared differences up to 15 queries, and for any number when d is no multiple
-// of 4 (the matrix cores need the three norms form, which is less exact where distances are small).
-constexpr int kCoarseRowMaxIp = 3, kCoarseRowMaxL2 = 16;
+// The row kernel walks the queries one after the other; measured against the matrix cores (us): 3
+// queries x 4096 x 768 7.4 / 6.2, x 1024 x 768 5.2 / 5.9, x 1024 x 2048 7.5 / 10.4, x 32768 x 1024 41 / 35;
+// 4 x 1024 x 768 6.4 / 6.2, x 1024 x 2048 9.2 / 10.4; 5 x 1024 x 2048 10.8 / 10.4; 8 x 4096 x 768 15 / 6.4.  So
+// it takes 3 and 4 queries of few centroids and wide rows (a wavefront of the matrix kernel then has a
+// longer chain), and always one or two.  Squared L2 keeps the direct sum of squared differences up to 15 queries, and
+// for any number when d is no multiple of 4 (the matrix cores need the three norms form, which is less exact
+// where distances are small).
+static bool coarse_by_rows(const CoarseArgs& a) {
+    if (a.metric != 0) return a.nq < 16 || (a.d & 3) != 0;
+    return a.nq < 3 || (a.nq <= 4 && a.nq * 256 <= a.d && a.nlist <= 2048);
+}
 constexpr int kSelectWaveSortMax = 4096;   // select: register sorting path up to this many clusters
 
 // RAGGED: d is no multiple of 4, rows start at any element.
@@ -88,6 +94,7 @@ __global__ __launch_bounds__(256) void coarse_rows_kernel(CoarseArgs a) {
 // through the elements, not the matrix cores.  (Tiles of 32 x 128 that walked all elements through
 // LDS slabs, a barrier pair per 32: 52.7, 55.5 and 117 us for 16 queries x 1024 x 768, 32 x 4096 x 768
 // and 256 x 8192 x 1024; this: 8.2, 12.6 and 94; the fp64 matrix peak for the last is 55 us.)
+// W = 1: a tile is one wavefront's, its sums go straight to memory and no LDS is used.
 // RAGGED: d is no multiple of 4, rows start at any element (the row kernel served such batches with
 // single elements: 272 and 1120 us for 256 queries x 2678 x 295 and x 8192 x 747; this: 20 and 75).
 // Workgroups that follow each other on one XCD share their centroids (blockIdx % 8 is the XCD):
@@ -176,7 +183,27 @@ __global__ __launch_bounds__(W * 64) void coarse_mfma_kernel(CoarseArgs a, int q
         if (k + 2 * step < a.d) request(k + 2 * step, st[0]);
         multiply(st[1]);
     }
-    // the four wavefronts' sums, added in order
+    if (W == 1) {
+#pragma unroll
+        for (int y = 0; y < CT; ++y) if (a.metric != 0) { nc2[y] += __shfl_xor(nc2[y], 16); nc2[y] += __shfl_xor(nc2[y], 32); }
+#pragma unroll
+        for (int x = 0; x < QT; ++x) {
+            if (a.metric != 0) { nq2[x] += __shfl_xor(nq2[x], 16); nq2[x] += __shfl_xor(nq2[x], 32); }
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+                const int i = x * 16 + 4 * r + fk;
+                const double qn = a.metric != 0 ? __shfl(nq2[x], 4 * r + fk) : 0.0;
+#pragma unroll
+                for (int y = 0; y < CT; ++y) {
+                    const int j = y * 16 + fi;
+                    const double s = a.metric != 0 ? fma(-2.0, acc[x][y][r], qn + nc2[y]) : acc[x][y][r];
+                    if (q0 + i < a.nq && c0 + j < a.nlist) a.scores[(size_t)(q0 + i) * a.nlist + c0 + j] = s;
+                }
+            }
+        }
+        return;
+    }
+    // the wavefronts' sums, added in order
 #pragma unroll
     for (int x = 0; x < QT; ++x)
 #pragma unroll
@@ -219,22 +246,30 @@ __global__ __launch_bounds__(W * 64) void coarse_mfma_kernel(CoarseArgs a, int q
 template <int QT, int CT, int W>
 static void launch_coarse_mfma(const CoarseArgs& a, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
     const int q_tiles = (a.nq + QT * 16 - 1) / (QT * 16), c_tiles = (a.nlist + CT * 16 - 1) / (CT * 16);
-    const size_t lds = (size_t)W * (QT * CT * 4 * 64 + QT * 16 + CT * 16) * sizeof(double);
+    const size_t lds = W == 1 ? 0 : (size_t)W * (QT * CT * 4 * 64 + QT * 16 + CT * 16) * sizeof(double);
     const dim3 grid((unsigned)((c_tiles + 7) / 8 * 8 * q_tiles));
     if (a.d & 3) IVF_LAUNCH((coarse_mfma_kernel<QT, CT, W, true>), grid, dim3(W * 64), lds, s, e0, e1, a, q_tiles);
     else IVF_LAUNCH((coarse_mfma_kernel<QT, CT, W, false>), grid, dim3(W * 64), lds, s, e0, e1, a, q_tiles);
 }
 
 hipError_t launch_coarse(const CoarseArgs& a, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
-    if (a.nq < (a.metric == 0 ? kCoarseRowMaxIp : kCoarseRowMaxL2) || (a.metric != 0 && (a.d & 3) != 0)) {
+    if (coarse_by_rows(a)) {
         if (a.d & 3) IVF_LAUNCH(coarse_rows_kernel<true>, dim3((a.nlist + 3) / 4), dim3(256), 0, s, e0, e1, a);
         else IVF_LAUNCH(coarse_rows_kernel<false>, dim3((a.nlist + 3) / 4), dim3(256), 0, s, e0, e1, a);
     } else {
         // Small tiles while they leave the chip short of work, measured with 1024, 4096 and 8192 lists:
         // 512 of them 12.9, 12.6, 14.3 us against 15.7, 16.1, 19.1 of the large ones; 768: 16.0 against
-        // 17.0; 1024: 19.3, 19.2, 22.5 against 17.0, 17.0, 19.5; 8192: 123 against 94.
+        // 17.0; 1024: 19.3, 19.2, 22.5 against 17.0, 17.0, 19.5; 8192: 123 against 94.  And for any number of
+        // lists when the queries fit one of them (4 queries x 65536 x 64, 128, 768: 11.5, 14.6, 51 us against
+        // 14.2, 18.2, 76).
+        // Large ones: split over four wavefronts while the chain counts.  One wavefront per tile when
+        // there are more than eight tiles per compute unit, or half of the four had no elements (256 queries x
+        // 16384 x 64, 65536 x 64, 16384 x 256, 65536 x 768: 26, 66, 58, 552 us against 31, 94, 64, 593; 2048
+        // tiles of 256 x 8192 x 768 85 against 81, but x 64 17.8 against 20.2).
         const size_t small_tiles = (size_t)((a.nlist + 15) / 16) * ((a.nq + 15) / 16);
-        if (small_tiles <= 768) launch_coarse_mfma<1, 1, 8>(a, s, e0, e1);
+        const size_t large_tiles = (size_t)((a.nlist + 31) / 32) * ((a.nq + 31) / 32);
+        if (small_tiles <= 768 || a.nq <= 16) launch_coarse_mfma<1, 1, 8>(a, s, e0, e1);
+        else if (large_tiles > 2048 || (a.d <= 64 && large_tiles >= 1024)) launch_coarse_mfma<2, 2, 1>(a, s, e0, e1);
         else launch_coarse_mfma<2, 2, 4>(a, s, e0, e1);
     }
     return hipGetLastError();

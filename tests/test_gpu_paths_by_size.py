@@ -69,10 +69,12 @@ def test_scheduler_walks_sorted_lists(streams, B, d, micro):
 @pytest.mark.parametrize("metric", ["ip", "l2"])
 @pytest.mark.parametrize("nq,nlist,d", [(2, 40, 64), (3, 15, 4), (3, 129, 768), (15, 17, 36), (16, 1, 260), (17, 33, 1028),
                                         (33, 6200, 20), (130, 1100, 96), (1, 9, 3), (2, 30, 257), (4, 33, 1), (5, 70, 2), (17, 40, 31),
-                                        (20, 300, 295), (40, 2000, 1023), (200, 50, 37)])
+                                        (20, 300, 295), (40, 2000, 1023), (200, 50, 37),
+                                        (3, 2048, 768), (4, 2049, 1024), (4, 31, 1028), (16, 13000, 33), (64, 16384, 64), (250, 8200, 100),
+                                        (250, 8200, 67)])
 def test_coarse_scores_by_batch_size(streams, nq, nlist, d, metric):
     """Row kernel, small and large matrix-core tiles: ragged in queries, centroids and elements (a
-    row's blocks of 32 elements are dealt to 4 or 8 wavefronts), two XCD groups and more."""
+    row's blocks of 32 elements are dealt to 1, 4 or 8 wavefronts), two XCD groups and more."""
     rng = np.random.default_rng(nq * nlist + d)
     cent = rng.standard_normal((nlist, d)).astype(np.float32)
     q = rng.standard_normal((nq, d)).astype(np.float32)
@@ -81,7 +83,7 @@ def test_coarse_scores_by_batch_size(streams, nq, nlist, d, metric):
                                compute_stream=streams[0], copy_stream=streams[1])
     got = index.ivf_coarse_scores(q)
     x, y = q.astype(np.float64), cent.astype(np.float64)
-    want = x @ y.T if metric == "ip" else ((x[:, None] - y[None]) ** 2).sum(2)
+    want = x @ y.T if metric == "ip" else np.stack([((one - y) ** 2).sum(1) for one in x])
     # a sum of d products rounded d times: d 2^-53 times the sum of the magnitudes, with room for the three norms form
     bound = 8 * d * 2.0 ** -53 * (np.abs(x) @ np.abs(y).T + (x * x).sum(1)[:, None] + (y * y).sum(1)[None])
     assert (np.abs(got - want) <= bound).all()
