@@ -90,29 +90,49 @@ constexpr int kSampleStep = kFrontThreads / 64 * 4;          // rows a workgroup
 // workgroups took 150 us of a 256-query batch.
 static int sample_parts(int nq) { return std::max(4, std::min(kSampleRows / kSampleStep, 1024 / nq)); }
 constexpr int kMapLdsLists = 8192;          // up to this many clusters the map is counted in LDS
+// With more clusters the pairs are counted in global memory: by the workgroup of the map itself while they
+// are few, else by the whole chip in two launches of their own.
+// Whole calls, us, map's workgroup / whole chip: 4096 pairs of 16384 clusters 137 / 140, 8192 164 / 162,
+// 16384 203 / 184, 131072 (256 queries x 512) 452 / 269; of 65536 clusters 4096 234 / 226, 131072 860 / 663.
+constexpr uint32_t kMapSpreadPairs = 8192;
+static bool map_counted_before(int nlist, int nq, int nprobe) {
+    return nlist > kMapLdsLists && (uint64_t)nq * (uint64_t)nprobe >= kMapSpreadPairs;
+}
+
+__global__ __launch_bounds__(256) void clear_counts_kernel(BatchedArgs a) {
+    const int c = (int)(blockIdx.x * 256u + threadIdx.x);
+    if (c < a.nlist) a.list_count[c] = 0u;
+}
+
+__global__ __launch_bounds__(256) void count_pairs_kernel(BatchedArgs a) {
+    const uint32_t pairs = (uint32_t)a.nq * (uint32_t)a.nprobe, i = blockIdx.x * 256u + threadIdx.x;
+    if (i < pairs) atomicAdd(&a.list_count[a.probe[i]], 1u);
+}
 
 // Map: queries per cluster, and their prefix sums qstart (= cursor) and tstart (tasks per cluster).
 // One workgroup: LDS atomics and a few rounds of prefix sums, beside the sample.  (The places of the
 // queries are filled in by the next launch: 131,072 scattered stores from one compute unit took
 // 140 us, from all of them 6.)
 template <bool LDS>
-__device__ __forceinline__ void build_map(const BatchedArgs& a, uint32_t* cnt) {
+__device__ __forceinline__ void build_map(const BatchedArgs& a, uint32_t* cnt, bool counted) {
     __shared__ uint32_t wsum_q[kFrontThreads / 64], wsum_t[kFrontThreads / 64];
     const int tid = threadIdx.x, lane = lane_id(), wave = wave_id();
     const uint32_t pairs = (uint32_t)a.nq * (uint32_t)a.nprobe;
     // counters in global memory are read past the L1 and ordered by device-wide fences
     auto meet = [&]() { if (!LDS) __threadfence(); __syncthreads(); };
     auto count_of = [&](int c) -> uint32_t { return LDS ? cnt[c] : __hip_atomic_load(&cnt[c], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
-    for (int c = tid; c <= a.nlist; c += kFrontThreads) {              // one more: pairs past the end count there
-        if (LDS) cnt[c] = 0u;
-        else __hip_atomic_store(&cnt[c], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
     if (tid == 0) *a.ticket = 0u;
-    meet();
+    if (!counted) {
+        for (int c = tid; c <= a.nlist; c += kFrontThreads) {          // one more: pairs past the end count there
+            if (LDS) cnt[c] = 0u;
+            else __hip_atomic_store(&cnt[c], 0u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        meet();
+    }
     // sixteen pairs per thread and pass: all requested before the first is used, and no branches that
     // differ between lanes, so that neither the reads nor the atomics wait for each other
 #pragma unroll 1
-    for (uint32_t i0 = 0; i0 < pairs; i0 += kFrontThreads * 16) {
+    for (uint32_t i0 = 0; i0 < pairs && !counted; i0 += kFrontThreads * 16) {
         int32_t c[16];
 #pragma unroll
         for (int u = 0; u < 16; ++u) c[u] = a.probe[min(i0 + (uint32_t)(u * kFrontThreads + tid), pairs - 1)];
@@ -212,11 +232,11 @@ __device__ __forceinline__ void prepare_query(const BatchedArgs& a, int qi) {
 }
 
 template <typename T>
-__global__ __launch_bounds__(kFrontThreads) void batch_front_kernel(BatchedArgs a, int parts) {
+__global__ __launch_bounds__(kFrontThreads) void batch_front_kernel(BatchedArgs a, int parts, int counted) {
     extern __shared__ __align__(16) unsigned char smem[];
     if (blockIdx.x == 0) {
-        if (a.nlist <= kMapLdsLists) build_map<true>(a, (uint32_t*)smem);
-        else build_map<false>(a, a.list_count);
+        if (a.nlist <= kMapLdsLists) build_map<true>(a, (uint32_t*)smem, false);
+        else build_map<false>(a, a.list_count, counted != 0);
         return;
     }
     constexpr int EPL = T::kPerLoad, U = kSampleStep / (kFrontThreads / 64), V = 4;      // rows of a wavefront, 16-byte loads per lane and row in flight
@@ -1074,11 +1094,15 @@ float batched_sample_coef(int d, int dtype, int metric) {
 
 hipError_t launch_batched(const BatchedArgs& a, int grid, hipStream_t s, hipEvent_t scan_start, hipEvent_t scan_stop, bool with_merge) {
     const size_t front_lds = std::max((size_t)a.d * 4, a.nlist <= kMapLdsLists ? ((size_t)a.nlist + 1) * 4 : (size_t)0);
-    const int parts = sample_parts(a.nq);
+    const int parts = sample_parts(a.nq), counted = map_counted_before(a.nlist, a.nq, a.nprobe);
+    if (counted) {
+        hipLaunchKernelGGL(clear_counts_kernel, dim3((unsigned)(a.nlist + 255) / 256), dim3(256), 0, s, a);
+        hipLaunchKernelGGL(count_pairs_kernel, dim3((unsigned)(((uint64_t)a.nq * (uint64_t)a.nprobe + 255) / 256)), dim3(256), 0, s, a);
+    }
     const dim3 front(1 + (unsigned)a.nq * (unsigned)(parts + 1)), tasks((unsigned)a.nq + (unsigned)std::min((a.nlist + 3) / 4, 1024));
-    if (a.dtype == 0) hipLaunchKernelGGL(batch_front_kernel<F32>, front, dim3(kFrontThreads), front_lds, s, a, parts);
-    else if (a.dtype == 1) hipLaunchKernelGGL(batch_front_kernel<F16>, front, dim3(kFrontThreads), front_lds, s, a, parts);
-    else hipLaunchKernelGGL(batch_front_kernel<BF16>, front, dim3(kFrontThreads), front_lds, s, a, parts);
+    if (a.dtype == 0) hipLaunchKernelGGL(batch_front_kernel<F32>, front, dim3(kFrontThreads), front_lds, s, a, parts, counted);
+    else if (a.dtype == 1) hipLaunchKernelGGL(batch_front_kernel<F16>, front, dim3(kFrontThreads), front_lds, s, a, parts, counted);
+    else hipLaunchKernelGGL(batch_front_kernel<BF16>, front, dim3(kFrontThreads), front_lds, s, a, parts, counted);
     hipLaunchKernelGGL(batch_tasks_kernel, tasks, dim3(256), 0, s, a);
     const BatchedScanFn scan = batched_scan_fn(a.dtype, a.metric);
     IVF_LAUNCH(scan, dim3(grid), dim3(kBatchThreads), batched_scan_lds(a.d, a.dtype), s, scan_start, scan_stop, a);

@@ -90,10 +90,11 @@ def test_coarse_scores_by_batch_size(streams, nq, nlist, d, metric):
     index.close()
 
 
-@pytest.mark.parametrize("nlist,nq,nprobe,k,d", [(8192, 5, 40, 3, 64), (8193, 5, 40, 3, 64), (9000, 70, 33, 100, 64), (3, 2, 3, 1, 128),
+@pytest.mark.parametrize("nlist,nq,nprobe,k,d", [(8192, 5, 40, 3, 64), (8193, 5, 40, 3, 64), (9000, 70, 33, 100, 64), (8193, 211, 39, 3, 64),
+                                                 (20000, 33, 250, 10, 64), (8192, 211, 39, 3, 64), (3, 2, 3, 1, 128),
                                                  (40, 300, 7, 20, 64), (700, 33, 512, 112, 128)])
 def test_front_of_a_list_major_batch(streams, nlist, nq, nprobe, k, d):
-    """The map from clusters to queries in LDS and in global memory, samples of fewer rows than k, one
+    """The map from clusters to queries in LDS, in global memory and counted by launches of its own, samples of fewer rows than k, one
     and several steps of the sample per workgroup: list-major equals query by query bit for bit."""
     rng = np.random.default_rng(nlist + nq)
     n = nlist * 9
