@@ -573,7 +573,7 @@ int ensure_batched_workspace(ivf_index* ix, int nq, int nprobe) {
     HIP_TRY(hipMalloc(&w.d_tstart, (nl + 1) * sizeof(uint32_t)));
     HIP_TRY(hipMalloc(&w.d_qidx, nqz * np2 * sizeof(uint32_t)));
     HIP_TRY(hipMalloc(&w.d_tasks, task_cap * sizeof(BatchTask)));
-    HIP_TRY(hipMalloc(&w.d_cand_count, nqz * sizeof(uint32_t)));
+    HIP_TRY(hipMalloc(&w.d_cand_count, nqz * kCountStride * sizeof(uint32_t)));
     HIP_TRY(hipMalloc(&w.d_cand_row, nqz * kCandCap * sizeof(uint32_t)));
     HIP_TRY(hipMalloc(&w.d_cand_score, nqz * kCandCap * sizeof(float)));
     HIP_TRY(hipMalloc(&w.d_eps, nqz * sizeof(float)));
@@ -1559,12 +1559,13 @@ extern "C" int ivf_batched_scores(ivf_index* ix, const float* q, int32_t nq, int
     b.nq = nq; b.nprobe = 1; b.k = 1; b.kprime = kprime_for(1); b.keep_all = 1;
     HIP_TRY(launch_batched(b, ix->batched_grid, ix->cs, nullptr, nullptr, false));
     HIP_TRY(hipStreamSynchronize(ix->cs));
-    std::vector<uint32_t> count((size_t)nq), rows((size_t)n_c);
+    std::vector<uint32_t> count((size_t)nq * kCountStride), rows((size_t)n_c);
     std::vector<float> sc((size_t)n_c);
-    HIP_TRY(hipMemcpy(count.data(), w.d_cand_count, (size_t)nq * sizeof(uint32_t), hipMemcpyDeviceToHost));
+    HIP_TRY(hipMemcpy(count.data(), w.d_cand_count, count.size() * sizeof(uint32_t), hipMemcpyDeviceToHost));
     HIP_TRY(hipMemcpy(eps, w.d_eps, (size_t)nq * sizeof(float), hipMemcpyDeviceToHost));
     for (int qi = 0; qi < nq; ++qi) {
-        if ((int64_t)count[qi] != n_c) return fail(IVF_ESTATE, "query %d: %u of %lld rows came back", qi, count[qi], (long long)n_c);
+        const uint32_t got = count[(size_t)qi * kCountStride];
+        if ((int64_t)got != n_c) return fail(IVF_ESTATE, "query %d: %u of %lld rows came back", qi, got, (long long)n_c);
         HIP_TRY(hipMemcpy(rows.data(), w.d_cand_row + (size_t)qi * kCandCap, (size_t)n_c * sizeof(uint32_t), hipMemcpyDeviceToHost));
         HIP_TRY(hipMemcpy(sc.data(), w.d_cand_score + (size_t)qi * kCandCap, (size_t)n_c * sizeof(float), hipMemcpyDeviceToHost));
         for (int64_t i = 0; i < n_c; ++i) scores[(size_t)qi * n_c + (rows[i] - (uint32_t)ix->h_off[cluster])] = sc[i];

@@ -227,7 +227,7 @@ __device__ __forceinline__ void prepare_query(const BatchedArgs& a, int qi) {
         a.eps[qi] = a.metric == 0 ? 1.01f * (ip_err + a.samp_coef * qn * ymax)
                                   : 1.01f * (2.f * ip_err + (a.samp_coef + 0x1p-21f) * (qn + ymax) * (qn + ymax));
         a.qq[qi] = (float)qq;
-        a.cand_count[qi] = 0;
+        a.cand_count[(size_t)qi * kCountStride] = 0;
     }
 }
 
@@ -590,7 +590,7 @@ __global__ __launch_bounds__(kBatchThreads) void batched_scan_kernel(BatchedArgs
         }
         if (pass) {
             // one reservation for all rows of this lane that passed
-            uint32_t pos = atomicAdd(&a.cand_count[qi], (uint32_t)__popc(pass));
+            uint32_t pos = atomicAdd(&a.cand_count[(size_t)qi * kCountStride], (uint32_t)__popc(pass));
 #pragma unroll
             for (int i = 0; i < 16; ++i) {
                 if ((pass >> i) & 1u) {
@@ -758,7 +758,7 @@ __global__ __launch_bounds__(kBatchThreads) void batched_scan_f32_kernel(Batched
             if (sc[i] >= thr && r < n) pass |= 1u << i;
         }
         if (pass) {
-            uint32_t pos = atomicAdd(&a.cand_count[qi], (uint32_t)__popc(pass));
+            uint32_t pos = atomicAdd(&a.cand_count[(size_t)qi * kCountStride], (uint32_t)__popc(pass));
 #pragma unroll
             for (int i = 0; i < 8; ++i) {
                 if ((pass >> i) & 1u) {
@@ -807,7 +807,7 @@ __global__ __launch_bounds__(kSelectThreads) void batched_merge_kernel(BatchedAr
     constexpr int nt = kSelectThreads;
     const int qi = blockIdx.x;
     const uint32_t k = (uint32_t)a.k;
-    const uint32_t n0 = a.cand_count[qi];
+    const uint32_t n0 = a.cand_count[(size_t)qi * kCountStride];
     if (n0 > (uint32_t)a.cand_cap) {                   // too many candidates: the host redoes this query
         if (tid == 0) a.overflow[qi] = 1;
         return;
