@@ -1548,9 +1548,12 @@ extern "C" int ivf_batched_scores(ivf_index* ix, const float* q, int32_t nq, int
     if ((rc = ensure_batched_workspace(ix, nq, 1))) return rc;
     Workspace& w = *ix->cw;
     if ((rc = stage_queries(ix, q, nq))) return rc;
-    // every query "selects" the one cluster
+    // every query "selects" the one cluster: what the selection would have left of it for the launches below
     std::vector<int32_t> probe((size_t)nq, cluster);
+    std::vector<uint32_t> rprefix((size_t)nq * 2, 0u);
+    for (int qi = 0; qi < nq; ++qi) rprefix[(size_t)qi * 2 + 1] = (uint32_t)n_c;
     HIP_TRY(hipMemcpyAsync(w.d_probe, probe.data(), (size_t)nq * sizeof(int32_t), hipMemcpyHostToDevice, ix->cs));
+    HIP_TRY(hipMemcpyAsync(w.slots.rprefix, rprefix.data(), rprefix.size() * sizeof(uint32_t), hipMemcpyHostToDevice, ix->cs));
     HIP_TRY(hipStreamSynchronize(ix->cs));
     if (ix->batched_grid == 0) ix->batched_grid = batched_resident_grid(ix->dtype, ix->metric, ix->d, ix->n_cu);
     BatchedArgs b{};

@@ -289,3 +289,26 @@ def test_equal_scores_do_not_stall_a_list_major_batch(streams):
         index.close()
     # measured 5 to 8 times a plain batch; 25 leaves room for a busy host
     assert took[1] < 25 * took[0], took
+
+
+@pytest.mark.parametrize("nq", [1, 32])
+def test_filter_scores_do_not_depend_on_earlier_searches(streams, nq):
+    """ivf_batched_scores leaves the launches it shares with a search what a selection would have
+    left: the same scores and bounds on a fresh index, after searches of other shapes, and for clusters
+    of one row and of many."""
+    rng = np.random.default_rng(nq)
+    nlist, d = 9, 128
+    assign = np.concatenate([[0], np.full(3000, 1), rng.integers(2, nlist, 4000)]).astype(np.int32)
+    cent = rng.standard_normal((nlist, d)).astype(np.float32)
+    rows = (cent[assign] + rng.standard_normal((assign.size, d))).astype(np.float16)
+    q = rng.standard_normal((nq, d)).astype(np.float32)
+    index = P.ivf_build_layout(rows, "f16", cent, assign, compute_stream=streams[0], copy_stream=streams[1])
+    sizes = (1, 3000)
+    fresh = [index.ivf_batched_scores(q, c, sizes[c]) for c in (0, 1)]
+    index.ivf_search(rng.standard_normal((40, d)).astype(np.float32), 7, 5)
+    for c in (0, 1):
+        for want, got in zip(fresh[c], index.ivf_batched_scores(q, c, sizes[c])):
+            np.testing.assert_array_equal(got, want)
+        s64 = q.astype(np.float64) @ rows[assign == c].astype(np.float64).T
+        assert (np.abs(fresh[c][0] - s64) <= fresh[c][1][:, None]).all()
+    index.close()
