@@ -194,24 +194,42 @@ def test_select_of_many_clusters(streams, nlist, nprobe, kind, metric):
                                      ("f16", 7), ("f16", 9), ("f16", 127), ("f16", 129), ("f16", 300), ("f16", 513), ("bf16", 31),
                                      ("bf16", 767), ("bf16", 1030), ("bf16", 4095)])
 def test_rows_that_are_not_whole_chunks(streams, dtype, d, metric):
-    """Every scan shape with a partial last chunk, rows at every alignment, an infinite element in
-    the part that two lanes load; the last row ends where the buffer does.  The oracle's results."""
+    """Every scan shape with a partial last chunk, rows at every alignment; the last row ends where the
+    buffer does.  The oracle's results.  Then an infinite element in the part of a row that two
+    lanes load: counted once it makes the row the nearest (inner product) or the farthest (L2), and
+    multiplied by the zero that the second lane has for it the row would be no number and lost."""
     rng = np.random.default_rng(d)
     n, nlist, k = 331, 5, 12
     om = O.IP if metric == "ip" else O.L2
     cent = rng.standard_normal((nlist, d)).astype(np.float32)
     assign = rng.integers(0, nlist, n).astype(np.int32)
     rows = (cent[assign] + rng.standard_normal((n, d))).astype(np.float32)
-    rows[7, d - 2] = -np.inf if metric == "ip" else np.inf
-    st, odt = stored(rows, dtype)
-    index = P.ivf_build_layout(st, dtype, cent, assign, metric=P.IVF_IP if metric == "ip" else P.IVF_L2,
-                               compute_stream=streams[0], copy_stream=streams[1])
+    q = np.abs(rng.standard_normal((4, d))).astype(np.float32) + 0.1
+
+    def search(rows, k):
+        st, odt = stored(rows, dtype)
+        index = P.ivf_build_layout(st, dtype, cent, assign, metric=P.IVF_IP if metric == "ip" else P.IVF_L2,
+                                   compute_stream=streams[0], copy_stream=streams[1])
+        out = index.ivf_search(q, nlist, k)
+        index.close()
+        return st, odt, out
+
+    st, odt, (gi, gd) = search(rows, k)
     off, perm = O.build_layout(assign, nlist)
-    q = np.abs(rng.standard_normal((4, d))).astype(np.float32)
-    gi, gd = index.ivf_search(q, nlist, k)
     for b in range(4):
         assert check_topk(gi[b], gd[b], st[perm], odt, off, perm.astype(np.int64), cent, q[b], nlist, k, om) == 0
-    index.close()
+    per_chunk = 4 if dtype == "f32" else 8
+    odd = int(gi[0][2])                                     # a row that is among the nearest
+    rows[odd, max(d - per_chunk, 0)] = np.inf               # the first element of the 16 bytes that end the row
+    assert d < per_chunk or max(d - per_chunk, 0) < d // per_chunk * per_chunk
+    _, _, (hi, hd) = search(rows, k)
+    for b in range(4):
+        others = [(i, x) for i, x in zip(gi[b], gd[b]) if i != odd]
+        got = list(zip(hi[b], hd[b]))
+        if metric == "ip":
+            assert got == [(odd, np.inf)] + others[:k - 1]
+        else:
+            assert odd not in hi[b] and got[:len(others)] == others
 
 
 @pytest.mark.parametrize("dtype,d,per_batch", [("f32", 64, 24), ("f16", 90, 24), ("f32", 128, 12), ("f32", 101, 12), ("bf16", 512, 6), ("f32", 255, 6)])
