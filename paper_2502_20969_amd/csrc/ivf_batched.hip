@@ -901,7 +901,6 @@ __global__ __launch_bounds__(kSelectThreads) void batched_merge_kernel(BatchedAr
     }
     // 3. fp64 re-scores of survivors c0 .. c1 - 1: a group of lanes per survivor, two rows in flight
     const float* q = a.q + (size_t)qi * a.d;
-    const bool whole = ((size_t)a.d * (a.dtype == 0 ? 4 : 2)) % 16 == 0;
     const int sub = tid % kRescoreLanes;
     auto rescore = [&](uint32_t c0, uint32_t c1) {
         constexpr uint32_t groups = nt / kRescoreLanes;
@@ -911,11 +910,7 @@ __global__ __launch_bounds__(kSelectThreads) void batched_merge_kernel(BatchedAr
             uint32_t row[kRescoreInFlight];
 #pragma unroll
             for (int r = 0; r < kRescoreInFlight; ++r) row[r] = s_row[min(c + groups * r, c1 - 1)];
-            if (whole) rescore_rows<kRescoreInFlight>(a.lists, q, a.d, a.dtype, a.metric, row, sub, s);
-            else {
-#pragma unroll
-                for (int r = 0; r < kRescoreInFlight; ++r) s[r] = rescore_row(a.lists, q, a.d, a.dtype, a.metric, row[r], sub);
-            }
+            rescore_rows<kRescoreInFlight>(a.lists, q, a.d, a.dtype, a.metric, row, sub, s);     // d is a multiple of 64
 #pragma unroll
             for (int r = 0; r < kRescoreInFlight; ++r)
                 if (sub == 0 && c + groups * r < c1) s_key[c + groups * r] = ordered(a.metric == 0 ? s[r] : -s[r]);
