@@ -127,7 +127,7 @@ __global__ void sort_near_kernel(const double* D, int B, uint32_t pad, int strid
 // their places).  A chain of LDS reads per micro-batch bounds it; the list of the query that will
 // most likely seed next is requested one micro-batch ahead, so that memory is not part of the
 // chain.  (Picking one query at a time with a workgroup-wide minimum: 892 us for 512 queries in
-// groups of 8; sort_near_kernel + this: 15 + 67 us.  4096 queries: 8.8 -> 1.3 ms for all three kernels.)
+// groups of 8; sort_near_kernel + this: 15 + 67 us.  4096 queries: 10.7 -> 2.25 ms for all three kernels.)
 __global__ __launch_bounds__(64) void greedy_groups_kernel(const uint16_t* near, int B, int stride, int m, int32_t* order) {
     __shared__ unsigned char taken[kScheduleMaxQueries + 64];
     const int lane = threadIdx.x;

@@ -66,6 +66,39 @@ def test_scheduler_walks_sorted_lists(streams, B, d, micro):
     index.close()
 
 
+def test_scheduler_calls_of_changing_size(streams):
+    """Batches whose workspace is kept, replaced by a larger one's or made for one call, in turn."""
+    rng = np.random.default_rng(7)
+    index = P.ivf_adopt_layout(torch.zeros(1, 20, device="cuda"), "f32", np.array([0, 1]), np.zeros((1, 20), np.float32),
+                               compute_stream=streams[0], copy_stream=streams[1])
+    for B in (100, 1024, 1025, 300, 2100, 1024):
+        q = rng.standard_normal((B, 20)).astype(np.float32)
+        assert list(index.ivf_schedule(q, 7)) == list(O.schedule(q, 7))
+    index.close()
+
+
+@pytest.mark.parametrize("value", [np.nan, np.inf])
+@pytest.mark.parametrize("B", [40, 700])
+def test_scheduler_distances_that_are_no_numbers(streams, B, value):
+    """A distance that is no number is farther than any other, an infinite one farther than any finite."""
+    rng = np.random.default_rng(B)
+    q = rng.standard_normal((B, 24)).astype(np.float32)
+    q[rng.permutation(B)[:B // 5], 3] = value
+    index = P.ivf_adopt_layout(torch.zeros(1, 24, device="cuda"), "f32", np.array([0, 1]), np.zeros((1, 24), np.float32),
+                               compute_stream=streams[0], copy_stream=streams[1])
+    order = list(index.ivf_schedule(q, 9))
+    index.close()
+    with np.errstate(invalid="ignore"):
+        dist = ((q.astype(np.float64)[:, None] - q.astype(np.float64)[None]) ** 2).sum(2)
+    left, want = list(range(B)), []
+    while left:
+        seed = left.pop(0)
+        near = sorted(left, key=lambda j: (np.isnan(dist[seed, j]), 0.0 if np.isnan(dist[seed, j]) else dist[seed, j], j))[:8]
+        want += [seed] + near
+        left = [j for j in left if j not in near]
+    assert order == want
+
+
 @pytest.mark.parametrize("metric", ["ip", "l2"])
 @pytest.mark.parametrize("nq,nlist,d", [(2, 40, 64), (3, 15, 4), (3, 129, 768), (15, 17, 36), (16, 1, 260), (17, 33, 1028),
                                         (33, 6200, 20), (130, 1100, 96), (1, 9, 3), (2, 30, 257), (4, 33, 1), (5, 70, 2), (17, 40, 31),
