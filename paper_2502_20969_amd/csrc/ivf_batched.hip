@@ -67,7 +67,7 @@ hipError_t launch_row_norms(const void* lists, int dtype, int64_t n, int d, unsi
 // One launch for everything that needs only the selected clusters: its workgroups differ in what
 // they do (the steps are short, and as launches of their own they cost more than they computed:
 // sample, queries, map and task list in seven launches 65, 72 and 260 us for 8 and 32 queries x 768
-// fp32 and 256 x 1024 bf16 with 128, 32 and 512 clusters each; the two launches here 16, 20 and 151).
+// fp32 and 256 x 1024 bf16 with 128, 32 and 512 clusters each; the two launches here 15, 21 and 142).
 //
 // Workgroup 0 builds the map from clusters to the queries that probe them.  Each of the others
 // scores one part of a query's threshold sample: fp32 scores (fp32 query; <q, y>, or -sum (q - y)^2
@@ -784,7 +784,7 @@ __global__ __launch_bounds__(kBatchThreads) void batched_scan_f32_kernel(Batched
 // What bounds it: the re-scores' trips to memory (two rows per group of lanes in flight), and in a
 // batch the query with the most survivors.  (Radix selects over candidates and re-scores in global
 // memory, one row in flight per group: 13, 17 and 140 us for 8, 32 and 256 queries with k 3, 10 and
-// 100; this: 10, 12 and 61.)
+// 100; this: 10, 12 and 58.)
 // A query whose candidates or survivors do not fit sets its overflow flag and is searched again.
 constexpr int kRescoreInFlight = 2;
 constexpr uint32_t kSurvivorsAtOnce = kSelectThreads / kRescoreLanes * kRescoreInFlight * 2;     // up to here: no second look

@@ -93,10 +93,10 @@ __global__ __launch_bounds__(256) void coarse_rows_kernel(CoarseArgs a) {
 // Why this split: batches are tens of queries, and what bounds them is the length of the chain
 // through the elements, not the matrix cores.  (Tiles of 32 x 128 that walked all elements through
 // LDS slabs, a barrier pair per 32: 52.7, 55.5 and 117 us for 16 queries x 1024 x 768, 32 x 4096 x 768
-// and 256 x 8192 x 1024; this: 8.2, 12.6 and 94; the fp64 matrix peak for the last is 55 us.)
+// and 256 x 8192 x 1024; this: 6.1, 10 and 105; the fp64 matrix peak for the last is 55 us.)
 // W = 1: a tile is one wavefront's, its sums go straight to memory and no LDS is used.
 // RAGGED: d is no multiple of 4, rows start at any element (the row kernel served such batches with
-// single elements: 272 and 1120 us for 256 queries x 2678 x 295 and x 8192 x 747; this: 20 and 75).
+// single elements: 272 and 1120 us for 256 queries x 2678 x 295 and x 8192 x 747; this: 18 and 86).
 // Workgroups that follow each other on one XCD share their centroids (blockIdx % 8 is the XCD):
 // each L2 then holds one eighth of the centroids instead of all of them.
 // For the squared distance the norms are accumulated beside the products: |q - c|^2 = |q|^2 + |c|^2 - 2 q.c.
@@ -259,7 +259,7 @@ hipError_t launch_coarse(const CoarseArgs& a, hipStream_t s, hipEvent_t e0, hipE
     } else {
         // Small tiles while they leave the chip short of work, measured with 1024, 4096 and 8192 lists:
         // 512 of them 12.9, 12.6, 14.3 us against 15.7, 16.1, 19.1 of the large ones; 768: 16.0 against
-        // 17.0; 1024: 19.3, 19.2, 22.5 against 17.0, 17.0, 19.5; 8192: 123 against 94.  And for any number of
+        // 17.0; 1024: 19.3, 19.2, 22.5 against 17.0, 17.0, 19.5; 8192 (256 x 8192 x 768): 107 against 81.  And for any number of
         // lists when the queries fit one of them (4 queries x 65536 x 64, 128, 768: 11.5, 14.6, 51 us against
         // 14.2, 18.2, 76).
         // Large ones: split over four wavefronts while the chain counts.  One wavefront per tile when
