@@ -124,19 +124,19 @@ struct MergeArgs {
 };
 hipError_t launch_merge(const MergeArgs& a, hipStream_t s, hipEvent_t start = nullptr, hipEvent_t stop = nullptr);
 
-// The exact second pass (exact_redo_kernel) for the queries merge_kernel flagged: `grid` workgroups of
-// kRedoListsPerWg wavefronts per query, each wavefront leaving a list of k entries.
+// The exact second pass (exact_redo_kernel) for the queries that a merge flagged: `grid` workgroups per
+// query of the call, shared by those that are flagged, of kRedoListsPerWg wavefronts that each leave a
+// list of k entries.
 constexpr int kRedoListsPerWg = 4;
 struct RedoArgs {
     const void* buf; const float* q;
     const int64_t* ids;          // [n] global row -> id, or nullptr
     SlotTables slots;
     const uint32_t* redo_flag; const double* redo_thr; uint32_t* redo_ticket;
-    unsigned long long* list_key;    // [nq x grid x kRedoListsPerWg x k] scores as ascending-order keys, 0 = empty
+    unsigned long long* list_key;    // [nq x grid x kRedoListsPerWg x k] ordered scores, larger is nearer, 0 = empty
     long long* list_id;              // [same] the rows' ids
     const HostCand* host_cand; const int32_t* host_count;
     int64_t* out_ids; float* out_dists;
-    unsigned long long* done; unsigned long long done_value;
     int d, dtype, metric, nprobe, nq, k, kprime;
 };
 hipError_t launch_redo(const RedoArgs& a, int grid, hipStream_t s);

@@ -191,3 +191,39 @@ def test_best_rows_concentrated_in_few_scan_wavefronts(k):
     index.ivf_synchronize()
     assert np.array_equal(ids_dev.cpu().numpy(), gi) and np.array_equal(d_dev.cpu().numpy(), gd)
     index.close()
+
+
+@pytest.mark.parametrize("nq,every,k", [(5, 2, 10), (70, 7, 3), (70, 1, 56), (300, 50, 112)])
+def test_flagged_queries_of_a_batch_share_the_second_pass(nq, every, k):
+    """Every `every`-th query of a batch (query by query, one call) has a hundred copies of its best row
+    among its lists, so its first result cannot be proven; the workgroups of the second pass are
+    dealt to those queries only.  Ids do not grow with positions."""
+    d, nlist, per = 96, 12, 700
+    rng = np.random.default_rng(nq + k)
+    cent = rng.standard_normal((nlist, d)).astype(np.float32)
+    assign = np.repeat(np.arange(nlist), per).astype(np.int32)
+    rows = (cent[assign] + 0.4 * rng.standard_normal((nlist * per, d))).astype(np.float32)
+    q = (cent[rng.integers(0, nlist, nq)] + 0.3 * rng.standard_normal((nq, d))).astype(np.float32)
+    flagged = range(0, nq, every) if every > 1 else range(0, min(nq, 40))
+    for j, b in enumerate(flagged):
+        at = rng.integers(0, rows.shape[0], 100)
+        rows[at] = q[b] * np.float32(1.0 + 0.01 * (j % 5))
+    ids = rng.permutation(rows.shape[0]).astype(np.int64) * 5 + 2
+    index = P.ivf_build_layout(rows, "f32", cent, assign, ids=ids, metric=P.IVF_IP,
+                               compute_stream=torch.cuda.Stream(), copy_stream=torch.cuda.Stream())
+    index.ivf_set_batch_mode(1)
+    qd = torch.from_numpy(q).cuda()
+    di = torch.empty(nq, k, dtype=torch.int64, device="cuda")
+    dd = torch.empty(nq, k, dtype=torch.float32, device="cuda")
+    torch.cuda.synchronize()
+    index.ivf_search_device(qd, nlist, k, di, dd)
+    torch.cuda.synchronize()
+    gi, gd, ss = index.ivf_search(q, nlist, k, with_stats=True)
+    assert np.array_equal(di.cpu().numpy(), gi) and np.array_equal(dd.cpu().numpy(), gd)
+    if k >= 8:
+        assert ss.n_exact_gpu >= 1
+    off, perm = O.build_layout(assign, nlist)
+    for b in sorted(set(list(flagged)[:3]) | {nq - 1}):
+        oi, osc = O.search(rows[perm], O.F32, off, ids[perm], cent, q[b], nlist, k, O.IP)
+        assert list(gi[b]) == list(oi)
+    index.close()
