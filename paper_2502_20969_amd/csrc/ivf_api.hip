@@ -564,7 +564,7 @@ int ensure_batched_workspace(ivf_index* ix, int nq, int nprobe) {
     w.b_nq = w.b_nprobe = 0;
     const size_t nqz = nq2, nl = ix->nlist;
     const uint64_t task_cap = batched_task_bound(ix->h_off.data(), ix->nlist, nq2, ix->dtype);
-    HIP_TRY(hipMalloc(&w.d_q_store, nqz * ix->d * 2));
+    HIP_TRY(hipMalloc(&w.d_q_store, nqz * batched_query_stride(ix->d, ix->dtype) * (ix->dtype == IVF_F32 ? 4 : 2)));
     HIP_TRY(hipMalloc(&w.d_qq, nqz * sizeof(float)));
     HIP_TRY(hipMalloc(&w.d_thr, nqz * sizeof(float)));
     HIP_TRY(hipMalloc(&w.d_thr_part, batched_sample_words(nq2) * sizeof(uint32_t)));
@@ -597,6 +597,8 @@ static void fill_batched_args(const ivf_index* ix, const Workspace& w, BatchedAr
     b.cand_cap = kCandCap;
     b.group_q = batched_group_q(ix->dtype);
     b.acc_coef = (float)ix->d * 0x1p-23f;            // d products accumulated in fp32, in an order the hardware chooses
+    b.max_lds = ix->max_lds;
+    b.dq = batched_query_stride(ix->d, ix->dtype);
     b.samp_coef = batched_sample_coef(ix->d, ix->dtype, ix->metric);
 }
 

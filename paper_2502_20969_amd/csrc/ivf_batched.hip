@@ -18,6 +18,7 @@
 #include "../../include/ivf.h"
 #include <hip/hip_ext.h>
 #include <algorithm>
+#include <type_traits>
 
 namespace ivf {
 using namespace dev;
@@ -204,11 +205,17 @@ __device__ __forceinline__ void prepare_query(const BatchedArgs& a, int qi) {
     __shared__ double p_qq[kFrontThreads / 64];
     float s = 0.f, res = 0.f;          // |q~|^2 of the rounded query and |q~ - q|^2 of the rounding
     double qq = 0.0;                   // |q|^2
-    for (int t = threadIdx.x; t < a.d; t += kFrontThreads) {
-        const float x = a.q[(size_t)qi * a.d + t];
+    const int epl = a.dtype == 0 ? 4 : 8, whole = a.d / epl * epl;      // elements in whole 16-byte chunks
+    for (int t = threadIdx.x; t < a.dq; t += kFrontThreads) {
+        // the scan takes a last, partial chunk from the 16 bytes that end the row, less what the chunk before it has
+        const int e = t < whole ? t : t < whole + epl && whole < a.d ? a.d - epl + t - whole : a.d;
+        const bool in = t < whole || (e >= whole && e < a.d);
+        const float x = in ? a.q[(size_t)qi * a.d + e] : 0.f;
         float xr = x;
-        if (a.dtype == 1) { _Float16 h = (_Float16)x; ((_Float16*)a.q_store)[(size_t)qi * a.d + t] = h; xr = (float)h; }
-        else if (a.dtype == 2) { __bf16 h = (__bf16)x; ((__bf16*)a.q_store)[(size_t)qi * a.d + t] = h; xr = (float)h; }
+        const size_t o = (size_t)qi * a.dq + t;
+        if (a.dtype == 1) { _Float16 h = (_Float16)x; ((_Float16*)a.q_store)[o] = h; xr = (float)h; }
+        else if (a.dtype == 2) { __bf16 h = (__bf16)x; ((__bf16*)a.q_store)[o] = h; xr = (float)h; }
+        else if (a.dq != a.d) ((float*)a.q_store)[o] = x;
         s = fmaf(xr, xr, s);
         res = fmaf(xr - x, xr - x, res);
         qq = fma((double)x, (double)x, qq);
@@ -224,14 +231,19 @@ __device__ __forceinline__ void prepare_query(const BatchedArgs& a, int qi) {
         const float ymax = sqrtf(__uint_as_float(*a.row_norm_max_bits));
         const float qn = sqrtf((float)qq);
         const float ip_err = (sqrtf(res) + a.acc_coef * sqrtf(s)) * ymax;
-        a.eps[qi] = a.metric == 0 ? 1.01f * (ip_err + a.samp_coef * qn * ymax)
-                                  : 1.01f * (2.f * ip_err + (a.samp_coef + 0x1p-21f) * (qn + ymax) * (qn + ymax));
+        const float eps = a.metric == 0 ? 1.01f * (ip_err + a.samp_coef * qn * ymax)
+                                        : 1.01f * (2.f * ip_err + (a.samp_coef + 0x1p-21f) * (qn + ymax) * (qn + ymax));
+        a.eps[qi] = eps;
         a.qq[qi] = (float)qq;
-        a.cand_count[(size_t)qi * kCountStride] = 0;
+        // The bound says nothing when it is no finite number (infinities, values beyond the storage type) or
+        // when squares and products underflow; such a query starts with a full candidate list: no row is
+        // added to it and it is searched again in fp64.
+        const bool bound = eps < INFINITY && (qq == 0.0 || qq >= 1e-25) && ymax * ymax >= 1e-25f;
+        a.cand_count[(size_t)qi * kCountStride] = bound || a.keep_all ? 0u : (uint32_t)a.cand_cap + 1u;
     }
 }
 
-template <typename T>
+template <typename T, bool TAIL>
 __global__ __launch_bounds__(kFrontThreads) void batch_front_kernel(BatchedArgs a, int parts, int counted) {
     extern __shared__ __align__(16) unsigned char smem[];
     if (blockIdx.x == 0) {
@@ -277,7 +289,7 @@ __global__ __launch_bounds__(kFrontThreads) void batch_front_kernel(BatchedArgs 
     const uint32_t rows = a.rprefix[(size_t)qi * (a.nprobe + 1) + a.nprobe];
     const uint32_t at_least = (uint32_t)((uint64_t)rows * (uint64_t)a.k * 2u / (uint64_t)a.cand_cap);
     const uint32_t want = min(max(max(read_lane(my_end, min(7, a.nprobe - 1)) / 16, at_least), max(512u, 8u * (uint32_t)a.k)), (uint32_t)kSampleRows);
-    const int chunks = a.d / EPL;
+    const int chunks = TAIL ? (a.d + EPL - 1) / EPL : a.d / EPL;
 #pragma unroll 1
     for (uint32_t r0 = (uint32_t)(part * kSampleStep + wave * U); r0 < (uint32_t)kSampleRows; r0 += (uint32_t)(parts * kSampleStep)) {
         uint32_t key = 0;                                 // lane u < U: the ordered score of sample row r0 + u, 0 = none
@@ -299,20 +311,26 @@ __global__ __launch_bounds__(kFrontThreads) void batch_front_kernel(BatchedArgs 
                 for (int w = 0; w < V; ++w) {
                     const int ch = min(c0 + 64 * w, chunks - 1);
 #pragma unroll
-                    for (int u = 0; u < U; ++u) v[w][u] = *(const uint4*)(rp[u] + (size_t)ch * 16);
+                    for (int u = 0; u < U; ++u) v[w][u] = load_chunk<TAIL>(rp[u] + (size_t)(TAIL ? min(ch * EPL, a.d - EPL) * T::kBytes : ch * 16));
                 }
 #pragma unroll
                 for (int w = 0; w < V; ++w) {
                     const int ch = c0 + 64 * w;
                     if (ch >= chunks) break;
+                    // TAIL: the last chunk of a row is the 16 bytes that end it, less what the chunk before has
+                    const int skip = TAIL ? max(ch * EPL - (a.d - EPL), 0) : 0;
+                    float qv[EPL];
+#pragma unroll
+                    for (int e = 0; e < EPL; ++e) qv[e] = e < skip ? 0.f : ql[ch * EPL + e - skip];
 #pragma unroll
                     for (int u = 0; u < U; ++u) {
                         float x[EPL];
                         Unpack<T>::run(v[w][u], x);
 #pragma unroll
                         for (int e = 0; e < EPL; ++e) {
-                            if (a.metric == 0) s[u] = fmaf(ql[ch * EPL + e], x[e], s[u]);
-                            else { const float df = ql[ch * EPL + e] - x[e]; s[u] = fmaf(df, df, s[u]); }
+                            if (TAIL && e < skip) x[e] = 0.f;
+                            if (a.metric == 0) s[u] = fmaf(qv[e], x[e], s[u]);
+                            else { const float df = qv[e] - x[e]; s[u] = fmaf(df, df, s[u]); }
                         }
                     }
                 }
@@ -346,8 +364,12 @@ __global__ __launch_bounds__(256) void batch_tasks_kernel(BatchedArgs a) {
             const uint32_t t0 = a.tstart[c], t1 = a.tstart[c + 1];
             if (t0 == t1) continue;
             const uint32_t n = (uint32_t)(a.off[c + 1] - a.off[c]);
-            const uint32_t tiles = (n + kTileRows - 1) / kTileRows;
-            for (uint32_t i = lane; i < t1 - t0; i += 64) a.tasks[t0 + i] = BatchTask{(uint32_t)c, i / tiles, i % tiles};
+            const uint32_t tiles = (n + kTileRows - 1) / kTileRows, lo = (uint32_t)a.off[c];
+            const uint32_t q0 = a.qstart[c], nq = a.qstart[c + 1] - q0, gq = (uint32_t)a.group_q;
+            for (uint32_t i = lane; i < t1 - t0; i += 64) {
+                const uint32_t group = i / tiles, row = i % tiles * kTileRows;
+                a.tasks[t0 + i] = BatchTask{lo + row, min((uint32_t)kTileRows, n - row), q0 + group * gq, min(gq, nq - group * gq)};
+            }
         }
         return;
     }
@@ -375,6 +397,10 @@ __global__ __launch_bounds__(256) void batch_tasks_kernel(BatchedArgs a) {
     }
     __syncthreads();
     const uint32_t cnt = s_cnt;
+    if (a.cand_count[(size_t)qi * kCountStride] != 0) {        // no bound for this query (prepare_query): nothing passes
+        if (tid == 0) a.thr[qi] = INFINITY;
+        return;
+    }
     if (cnt < k || a.keep_all) {                               // fewer than k rows sampled: everything passes
         if (tid == 0) a.thr[qi] = -INFINITY;
         return;
@@ -408,43 +434,53 @@ __global__ __launch_bounds__(256) void batch_tasks_kernel(BatchedArgs a) {
 // (remaining / (4 x workgroups), at least one), so that all workgroups finish within about a task
 // of each other.  Every workgroup leaves once a run starts past the end of the list.
 constexpr uint32_t kRunMax = 8;
+
+// A load of wave-uniform data that this kernel does not write: through the scalar cache, beside
+// the vector loads, which return in order and would hold it back.
+template <typename V>
+__device__ __forceinline__ V load_scalar(const V* p) {
+    return *(const __attribute__((address_space(4))) V*)(uintptr_t)p;
+}
+
 struct TaskFeed {
     uint32_t t, t_stop, total;      // same in all threads: next task, end of the run, end of the list
+    uint32_t flip;                  // which half of s_run the next run goes to
     uint32_t ahead_t0, ahead_n;     // thread 0: the run reserved ahead
-    __device__ __forceinline__ uint32_t run_length(uint32_t counter_seen) const {
-        const uint32_t left = total - min(total, counter_seen);
-        return max(1u, min(kRunMax, left / (4u * gridDim.x)));
-    }
-    __device__ __forceinline__ void reserve(const BatchedArgs& a, uint32_t counter_seen) {
-        ahead_n = run_length(counter_seen);
+    __device__ __forceinline__ void reserve(const BatchedArgs& a) {
+        const uint32_t left = total - min(total, ahead_t0 + ahead_n);
+        ahead_n = max(1u, min(kRunMax, left / (4u * gridDim.x)));
         ahead_t0 = atomicAdd(a.ticket, ahead_n);
     }
     __device__ __forceinline__ void start(const BatchedArgs& a) {
-        total = (uint32_t)__builtin_amdgcn_readfirstlane((int)a.tstart[a.nlist]);
+        total = load_scalar(&a.tstart[a.nlist]);
         t = t_stop = 0;
+        flip = 0;
         ahead_t0 = ahead_n = 0;
-        if (threadIdx.x == 0) reserve(a, 0);
+        if (threadIdx.x == 0) reserve(a);
     }
-    // the next task's index, or false when the list is used up; all threads of the workgroup call it together.
-    // s_run: four words of LDS (16 bytes, so that the dynamic LDS area behind the static one stays 16-byte aligned)
-    __device__ __forceinline__ bool next(const BatchedArgs& a, uint32_t* s_run, uint32_t& index) {
+    // the next task, or false when the list is used up; all threads of the workgroup call it together.
+    // s_run: two halves used in turn, so that one barrier separates writing from reading (16 bytes, so that the
+    // dynamic LDS area behind the static one stays 16-byte aligned)
+    __device__ __forceinline__ bool next(const BatchedArgs& a, uint32_t (*s_run)[2], BatchTask& task) {
         if (t == t_stop) {
-            __syncthreads();                              // s_run of the previous run has been read by everyone
             if (threadIdx.x == 0) {
-                s_run[0] = ahead_t0;
-                s_run[1] = min(ahead_t0 + ahead_n, total);
+                s_run[flip][0] = ahead_t0;
+                s_run[flip][1] = min(ahead_t0 + ahead_n, total);
             }
             __syncthreads();
             // (read from LDS: the compiler is told that the values are the same in every lane, so
             // that the task and everything derived from it stay in scalar registers)
-            t = (uint32_t)__builtin_amdgcn_readfirstlane((int)s_run[0]);
-            t_stop = (uint32_t)__builtin_amdgcn_readfirstlane((int)s_run[1]);
+            t = (uint32_t)__builtin_amdgcn_readfirstlane((int)s_run[flip][0]);
+            t_stop = (uint32_t)__builtin_amdgcn_readfirstlane((int)s_run[flip][1]);
+            flip ^= 1u;
             if (t >= total) return false;
             // the run after this one: asked for behind the barrier, so that only this wavefront
             // waits for the counter while the others are already at work
-            if (threadIdx.x == 0) reserve(a, ahead_t0 + ahead_n);
+            if (threadIdx.x == 0) reserve(a);
         }
-        index = t++;
+        const u4_t v = load_scalar((const u4_t*)(a.tasks + t));
+        task = BatchTask{v.x, v.y, v.z, v.w};
+        ++t;
         return true;
     }
 };
@@ -471,51 +507,57 @@ template <> struct Mfma<BF16> {
 // row l % 32, eight elements per step) through a small LDS area of its own, and reads the B
 // fragments (lane l: query l % 32, the same elements) from the staged queries.  Scores that reach
 // the query's threshold are appended to the query's candidate list.
-template <typename T, int METRIC>
-__global__ __launch_bounds__(kBatchThreads) void batched_scan_kernel(BatchedArgs a) {
+//
+// TAIL: rows that are not whole blocks of 64 elements, or not whole 16-byte chunks and so start at any
+// element.  A lane whose chunk reaches past the end of the row loads the 16 bytes that END with the row
+// and clears what does not count (the staged queries are laid out the same way): no load leaves the row.
+// These loads are cached ones: the 128-byte pieces of such rows straddle lines, which streaming loads
+// fetched 1.56 times (48 x 100 fp32: 82 us, 99 with them; 106 x 283 fp16: 238, 268).
+template <typename T, int METRIC, bool TAIL>
+__global__ __launch_bounds__(kBatchThreads) void batched_scan_kernel(BatchedArgs a, int resident) {
     typedef typename Mfma<T>::frag frag;
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ uint32_t s_q[kGroupQ];
-    __shared__ float s_thr[kGroupQ];
-    __shared__ float s_qq[kGroupQ];
     const int lane = lane_id(), wave = wave_id();
-    const int d = a.d, qstride = d + kQPad;
-    uint16_t* qs = (uint16_t*)smem;                      // [kGroupQ][d + kQPad] storage-type queries
-    uint16_t* stage = qs + (size_t)kGroupQ * qstride + (size_t)wave * 32 * kStageLd;   // [32][kStageLd], this wavefront's
-    __shared__ __align__(16) uint32_t s_run[4];
+    const int d = a.d, dq = TAIL ? a.dq : a.d, qstride = dq + kQPad;
+    // queries, their thresholds and norms: of the whole batch (resident), or of one group
+    const int slots = resident ? a.nq : kGroupQ;
+    uint16_t* stage = (uint16_t*)smem + (size_t)wave * 32 * kStageLd;    // [32][kStageLd], this wavefront's
+    uint16_t* qs = (uint16_t*)smem + (size_t)kBatchWaves * 32 * kStageLd;     // [slots][dq + kQPad] storage-type queries
+    float* s_thr = (float*)(qs + (size_t)slots * qstride);
+    float* s_qq = s_thr + slots;
+    const int chunks = dq / 8;                           // 16-byte chunks per query row
+    if (resident) {
+        for (int i = threadIdx.x; i < a.nq * chunks; i += blockDim.x) {
+            const int qi = i / chunks, ch = i - qi * chunks;
+            *(uint4*)(qs + (size_t)qi * qstride + ch * 8) = *(const uint4*)((const uint16_t*)a.q_store + (size_t)qi * dq + ch * 8);
+        }
+        for (int i = threadIdx.x; i < a.nq; i += blockDim.x) { s_thr[i] = a.thr[i]; s_qq[i] = a.qq[i]; }
+        __syncthreads();
+    }
+    __shared__ __align__(16) uint32_t s_run[2][2];
     TaskFeed feed;
     feed.start(a);
-    uint32_t staged_cluster = 0xFFFFFFFFu, staged_group = 0xFFFFFFFFu;
+    uint32_t staged = 0xFFFFFFFFu;
+    BatchTask task;
     const int col = lane & 31, khalf = lane >> 5;
-    for (uint32_t t = 0; feed.next(a, s_run, t);) {
-        const BatchTask task = a.tasks[t];
-        const uint32_t c = task.cluster;
-        const uint32_t qbase = a.qstart[c] + task.group * kGroupQ;
-        const uint32_t nqg = min((uint32_t)kGroupQ, a.qstart[c + 1] - qbase);
-        if (c != staged_cluster || task.group != staged_group) {
+    while (feed.next(a, s_run, task)) {
+        const uint32_t qbase = task.qbase, nqg = task.nq;
+        if (!resident && qbase != staged) {
             __syncthreads();                              // everyone is done with the previous queries
-            if (threadIdx.x < kGroupQ) {
-                bool ok = threadIdx.x < nqg;
-                uint32_t qi = ok ? a.qidx[qbase + threadIdx.x] : 0;
-                s_q[threadIdx.x] = ok ? qi : 0xFFFFFFFFu;
-                s_thr[threadIdx.x] = ok ? a.thr[qi] : INFINITY;
-                s_qq[threadIdx.x] = ok ? a.qq[qi] : 0.f;
+            if (threadIdx.x < nqg) {
+                const uint32_t qi = a.qidx[qbase + threadIdx.x];
+                s_q[threadIdx.x] = qi; s_thr[threadIdx.x] = a.thr[qi]; s_qq[threadIdx.x] = a.qq[qi];
             }
             __syncthreads();
-            const int chunks = d / 8;                     // 16-byte chunks per query row
-            for (int i = threadIdx.x; i < kGroupQ * chunks; i += blockDim.x) {
-                int qq = i / chunks, ch = i - qq * chunks;
-                uint32_t qi = s_q[qq];
-                uint4 v = make_uint4(0, 0, 0, 0);
-                if (qi != 0xFFFFFFFFu) v = *(const uint4*)((const uint16_t*)a.q_store + (size_t)qi * d + ch * 8);
-                *(uint4*)(qs + (size_t)qq * qstride + ch * 8) = v;
+            for (int i = threadIdx.x; i < (int)nqg * chunks; i += blockDim.x) {
+                const int p = i / chunks, ch = i - p * chunks;
+                *(uint4*)(qs + (size_t)p * qstride + ch * 8) = *(const uint4*)((const uint16_t*)a.q_store + (size_t)s_q[p] * dq + ch * 8);
             }
             __syncthreads();
-            staged_cluster = c; staged_group = task.group;
+            staged = qbase;
         }
-        const int64_t lo = a.off[c];
-        const uint32_t n = (uint32_t)(a.off[c + 1] - lo);
-        const uint32_t r0 = task.tile * kTileRows + wave * 32;     // first row of this wavefront
+        const uint32_t lo = task.row0, n = task.rows, r0 = wave * 32;      // first row of this wavefront in the task
         if (r0 >= n) continue;
         // Loading role of a lane: 16-byte chunk lane % 8 of rows lane / 8 + {0, 8, 16, 24} of each
         // 64-element block (rows past the end re-read the last one).  Element order inside the dot
@@ -525,8 +567,16 @@ __global__ __launch_bounds__(kBatchThreads) void batched_scan_kernel(BatchedArgs
         const uint16_t* lptr[4];
 #pragma unroll
         for (int u = 0; u < 4; ++u)
-            lptr[u] = (const uint16_t*)a.lists + ((size_t)lo + min(r0 + (uint32_t)(lrow + 8 * u), n - 1)) * d + lchunk * 8;
-        const uint16_t* brow = qs + (size_t)col * qstride + khalf * 32;
+            lptr[u] = (const uint16_t*)a.lists + ((size_t)lo + min(r0 + (uint32_t)(lrow + 8 * u), n - 1)) * d + (TAIL ? 0 : lchunk * 8);
+        uint32_t keep[4] = {~0u, ~0u, ~0u, ~0u};          // TAIL: what counts of this lane's chunk in the last block
+        if (TAIL) {
+            const int at = (d - 1) / 64 * 64 + lchunk * 8, skip = max(at - (d - 8), 0);
+#pragma unroll
+            for (int e = 0; e < 8; ++e) if (e < skip) keep[e / 2] &= (e & 1) ? 0x0000FFFFu : 0xFFFF0000u;
+        }
+        // the query of this lane's scores (places of the group that no query has: one again), and where it is in LDS
+        const uint32_t place = min((uint32_t)col, nqg - 1), qi = a.qidx[qbase + place], slot = resident ? qi : place;
+        const uint16_t* brow = qs + (size_t)slot * qstride + khalf * 32;
         uint16_t* wpos = stage + lrow * kStageLd + lchunk * 8;
         const uint16_t* rpos = stage + col * kStageLd + khalf * 32;
         float16_t acc;
@@ -544,8 +594,11 @@ __global__ __launch_bounds__(kBatchThreads) void batched_scan_kernel(BatchedArgs
 #pragma unroll
             for (int b = 0; b < kStage16; ++b) {
 #pragma unroll
-                for (int u = 0; u < 4; ++u)
-                    v[b * 4 + u] = k0 + b * 64 < d ? load_stream16(lptr[u] + k0 + b * 64) : make_uint4(0, 0, 0, 0);
+                for (int u = 0; u < 4; ++u) {
+                    if (k0 + b * 64 >= d) v[b * 4 + u] = make_uint4(0, 0, 0, 0);
+                    else if (TAIL) v[b * 4 + u] = load_chunk<true>(lptr[u] + min(k0 + b * 64 + lchunk * 8, d - 8));
+                    else v[b * 4 + u] = load_stream16(lptr[u] + k0 + b * 64);
+                }
             }
         };
         auto consume = [&](int k0, const uint4 (&v)[4 * kStage16]) {
@@ -555,7 +608,11 @@ __global__ __launch_bounds__(kBatchThreads) void batched_scan_kernel(BatchedArgs
                     // through LDS: written in the loading layout, read back as fragments.  A
                     // wavefront's LDS operations complete in order, so no barrier is needed.
 #pragma unroll
-                    for (int u = 0; u < 4; ++u) *(uint4*)(wpos + u * 8 * kStageLd) = v[b * 4 + u];
+                    for (int u = 0; u < 4; ++u) {
+                        uint4 w = v[b * 4 + u];
+                        if (TAIL && k0 + b * 64 + 64 >= d) { w.x &= keep[0]; w.y &= keep[1]; w.z &= keep[2]; w.w &= keep[3]; }
+                        *(uint4*)(wpos + u * 8 * kStageLd) = w;
+                    }
 #pragma unroll
                     for (int j = 0; j < 4; ++j) {
                         const uint4 av4 = *(const uint4*)(rpos + j * 8);
@@ -575,10 +632,9 @@ __global__ __launch_bounds__(kBatchThreads) void batched_scan_kernel(BatchedArgs
             consume(k0 + kStep, av[1]);
         }
         // lane holds query `col`, rows (i / 4) * 8 + khalf * 4 + i % 4
-        const float thr = s_thr[col];
-        const uint32_t qi = s_q[col];
+        const float thr = s_thr[slot];
         if (METRIC != 0) {
-            const float qq = s_qq[col];
+            const float qq = s_qq[slot];
 #pragma unroll
             for (int i = 0; i < 16; ++i) acc[i] = fmaf(2.f, acc[i], -yy[i]) - qq;
         }
@@ -586,7 +642,7 @@ __global__ __launch_bounds__(kBatchThreads) void batched_scan_kernel(BatchedArgs
 #pragma unroll
         for (int i = 0; i < 16; ++i) {
             const uint32_t r = r0 + (i / 4) * 8 + khalf * 4 + (i % 4);
-            if (acc[i] >= thr && r < n) pass |= 1u << i;
+            if (acc[i] >= thr && r < n && (uint32_t)col < nqg) pass |= 1u << i;
         }
         if (pass) {
             // one reservation for all rows of this lane that passed
@@ -605,171 +661,266 @@ __global__ __launch_bounds__(kBatchThreads) void batched_scan_kernel(BatchedArgs
     }
 }
 
-// fp32 rows: v_mfma_f32_16x16x4_f32 multiplies a 16 x 4 block of rows (lane l: row l % 16,
-// element l / 16) with a 4 x 16 block of queries (lane l: query l % 16, the same element).  The
-// order of the elements inside a dot product is free, so the MFMA lane (row i, part p) takes the
-// 16-byte chunk p of each 16-element block of its row and the four values of the chunk feed four
-// MFMA steps; the query operand is read the same way from the group's queries in LDS.  The rows
-// are LOADED in another lane order, eight consecutive lanes on one 128-byte line of a row (MFMA
-// lanes of one row are 16 lanes apart: loading in that order makes every group of four lanes touch
-// four different lines, and half lines per instruction, which costs a quarter of the bandwidth),
-// and register moves across lanes (a DPP row shift and a ds_bpermute per value: no LDS memory)
-// take each value to its MFMA lane.  A wavefront scores two blocks of 16 rows against up to 16
-// queries; four 32-element pieces of its 32 rows are in flight while the previous four are consumed
-// (16 KB per wavefront: the depth per wavefront matters more here than a second workgroup per CU).
+// fp32 rows.  Eight consecutive lanes take one 128-byte piece of a row (lane l: chunk l % 8 of rows
+// l / 8 + {0, 8, 16, 24} of the wavefront's 32), three pieces of the 32 rows are in flight while the
+// previous three are multiplied (12 KB per wavefront).
+// Groups of up to 8 queries (most: a cluster is selected by one to four queries of a batch) are multiplied by
+// the vector units: a lane adds up the products of its chunks for every query, whose chunks it
+// reads from LDS, and at the end of a row the eight lanes' sums are added by a butterfly that
+// leaves lane l with query l % 8.  The walk comes in sizes M = 1, 2, 4 and 8, each as long as its queries.
+// Larger groups go to v_mfma_f32_16x16x4_f32, which is twice as fast for 16 queries and takes as long for fewer:
+// a 16 x 4 block of rows (lane l: row l % 16, element l / 16) times a 4 x 16 block of queries (lane l: query
+// l % 16, the same element).  The order of the elements inside a dot product is free, so the MFMA lane
+// (row i, part p) takes the 16-byte chunk p of each 16-element block of its row and the four values of the
+// chunk feed four MFMA steps; register moves across lanes (a DPP row shift and a ds_bpermute per
+// value) take each value there.
+// What it measured, us, all groups on the matrix cores / this: 32 queries x 768, squared L2 (1.85 GB; rows
+// from the cache instead of HBM took 232 of it) 310 / 286, 8 x 768 (4.1 GB) 636 / 608, 199 x 256 with six
+// queries per cluster (4.8 GB) 783 / 702, 48 x 100 (287 MB) 101 / 62, 9 x 687 (32 MB) 67 / 36.
+// TAIL: as in batched_scan_kernel, for rows that are not whole pieces of 32 elements.
 typedef float float4_t __attribute__((ext_vector_type(4)));
-constexpr int kGroupQ32 = 16;      // queries per task for fp32 rows: one MFMA tile wide
-constexpr int kQPad32 = 4;         // padding (floats) of a staged query row: consecutive queries start 4 banks apart
-constexpr int kStage32 = 4;        // 32-element pieces of a row per pipeline stage
+constexpr int kGroupQ32 = 16;      // queries per task for fp32 rows
+constexpr int kQPad32 = 4;         // padding (floats) of a staged query row
+constexpr int kStage32 = 3;        // 32-element pieces of a row per pipeline stage
 
-template <int METRIC>
-__global__ __launch_bounds__(kBatchThreads) void batched_scan_f32_kernel(BatchedArgs a) {
+// Sums of M values over eight consecutive lanes: lane l of the eight ends with value l % M of `v` (M <= 8).
+template <int M>
+__device__ __forceinline__ float sums_over_8(float (&v)[M]) {
+    const int lane = lane_id();
+    // partners: 7 - l (row_half_mirror), l ^ 2, l ^ 1; while more than one value is left a lane
+    // keeps the half its own bit names and hands the other half over
+    auto halve = [&](int n, bool upper, auto move) {
+#pragma unroll
+        for (int j = 0; j < n; ++j) {
+            const float keep = upper ? v[j + n] : v[j], give = upper ? v[j] : v[j + n];
+            v[j] = keep + move(give);
+        }
+    };
+    auto m4 = [](float x) { return dpp_move<0x141>(x); };
+    auto m2 = [](float x) { return dpp_move<0x4E>(x); };
+    auto m1 = [](float x) { return dpp_move<0xB1>(x); };
+    if constexpr (M == 8) halve(4, (lane & 4) != 0, m4);
+    else {
+#pragma unroll
+        for (int j = 0; j < M; ++j) v[j] += m4(v[j]);
+    }
+    if constexpr (M >= 4) halve(2, (lane & 2) != 0, m2);
+    else {
+#pragma unroll
+        for (int j = 0; j < M; ++j) v[j] += m2(v[j]);
+    }
+    if constexpr (M >= 2) halve(1, (lane & 1) != 0, m1);
+    else v[0] += m1(v[0]);
+    return v[0];
+}
+
+template <int METRIC, bool TAIL>
+__global__ __launch_bounds__(kBatchThreads) void batched_scan_f32_kernel(BatchedArgs a, int resident) {
     extern __shared__ __align__(16) unsigned char smem[];
     __shared__ uint32_t s_q[kGroupQ32];
-    __shared__ float s_thr[kGroupQ32];
-    __shared__ float s_qq[kGroupQ32];
     const int lane = lane_id(), wave = wave_id();
-    const int d = a.d, qstride = d + kQPad32;
-    float* qs = (float*)smem;                            // [kGroupQ32][d + kQPad32] queries
-    __shared__ __align__(16) uint32_t s_run[4];
+    const int d = a.d, dq = TAIL ? a.dq : a.d, qstride = dq + kQPad32;
+    // queries, their thresholds and norms: of the whole batch (resident), or of one group
+    const int slots = resident ? a.nq : kGroupQ32;
+    float* qs = (float*)smem;                            // [slots][dq + kQPad32]
+    float* s_thr = qs + (size_t)slots * qstride;
+    float* s_qq = s_thr + slots;
+    const float* q_rows = TAIL && dq != d ? (const float*)a.q_store : a.q;
+    __shared__ __align__(16) uint32_t s_run[2][2];
     TaskFeed feed;
     feed.start(a);
-    uint32_t staged_cluster = 0xFFFFFFFFu, staged_group = 0xFFFFFFFFu;
-    const int col = lane & 15, kq = lane >> 4;
-    for (uint32_t t = 0; feed.next(a, s_run, t);) {
-        const BatchTask task = a.tasks[t];
-        const uint32_t c = task.cluster;
-        const uint32_t qbase = a.qstart[c] + task.group * kGroupQ32;
-        const uint32_t nqg = min((uint32_t)kGroupQ32, a.qstart[c + 1] - qbase);
-        if (c != staged_cluster || task.group != staged_group) {
+    uint32_t staged = 0xFFFFFFFFu;
+    BatchTask task;
+    const int sub = lane & 7;
+    const uint32_t r0 = wave * 32, lrow = (uint32_t)(lane >> 3);
+    uint32_t keep[4] = {~0u, ~0u, ~0u, ~0u};              // TAIL: what counts of this lane's chunk in the last piece of a row (nothing past its end)
+    if (TAIL) {
+        const int at = (d - 1) / 32 * 32 + sub * 4, skip = max(at - (d - 4), 0);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) if (e < skip) keep[e] = 0u;
+    }
+    const float* bq = qs + sub * 4;
+    const int chunks = dq / 4;                            // 16-byte chunks per query row
+    if (resident) {
+        for (int i = threadIdx.x; i < a.nq * chunks; i += blockDim.x) {
+            const int qi = i / chunks, ch = i - qi * chunks;
+            *(uint4*)(qs + (size_t)qi * qstride + ch * 4) = *(const uint4*)(q_rows + (size_t)qi * dq + ch * 4);
+        }
+        for (int i = threadIdx.x; i < a.nq; i += blockDim.x) { s_thr[i] = a.thr[i]; s_qq[i] = a.qq[i]; }
+        __syncthreads();
+    }
+    while (feed.next(a, s_run, task)) {
+        const uint32_t nqg = task.nq;
+        if (!resident && task.qbase != staged) {
             __syncthreads();                              // everyone is done with the previous queries
-            if (threadIdx.x < kGroupQ32) {
-                bool ok = threadIdx.x < nqg;
-                uint32_t qi = ok ? a.qidx[qbase + threadIdx.x] : 0;
-                s_q[threadIdx.x] = ok ? qi : 0xFFFFFFFFu;
-                s_thr[threadIdx.x] = ok ? a.thr[qi] : INFINITY;
-                s_qq[threadIdx.x] = ok ? a.qq[qi] : 0.f;
+            if (threadIdx.x < nqg) {
+                const uint32_t qi = a.qidx[task.qbase + threadIdx.x];
+                s_q[threadIdx.x] = qi; s_thr[threadIdx.x] = a.thr[qi]; s_qq[threadIdx.x] = a.qq[qi];
             }
             __syncthreads();
-            const int chunks = d / 4;                     // 16-byte chunks per query row
-            for (int i = threadIdx.x; i < kGroupQ32 * chunks; i += blockDim.x) {
-                int qq = i / chunks, ch = i - qq * chunks;
-                uint32_t qi = s_q[qq];
-                uint4 v = make_uint4(0, 0, 0, 0);
-                if (qi != 0xFFFFFFFFu) v = *(const uint4*)(a.q + (size_t)qi * d + ch * 4);
-                *(uint4*)(qs + (size_t)qq * qstride + ch * 4) = v;
+            for (int i = threadIdx.x; i < (int)nqg * chunks; i += blockDim.x) {
+                const int p = i / chunks, ch = i - p * chunks;
+                *(uint4*)(qs + (size_t)p * qstride + ch * 4) = *(const uint4*)(q_rows + (size_t)s_q[p] * dq + ch * 4);
             }
             __syncthreads();
-            staged_cluster = c; staged_group = task.group;
+            staged = task.qbase;
         }
-        const int64_t lo = a.off[c];
-        const uint32_t n = (uint32_t)(a.off[c + 1] - lo);
-        const uint32_t r0 = task.tile * kTileRows + wave * 32;     // first row of this wavefront
-        if (r0 >= n) continue;
-        // Loading role of a lane: 16-byte chunk lane % 8 of rows lane / 8 and lane / 8 + 8 of each row
-        // block, for every 32-element (128-byte) piece of the rows; rows past the end re-read the last one.
-        const float* lp[4];            // [row block][row half]
+        if (r0 >= task.rows) continue;
+        const float* lp[4];                               // rows past the end re-read the last one
 #pragma unroll
-        for (int j = 0; j < 4; ++j)
-            lp[j] = (const float*)a.lists + ((size_t)lo + min(r0 + 8u * j + (uint32_t)(lane >> 3), n - 1)) * d + (lane & 7) * 4;
-        // lane that holds, after the exchange below, what this MFMA lane (row col, part kq) needs
-        const int from = (((col & 7) << 3) | ((col >> 3) << 2) | kq) << 2;
-        const float* bq = qs + (size_t)col * qstride + kq * 4;
-        float4_t acc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
-        float yy[8];                   // L2: squared norms of the rows this lane will hold scores of
-        if (METRIC != 0) {
+        for (int u = 0; u < 4; ++u)
+            lp[u] = (const float*)a.lists + ((size_t)task.row0 + min(r0 + 8u * u + lrow, task.rows - 1)) * d + (TAIL ? 0 : sub * 4);
+        // rows of `task` against M places of the group on the vector units, or (M = 16) on the matrix cores
+        auto walk = [&](auto size) __attribute__((always_inline)) {
+            constexpr int M = decltype(size)::value;
+            constexpr bool MATRIX = M > 8;
+            constexpr int N = MATRIX ? 8 : 4;             // scores of a lane
+            // query of this lane's scores, and where it is in LDS
+            const uint32_t place = MATRIX ? (uint32_t)(lane & 15) : (uint32_t)sub;
+            const uint32_t qi = a.qidx[task.qbase + min(place, nqg - 1)], slot = resident ? qi : min(place, nqg - 1);
+            // row of score i in the wavefront's 32
+            auto row_of = [&](int i) { return MATRIX ? (uint32_t)((i / 4) * 16 + (lane >> 4) * 4 + (i % 4)) : 8u * (uint32_t)i + lrow; };
+            float yy[N];                                  // L2: squared norms of those rows
+            if (METRIC != 0) {
 #pragma unroll
-            for (int i = 0; i < 8; ++i)
-                yy[i] = a.row_norm[(size_t)lo + min(r0 + (uint32_t)((i / 4) * 16 + kq * 4 + (i % 4)), n - 1)];
-        }
-        uint4 av[2][4 * kStage32];
-        auto issue = [&](int k0, uint4 (&v)[4 * kStage32]) {
-#pragma unroll
-            for (int b = 0; b < kStage32; ++b) {
-                const bool in = k0 + b * 32 < d;
-#pragma unroll
-                for (int j = 0; j < 4; ++j) v[4 * b + j] = in ? load_stream16(lp[j] + k0 + b * 32) : make_uint4(0, 0, 0, 0);
+                for (int i = 0; i < N; ++i) yy[i] = a.row_norm[(size_t)task.row0 + min(r0 + row_of(i), task.rows - 1)];
             }
-        };
-        // One loaded value to its MFMA lanes.  Lanes with chunk >= 4 hold the second 16-element
-        // block of the piece.  A move by four lanes inside each row of 16 lanes (DPP row shift,
-        // written only to the lanes of one chunk half) gathers the first block of both row halves
-        // in one register (lane (r, c): row r + 8 (c / 4), chunk c % 4) and the second block in
-        // another; one lane permutation each then puts them in MFMA order.
-        auto to_mfma = [&](uint32_t lo_half, uint32_t hi_half, float& first, float& second) {
-            const int f = __builtin_amdgcn_update_dpp((int)lo_half, (int)hi_half, 0x114, 0xF, 0xA, false);   // row_shr:4 into chunks 4..7
-            const int g = __builtin_amdgcn_update_dpp((int)hi_half, (int)lo_half, 0x104, 0xF, 0x5, false);   // row_shl:4 into chunks 0..3
-            first = __int_as_float(__builtin_amdgcn_ds_bpermute(from, f));
-            second = __int_as_float(__builtin_amdgcn_ds_bpermute(from, g));
-        };
-        auto consume = [&](int k0, const uint4 (&v)[4 * kStage32]) {
+            uint32_t at[MATRIX ? 1 : M];                  // LDS row of place m
+            if (!MATRIX) {
 #pragma unroll
-            for (int b = 0; b < kStage32; ++b) {
-                if (k0 + b * 32 < d) {
-                    const float4 bv0 = *(const float4*)(bq + k0 + b * 32);
-                    const float4 bv1 = *(const float4*)(bq + k0 + b * 32 + 16);
-                    float x[2][2][4];          // [row block][16-element block][value of the chunk]
+                for (int m = 0; m < M; ++m) {
+                    const uint32_t p = min((uint32_t)m, nqg - 1);
+                    at[m] = (resident ? load_scalar(&a.qidx[task.qbase + p]) : p) * (uint32_t)qstride;
+                }
+            }
+            const float* bm = qs + (size_t)slot * qstride + (lane >> 4) * 4;     // MATRIX: this lane's query operand
+            const int from = (((lane & 7) << 3) | (((lane >> 3) & 1) << 2) | (lane >> 4)) << 2;
+            float acc[MATRIX ? 1 : 4][MATRIX ? 1 : M];
+            float4_t macc[2] = {{0.f, 0.f, 0.f, 0.f}, {0.f, 0.f, 0.f, 0.f}};
 #pragma unroll
-                    for (int rb = 0; rb < 2; ++rb) {
-                        const uint4 h0 = v[4 * b + 2 * rb], h1 = v[4 * b + 2 * rb + 1];
-                        to_mfma(h0.x, h1.x, x[rb][0][0], x[rb][1][0]);
-                        to_mfma(h0.y, h1.y, x[rb][0][1], x[rb][1][1]);
-                        to_mfma(h0.z, h1.z, x[rb][0][2], x[rb][1][2]);
-                        to_mfma(h0.w, h1.w, x[rb][0][3], x[rb][1][3]);
+            for (int u = 0; u < (MATRIX ? 1 : 4); ++u)
+#pragma unroll
+                for (int m = 0; m < (MATRIX ? 1 : M); ++m) acc[u][m] = 0.f;
+            uint4 av[2][4 * kStage32];
+            auto issue = [&](int k0, uint4 (&v)[4 * kStage32]) __attribute__((always_inline)) {
+#pragma unroll
+                for (int b = 0; b < kStage32; ++b) {
+                    if (k0 + b * 32 >= d) break;
+#pragma unroll
+                    for (int u = 0; u < 4; ++u)
+                        v[4 * b + u] = TAIL ? load_chunk<true>(lp[u] + min(k0 + b * 32 + sub * 4, d - 4)) : load_stream16(lp[u] + k0 + b * 32);
+                }
+            };
+            // One loaded value to its MFMA lanes.  Lanes with chunk >= 4 hold the second 16-element
+            // block of the piece.  A move by four lanes inside each row of 16 lanes (DPP row shift,
+            // written only to the lanes of one chunk half) gathers the first block of both row halves
+            // in one register (lane (r, c): row r + 8 (c / 4), chunk c % 4) and the second block in
+            // another; one lane permutation each then puts them in MFMA order.
+            auto to_mfma = [&](uint32_t lo_half, uint32_t hi_half, float& first, float& second) {
+                const int f = __builtin_amdgcn_update_dpp((int)lo_half, (int)hi_half, 0x114, 0xF, 0xA, false);   // row_shr:4 into chunks 4..7
+                const int g = __builtin_amdgcn_update_dpp((int)hi_half, (int)lo_half, 0x104, 0xF, 0x5, false);   // row_shl:4 into chunks 0..3
+                first = __int_as_float(__builtin_amdgcn_ds_bpermute(from, f));
+                second = __int_as_float(__builtin_amdgcn_ds_bpermute(from, g));
+            };
+            auto consume = [&](int k0, const uint4 (&v)[4 * kStage32]) __attribute__((always_inline)) {
+#pragma unroll
+                for (int b = 0; b < kStage32; ++b) {
+                    if (k0 + b * 32 >= d) break;
+                    uint4 h[4];
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) {
+                        h[u] = v[4 * b + u];
+                        if (TAIL && k0 + b * 32 + 32 >= d) { h[u].x &= keep[0]; h[u].y &= keep[1]; h[u].z &= keep[2]; h[u].w &= keep[3]; }
                     }
-                    const float q0[4] = {bv0.x, bv0.y, bv0.z, bv0.w}, q1[4] = {bv1.x, bv1.y, bv1.z, bv1.w};
+                    if constexpr (MATRIX) {
+                        const float4 bv0 = *(const float4*)(bm + k0 + b * 32);
+                        const float4 bv1 = *(const float4*)(bm + k0 + b * 32 + 16);
+                        float x[2][2][4];          // [row block][16-element block][value of the chunk]
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        acc[0] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[0][0][e], q0[e], acc[0], 0, 0, 0);
-                        acc[1] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[1][0][e], q0[e], acc[1], 0, 0, 0);
+                        for (int rb = 0; rb < 2; ++rb) {
+                            const uint4 h0 = h[2 * rb], h1 = h[2 * rb + 1];
+                            to_mfma(h0.x, h1.x, x[rb][0][0], x[rb][1][0]);
+                            to_mfma(h0.y, h1.y, x[rb][0][1], x[rb][1][1]);
+                            to_mfma(h0.z, h1.z, x[rb][0][2], x[rb][1][2]);
+                            to_mfma(h0.w, h1.w, x[rb][0][3], x[rb][1][3]);
+                        }
+                        const float q0[4] = {bv0.x, bv0.y, bv0.z, bv0.w}, q1[4] = {bv1.x, bv1.y, bv1.z, bv1.w};
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) {
+                            macc[0] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[0][0][e], q0[e], macc[0], 0, 0, 0);
+                            macc[1] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[1][0][e], q0[e], macc[1], 0, 0, 0);
+                        }
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) {
+                            macc[0] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[0][1][e], q1[e], macc[0], 0, 0, 0);
+                            macc[1] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[1][1][e], q1[e], macc[1], 0, 0, 0);
+                        }
+                    } else {
+                        float x[4][4];
+#pragma unroll
+                        for (int u = 0; u < 4; ++u) Unpack<F32>::run(h[u], x[u]);
+#pragma unroll
+                        for (int m = 0; m < M; ++m) {
+                            const float4 q4 = *(const float4*)(bq + at[m] + k0 + b * 32);
+#pragma unroll
+                            for (int u = 0; u < 4; ++u) {
+                                acc[u][m] = fmaf(x[u][0], q4.x, acc[u][m]);
+                                acc[u][m] = fmaf(x[u][1], q4.y, acc[u][m]);
+                                acc[u][m] = fmaf(x[u][2], q4.z, acc[u][m]);
+                                acc[u][m] = fmaf(x[u][3], q4.w, acc[u][m]);
+                            }
+                        }
                     }
+                }
+            };
+            constexpr int kStep = kStage32 * 32;          // elements per stage
+            issue(0, av[0]);
+#pragma unroll 1
+            for (int k0 = 0; k0 < d; k0 += 2 * kStep) {
+                if (k0 + kStep < d) issue(k0 + kStep, av[1]);
+                consume(k0, av[0]);
+                if (k0 + kStep >= d) break;
+                if (k0 + 2 * kStep < d) issue(k0 + 2 * kStep, av[0]);
+                consume(k0 + kStep, av[1]);
+            }
+            float sc[N];
+            if constexpr (MATRIX) {
 #pragma unroll
-                    for (int e = 0; e < 4; ++e) {
-                        acc[0] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[0][1][e], q1[e], acc[0], 0, 0, 0);
-                        acc[1] = __builtin_amdgcn_mfma_f32_16x16x4f32(x[1][1][e], q1[e], acc[1], 0, 0, 0);
+                for (int i = 0; i < 4; ++i) { sc[i] = macc[0][i]; sc[4 + i] = macc[1][i]; }
+            } else {
+#pragma unroll
+                for (int u = 0; u < 4; ++u) sc[u] = sums_over_8<M>(acc[u]);
+            }
+            if (place >= nqg) return;
+            const float thr = s_thr[slot];
+            if (METRIC != 0) {
+                const float qq = s_qq[slot];
+#pragma unroll
+                for (int i = 0; i < N; ++i) sc[i] = fmaf(2.f, sc[i], -yy[i]) - qq;
+            }
+            uint32_t pass = 0;
+#pragma unroll
+            for (int i = 0; i < N; ++i) if (sc[i] >= thr && r0 + row_of(i) < task.rows) pass |= 1u << i;
+            if (pass) {
+                // one reservation for all rows of this lane that passed
+                uint32_t pos = atomicAdd(&a.cand_count[(size_t)qi * kCountStride], (uint32_t)__popc(pass));
+#pragma unroll
+                for (int i = 0; i < N; ++i) {
+                    if ((pass >> i) & 1u) {
+                        if (pos < (uint32_t)a.cand_cap) {
+                            a.cand_row[(size_t)qi * a.cand_cap + pos] = task.row0 + r0 + row_of(i);
+                            a.cand_score[(size_t)qi * a.cand_cap + pos] = sc[i];
+                        }
+                        ++pos;
                     }
                 }
             }
         };
-        constexpr int kStep = kStage32 * 32;              // elements per stage
-        issue(0, av[0]);
-        for (int k0 = 0; k0 < d; k0 += 2 * kStep) {
-            if (k0 + kStep < d) issue(k0 + kStep, av[1]);
-            consume(k0, av[0]);
-            if (k0 + kStep >= d) break;
-            if (k0 + 2 * kStep < d) issue(k0 + 2 * kStep, av[0]);
-            consume(k0 + kStep, av[1]);
-        }
-        // lane holds query `col`, rows (i / 4) * 16 + kq * 4 + i % 4
-        const float thr = s_thr[col];
-        const uint32_t qi = s_q[col];
-        float sc[8];
-#pragma unroll
-        for (int i = 0; i < 4; ++i) { sc[i] = acc[0][i]; sc[4 + i] = acc[1][i]; }
-        if (METRIC != 0) {
-            const float qq = s_qq[col];
-#pragma unroll
-            for (int i = 0; i < 8; ++i) sc[i] = fmaf(2.f, sc[i], -yy[i]) - qq;
-        }
-        uint32_t pass = 0;
-#pragma unroll
-        for (int i = 0; i < 8; ++i) {
-            const uint32_t r = r0 + (i / 4) * 16 + kq * 4 + (i % 4);
-            if (sc[i] >= thr && r < n) pass |= 1u << i;
-        }
-        if (pass) {
-            uint32_t pos = atomicAdd(&a.cand_count[(size_t)qi * kCountStride], (uint32_t)__popc(pass));
-#pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                if ((pass >> i) & 1u) {
-                    if (pos < (uint32_t)a.cand_cap) {
-                        a.cand_row[(size_t)qi * a.cand_cap + pos] = (uint32_t)(lo + r0 + (i / 4) * 16 + kq * 4 + (i % 4));
-                        a.cand_score[(size_t)qi * a.cand_cap + pos] = sc[i];
-                    }
-                    ++pos;
-                }
-            }
-        }
+        if (nqg > 8) walk(std::integral_constant<int, 16>{});
+        else if (nqg > 4) walk(std::integral_constant<int, 8>{});
+        else if (nqg > 2) walk(std::integral_constant<int, 4>{});
+        else if (nqg > 1) walk(std::integral_constant<int, 2>{});
+        else walk(std::integral_constant<int, 1>{});
     }
 }
 
@@ -808,8 +959,19 @@ __global__ __launch_bounds__(kSelectThreads) void batched_merge_kernel(BatchedAr
     const int qi = blockIdx.x;
     const uint32_t k = (uint32_t)a.k;
     const uint32_t n0 = a.cand_count[(size_t)qi * kCountStride];
-    if (n0 > (uint32_t)a.cand_cap) {                   // too many candidates: the host redoes this query
-        if (tid == 0) a.overflow[qi] = 1;
+    // too many candidates or survivors: the query is searched again, by the host or, with redo_flag, by the
+    // exact pass that follows on the stream (rows below `at_least` do not count)
+    auto search_again = [&](uint32_t again, double at_least) {
+        if (tid != 0) return;
+        a.overflow[qi] = (int32_t)again;
+        if (a.redo_flag) {
+            a.redo_flag[qi] = again;
+            a.redo_thr[qi] = at_least;
+            a.redo_ticket[qi] = 0u;
+        }
+    };
+    if (n0 > (uint32_t)a.cand_cap) {
+        search_again(1u, -INFINITY);
         return;
     }
     const float* sc = a.cand_score + (size_t)qi * a.cand_cap;
@@ -896,7 +1058,7 @@ __global__ __launch_bounds__(kSelectThreads) void batched_merge_kernel(BatchedAr
     __syncthreads();
     const uint32_t n_top = s_n, n_back = s_m;
     if (n_top + n_back > (uint32_t)kBatchSurvivors) {  // cannot happen unless scores are massively tied
-        if (tid == 0) a.overflow[qi] = 1;
+        search_again(1u, (double)kth - 1.0001 * (double)eps);       // k rows have scores of at least kth, each within eps
         return;
     }
     // 3. fp64 re-scores of survivors c0 .. c1 - 1: a group of lanes per survivor, two rows in flight
@@ -910,7 +1072,7 @@ __global__ __launch_bounds__(kSelectThreads) void batched_merge_kernel(BatchedAr
             uint32_t row[kRescoreInFlight];
 #pragma unroll
             for (int r = 0; r < kRescoreInFlight; ++r) row[r] = s_row[min(c + groups * r, c1 - 1)];
-            rescore_rows<kRescoreInFlight>(a.lists, q, a.d, a.dtype, a.metric, row, sub, s);     // d is a multiple of 64
+            rescore_rows<kRescoreInFlight>(a.lists, q, a.d, a.dtype, a.metric, row, sub, s);
 #pragma unroll
             for (int r = 0; r < kRescoreInFlight; ++r)
                 if (sub == 0 && c + groups * r < c1) s_key[c + groups * r] = ordered(a.metric == 0 ? s[r] : -s[r]);
@@ -1035,7 +1197,7 @@ __global__ __launch_bounds__(kSelectThreads) void batched_merge_kernel(BatchedAr
             if (sub8 == 0 && rank < k) put(rank, (int64_t)id, unordered(o_key[tie]));
         }
     }
-    if (tid == 0) a.overflow[qi] = 0;
+    search_again(0u, 0.0);
     __syncthreads();
     // in order: the outputs may be host memory
     for (uint32_t i = tid; i < k; i += nt) {
@@ -1047,9 +1209,24 @@ __global__ __launch_bounds__(kSelectThreads) void batched_merge_kernel(BatchedAr
 // ---- launch sequence ---------------------------------------------------------------------------------------
 int batched_group_q(int dtype) { return dtype == 0 ? kGroupQ32 : kGroupQ; }
 
-size_t batched_scan_lds(int d, int dtype) {
-    if (dtype == 0) return (size_t)kGroupQ32 * (d + kQPad32) * 4;
-    return (size_t)kGroupQ * (d + kQPad) * 2 + (size_t)kBatchWaves * 32 * kStageLd * 2;
+int batched_query_stride(int d, int dtype) { return dtype == 0 ? (d + 31) / 32 * 32 : (d + 63) / 64 * 64; }
+
+// LDS of the scan with the queries, thresholds and norms of `slots` queries, beside its staging area (2-byte rows)
+static size_t batched_lds_for(int slots, int dq, int dtype) {
+    if (dtype == 0) return (size_t)slots * ((size_t)(dq + kQPad32) * 4 + 8);
+    return (size_t)slots * ((size_t)(dq + kQPad) * 2 + 8) + (size_t)kBatchWaves * 32 * kStageLd * 2;
+}
+size_t batched_scan_lds(int d, int dtype) { return batched_lds_for(batched_group_q(dtype), batched_query_stride(d, dtype), dtype); }
+
+// The scan keeps the queries of the whole batch in LDS when they fit and rows are narrow: tasks are then
+// short (256 rows of 400 bytes: 3.7 us of streaming), and staging the queries of every group anew, three
+// barriers and two trips to memory, is a large part of them: 48 queries x 100 fp32 (287 MB) 69 us with
+// groups, 62 so; 106 x 283 fp16 (994 MB) 282, 238; 134 x 46 fp16 (726 MB) 285, 245.  Rows of 1536 and 4096
+// bytes lose by it: 32 x 768 fp16 (4.3 GB) 625, 633; 20 x 1024 fp32 (1.9 GB) 308, 316; of 1024 bytes nothing.
+constexpr size_t kResidentRowBytes = 1024;
+constexpr size_t kScanStaticLds = 512;          // what the scan kernels hold beside that (at most)
+static bool queries_resident(const BatchedArgs& a) {
+    return (size_t)a.d * (a.dtype == 0 ? 4 : 2) <= kResidentRowBytes && batched_lds_for(a.nq, a.dq, a.dtype) + kScanStaticLds <= a.max_lds;
 }
 
 uint64_t batched_task_bound(const int64_t* off_host, int nlist, int nq, int dtype) {
@@ -1062,16 +1239,20 @@ uint64_t batched_task_bound(const int64_t* off_host, int nlist, int nq, int dtyp
 
 size_t batched_sample_words(int nq) { return (size_t)nq * kSampleRows; }
 
-typedef void (*BatchedScanFn)(BatchedArgs);
-static BatchedScanFn batched_scan_fn(int dtype, int metric) {
-    if (dtype == 0) return metric == 0 ? batched_scan_f32_kernel<0> : batched_scan_f32_kernel<1>;
-    if (dtype == 1) return metric == 0 ? batched_scan_kernel<F16, 0> : batched_scan_kernel<F16, 1>;
-    return metric == 0 ? batched_scan_kernel<BF16, 0> : batched_scan_kernel<BF16, 1>;
+typedef void (*BatchedScanFn)(BatchedArgs, int);
+template <bool TAIL>
+static BatchedScanFn batched_scan_fn_for(int dtype, int metric) {
+    if (dtype == 0) return metric == 0 ? batched_scan_f32_kernel<0, TAIL> : batched_scan_f32_kernel<1, TAIL>;
+    if (dtype == 1) return metric == 0 ? batched_scan_kernel<F16, 0, TAIL> : batched_scan_kernel<F16, 1, TAIL>;
+    return metric == 0 ? batched_scan_kernel<BF16, 0, TAIL> : batched_scan_kernel<BF16, 1, TAIL>;
+}
+static BatchedScanFn batched_scan_fn(int dtype, int metric, int d) {
+    return d % 64 != 0 ? batched_scan_fn_for<true>(dtype, metric) : batched_scan_fn_for<false>(dtype, metric);
 }
 
 int batched_resident_grid(int dtype, int metric, int d, int n_cu) {
     int per_cu = 0;
-    hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void*)batched_scan_fn(dtype, metric), kBatchThreads,
+    hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, (const void*)batched_scan_fn(dtype, metric, d), kBatchThreads,
                                                                 batched_scan_lds(d, dtype));
     if (e != hipSuccess || per_cu < 1) per_cu = 1;
     if (per_cu > 4) per_cu = 4;
@@ -1082,7 +1263,7 @@ int batched_resident_grid(int dtype, int metric, int d, int n_cu) {
 // the lanes, and for L2 the rounded difference and its square
 float batched_sample_coef(int d, int dtype, int metric) {
     const int epl = dtype == 0 ? 4 : 8;
-    const int chunks = d / epl;
+    const int chunks = (d + epl - 1) / epl;
     const int terms = epl * ((chunks + 63) / 64) + 6 + (metric != 0 ? 3 : 0);
     return 1.05f * (float)(terms + 2) * 0x1p-24f;
 }
@@ -1095,12 +1276,17 @@ hipError_t launch_batched(const BatchedArgs& a, int grid, hipStream_t s, hipEven
         hipLaunchKernelGGL(count_pairs_kernel, dim3((unsigned)(((uint64_t)a.nq * (uint64_t)a.nprobe + 255) / 256)), dim3(256), 0, s, a);
     }
     const dim3 front(1 + (unsigned)a.nq * (unsigned)(parts + 1)), tasks((unsigned)a.nq + (unsigned)std::min((a.nlist + 3) / 4, 1024));
-    if (a.dtype == 0) hipLaunchKernelGGL(batch_front_kernel<F32>, front, dim3(kFrontThreads), front_lds, s, a, parts, counted);
-    else if (a.dtype == 1) hipLaunchKernelGGL(batch_front_kernel<F16>, front, dim3(kFrontThreads), front_lds, s, a, parts, counted);
-    else hipLaunchKernelGGL(batch_front_kernel<BF16>, front, dim3(kFrontThreads), front_lds, s, a, parts, counted);
+    typedef void (*FrontFn)(BatchedArgs, int, int);
+    const bool tail = a.d % (a.dtype == 0 ? 4 : 8) != 0;
+    const FrontFn front_fn = a.dtype == 0 ? (tail ? (FrontFn)batch_front_kernel<F32, true> : (FrontFn)batch_front_kernel<F32, false>)
+                           : a.dtype == 1 ? (tail ? (FrontFn)batch_front_kernel<F16, true> : (FrontFn)batch_front_kernel<F16, false>)
+                                          : (tail ? (FrontFn)batch_front_kernel<BF16, true> : (FrontFn)batch_front_kernel<BF16, false>);
+    hipLaunchKernelGGL(front_fn, front, dim3(kFrontThreads), front_lds, s, a, parts, counted);
     hipLaunchKernelGGL(batch_tasks_kernel, tasks, dim3(256), 0, s, a);
-    const BatchedScanFn scan = batched_scan_fn(a.dtype, a.metric);
-    IVF_LAUNCH(scan, dim3(grid), dim3(kBatchThreads), batched_scan_lds(a.d, a.dtype), s, scan_start, scan_stop, a);
+    const BatchedScanFn scan = batched_scan_fn(a.dtype, a.metric, a.d);
+    const int resident = queries_resident(a) ? 1 : 0;
+    const size_t scan_lds = resident ? batched_lds_for(a.nq, a.dq, a.dtype) : batched_scan_lds(a.d, a.dtype);
+    IVF_LAUNCH(scan, dim3(grid), dim3(kBatchThreads), scan_lds, s, scan_start, scan_stop, a, resident);
     if (with_merge) hipLaunchKernelGGL(batched_merge_kernel, dim3(a.nq), dim3(kSelectThreads), 0, s, a);
     return hipGetLastError();
 }

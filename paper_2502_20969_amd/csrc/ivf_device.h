@@ -75,6 +75,14 @@ __device__ __forceinline__ uint4 load_stream16_any(const void* p) {
     return make_uint4(t.x, t.y, t.z, t.w);
 }
 
+// A cached 16-byte load: ANY from an address that is aligned to elements only.
+template <bool ANY>
+__device__ __forceinline__ uint4 load_chunk(const void* p) {
+    if (!ANY) return *(const uint4*)p;
+    const u4_t t = *(const u4_any_t*)p;
+    return make_uint4(t.x, t.y, t.z, t.w);
+}
+
 // Four floats from an address that is aligned to one float.
 typedef float f4_any_t __attribute__((ext_vector_type(4), aligned(4)));
 __device__ __forceinline__ float4 load_float4_any(const float* p) {
@@ -236,19 +244,45 @@ __device__ __forceinline__ double rescore_row(const void* buf, const float* q, i
     return s;
 }
 
-// The same for R rows at once, whole 16-byte chunks only: their loads overlap, every row's order of
-// operations is that of rescore_row.
+// The same for R rows at once: their loads overlap, every row's order of operations is that of rescore_row.
 template <int R>
 __device__ __forceinline__ void rescore_rows(const void* buf, const float* q, int d, int dtype, int metric,
                                              const uint32_t (&brow)[R], int sub, double (&s)[R]) {
     constexpr int lpc = kRescoreLanes;
     const size_t row_bytes = (size_t)d * (dtype == 0 ? 4 : 2);
-    const unsigned char* rp[R];
+    if (row_bytes % 16 == 0) {
+        const unsigned char* rp[R];
 #pragma unroll
-    for (int r = 0; r < R; ++r) rp[r] = (const unsigned char*)buf + brow[r] * row_bytes;
-    if (dtype == 0) rescore_partial<F32, R>(rp, q, d, metric, sub, lpc, s);
-    else if (dtype == 1) rescore_partial<F16, R>(rp, q, d, metric, sub, lpc, s);
-    else rescore_partial<BF16, R>(rp, q, d, metric, sub, lpc, s);
+        for (int r = 0; r < R; ++r) rp[r] = (const unsigned char*)buf + brow[r] * row_bytes;
+        if (dtype == 0) rescore_partial<F32, R>(rp, q, d, metric, sub, lpc, s);
+        else if (dtype == 1) rescore_partial<F16, R>(rp, q, d, metric, sub, lpc, s);
+        else rescore_partial<BF16, R>(rp, q, d, metric, sub, lpc, s);
+    } else {
+        constexpr int U = 4;
+#pragma unroll
+        for (int r = 0; r < R; ++r) s[r] = 0.0;
+#pragma unroll 1
+        for (int t0 = sub; t0 < d; t0 += U * lpc) {
+            double x[U], y[R][U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const int t = min(t0 + u * lpc, d - 1);
+                x[u] = (double)q[t];
+#pragma unroll
+                for (int r = 0; r < R; ++r) y[r][u] = widen(buf, dtype, (size_t)brow[r] * d + t);
+            }
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                if (t0 + u * lpc < d) {
+#pragma unroll
+                    for (int r = 0; r < R; ++r) {
+                        if (metric == 0) s[r] = fma(x[u], y[r][u], s[r]);
+                        else { const double df = x[u] - y[r][u]; s[r] = fma(df, df, s[r]); }
+                    }
+                }
+            }
+        }
+    }
 #pragma unroll 1
     for (int o = 1; o < lpc; o <<= 1) {
 #pragma unroll

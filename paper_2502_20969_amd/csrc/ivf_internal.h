@@ -168,7 +168,9 @@ constexpr int kScheduleMaxQueries = 4096;
 // 125,000 x 768 fp16 with k 10 and 100, 256 x 1,000,000 x 256 bf16 with k 100); with a line each 251, 274 and 1267.
 constexpr int kCountStride = 32;
 constexpr int kBatchSurvivors = 4096;      // candidates of a query that are re-scored in fp64
-struct BatchTask { uint32_t cluster, group, tile; };    // tile: 256 rows of the cluster; group: up to 32 (fp32 rows: 16) of the queries probing it
+// Up to 256 rows of a cluster, from global row row0 on, against up to 32 (fp32 rows: 16) of the queries that probe it,
+// qidx[qbase] and on.
+struct alignas(16) BatchTask { uint32_t row0, rows, qbase, nq; };
 
 struct BatchedArgs {
     const void* lists;           // device lists (device placement)
@@ -177,7 +179,7 @@ struct BatchedArgs {
     const float* q;              // [nq x d] fp32 queries
     const int32_t* probe;        // [nq x nprobe] selected clusters
     const uint32_t* rprefix;     // [nq x (nprobe+1)] SlotTables::rprefix: the last entry is a query's selected rows
-    void* q_store;               // [nq x d] queries rounded to the storage type (out)
+    void* q_store;               // [nq x dq] queries rounded to the storage type, laid out as the scan loads rows (out)
     float* thr;                  // [nq] out: filter threshold
     uint32_t* thr_part;          // [batched_sample_words(nq)] ordered scores of the threshold sample, 0 = none
     const unsigned int* row_norm_max_bits;   // largest squared row norm of the lists, as float bits
@@ -202,6 +204,10 @@ struct BatchedArgs {
     int group_q;                 // queries per task: batched_group_q(dtype)
     float acc_coef;              // fp32 accumulation of the MFMA: |error| <= acc_coef |q| |y|
     float samp_coef;             // batched_sample_coef(d, dtype, metric)
+    size_t max_lds;              // LDS bytes one workgroup may use
+    int dq;                      // batched_query_stride(d, dtype)
+    // Nullable (all or none): queries that have to be searched again, for launch_redo behind the merge
+    uint32_t* redo_flag; double* redo_thr; uint32_t* redo_ticket;
     int keep_all;                // 1: the threshold is -inf, every scanned row becomes a candidate (stage-level test entry)
 };
 // upper bound of the number of tasks for a batch of nq queries
@@ -213,6 +219,7 @@ float batched_sample_coef(int d, int dtype, int metric);
 // with_merge = false stops after the scan: the candidate lists hold what passed the filter
 hipError_t launch_batched(const BatchedArgs& a, int grid, hipStream_t s, hipEvent_t scan_start = nullptr,
                           hipEvent_t scan_stop = nullptr, bool with_merge = true);
+int batched_query_stride(int d, int dtype);     // elements of a staged query: whole blocks of the scan
 int batched_resident_grid(int dtype, int metric, int d, int n_cu);
 size_t batched_sample_words(int nq);
 size_t batched_scan_lds(int d, int dtype);      // LDS bytes of the batched scan kernel (one group of queries)

@@ -197,3 +197,29 @@ def test_filter_scores_stay_within_the_assumed_bound(streams, dtype, d, metric):
     # (fp32 rows: within three, the accumulation order inside the matrix cores is not known)
     assert (err / eps).max() > (0.001 if dtype == "f32" else 0.01)
     index.close()
+
+
+@pytest.mark.parametrize("nq", [2, 3, 4, 5, 8, 9, 16, 17, 33])
+@pytest.mark.parametrize("dtype,d,metric", [("f32", 64, "ip"), ("f32", 256, "l2"), ("f32", 320, "ip"), ("f32", 832, "l2"),
+                                            ("f16", 512, "ip"), ("bf16", 576, "l2")])
+def test_groups_of_every_size(streams, dtype, d, nq, metric):
+    """The scan of fp32 rows walks groups of 1, 2, 4, 8 and more queries in code of their own, and the
+    queries of narrow rows (up to 1 KB) stay in LDS for the whole scan: clusters that all nq queries,
+    or only some of them, select, in lists that end inside a tile."""
+    nlist, n, k, nprobe = 7, 3700, 9, 3
+    rng = np.random.default_rng(nq * 100 + d)
+    cent = rng.standard_normal((nlist, d)).astype(np.float32)
+    off = np.array([0, 1, 258, 514, 900, 2000, 2000, n], dtype=np.int64)
+    rows = (np.repeat(cent, np.diff(off), 0) + 0.5 * rng.standard_normal((n, d))).astype(np.float32)
+    q = (cent[[3] * (nq - nq // 3) + [6] * (nq // 3)] + 0.3 * rng.standard_normal((nq, d))).astype(np.float32)
+    dev = torch.from_numpy(rows).to({"f32": torch.float32, "f16": torch.float16, "bf16": torch.bfloat16}[dtype]).cuda()
+    index = P.ivf_adopt_layout(dev, dtype, off, cent, metric=P.IVF_IP if metric == "ip" else P.IVF_L2,
+                               compute_stream=streams[0], copy_stream=streams[1])
+    index.ivf_set_batch_mode(2)
+    for m in (nprobe, nlist):
+        gi, gd = index.ivf_search(q, m, k)
+        index.ivf_set_batch_mode(1)
+        pi, pd = index.ivf_search(q, m, k)
+        index.ivf_set_batch_mode(2)
+        assert np.array_equal(gi, pi) and np.array_equal(gd, pd)
+    index.close()
