@@ -183,7 +183,8 @@ int ivf_search(ivf_index* index, const float* q_out, int32_t nq, int32_t nprobe,
 int ivf_search_device(ivf_index* index, const float* q_dev, int32_t nq, int32_t nprobe,
                       int32_t k, int64_t* ids_dev, float* dists_dev);
 
-/* Sizes the workspace for searches up to (nq, nprobe, k) so that later calls allocate nothing. */
+/* Sizes the workspace for searches up to (nq, nprobe, k) so that later calls allocate nothing (a list-major
+ * batch of rows whose d is a multiple of 64 sizes more of it in the first such call). */
 int ivf_reserve(ivf_index* index, int32_t nq, int32_t nprobe, int32_t k);
 
 /*
@@ -224,10 +225,12 @@ int ivf_synchronize(ivf_index* index);
 
 /*
  * How a call with several queries is executed (Sec. 4.2 "Batching").
- *   0  automatic: batches of 4 or more queries on a device-resident fp16 / bf16 inner-product
- *      index with d a multiple of 64 are searched list-major (each selected cluster is read
- *      once per group of up to 32 queries that probe it, scores by MFMA); anything else query
- *      by query
+ *   0  automatic: batches of 4 or more queries on an index that has the list-major path are
+ *      searched list-major (each selected cluster is read once per group of up to 32 queries,
+ *      16 of fp32 rows, that probe it).  So are larger batches on a device-resident index whose d
+ *      is no multiple of 64, but these behave like a query-by-query call in every respect: outputs
+ *      of ivf_search_device are complete in stream order, bytes_gpu counts every query's clusters,
+ *      and a call under stream capture is enqueued query by query.  Anything else query by query
  *   1  always query by query
  *   2  list-major from 2 queries on; IVF_ESTATE (and the mode stays) when the index has no
  *      list-major path

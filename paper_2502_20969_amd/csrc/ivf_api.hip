@@ -175,6 +175,7 @@ struct ivf_index {
     std::vector<uint64_t> rows_desc_prefix;   // prefix sums of list sizes, largest first
     int resident_grid[2] = {0, 0};            // scan workgroups resident at once, for kprime <= 64 / > 64
     int batched_grid = 0;                     // resident workgroups of the batched scan kernel
+    bool any_width_off = false;               // no memory for the list-major workspace of any_width_eligible batches
     int batch_mode = 0;                       // 0 auto, 1 always query by query, 2 list-major when eligible
     unsigned int* d_row_norm_max = nullptr;   // largest squared row norm (float bits); device placement
     float* d_row_norm = nullptr;              // squared norm of every row; device placement with squared L2
@@ -540,13 +541,40 @@ int enqueue_redo(ivf_index* ix, const float* q_dev, int nq, int nprobe, int k, i
 // ---- batched (list-major) search ----------------------------------------------------------------
 constexpr int kCandCap = 65536;          // candidates a query may collect in the batched scan
 
-bool batched_eligible(const ivf_index* ix, int nq) {
-    if (ix->batch_mode == 1 || nq < 2) return false;
+// rows that the list-major scan can read: all in HBM, with what it needs to know of their norms
+bool has_list_major(const ivf_index* ix) {
     if (ix->placement != IVF_PLACE_DEVICE || !ix->d_row_norm_max || ix->n >= (int64_t)1 << 32) return false;
     if (ix->metric != IVF_IP && !ix->d_row_norm) return false;
-    if (ix->d % 64 != 0) return false;                          // the MFMA kernels walk whole blocks of elements
-    if (batched_scan_lds(ix->d, ix->dtype) > ix->max_lds) return false;    // a group's queries must fit LDS
-    return ix->batch_mode == 2 || nq >= 4;
+    return batched_scan_lds(ix->d, ix->dtype) <= ix->max_lds;              // a group's queries must fit LDS
+}
+
+bool batched_eligible(const ivf_index* ix, int nq) {
+    if (ix->batch_mode == 1 || nq < 2 || ix->d % 64 != 0) return false;
+    return has_list_major(ix) && (ix->batch_mode == 2 || nq >= 4);
+}
+
+// Whether a batch is large enough for the launches in front of a list-major scan (sample, tasks: 20 to 25
+// us) to pay.  A query-by-query scan of clusters of mean size runs at about 4.8 TB/s and at most 10
+// rows a nanosecond; below 40 us of that it is the faster way, or within a few us of it.  Whole calls, us,
+// list-major / query by query, with that estimate: 17 queries x 5 clusters of 355 bf16 (2 us) 82 / 59, 27 x 7
+// of 743 fp32 (27) 100 / 67, 9 x 40 of 687 fp32 (31) 87 / 60, 6 x 113 of 598 fp32 (38) 122 / 99, 12 x 39 of 47
+// fp32 (46) 92 / 130, 48 x 24 of 100 fp32 (96) 114 / 123, 53 x 58 of 78 fp32 (147) 125 / 182, 250 x 53
+// of 731 bf16 (520) 244 / 809.  Few queries share little: 5 x 206 of 53 bf16 (110) 114 / 104.
+bool worth_list_major(const ivf_index* ix, int nq, int nprobe) {
+    const double rows = (double)ix->n / ix->nlist * nprobe * nq;
+    const double us = std::max(rows * (double)ix->row_bytes / 4.8e6, rows / 1e4);
+    return us >= (nq < 8 ? 120.0 : 40.0);
+}
+
+// Batches of automatic mode over rows that are not whole blocks of 64 elements are searched list-major
+// too, completed on the stream by the exact pass (enqueue_any_width), so that they keep what the
+// query-by-query path promises them: outputs complete in stream order.  Not while the stream is
+// being captured, where their workspace could not be sized.
+bool any_width_eligible(const ivf_index* ix, int nq, int nprobe, hipStream_t stream) {
+    if (ix->batch_mode != 0 || nq < 4 || ix->d % 64 == 0 || ix->any_width_off) return false;
+    if (ix->row_bytes < 16 || !has_list_major(ix) || !worth_list_major(ix, nq, nprobe)) return false;
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    return hipStreamIsCapturing(stream, &st) == hipSuccess && st == hipStreamCaptureStatusNone;
 }
 
 int ensure_batched_workspace(ivf_index* ix, int nq, int nprobe) {
@@ -584,6 +612,18 @@ int ensure_batched_workspace(ivf_index* ix, int nq, int nprobe) {
     return IVF_OK;
 }
 
+// The workspaces of an any_width_eligible batch; false when there is no memory for the list-major one (the
+// batch is then searched query by query, and so are later ones).
+bool any_width_workspace(ivf_index* ix, int nq, int nprobe, int k, int* rc) {
+    if ((*rc = ensure_workspace(ix, nq, nprobe, k))) return false;
+    const int r = ensure_batched_workspace(ix, nq, nprobe);
+    if (r == IVF_OK) return true;
+    (void)hipGetLastError();
+    if (r == IVF_ENOMEM) ix->any_width_off = true;
+    else *rc = r;
+    return false;
+}
+
 // the parts of the batched scan's arguments that do not depend on the call
 static void fill_batched_args(const ivf_index* ix, const Workspace& w, BatchedArgs& b) {
     b.lists = ix->d_buf; b.off = ix->d_off; b.ids = ix->d_ids; b.probe = w.d_probe; b.rprefix = w.slots.rprefix;
@@ -604,7 +644,9 @@ static void fill_batched_args(const ivf_index* ix, const Workspace& w, BatchedAr
 
 // coarse + select for the batch, then the list-major scan and the final ranking into (out_ids,
 // out_dists) (as the device addresses them); the overflow flags land in the workspace's pinned array
-int enqueue_batched(ivf_index* ix, const float* q_dev, int nq, int nprobe, int k, int64_t* out_ids, float* out_dists) {
+// with_redo: the merge also marks the queries that overflowed for an exact pass on the device (enqueue_redo)
+int enqueue_batched(ivf_index* ix, const float* q_dev, int nq, int nprobe, int k, int64_t* out_ids, float* out_dists,
+                    bool with_redo = false) {
     Workspace& w = *ix->cw;
     int rc;
     if ((rc = enqueue_probe(ix, q_dev, nq, nprobe, 1, false, true))) return rc;
@@ -613,6 +655,7 @@ int enqueue_batched(ivf_index* ix, const float* q_dev, int nq, int nprobe, int k
     fill_batched_args(ix, w, b);
     b.q = q_dev; b.out_ids = out_ids; b.out_dists = out_dists;
     b.rows_counter = ix->profiling ? ix->d_prof_rows : nullptr;
+    if (with_redo) { b.redo_flag = w.d_redo_flag; b.redo_thr = w.d_redo_thr; b.redo_ticket = w.d_redo_ticket; }
     b.nq = nq; b.nprobe = nprobe; b.k = k; b.kprime = kprime_for(k);
     hipEvent_t e0, e1, m0, m1;
     if ((rc = prof_events(ix, 2, &e0, &e1))) return rc;
@@ -867,6 +910,7 @@ extern "C" int ivf_reserve(ivf_index* ix, int32_t nq, int32_t nprobe, int32_t k)
     for (size_t i = 0; i < ix->lanes.size(); ++i) {
         use_lane(ix, i);
         int rc = ensure_workspace(ix, nq, std::min(nprobe, ix->nlist), k);
+        if (!rc && any_width_eligible(ix, nq, nprobe, ix->cs)) (void)any_width_workspace(ix, nq, std::min(nprobe, ix->nlist), k, &rc);
         if (rc) { use_lane(ix, 0); return rc; }
     }
     use_lane(ix, 0);
@@ -1000,7 +1044,10 @@ extern "C" int ivf_search_device(ivf_index* ix, const float* q_dev, int32_t nq, 
     ix->lanes[lane].quiet = false;
     ix->next_lane = (ix->next_lane + 1) % ix->lanes.size();
     if (batched_eligible(ix, nq)) rc = run_batched(ix, lane, q_dev, nq, nprobe, k, ids_dev, dists_dev, true);
-    else {
+    else if (any_width_eligible(ix, nq, nprobe, ix->cs) && any_width_workspace(ix, nq, nprobe, k, &rc)) {
+        rc = enqueue_batched(ix, q_dev, nq, nprobe, k, ids_dev, dists_dev, true);
+        if (rc == IVF_OK) rc = enqueue_redo(ix, q_dev, nq, nprobe, k, kprime_for(k), false, ids_dev, dists_dev);
+    } else if (rc == IVF_OK) {
         // one stream: the exact second pass follows every merge on the stream, outputs are complete in
         // stream order.  Several: it is decided when the lane is next needed or in ivf_synchronize.
         const bool lazy = ix->lanes.size() > 1;
@@ -1128,6 +1175,27 @@ extern "C" int ivf_search(ivf_index* ix, const float* q_out, int32_t nq, int32_t
         }
         return IVF_OK;
     }
+    if (any_width_eligible(ix, nq, nprobe, ix->cs) && any_width_workspace(ix, nq, nprobe, k, &rc)) {
+        if ((rc = enqueue_batched(ix, w.d_q, nq, nprobe, k, w.hd_out_ids, w.hd_out_dists, true))) return rc;
+        if (stats) HIP_TRY(hipMemcpyAsync(w.h_probe, w.d_probe, (size_t)nq * nprobe * sizeof(int32_t), hipMemcpyDeviceToHost, ix->cs));
+        HIP_TRY(hipStreamSynchronize(ix->cs));
+        for (int qi = 0; qi < nq; ++qi) st.n_exact_gpu += w.h_overflow[qi] != 0 ? 1 : 0;
+        if (st.n_exact_gpu) {
+            if ((rc = enqueue_redo(ix, w.d_q, nq, nprobe, k, kprime, false, w.hd_out_ids, w.hd_out_dists))) return rc;
+            HIP_TRY(hipStreamSynchronize(ix->cs));
+        }
+        memcpy(ids, w.h_out_ids, (size_t)nq * k * sizeof(int64_t));
+        memcpy(dists, w.h_out_dists, (size_t)nq * k * sizeof(float));
+        if (stats) {
+            for (size_t i = 0; i < (size_t)nq * nprobe; ++i)
+                st.bytes_gpu += (uint64_t)(ix->h_off[w.h_probe[i] + 1] - ix->h_off[w.h_probe[i]]) * ix->row_bytes;
+            st.n_probed = nq * nprobe; st.n_overlap = nq * nprobe; st.hit_rate = 1.f;
+            st.ms_total = (float)(now_ms() - t0);
+            *stats = st;
+        }
+        return IVF_OK;
+    }
+    if (rc) return rc;
     if (hybrid && ix->pf_recorded) HIP_TRY(hipStreamWaitEvent(ix->cs, ix->ev_pf_done, 0));
     if ((rc = enqueue_probe(ix, w.d_q, nq, nprobe, grid, true, true))) return rc;
     const bool want_probe = hybrid || stats;

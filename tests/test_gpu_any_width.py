@@ -1,0 +1,170 @@
+"""List-major batches over rows of any width (automatic mode, rows that are not whole blocks of 64
+elements): bit-equal to the query-by-query path, complete in stream order."""
+import numpy as np
+import pytest
+import torch
+
+import oracle as O
+import paper_2502_20969_amd as P
+from parity import check_topk, stored
+
+pytestmark = pytest.mark.gpu
+TORCH = {"f32": torch.float32, "f16": torch.float16, "bf16": torch.bfloat16}
+METRIC = {"ip": (P.IVF_IP, O.IP), "l2": (P.IVF_L2, O.L2)}
+
+
+def _problem(seed, dtype, n, d, nlist, nq, spread, scale=1.0):
+    """Rows around nlist centres in uneven lists (one of them empty), queries around `spread` of the centres."""
+    rng = np.random.default_rng(seed)
+    cent = rng.standard_normal((nlist, d)).astype(np.float32)
+    w = rng.uniform(0.3, 1.7, nlist)
+    w[nlist // 2] = 0.0
+    sizes = np.floor(w / w.sum() * n).astype(np.int64)
+    sizes[0] += n - sizes.sum()
+    off = np.concatenate([[0], np.cumsum(sizes)])
+    rows = np.repeat(cent, sizes, 0) + 0.5 * rng.standard_normal((n, d)).astype(np.float32)
+    q = cent[rng.integers(0, spread, nq)] + 0.3 * rng.standard_normal((nq, d)).astype(np.float32)
+    dev = torch.from_numpy((rows * scale).astype(np.float32)).to(TORCH[dtype]).cuda()
+    return dev, off, (cent * scale).astype(np.float32), (q * scale).astype(np.float32)
+
+
+def _adopt(rows, dtype, off, cent, metric, ids=None):
+    return P.ivf_adopt_layout(rows, dtype, off, cent, ids=ids, metric=METRIC[metric][0],
+                              compute_stream=torch.cuda.Stream(), copy_stream=torch.cuda.Stream())
+
+
+def _rows_scanned(index, q, nprobe, k):
+    """Results of a host call, and the rows its scan read (list-major: each selected cluster once)."""
+    index.ivf_profile_enable(True)
+    index.ivf_profile_reset()
+    out = index.ivf_search(q, nprobe, k)
+    read = index.ivf_profile_read().scan_rows
+    index.ivf_profile_enable(False)
+    return out, read
+
+
+# widths around the pieces (32 fp32, 64 two-byte elements), the 16-byte chunks, the two stages in flight and the
+# width up to which the queries of the whole batch stay in LDS; groups of 1 to more than 32 queries per cluster
+@pytest.mark.parametrize("dtype,d,nq,spread,metric,k", [
+    ("f32", 4, 40, 7, "ip", 5), ("f32", 5, 48, 2, "l2", 3), ("f32", 31, 40, 7, "ip", 10), ("f32", 33, 43, 1, "l2", 7),
+    ("f32", 95, 40, 3, "ip", 1), ("f32", 97, 64, 7, "ip", 33), ("f32", 100, 40, 7, "l2", 20), ("f32", 200, 70, 1, "ip", 100),
+    ("f32", 255, 40, 4, "ip", 8), ("f32", 257, 40, 7, "l2", 8), ("f32", 415, 41, 2, "ip", 10), ("f32", 1001, 40, 7, "ip", 4),
+    ("f16", 8, 40, 7, "ip", 5), ("f16", 9, 50, 1, "l2", 3), ("f16", 63, 40, 7, "ip", 10), ("f16", 65, 75, 2, "l2", 12),
+    ("f16", 129, 40, 1, "ip", 112), ("f16", 300, 48, 7, "l2", 10), ("f16", 511, 40, 3, "ip", 9), ("f16", 1003, 40, 7, "ip", 2),
+    ("bf16", 10, 64, 7, "ip", 6), ("bf16", 71, 40, 1, "ip", 56), ("bf16", 104, 44, 7, "l2", 10), ("bf16", 250, 90, 2, "ip", 30),
+    ("bf16", 513, 40, 7, "l2", 5), ("bf16", 760, 40, 5, "ip", 10),
+])
+def test_list_major_of_any_width_equals_query_by_query(dtype, d, nq, spread, metric, k):
+    n, nlist, nprobe = 24000, 8, 5
+    rows, off, cent, q = _problem(d * 7 + nq, dtype, n, d, nlist, nq, spread)
+    ids = np.random.default_rng(d).permutation(n).astype(np.int64) * 3 + 1
+    index = _adopt(rows, dtype, off, cent, metric, ids)
+    (gi, gd), read = _rows_scanned(index, q, nprobe, k)
+    assert 0 < read <= n                                     # list-major: no cluster more than once
+    q_dev = torch.from_numpy(q).cuda()
+    di, dd = torch.empty(nq, k, dtype=torch.int64, device="cuda"), torch.empty(nq, k, device="cuda")
+    torch.cuda.synchronize()
+    index.ivf_search_device(q_dev, nprobe, k, di, dd)
+    torch.cuda.synchronize()                                 # stream order is enough: no ivf_synchronize
+    index.ivf_set_batch_mode(1)
+    (pi, pd), read = _rows_scanned(index, q, nprobe, k)
+    assert read > n
+    assert np.array_equal(gi, pi) and np.array_equal(gd, pd)
+    assert np.array_equal(di.cpu().numpy(), pi) and np.array_equal(dd.cpu().numpy(), pd)
+    lists = rows.cpu().numpy() if dtype != "bf16" else rows.cpu().view(torch.int16).numpy().view(np.uint16)
+    odt = {"f32": O.F32, "f16": O.F16, "bf16": O.BF16}[dtype]
+    for b in (0, nq - 1):
+        assert check_topk(gi[b], gd[b], lists, odt, off, ids, cent, q[b], nprobe, k, METRIC[metric][1]) == 0
+    # the second mode is still refused for such rows
+    with pytest.raises(P.IvfError):
+        index.ivf_set_batch_mode(2)
+    index.close()
+
+
+@pytest.mark.parametrize("dtype,d", [("f32", 100), ("f32", 128), ("f16", 100), ("f16", 128), ("bf16", 72), ("bf16", 128)])
+@pytest.mark.parametrize("kind", ["inf", "nan", "beyond", "tiny", "zero"])
+@pytest.mark.parametrize("metric", ["ip", "l2"])
+def test_values_without_an_error_bound(dtype, d, kind, metric):
+    """Infinities, no numbers, queries beyond the storage type, squares that underflow: the filter's bound
+    says nothing there, the results are those of the query-by-query path all the same."""
+    nq, nprobe, k, n = 64, 5, 10, 24000
+    scale = {"tiny": {"f16": 1e-6, "bf16": 1e-19, "f32": 1e-19}[dtype]}.get(kind, 1.0)
+    rows, off, cent, q = _problem(3, dtype, n, d, 8, nq, 7, scale)
+    if kind == "inf":
+        rows[5, d - 1] = float("inf"); rows[17, 0] = float("-inf"); rows[n - 1, d // 2] = float("inf")
+    elif kind == "nan":
+        rows[6, d - 1] = float("nan"); rows[7, 0] = float("nan"); rows[n - 1, d - 1] = float("nan")
+    elif kind == "beyond":
+        q[3] *= 1e6; q[5] *= 1e19
+    elif kind == "zero":
+        q[0] = 0.0; q[9] = 0.0; rows[::3] = 0
+    index = _adopt(rows, dtype, off, cent, metric)
+    gi, gd = index.ivf_search(q, nprobe, k)
+    q_dev = torch.from_numpy(q).cuda()
+    di, dd = torch.empty(nq, k, dtype=torch.int64, device="cuda"), torch.empty(nq, k, device="cuda")
+    torch.cuda.synchronize()
+    index.ivf_search_device(q_dev, nprobe, k, di, dd)
+    if d % 64 == 0:
+        index.ivf_synchronize()
+    torch.cuda.synchronize()
+    index.ivf_set_batch_mode(1)
+    pi, pd = index.ivf_search(q, nprobe, k)
+    assert np.array_equal(gi, pi) and np.array_equal(gd, pd, equal_nan=True)
+    assert np.array_equal(di.cpu().numpy(), pi) and np.array_equal(dd.cpu().numpy(), pd, equal_nan=True)
+    index.close()
+
+
+@pytest.mark.parametrize("depth", [1, 3])
+def test_overflowing_queries_are_finished_on_the_stream(depth):
+    """More identical rows than a candidate list holds: the exact pass behind the merge answers, on the
+    same stream (depth 1: without ivf_synchronize), for every batch in flight."""
+    n, d, nlist, nq, nprobe, k = 120000, 72, 4, 12, 3, 7
+    rng = np.random.default_rng(5)
+    rows_np = rng.standard_normal((n, d)).astype(np.float16)
+    rows_np[:90000] = np.float16(0.125)
+    off = np.arange(0, n + 1, n // nlist, dtype=np.int64)
+    cent = rng.standard_normal((nlist, d)).astype(np.float32)
+    cent[0], cent[1], cent[2] = 1.0, 0.9, 0.8
+    ids = rng.permutation(n).astype(np.int64)
+    index = _adopt(torch.from_numpy(rows_np).cuda(), "f16", off, cent, "ip", ids)
+    index.ivf_set_pipeline_depth(depth)
+    qs = [torch.from_numpy(np.abs(rng.standard_normal((nq, d))).astype(np.float32)).cuda() for _ in range(4)]
+    for q in qs[1::2]:
+        q[::2] *= -1.0                                       # these select the list of different rows first
+    outs = [(torch.empty(nq, k, dtype=torch.int64, device="cuda"), torch.empty(nq, k, device="cuda")) for _ in qs]
+    torch.cuda.synchronize()
+    for q, (i, s) in zip(qs, outs):
+        index.ivf_search_device(q, nprobe, k, i, s)
+    if depth > 1:
+        index.ivf_synchronize()
+    torch.cuda.synchronize()
+    index.ivf_set_pipeline_depth(1)
+    index.ivf_set_batch_mode(1)
+    for q, (i, s) in zip(qs, outs):
+        pi, pd = index.ivf_search(q.cpu().numpy(), nprobe, k)
+        assert np.array_equal(i.cpu().numpy(), pi) and np.array_equal(s.cpu().numpy(), pd)
+    index.close()
+
+
+def test_reserved_batch_can_be_captured():
+    """After ivf_reserve a batch allocates nothing and can be captured; every replay gives the eager result."""
+    n, d, nq, nprobe, k = 24000, 100, 48, 5, 10
+    rows, off, cent, q = _problem(8, "f32", n, d, 8, nq, 7)
+    stream = torch.cuda.Stream()
+    index = P.ivf_adopt_layout(rows, "f32", off, cent, metric=P.IVF_IP, compute_stream=stream, copy_stream=torch.cuda.Stream())
+    index.ivf_reserve(nq, nprobe, k)
+    want_i, want_d = index.ivf_search(q, nprobe, k)
+    q_dev = torch.from_numpy(q).cuda()
+    di, dd = torch.empty(nq, k, dtype=torch.int64, device="cuda"), torch.empty(nq, k, device="cuda")
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=stream):
+        index.ivf_search_device(q_dev, nprobe, k, di, dd)
+    for _ in range(3):
+        di.zero_(); dd.zero_()
+        torch.cuda.synchronize()
+        graph.replay()
+        torch.cuda.synchronize()
+        assert np.array_equal(di.cpu().numpy(), want_i) and np.array_equal(dd.cpu().numpy(), want_d)
+        index.ivf_search(q, nprobe, k)                       # eager work between the replays
+    index.close()
