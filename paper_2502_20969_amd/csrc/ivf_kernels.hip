@@ -6,6 +6,7 @@
 #include "../../include/ivf.h"
 #include <hip/hip_ext.h>
 #include <algorithm>
+#include <type_traits>
 
 namespace ivf {
 using namespace dev;
@@ -19,7 +20,8 @@ using namespace dev;
 // at once; HBM-bound on the nlist*d*4 bytes of the centroid matrix, in practice one memory
 // latency.  A batch of queries: a dense contraction Q x C^T on the fp64 matrix cores.
 // =============================================================================================
-// The row kernel walks the queries one after the other; measured against the matrix cores (us): 3
+// Sums per pair of query and centroid, by the vector units; measured against the matrix cores (us; the row kernel
+// walked the queries one after the other then): 3
 // queries x 4096 x 768 7.4 / 6.2, x 1024 x 768 5.2 / 5.9, x 1024 x 2048 7.5 / 10.4, x 32768 x 1024 41 / 35;
 // 4 x 1024 x 768 6.4 / 6.2, x 1024 x 2048 9.2 / 10.4; 5 x 1024 x 2048 10.8 / 10.4; 8 x 4096 x 768 15 / 6.4.  So
 // it takes 3 and 4 queries of few centroids and wide rows (a wavefront of the matrix kernel then has a
@@ -30,17 +32,33 @@ static bool coarse_by_rows(const CoarseArgs& a) {
     if (a.metric != 0) return a.nq < 16 || (a.d & 3) != 0;
     return a.nq < 3 || (a.nq <= 4 && a.nq * 256 <= a.d && a.nlist <= 2048);
 }
+// queries per wavefront of the row kernel (at most 65535 workgroups side by side in the grid's second direction)
+constexpr int kCoarseRowWaves = 8192;
+static int coarse_rows_queries(const CoarseArgs& a) {
+    const int64_t per = std::max(((int64_t)a.nq * a.nlist + kCoarseRowWaves - 1) / kCoarseRowWaves, ((int64_t)a.nq + 65534) / 65535);
+    return (int)std::min<int64_t>(per, a.nq);
+}
+// From this many pairs on the row kernel's batches go four by four (coarse_pairs_kernel).  Squared L2, us, one pair at a
+// time / four by four: 8 queries x 1000 x 100 5.1 / 5.2, 15 x 300 x 64 4.3 / 5.4, 15 x 1024 x 768 9.0 / 8.2, 4 x 4096 x
+// 768 8.7 / 7.9, 143 x 307 x 265 17.8 / 14.3, 36 x 1740 x 42 17.4 / 8.8, 37 x 3819 x 158 38 / 17, 4 x 65536 x 65
+// 57 / 23, 256 x 8192 x 747 785 / 356.
+constexpr int64_t kPairsMin = 12288;
+constexpr int kPairTile = 4;
+constexpr int64_t kCoarsePairWgs = 2048;         // workgroups of that kernel; more pairs make their walks longer
+static bool coarse_in_pairs(const CoarseArgs& a) { return a.d >= 4 && a.nq >= 3 && (int64_t)a.nq * a.nlist >= kPairsMin; }
 constexpr int kSelectWaveSortMax = 4096;   // select: register sorting path up to this many clusters
 
 // RAGGED: d is no multiple of 4, rows start at any element.
+// A wavefront takes one centroid for `per` queries, one after the other: as few as still make no more
+// wavefronts than the chip holds at once.  What bounds it is the length of that chain.
 template <bool RAGGED>
-__global__ __launch_bounds__(256) void coarse_rows_kernel(CoarseArgs a) {
+__global__ __launch_bounds__(256) void coarse_rows_kernel(CoarseArgs a, int per) {
     const int lane = lane_id(), wave = wave_id();
     const int row = blockIdx.x * 4 + wave;
     if (row >= a.nlist) return;
     const float* c = a.centroids + (size_t)row * a.d;
 #pragma unroll 1
-    for (int qi = 0; qi < a.nq; ++qi) {
+    for (int qi = (int)blockIdx.y * per; qi < min(a.nq, ((int)blockIdx.y + 1) * per); ++qi) {
         const float* q = a.q + (size_t)qi * a.d;
         double acc = 0.0;
         if (!RAGGED || a.d >= 4) {
@@ -80,6 +98,77 @@ __global__ __launch_bounds__(256) void coarse_rows_kernel(CoarseArgs a) {
         }
         const double s = wave_sum(acc);
         if (lane == 0) a.scores[(size_t)qi * a.nlist + row] = s;
+    }
+}
+
+// The same sums, four centroids by four queries to a wavefront: for batches, where one pair at a time is bound by
+// the rows' way from the caches (two rows per pair; here half a row) and by the wavefront's sum.  A
+// pair's products are added in the order of the row kernel and the lanes' sums by the same
+// butterfly, which hands the halves of the sixteen values on as it goes: bit for bit the same scores.
+template <bool RAGGED>
+__global__ __launch_bounds__(256) void coarse_pairs_kernel(CoarseArgs a, int per) {
+    constexpr int T = kPairTile;
+    const int lane = lane_id(), c0 = (int)(blockIdx.x * 4 + wave_id()) * T;
+    if (c0 >= a.nlist) return;
+    const int q_tiles = (a.nq + T - 1) / T;
+    const float* crow[T];
+#pragma unroll
+    for (int i = 0; i < T; ++i) crow[i] = a.centroids + (size_t)min(c0 + i, a.nlist - 1) * a.d;
+#pragma unroll 1
+    for (int g = (int)blockIdx.y * per; g < min(q_tiles, ((int)blockIdx.y + 1) * per); ++g) {
+        const float* qrow[T];
+#pragma unroll
+        for (int j = 0; j < T; ++j) qrow[j] = a.q + (size_t)min(g * T + j, a.nq - 1) * a.d;
+        double acc[T * T];
+#pragma unroll
+        for (int p = 0; p < T * T; ++p) acc[p] = 0.0;
+#pragma unroll 2
+        for (int t0 = lane * 4; t0 < a.d; t0 += 256) {
+            const int t = RAGGED ? min(t0, a.d - 4) : t0, skip = t0 - t;      // as in the row kernel
+            float4 cv[T], qv[T];
+#pragma unroll
+            for (int i = 0; i < T; ++i) cv[i] = RAGGED ? load_float4_any(crow[i] + t) : *(const float4*)(crow[i] + t);
+#pragma unroll
+            for (int j = 0; j < T; ++j) qv[j] = RAGGED ? load_float4_any(qrow[j] + t) : *(const float4*)(qrow[j] + t);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) {
+                const bool out = RAGGED && e < skip;
+                double x[T], y[T];
+#pragma unroll
+                for (int i = 0; i < T; ++i) {
+                    const float ce = e == 0 ? cv[i].x : e == 1 ? cv[i].y : e == 2 ? cv[i].z : cv[i].w;
+                    const float qe = e == 0 ? qv[i].x : e == 1 ? qv[i].y : e == 2 ? qv[i].z : qv[i].w;
+                    y[i] = out ? 0.0 : (double)ce;
+                    x[i] = out ? 0.0 : (double)qe;
+                }
+#pragma unroll
+                for (int i = 0; i < T; ++i)
+#pragma unroll
+                    for (int j = 0; j < T; ++j) {
+                        if (a.metric == 0) acc[i * T + j] = fma(x[j], y[i], acc[i * T + j]);
+                        else { const double df = x[j] - y[i]; acc[i * T + j] = fma(df, df, acc[i * T + j]); }
+                    }
+            }
+        }
+        // lane l ends with pair l / 4
+        auto halve = [&](auto size, int m) {
+            constexpr int n = decltype(size)::value;
+            const bool upper = (lane & m) != 0;
+#pragma unroll
+            for (int p = 0; p < n; ++p) {
+                const double keep = upper ? acc[p + n] : acc[p], give = upper ? acc[p] : acc[p + n];
+                acc[p] = keep + __shfl_xor(give, m);
+            }
+        };
+        halve(std::integral_constant<int, 8>{}, 32);
+        halve(std::integral_constant<int, 4>{}, 16);
+        halve(std::integral_constant<int, 2>{}, 8);
+        halve(std::integral_constant<int, 1>{}, 4);
+        double s = acc[0];
+        s += __shfl_xor(s, 2);
+        s += __shfl_xor(s, 1);
+        const int i = lane >> 4, j = (lane >> 2) & 3;
+        if ((lane & 3) == 0 && c0 + i < a.nlist && g * T + j < a.nq) a.scores[(size_t)(g * T + j) * a.nlist + c0 + i] = s;
     }
 }
 
@@ -254,8 +343,18 @@ static void launch_coarse_mfma(const CoarseArgs& a, hipStream_t s, hipEvent_t e0
 
 hipError_t launch_coarse(const CoarseArgs& a, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
     if (coarse_by_rows(a)) {
-        if (a.d & 3) IVF_LAUNCH(coarse_rows_kernel<true>, dim3((a.nlist + 3) / 4), dim3(256), 0, s, e0, e1, a);
-        else IVF_LAUNCH(coarse_rows_kernel<false>, dim3((a.nlist + 3) / 4), dim3(256), 0, s, e0, e1, a);
+        if (coarse_in_pairs(a)) {
+            const int c_wgs = (a.nlist + 4 * kPairTile - 1) / (4 * kPairTile), q_tiles = (a.nq + kPairTile - 1) / kPairTile;
+            const int per = (int)std::min<int64_t>(std::max<int64_t>(((int64_t)q_tiles * c_wgs + kCoarsePairWgs - 1) / kCoarsePairWgs, (q_tiles + 65534) / 65535), q_tiles);
+            const dim3 grid((unsigned)c_wgs, (unsigned)((q_tiles + per - 1) / per));
+            if (a.d & 3) IVF_LAUNCH(coarse_pairs_kernel<true>, grid, dim3(256), 0, s, e0, e1, a, per);
+            else IVF_LAUNCH(coarse_pairs_kernel<false>, grid, dim3(256), 0, s, e0, e1, a, per);
+            return hipGetLastError();
+        }
+        const int per = coarse_rows_queries(a);
+        const dim3 grid((unsigned)(a.nlist + 3) / 4, (unsigned)((a.nq + per - 1) / per));
+        if (a.d & 3) IVF_LAUNCH(coarse_rows_kernel<true>, grid, dim3(256), 0, s, e0, e1, a, per);
+        else IVF_LAUNCH(coarse_rows_kernel<false>, grid, dim3(256), 0, s, e0, e1, a, per);
     } else {
         // Small tiles while they leave the chip short of work, measured with 1024, 4096 and 8192 lists:
         // 512 of them 12.9, 12.6, 14.3 us against 15.7, 16.1, 19.1 of the large ones; 768: 16.0 against

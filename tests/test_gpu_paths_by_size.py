@@ -363,3 +363,23 @@ def test_filter_scores_do_not_depend_on_earlier_searches(streams, nq):
         s64 = q.astype(np.float64) @ rows[assign == c].astype(np.float64).T
         assert (np.abs(fresh[c][0] - s64) <= fresh[c][1][:, None]).all()
     index.close()
+
+
+@pytest.mark.parametrize("nq,nlist,d", [(3, 4096, 4), (3, 4097, 5), (4, 3073, 7), (5, 2460, 255), (15, 820, 256), (15, 819, 257), (15, 5000, 1028),
+                                        (16, 769, 259), (63, 200, 513), (130, 1037, 102), (300, 9001, 30)])
+def test_coarse_scores_four_by_four(streams, nq, nlist, d):
+    """Squared L2 that the matrix cores do not take: from 12,288 pairs of query and centroid on, four by
+    four.  The scores are sums of squared differences in fp64, the same bit for bit as of single queries (which
+    are never taken four by four); edges of the tiles, of the chunks and of rows that are no multiple of 4."""
+    rng = np.random.default_rng(nq + d)
+    cent = rng.standard_normal((nlist, d)).astype(np.float32)
+    q = rng.standard_normal((nq, d)).astype(np.float32)
+    q[nq // 2] = cent[nlist // 3]
+    index = P.ivf_adopt_layout(torch.zeros(nlist, d, device="cuda"), "f32", np.arange(nlist + 1), cent, metric=P.IVF_L2,
+                               compute_stream=streams[0], copy_stream=streams[1])
+    got = index.ivf_coarse_scores(q)
+    for b in {0, 1, nq // 2, nq - 1}:
+        assert np.array_equal(got[b], index.ivf_coarse_scores(q[b:b + 1])[0])
+        want = ((q[b].astype(np.float64) - cent.astype(np.float64)) ** 2).sum(1)
+        np.testing.assert_allclose(got[b], want, rtol=1e-12)
+    index.close()
