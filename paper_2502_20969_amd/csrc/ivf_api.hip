@@ -168,6 +168,11 @@ struct ivf_index {
     bool own_h_lists = false;
     std::vector<int64_t> h_res_off; // host mirror of d_res_off
     int64_t* h_res_stage = nullptr; // pinned copy used as the source of the table upload
+    MoveDesc* h_fetch = nullptr;    // pinned [nlist]: the lists of a prefetch, staged to d_fetch
+    MoveDesc* hd_fetch = nullptr;   // ... as the device addresses it
+    MoveDesc* d_fetch = nullptr;
+    hipEvent_t ev_fetch = nullptr;  // h_fetch has been staged
+    bool fetch_recorded = false;
     size_t buf_used = 0;
     hipEvent_t ev_pf_begin = nullptr, ev_pf_done = nullptr, ev_probe = nullptr, ev_pf_table = nullptr;
     bool pf_recorded = false;
@@ -722,6 +727,10 @@ int finish_tables(ivf_index* ix, size_t device_buffer_bytes) {
         if (device_buffer_bytes > 0) HIP_TRY(hipMalloc(&ix->d_buf, device_buffer_bytes));
         ix->own_buf = true;
         HIP_TRY(hipHostMalloc(&ix->h_res_stage, (size_t)nlist * sizeof(int64_t)));
+        HIP_TRY(hipHostMalloc(&ix->h_fetch, (size_t)nlist * sizeof(MoveDesc)));
+        HIP_TRY(hipHostGetDevicePointer((void**)&ix->hd_fetch, ix->h_fetch, 0));
+        HIP_TRY(hipMalloc(&ix->d_fetch, (size_t)nlist * sizeof(MoveDesc)));
+        HIP_TRY(hipEventCreateWithFlags(&ix->ev_fetch, hipEventDisableTiming));
         unsigned hw = std::thread::hardware_concurrency();
         int nt = hw == 0 ? 8 : (int)std::min(hw, 64u);
         ix->pool.reset(new ThreadPool(nt));
@@ -787,6 +796,8 @@ extern "C" void ivf_free(ivf_index* ix) {
     if (ix->own_buf) dfree(ix->d_buf);
     if (ix->own_h_lists) hfree(ix->h_lists);
     hfree(ix->h_res_stage);
+    hfree(ix->h_fetch); dfree(ix->d_fetch);
+    if (ix->ev_fetch) (void)hipEventDestroy(ix->ev_fetch);
     if (ix->ev_pf_begin) (void)hipEventDestroy(ix->ev_pf_begin);
     if (ix->ev_pf_done) (void)hipEventDestroy(ix->ev_pf_done);
     if (ix->ev_probe) (void)hipEventDestroy(ix->ev_probe);
@@ -1293,6 +1304,27 @@ extern "C" int ivf_prefetch_amount(double bandwidth, double t_llm, int32_t nprob
     return IVF_OK;
 }
 
+// The device address of the host lists when all of them lie in one pinned allocation, else nullptr (memory
+// that was never pinned is copied by the runtime).  Asked for at every prefetch: a kernel that reads
+// memory which is no longer pinned faults.
+static const void* lists_on_device(const ivf_index* ix) {
+    const size_t bytes = (size_t)ix->n * ix->row_bytes;
+    void *dev = nullptr, *start = nullptr;
+    size_t size = 0;
+    hipPointerAttribute_t at{};
+    const bool ok = hipPointerGetAttributes(&at, ix->h_lists) == hipSuccess && at.type == hipMemoryTypeHost && at.devicePointer &&
+                    hipPointerGetAttribute(&start, HIP_POINTER_ATTRIBUTE_RANGE_START_ADDR, (hipDeviceptr_t)at.devicePointer) == hipSuccess &&
+                    hipPointerGetAttribute(&size, HIP_POINTER_ATTRIBUTE_RANGE_SIZE, (hipDeviceptr_t)at.devicePointer) == hipSuccess;
+    if (ok && (uintptr_t)at.devicePointer >= (uintptr_t)start && (uintptr_t)at.devicePointer + bytes <= (uintptr_t)start + size) dev = at.devicePointer;
+    (void)hipGetLastError();
+    return dev;
+}
+
+// Lists of up to this mean size are fetched by a kernel (57 GB/s; the copy engine, one copy per list: 23 GB/s for
+// 0.39 MB each, 46 for 2.4, 54 for 4.7).  Larger ones keep the copy engine busy by themselves and leave every
+// compute unit to what runs beside the prefetch.
+constexpr size_t kFetchMeanBytes = (size_t)4 << 20;
+
 extern "C" int ivf_prefetch(ivf_index* ix, const float* q_in, int32_t nq, int32_t nprobe,
                             size_t budget_bytes, uint32_t flags, ivf_prefetch_stats* stats) {
     int rc = check_query_args(ix, q_in, nq, nprobe);
@@ -1325,11 +1357,30 @@ extern "C" int ivf_prefetch(ivf_index* ix, const float* q_in, int32_t nq, int32_
     std::vector<int32_t> taken;
     plan_prefetch(w.h_probe, nq, nprobe, ix->h_off.data(), rb, budget_bytes, ix->buf_bytes, buf_used, res_off.data(), taken, st);
     auto enqueue = [&]() -> int {
-        // One stream: spread over two to four streams the copies of a fresh process ran at 36 to 49 GB/s
-        // instead of 23, but after some thousand copies the runtime takes a slow path (4 GB/s per
-        // stream) for stretches of a thousand copies, with several streams most of the time.
         HIP_TRY(hipEventRecord(ix->ev_pf_begin, ix->copy));
+        size_t total = 0;
+        int n_lists = 0;
         for (int32_t c : taken) {
+            const size_t bytes = (size_t)(ix->h_off[c + 1] - ix->h_off[c]) * rb;
+            total += bytes;
+            n_lists += bytes > 0 ? 1 : 0;
+        }
+        const void* lists_dev = n_lists > 1 && total <= kFetchMeanBytes * (size_t)n_lists ? lists_on_device(ix) : nullptr;
+        if (lists_dev) {
+            if (ix->fetch_recorded) HIP_TRY(hipEventSynchronize(ix->ev_fetch));       // the previous plan has left h_fetch
+            uint32_t chunks = 0;
+            n_lists = 0;
+            for (int32_t c : taken) {
+                const uint64_t bytes = (uint64_t)(ix->h_off[c + 1] - ix->h_off[c]) * rb;
+                if (bytes == 0) continue;
+                ix->h_fetch[n_lists++] = MoveDesc{(uint64_t)ix->h_off[c] * rb, (uint64_t)res_off[c] * rb, bytes, chunks, 0u};
+                chunks += move_chunks(bytes);
+            }
+            HIP_TRY(launch_stage_query((const float*)ix->hd_fetch, (float*)ix->d_fetch, (size_t)n_lists * sizeof(MoveDesc) / sizeof(float), ix->copy));
+            HIP_TRY(hipEventRecord(ix->ev_fetch, ix->copy));
+            ix->fetch_recorded = true;
+            HIP_TRY(launch_fetch_lists(lists_dev, ix->d_buf, ix->d_fetch, n_lists, chunks, ix->copy));
+        } else for (int32_t c : taken) {
             const size_t bytes = (size_t)(ix->h_off[c + 1] - ix->h_off[c]) * rb;
             if (bytes > 0)
                 HIP_TRY(hipMemcpyAsync((char*)ix->d_buf + (size_t)res_off[c] * rb,

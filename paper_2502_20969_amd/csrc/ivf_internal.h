@@ -150,6 +150,10 @@ uint32_t move_chunks(uint64_t bytes);
 // one launch for a group of moves that do not disturb each other; moves_dev holds n_moves entries
 hipError_t launch_gather_moves(void* buf, const MoveDesc* moves_dev, int n_moves, uint32_t n_chunks, int n_cu, hipStream_t s);
 
+// The lists of a prefetch, from pinned host memory (its device address) to the buffer: from_byte counts from lists_dev,
+// to_byte from buf, chunks as in launch_gather_moves.
+hipError_t launch_fetch_lists(const void* lists_dev, void* buf, const MoveDesc* moves_dev, int n_moves, uint32_t n_chunks, hipStream_t s);
+
 // cluster cache bookkeeping: hot[c] < 0 = not cached
 hipError_t launch_cache_admit(float* hot, uint32_t* used, const int64_t* res_off, int nlist, float h_init, int reset,
                               hipStream_t s);

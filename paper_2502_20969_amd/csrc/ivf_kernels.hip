@@ -2094,6 +2094,58 @@ hipError_t launch_gather_moves(void* buf, const MoveDesc* moves_dev, int n_moves
 }
 
 // =============================================================================================
+// Prefetched clusters (Sec. 4.1 step 1): one launch reads all lists of a prefetch from pinned host memory and
+// writes them to their places in the device buffer, in the order of the plan.  Bound by the link to the
+// host: eight workgroups with 32 KB on its way each saturate it (57 GB/s, what the copy engine
+// reaches in one piece of 256 MB; 16 here cover the look-ups between chunks), so the other compute
+// units stay with the searches.  Rows may start at any element: 16-byte stores to aligned places, from
+// loads at any address.  (One hipMemcpyAsync per list: 23 GB/s for lists of 390 KB, half of a list's time
+// passes before its first byte.)
+// =============================================================================================
+constexpr uint32_t kFetchWgs = 16;
+
+__global__ __launch_bounds__(256) void fetch_lists_kernel(const unsigned char* lists, unsigned char* buf, const MoveDesc* moves,
+                                                          int n_moves, uint32_t n_chunks) {
+    constexpr int U = 8;                           // loads of a lane in flight
+    for (uint32_t ch = blockIdx.x; ch < n_chunks; ch += gridDim.x) {
+        int lo = 0, hi = n_moves;                  // moves[lo].chunk0 <= ch < moves[hi].chunk0
+        while (hi - lo > 1) {
+            const int mid = (lo + hi) >> 1;
+            if (moves[mid].chunk0 <= ch) lo = mid; else hi = mid;
+        }
+        const MoveDesc m = moves[lo];
+        const uint64_t o = (uint64_t)(ch - m.chunk0) * kMoveChunk;
+        const uint32_t len = (uint32_t)min((uint64_t)kMoveChunk, m.bytes - o);
+        const unsigned char* src = lists + m.from_byte + o;
+        unsigned char* dst = buf + m.to_byte + o;
+        // to the first 16-byte boundary of the destination element by element (of 2 bytes), then 16 bytes at a
+        // time, then the rest
+        const uint32_t head = min((uint32_t)(-(uintptr_t)dst & 15u), len), vec = (len - head) / 16, tail = head + vec * 16;
+        const uint32_t e = threadIdx.x * 2;
+        if (e < head) *(uint16_t*)(dst + e) = *(const uint16_t*)(src + e);
+        if (tail + e < len) *(uint16_t*)(dst + tail + e) = *(const uint16_t*)(src + tail + e);
+#pragma unroll 1
+        for (uint32_t i0 = 0; i0 < vec; i0 += U * 256) {
+            uint4 v[U];
+#pragma unroll
+            for (int u = 0; u < U; ++u) v[u] = load_chunk<true>(src + head + (size_t)min(i0 + u * 256 + threadIdx.x, vec - 1) * 16);
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const uint32_t i = i0 + u * 256 + threadIdx.x;
+                if (i < vec) store_stream16(dst + head + (size_t)i * 16, v[u]);
+            }
+        }
+    }
+}
+
+hipError_t launch_fetch_lists(const void* lists_dev, void* buf, const MoveDesc* moves_dev, int n_moves, uint32_t n_chunks, hipStream_t s) {
+    if (n_moves <= 0 || n_chunks == 0) return hipSuccess;
+    hipLaunchKernelGGL(fetch_lists_kernel, dim3(std::min(n_chunks, kFetchWgs)), dim3(256), 0, s, (const unsigned char*)lists_dev,
+                       (unsigned char*)buf, moves_dev, n_moves, n_chunks);
+    return hipGetLastError();
+}
+
+// =============================================================================================
 // Queries handed over in host memory: a few KB that a kernel reads from the pinned buffer itself
 // (one dispatch on the search stream) instead of a copy engine transfer set up by the runtime.
 // =============================================================================================

@@ -259,3 +259,41 @@ def test_hybrid_search_finds_every_row_by_its_own_query(streams, dtype, d):
         want = np.arange(lo, min(lo + 64, n))
         assert np.array_equal(gi[:, 0], want), f"rows {want[gi[:, 0] != want][:8]} (on the GPU: {on_gpu[want[gi[:, 0] != want][:8]]})"
     index.close()
+
+
+@pytest.mark.parametrize("dtype,d,shift,pinned", [("f32", 768, 0, True), ("f32", 101, 0, True), ("f32", 5, 3, True), ("f16", 301, 0, True),
+                                                  ("f16", 64, 1, True), ("bf16", 7, 5, True), ("f16", 1, 3, True), ("bf16", 2047, 9, True),
+                                                  ("f32", 33, 1, False), ("f16", 301, 0, False)])
+def test_lists_fetched_by_a_kernel(monkeypatch, dtype, d, shift, pinned):
+    """Small lists are read from pinned host memory by a kernel: rows and lists that start at any element, in
+    memory and in the buffer (where the places follow the order of the plan), lists of no, one and a few
+    rows and of several chunks, a list that ends its allocation.  Memory that was never pinned is
+    copied by the runtime.  What is resident is searched on the GPU alone and must give the results of
+    an index that holds everything in HBM."""
+    rng = np.random.default_rng(d + shift)
+    nlist, k = 40, 6
+    sizes = np.concatenate([rng.integers(0, 60, nlist - 3), [0, 1, 200000 // d + 1]]).astype(np.int64)
+    off = np.concatenate([[0], np.cumsum(sizes)])
+    n = int(off[-1])
+    t = {"f32": torch.float32, "f16": torch.float16, "bf16": torch.bfloat16}[dtype]
+    whole = torch.empty(n * d + shift, dtype=t, pin_memory=pinned)
+    rows = whole[shift:].view(n, d)
+    rows.copy_(torch.from_numpy(rng.standard_normal((n, d)).astype(np.float32)))
+    cent = rng.standard_normal((nlist, d)).astype(np.float32)
+    q = rng.standard_normal((3, d)).astype(np.float32)
+    streams = dict(compute_stream=torch.cuda.Stream(), copy_stream=torch.cuda.Stream())
+    plain = P.ivf_adopt_layout(rows.cuda(), dtype, off, cent, metric=P.IVF_L2, **streams)
+    if not pinned:                                          # the binding asks for pinned memory, the C interface does not
+        monkeypatch.setattr(torch.Tensor, "is_pinned", lambda self: True)
+    index = P.ivf_adopt_layout(rows, dtype, off, cent, metric=P.IVF_L2, placement=P.IVF_PLACE_HOST,
+                               device_buffer_bytes=n * d * rows.element_size() + 4096, **streams)
+    for budget in (1 << 40, n * d * rows.element_size() // 3):
+        index.ivf_prefetch(q, nlist, budget, P.IVF_PREFETCH_RESET)
+        index.ivf_prefetch(q[1:2], nlist, budget)           # a second plan while the first one may be on its way
+        gi, gd, st = index.ivf_search(q, nlist, k, with_stats=True)
+        pi, pd = plain.ivf_search(q, nlist, k)
+        assert np.array_equal(gi, pi) and np.array_equal(gd, pd)
+        if budget == 1 << 40:
+            assert st.n_miss == 0
+    index.close()
+    plain.close()
