@@ -118,7 +118,7 @@ constexpr int kSchedKept = 1024;
 struct SchedSpace {
     int nq = 0;
     float* d_q = nullptr; double* d_dist = nullptr; uint16_t* d_near = nullptr;
-    float* h_q = nullptr;                                     // pinned; batches that are kept only
+    float *h_q = nullptr, *hd_q = nullptr;                    // pinned; batches that are kept only; as the device addresses it
 };
 // its answer (16 KB) and events, kept for batches of any size
 struct SchedAnswer {
@@ -451,11 +451,12 @@ int prof_events(ivf_index* ix, int which, hipEvent_t* e0, hipEvent_t* e1) {
 // ---- kernel sequences ---------------------------------------------------------------------
 // queries from the caller's host memory into d_q of the current workspace (which holds nq of them):
 // through the pinned buffer, then by a kernel when they are few and by the copy engine otherwise
+constexpr size_t kStageBytes = (size_t)256 << 10;       // 1 and 3 MB are as fast by the copy engine
 static int stage_queries(ivf_index* ix, const float* q_host, int nq) {
     Workspace& w = *ix->cw;
     const size_t n = (size_t)nq * ix->d;
     memcpy(w.h_q, q_host, n * sizeof(float));
-    if (n * sizeof(float) <= (size_t)256 << 10) HIP_TRY(launch_stage_query(w.hd_q, w.d_q, n, ix->cs));
+    if (n * sizeof(float) <= kStageBytes) HIP_TRY(launch_stage_query(w.hd_q, w.d_q, n, ix->cs));
     else HIP_TRY(hipMemcpyAsync(w.d_q, w.h_q, n * sizeof(float), hipMemcpyHostToDevice, ix->cs));
     return IVF_OK;
 }
@@ -1443,16 +1444,19 @@ extern "C" int ivf_schedule(ivf_index* ix, const float* q, int32_t nq, int32_t m
         HIP_TRY(hipMalloc(&w.d_q, bytes));
         HIP_TRY(hipMalloc(&w.d_dist, nqz * nqz * sizeof(double)));
         HIP_TRY(hipMalloc(&w.d_near, nqz * schedule_near_stride(nq) * sizeof(uint16_t)));
-        if (kept) HIP_TRY(hipHostMalloc(&w.h_q, bytes));
+        if (kept) {
+            HIP_TRY(hipHostMalloc(&w.h_q, bytes));
+            HIP_TRY(hipHostGetDevicePointer((void**)&w.hd_q, w.h_q, 0));
+        }
         w.nq = nq;
     }
     if (kept) {
-        // through the pinned buffer piece by piece: one piece is copied on while the next is filled
-        const size_t piece = (size_t)256 << 10;
-        for (size_t o = 0; o < bytes; o += piece) {
-            const size_t m = std::min(piece, bytes - o);
-            memcpy((char*)w.h_q + o, (const char*)q + o, m);
-            HIP_TRY(hipMemcpyAsync((char*)w.d_q + o, (const char*)w.h_q + o, m, hipMemcpyHostToDevice, ix->cs));
+        // through the pinned buffer piece by piece: a kernel brings one piece on while the next is filled
+        const size_t n = nqz * ix->d, piece = (size_t)128 << 10;          // floats
+        for (size_t o = 0; o < n; o += piece) {
+            const size_t m = std::min(piece, n - o);
+            memcpy(w.h_q + o, q + o, m * sizeof(float));
+            HIP_TRY(launch_stage_query(w.hd_q + o, w.d_q + o, m, ix->cs));
         }
     } else {
         // pinning memory for one call costs more than it saves (1025, 2048 and 4096 queries x 768: 0.71, 1.27

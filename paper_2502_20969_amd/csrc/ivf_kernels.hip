@@ -2154,8 +2154,28 @@ __global__ void stage_query_kernel(const float* src, float* dst, size_t n) {
     for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += stride) dst[i] = src[i];
 }
 
+// More than kStageOne floats: four to a load, four loads of a lane in flight, so that the link is busy throughout (an engine
+// copy of 256 KB takes 10 us and the next one starts 10 us later).
+constexpr size_t kStageOne = 16384;
+__global__ __launch_bounds__(256) void stage_many_kernel(const float* src, float* dst, size_t n) {
+    constexpr int U = 4;
+    const size_t quads = n / 4, stride = (size_t)gridDim.x * 256 * U;
+    for (size_t i0 = (size_t)blockIdx.x * 256 * U + threadIdx.x; i0 < quads; i0 += stride) {
+        float4 v[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) v[u] = ((const float4*)src)[min(i0 + u * 256, quads - 1)];
+#pragma unroll
+        for (int u = 0; u < U; ++u) if (i0 + u * 256 < quads) ((float4*)dst)[i0 + u * 256] = v[u];
+    }
+    if (blockIdx.x == 0 && threadIdx.x < n % 4) dst[quads * 4 + threadIdx.x] = src[quads * 4 + threadIdx.x];
+}
+
 hipError_t launch_stage_query(const float* src_pinned, float* dst, size_t n, hipStream_t s) {
     if (n == 0) return hipSuccess;
+    if (n > kStageOne && (((uintptr_t)src_pinned | (uintptr_t)dst) & 15u) == 0) {
+        hipLaunchKernelGGL(stage_many_kernel, dim3((unsigned)std::min<size_t>((n / 4 + 1023) / 1024, 64)), dim3(256), 0, s, src_pinned, dst, n);
+        return hipGetLastError();
+    }
     const size_t blocks = std::min<size_t>((n + 255) / 256, 64);
     hipLaunchKernelGGL(stage_query_kernel, dim3((unsigned)blocks), dim3(256), 0, s, src_pinned, dst, n);
     return hipGetLastError();

@@ -90,7 +90,8 @@ constexpr int kNearStep = 512;
 // a bitonic sort of (bits, index) pairs in LDS over the next power of two.  The sorts of all rows
 // run side by side, so that the greedy pick, which is sequential, only walks lists.
 // A row of near is a multiple of kNearStep entries, so that one wavefront reads kNearStep of them
-// with one 16-byte load per lane; entries past B are 0xFFFF.
+// with one 16-byte load per lane; lane l gets entries l, l + 64, ... of them in that order, and entries
+// past B are 0xFFFF.
 __global__ void sort_near_kernel(const double* D, int B, uint32_t pad, int stride, uint16_t* near) {
     extern __shared__ __align__(16) unsigned char s_raw[];
     unsigned long long* key = (unsigned long long*)s_raw;
@@ -117,19 +118,24 @@ __global__ void sort_near_kernel(const double* D, int B, uint32_t pad, int strid
             __syncthreads();
         }
     }
-    for (int i = (int)tid; i < stride; i += (int)nt) near[(size_t)row * stride + i] = i < (int)pad ? idx[i] : (uint16_t)0xFFFFu;
+    for (int o = (int)tid; o < stride; o += (int)nt) {
+        const int i = o / kNearStep * kNearStep + o % 8 * 64 + o % kNearStep / 8;
+        near[(size_t)row * stride + o] = i < (int)pad ? idx[i] : (uint16_t)0xFFFFu;
+    }
 }
 
 // Greedy pick by one wavefront.  While queries remain: the remaining query of lowest index seeds a
 // micro-batch; the m - 1 remaining queries nearest to it follow, nearest first, equal distances by
-// lower index: the first m - 1 entries of its sorted list that are not taken.  512 entries of the
-// list are looked at per step (eight per lane: free ones counted, a prefix over the lanes gives
-// their places).  A chain of LDS reads per micro-batch bounds it; the list of the query that will
-// most likely seed next is requested one micro-batch ahead, so that memory is not part of the
-// chain.  (Picking one query at a time with a workgroup-wide minimum: 892 us for 512 queries in
-// groups of 8; sort_near_kernel + this: 15 + 67 us.  4096 queries: 10.7 -> 2.25 ms for all three kernels.)
+// lower index: the first m - 1 entries of its sorted list that are not taken.  Whether they are is read
+// for 512 entries at once, then 64 at a time are numbered by one ballot until enough are found.  A
+// chain of LDS reads per micro-batch bounds it: the list of the query that will most likely seed next is
+// requested one micro-batch ahead, and the order is kept in LDS until the end, because a load waits for
+// the stores before it, and stores to host memory take longer than a micro-batch.  (Picking one query at a
+// time with a workgroup-wide minimum: 892 us for 512 queries in groups of 8; sorted lists, with the order
+// stored as it was found and the places counted by a prefix over the lanes: 67; this: 38.)
 __global__ __launch_bounds__(64) void greedy_groups_kernel(const uint16_t* near, int B, int stride, int m, int32_t* order) {
     __shared__ unsigned char taken[kScheduleMaxQueries + 64];
+    __shared__ uint16_t found[kScheduleMaxQueries];
     const int lane = threadIdx.x;
     for (int i = lane; i < kScheduleMaxQueries + 64; i += 64) taken[i] = i < B ? 0 : 1;
     __syncthreads();
@@ -145,7 +151,7 @@ __global__ __launch_bounds__(64) void greedy_groups_kernel(const uint16_t* near,
     int pos = 0, seed = 0;
     uint4 cur = fetch(0, 0);
     while (seed < B) {
-        if (lane == 0) { taken[seed] = 1; order[pos] = seed; }
+        if (lane == 0) { taken[seed] = 1; found[pos] = (uint16_t)seed; }
         __syncthreads();
         ++pos;
         const int guess = lowest_free(seed + 1);
@@ -155,39 +161,31 @@ __global__ __launch_bounds__(64) void greedy_groups_kernel(const uint16_t* near,
         for (int at = 0; need > 0 && at < stride; at += kNearStep) {
             const uint4 v = at == 0 ? cur : fetch(seed, at);
             const uint32_t w[4] = {v.x, v.y, v.z, v.w};
-            uint32_t x[8], is_free = 0;
+            uint32_t x[8];
+            unsigned char t[8];
 #pragma unroll
             for (int e = 0; e < 8; ++e) x[e] = (w[e >> 1] >> (16 * (e & 1))) & 0xFFFFu;
-            unsigned char t[8];
 #pragma unroll
             for (int e = 0; e < 8; ++e) t[e] = taken[min(x[e], (uint32_t)kScheduleMaxQueries)];      // 0xFFFF: reads as taken
 #pragma unroll
-            for (int e = 0; e < 8; ++e) is_free |= (uint32_t)(t[e] == 0) << e;
-            const int mine = __popc(is_free);
-            int before = mine;                              // free entries in this lane and all lower ones
-#pragma unroll
-            for (int o = 1; o < 64; o <<= 1) {
-                const int up = __shfl_up(before, o);
-                if (lane >= o) before += up;
-            }
-            const int total = __builtin_amdgcn_readlane(before, 63);
-            int rank = before - mine;
-#pragma unroll
             for (int e = 0; e < 8; ++e) {
-                if ((is_free >> e) & 1u) {
-                    if (rank < need) { taken[x[e]] = 1; order[pos + rank] = (int32_t)x[e]; }
-                    ++rank;
+                if (need > 0) {
+                    const uint64_t is_free = __ballot(t[e] == 0);
+                    const int rank = __popcll(is_free & ((1ull << lane) - 1ull));
+                    if (t[e] == 0 && rank < need) { taken[x[e]] = 1; found[pos + rank] = (uint16_t)x[e]; }
+                    const int got = min(__popcll(is_free), need);
+                    pos += got;
+                    need -= got;
                 }
             }
-            const int got = min(total, need);
-            pos += got;
-            need -= got;
             __syncthreads();
         }
         const int next = lowest_free(seed + 1);
         cur = next == guess || next >= B ? ahead : fetch(next, 0);
         seed = next;
     }
+    __syncthreads();
+    for (int i = lane; i < B; i += 64) order[i] = (int32_t)found[i];
 }
 
 size_t schedule_near_stride(int B) { return (size_t)((B + kNearStep - 1) / kNearStep) * kNearStep; }
