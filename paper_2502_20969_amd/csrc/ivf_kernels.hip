@@ -1353,19 +1353,14 @@ struct MergeLds {
 __device__ __forceinline__ void rank_pool(Cand* pool, uint32_t cnt, int kp, MergeLds& L) {
     const int tid = threadIdx.x, nt = blockDim.x, lane = lane_id(), wave = wave_id(), nw = nt >> 6;
     if (cnt <= (uint32_t)nt) {
-        // each counts the candidates ahead of it (eight per pass, all read before any is
-        // compared) and the first kprime take their places
-        const Cand mine = (uint32_t)tid < cnt ? pool[tid] : (Cand)0;
-        uint32_t rank = 0;
+        // eight lanes per candidate count those ahead of it, and the first kprime take their places
 #pragma unroll 1
-        for (uint32_t j0 = 0; j0 < cnt; j0 += 8) {
-            Cand o[8];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) o[u] = pool[min(j0 + u, cnt - 1)];
-#pragma unroll
-            for (int u = 0; u < 8; ++u) rank += (uint32_t)((o[u] > mine) & (j0 + u < cnt));
+        for (uint32_t t = (uint32_t)tid / 8; t < cnt; t += (uint32_t)nt / 8) {
+            const Cand me = pool[t];
+            uint32_t rank, equal;
+            count_above(pool, cnt, me, (uint32_t)tid & 7u, rank, equal);
+            if ((tid & 7) == 0 && rank < (uint32_t)kp) L.c_cand[rank] = me;
         }
-        if ((uint32_t)tid < cnt && rank < (uint32_t)kp) L.c_cand[rank] = mine;
         __syncthreads();
         if (tid == 0) L.sh[4] = min(cnt, (uint32_t)kp);
         __syncthreads();
