@@ -1736,30 +1736,33 @@ __global__ __launch_bounds__(kMergeFastThreads) void merge_kernel(MergeArgs a) {
     // 4. rank by counting; nearest first, ties by smaller id
     const uint32_t tot = m + nh;
     const int k = a.k;
-    if ((uint32_t)tid < tot) {
-        double mk = L.f_key[tid]; int64_t mi = L.f_id[tid];
+    // eight lanes per candidate
+    for (uint32_t t = (uint32_t)tid / 8; t < tot; t += (uint32_t)nt / 8) {
+        const double mk = L.f_key[t];
+        const int64_t mi = L.f_id[t];
         uint32_t rank = 0;
-        // eight others per pass, all read before any is compared, and no branches: a compare that
+        // four others per lane and pass, all read before any is compared, and no branches: a compare that
         // waits for its own LDS read every time costs more than the whole pass
 #pragma unroll 1
-        for (uint32_t j0 = 0; j0 < tot; j0 += 8) {
-            double ok[8]; int64_t oi[8];
+        for (uint32_t j0 = (uint32_t)tid & 7u; j0 < tot; j0 += 32) {
+            double ok[4]; int64_t oi[4];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const uint32_t j = min(j0 + u, tot - 1);
+            for (int u = 0; u < 4; ++u) {
+                const uint32_t j = min(j0 + 8u * u, tot - 1);
                 ok[u] = L.f_key[j]; oi[u] = L.f_id[j];
             }
 #pragma unroll
-            for (int u = 0; u < 8; ++u) {
+            for (int u = 0; u < 4; ++u) {
                 const bool ahead = (ok[u] > mk) | ((ok[u] == mk) & (oi[u] < mi));
-                rank += (uint32_t)(ahead & (j0 + u < tot));
+                rank += (uint32_t)(ahead & (j0 + 8u * u < tot));
             }
         }
-        if (rank < (uint32_t)k) {
+        rank = sum_of_8(rank);
+        if ((tid & 7) == 0 && rank < (uint32_t)k) {
             a.out_ids[(size_t)qi * k + rank] = mi;
             a.out_dists[(size_t)qi * k + rank] = (float)(a.metric == 0 ? mk : -mk);
         }
-        if (rank == (uint32_t)k - 1) s_kth = mk;
+        if ((tid & 7) == 0 && rank == (uint32_t)k - 1) s_kth = mk;
     }
     for (uint32_t i = tot + tid; i < (uint32_t)k; i += nt) {
         a.out_ids[(size_t)qi * k + i] = -1;
