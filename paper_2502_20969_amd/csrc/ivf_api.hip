@@ -554,22 +554,33 @@ bool has_list_major(const ivf_index* ix) {
     return batched_scan_lds(ix->d, ix->dtype) <= ix->max_lds;              // a group's queries must fit LDS
 }
 
-bool batched_eligible(const ivf_index* ix, int nq) {
+// Time that query-by-query scans of `rows` rows take, us: about 4.8 TB/s and at most 10 rows a nanosecond.
+double scan_us(const ivf_index* ix, double rows) { return std::max(rows * (double)ix->row_bytes / 4.8e6, rows / 1e4); }
+
+// Automatic mode: batches so small that even the largest lists, scanned query by query, take less than the launches in
+// front of a list-major scan and what that loses by its few tasks.  Whole calls, us, list-major / query by query,
+// with that bound: 16 queries x 12 clusters of 384 fp16 (19) 63 / 45, 14 x 6 of 256 fp32 (28) 64 / 44, 4 x 144 of 64
+// bf16 (30) 68 / 58, 10 x 9 of 1024 bf16 (30) 66 / 49, 17 x 7 of 256 fp16 (38) 65 / 58, 5 x 123 of 512 fp16 (39) 75 / 68,
+// 11 x 23 of 768 bf16 (46) 70 / 50, 101 x 4 of 512 bf16 (86) 84 / 85.
+bool small_batch(const ivf_index* ix, int nq, int nprobe) { return scan_us(ix, (double)most_rows(ix, nprobe) * nq) < 60.0; }
+
+// list-major by the batch mode and the number of queries (modes 0 and 2), for rows of whole blocks
+bool list_major_mode(const ivf_index* ix, int nq) {
     if (ix->batch_mode == 1 || nq < 2 || ix->d % 64 != 0) return false;
     return has_list_major(ix) && (ix->batch_mode == 2 || nq >= 4);
 }
+bool batched_eligible(const ivf_index* ix, int nq, int nprobe) {
+    return list_major_mode(ix, nq) && (ix->batch_mode == 2 || !small_batch(ix, nq, nprobe));
+}
 
 // Whether a batch is large enough for the launches in front of a list-major scan (sample, tasks: 20 to 25
-// us) to pay.  A query-by-query scan of clusters of mean size runs at about 4.8 TB/s and at most 10
-// rows a nanosecond; below 40 us of that it is the faster way, or within a few us of it.  Whole calls, us,
-// list-major / query by query, with that estimate: 17 queries x 5 clusters of 355 bf16 (2 us) 82 / 59, 27 x 7
+// us) to pay: below 40 us of scans of clusters of mean size query by query is the faster way, or within a few
+// us of it.  Whole calls, us, list-major / query by query, with that estimate: 17 queries x 5 clusters of 355 bf16 (2 us) 82 / 59, 27 x 7
 // of 743 fp32 (27) 100 / 67, 9 x 40 of 687 fp32 (31) 87 / 60, 6 x 113 of 598 fp32 (38) 122 / 99, 12 x 39 of 47
 // fp32 (46) 92 / 130, 48 x 24 of 100 fp32 (96) 114 / 123, 53 x 58 of 78 fp32 (147) 125 / 182, 250 x 53
 // of 731 bf16 (520) 244 / 809.  Few queries share little: 5 x 206 of 53 bf16 (110) 114 / 104.
 bool worth_list_major(const ivf_index* ix, int nq, int nprobe) {
-    const double rows = (double)ix->n / ix->nlist * nprobe * nq;
-    const double us = std::max(rows * (double)ix->row_bytes / 4.8e6, rows / 1e4);
-    return us >= (nq < 8 ? 120.0 : 40.0);
+    return scan_us(ix, (double)ix->n / ix->nlist * nprobe * nq) >= (nq < 8 ? 120.0 : 40.0);
 }
 
 // Batches of automatic mode over rows that are not whole blocks of 64 elements are searched list-major
@@ -1031,7 +1042,7 @@ extern "C" int ivf_set_batch_mode(ivf_index* ix, int32_t mode) {
     if (mode == 2) {
         const int saved = ix->batch_mode;
         ix->batch_mode = 2;
-        const bool ok = batched_eligible(ix, 2);
+        const bool ok = list_major_mode(ix, 2);
         ix->batch_mode = saved;
         if (!ok) return fail(IVF_ESTATE, "this index has no list-major scan (needs all rows in HBM, fewer than 2^32 of them, and d a multiple of 64 that fits LDS)");
     }
@@ -1055,7 +1066,7 @@ extern "C" int ivf_search_device(ivf_index* ix, const float* q_dev, int32_t nq, 
     use_lane(ix, lane);
     ix->lanes[lane].quiet = false;
     ix->next_lane = (ix->next_lane + 1) % ix->lanes.size();
-    if (batched_eligible(ix, nq)) rc = run_batched(ix, lane, q_dev, nq, nprobe, k, ids_dev, dists_dev, true);
+    if (batched_eligible(ix, nq, nprobe)) rc = run_batched(ix, lane, q_dev, nq, nprobe, k, ids_dev, dists_dev, true);
     else if (any_width_eligible(ix, nq, nprobe, ix->cs) && any_width_workspace(ix, nq, nprobe, k, &rc)) {
         rc = enqueue_batched(ix, q_dev, nq, nprobe, k, ids_dev, dists_dev, true);
         if (rc == IVF_OK) rc = enqueue_redo(ix, q_dev, nq, nprobe, k, kprime_for(k), false, ids_dev, dists_dev);
@@ -1168,7 +1179,7 @@ extern "C" int ivf_search(ivf_index* ix, const float* q_out, int32_t nq, int32_t
     ivf_search_stats st{};
 
     if ((rc = stage_queries(ix, q_out, nq))) return rc;
-    if (batched_eligible(ix, nq)) {
+    if (batched_eligible(ix, nq, nprobe)) {
         // list-major batched search: every selected cluster is read once per group of 32 queries
         // (the merge kernel stores the results in the pinned buffers itself: no copies to wait for)
         if ((rc = run_batched(ix, 0, w.d_q, nq, nprobe, k, w.hd_out_ids, w.hd_out_dists, false))) return rc;
@@ -1222,6 +1233,8 @@ extern "C" int ivf_search(ivf_index* ix, const float* q_out, int32_t nq, int32_t
         st.ms_probe = (float)(now_ms() - t0);
         double hit_sum = 0.0;
         std::vector<int32_t> miss;
+        // a small batch of automatic mode reports what a list-major one does: every cluster once
+        std::vector<uint8_t> seen(list_major_mode(ix, nq) ? ix->nlist : 0, 0);
         const double ts = now_ms();
         for (int qi = 0; qi < nq; ++qi) {
             miss.clear();
@@ -1229,7 +1242,11 @@ extern "C" int ivf_search(ivf_index* ix, const float* q_out, int32_t nq, int32_t
             for (int i = 0; i < nprobe; ++i) {
                 int32_t c = w.h_probe[(size_t)qi * nprobe + i];
                 uint64_t bytes = (uint64_t)(ix->h_off[c + 1] - ix->h_off[c]) * ix->row_bytes;
-                if (ix->h_res_off[c] >= 0) { ++overlap; st.bytes_gpu += bytes; }
+                if (ix->h_res_off[c] >= 0) {
+                    ++overlap;
+                    if (seen.empty() || !seen[c]) st.bytes_gpu += bytes;
+                    if (!seen.empty()) seen[c] = 1;
+                }
                 else { miss.push_back(c); st.bytes_host += bytes; }
             }
             st.n_probed += nprobe; st.n_overlap += overlap; st.n_miss += (int)miss.size();
@@ -1677,7 +1694,7 @@ extern "C" int ivf_batched_scores(ivf_index* ix, const float* q, int32_t nq, int
     if (nq > 32) return fail(IVF_ELIMIT, "at most 32 queries (one group of the list-major scan)");
     const int saved_mode = ix->batch_mode;
     ix->batch_mode = 2;
-    const bool ok = batched_eligible(ix, 2);
+    const bool ok = list_major_mode(ix, 2);
     ix->batch_mode = saved_mode;
     if (!ok) return fail(IVF_ESTATE, "this index has no list-major scan (needs all rows in HBM, fewer than 2^32 of them, and d a multiple of 64 that fits LDS)");
     const int64_t n_c = ix->h_off[cluster + 1] - ix->h_off[cluster];

@@ -168,3 +168,26 @@ def test_reserved_batch_can_be_captured():
         assert np.array_equal(di.cpu().numpy(), want_i) and np.array_equal(dd.cpu().numpy(), want_d)
         index.ivf_search(q, nprobe, k)                       # eager work between the replays
     index.close()
+
+
+@pytest.mark.parametrize("dtype,d,nq,nprobe,k", [("f32", 64, 4, 3, 5), ("f16", 256, 16, 6, 20), ("bf16", 128, 60, 2, 3)])
+def test_small_batches_of_automatic_mode(dtype, d, nq, nprobe, k):
+    """Whole blocks of elements, but too few rows for a list-major scan to pay: query by query, with the
+    results and the reported bytes (each cluster once) of the list-major mode."""
+    rows, off, cent, q = _problem(d + nq, dtype, 6000, d, 30, nq, 5)
+    index = _adopt(rows, dtype, off, cent, "ip")
+    (gi, gd), read = _rows_scanned(index, q, nprobe, k)
+    _, _, st = index.ivf_search(q, nprobe, k, with_stats=True)
+    q_dev = torch.from_numpy(q).cuda()
+    di, dd = torch.empty(nq, k, dtype=torch.int64, device="cuda"), torch.empty(nq, k, device="cuda")
+    torch.cuda.synchronize()
+    index.ivf_search_device(q_dev, nprobe, k, di, dd)
+    index.ivf_synchronize()
+    index.ivf_set_batch_mode(2)
+    (mi, md), once = _rows_scanned(index, q, nprobe, k)
+    _, _, mst = index.ivf_search(q, nprobe, k, with_stats=True)
+    assert read > once
+    assert np.array_equal(gi, mi) and np.array_equal(gd, md)
+    assert np.array_equal(di.cpu().numpy(), mi) and np.array_equal(dd.cpu().numpy(), md)
+    assert st.bytes_gpu == mst.bytes_gpu and st.n_probed == mst.n_probed and st.hit_rate == mst.hit_rate
+    index.close()
