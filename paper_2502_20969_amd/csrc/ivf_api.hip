@@ -573,14 +573,17 @@ bool batched_eligible(const ivf_index* ix, int nq, int nprobe) {
     return list_major_mode(ix, nq) && (ix->batch_mode == 2 || !small_batch(ix, nq, nprobe));
 }
 
-// Whether a batch is large enough for the launches in front of a list-major scan (sample, tasks: 20 to 25
-// us) to pay: below 40 us of scans of clusters of mean size query by query is the faster way, or within a few
-// us of it.  Whole calls, us, list-major / query by query, with that estimate: 17 queries x 5 clusters of 355 bf16 (2 us) 82 / 59, 27 x 7
-// of 743 fp32 (27) 100 / 67, 9 x 40 of 687 fp32 (31) 87 / 60, 6 x 113 of 598 fp32 (38) 122 / 99, 12 x 39 of 47
-// fp32 (46) 92 / 130, 48 x 24 of 100 fp32 (96) 114 / 123, 53 x 58 of 78 fp32 (147) 125 / 182, 250 x 53
-// of 731 bf16 (520) 244 / 809.  Few queries share little: 5 x 206 of 53 bf16 (110) 114 / 104.
+// Whether a batch over rows of any width shares enough for the launches in front of a list-major scan (sample, tasks:
+// 20 to 25 us) to pay: what query-by-query scans of clusters of mean size would take, less what one scan of
+// their union takes, were the queries independent.  From 20 us of that on every batch measured is as fast
+// or faster list-major; below it either way may be, and the query-by-query one is kept.  Whole calls, us, list-major /
+// query by query, with the estimate: 21 queries x 58 fp32 (1) 85 / 69, 12 x 47 fp32 (1) 92 / 115, 41 x 80 bf16 (8)
+// 92 / 72, 8 x 1022 bf16 (13) 114 / 86, 53 x 78 fp32 (30) 125 / 172, 48 x 100 fp32 (46) 114 / 118, 5 x 898 bf16 (58) 157 / 161,
+// 25 x 62 fp16 (86) 72 / 77, 36 x 230 fp32 (127) 88 / 152, 143 x 265 bf16 (200) 116 / 257.
 bool worth_list_major(const ivf_index* ix, int nq, int nprobe) {
-    return scan_us(ix, (double)ix->n / ix->nlist * nprobe * nq) >= (nq < 8 ? 120.0 : 40.0);
+    const double share = std::min(1.0, (double)nprobe / ix->nlist), picked = share * nq;
+    const double once = (1.0 - std::pow(1.0 - share, nq)) / picked;        // union / sum of the queries' clusters
+    return scan_us(ix, (double)ix->n * picked) * (1.0 - once) >= 20.0;
 }
 
 // Batches of automatic mode over rows that are not whole blocks of 64 elements are searched list-major
