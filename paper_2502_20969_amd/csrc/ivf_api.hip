@@ -575,24 +575,24 @@ bool batched_eligible(const ivf_index* ix, int nq, int nprobe) {
 
 // Whether a batch over rows of any width shares enough for the launches in front of a list-major scan (sample, tasks:
 // 20 to 25 us) to pay: what query-by-query scans of clusters of mean size would take, less what one scan of
-// their union takes, were the queries independent.  From 20 us of that on every batch measured is as fast
-// or faster list-major; below it either way may be, and the query-by-query one is kept.  Whole calls, us, list-major /
-// query by query, with the estimate: 21 queries x 58 fp32 (1) 85 / 69, 12 x 47 fp32 (1) 92 / 115, 41 x 80 bf16 (8)
-// 92 / 72, 8 x 1022 bf16 (13) 114 / 86, 53 x 78 fp32 (30) 125 / 172, 48 x 100 fp32 (46) 114 / 118, 5 x 898 bf16 (58) 157 / 161,
+// their union takes, were the queries independent.  From 50 us of that on (20 for more than 56 results, whose
+// query-by-query merge is the longer one) every batch measured is as fast or faster list-major; below it
+// either way may be, and the query-by-query one is kept.  Whole calls, us, list-major / query by query, with the estimate: 21 queries x 58 fp32 (1) 85 / 69, 12 x 47 fp32 (1) 92 / 115, 41 x 80 bf16 (8)
+// 92 / 72, 8 x 1022 bf16 (13) 114 / 86, 53 x 78 fp32 (30) 125 / 172, 48 x 100 fp32 (46) 114 to 120 / 113 to 118, 125 x 83 bf16 with k 93 (45) 175 / 759, 5 x 898 bf16 (58) 157 / 161,
 // 25 x 62 fp16 (86) 72 / 77, 36 x 230 fp32 (127) 88 / 152, 143 x 265 bf16 (200) 116 / 257.
-bool worth_list_major(const ivf_index* ix, int nq, int nprobe) {
+bool worth_list_major(const ivf_index* ix, int nq, int nprobe, int k) {
     const double share = std::min(1.0, (double)nprobe / ix->nlist), picked = share * nq;
     const double once = (1.0 - std::pow(1.0 - share, nq)) / picked;        // union / sum of the queries' clusters
-    return scan_us(ix, (double)ix->n * picked) * (1.0 - once) >= 20.0;
+    return scan_us(ix, (double)ix->n * picked) * (1.0 - once) >= (k > 56 ? 20.0 : 50.0);
 }
 
 // Batches of automatic mode over rows that are not whole blocks of 64 elements are searched list-major
 // too, completed on the stream by the exact pass (enqueue_any_width), so that they keep what the
 // query-by-query path promises them: outputs complete in stream order.  Not while the stream is
 // being captured, where their workspace could not be sized.
-bool any_width_eligible(const ivf_index* ix, int nq, int nprobe, hipStream_t stream) {
+bool any_width_eligible(const ivf_index* ix, int nq, int nprobe, int k, hipStream_t stream) {
     if (ix->batch_mode != 0 || nq < 4 || ix->d % 64 == 0 || ix->any_width_off) return false;
-    if (ix->row_bytes < 16 || !has_list_major(ix) || !worth_list_major(ix, nq, nprobe)) return false;
+    if (ix->row_bytes < 16 || !has_list_major(ix) || !worth_list_major(ix, nq, nprobe, k)) return false;
     hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
     return hipStreamIsCapturing(stream, &st) == hipSuccess && st == hipStreamCaptureStatusNone;
 }
@@ -936,7 +936,7 @@ extern "C" int ivf_reserve(ivf_index* ix, int32_t nq, int32_t nprobe, int32_t k)
     for (size_t i = 0; i < ix->lanes.size(); ++i) {
         use_lane(ix, i);
         int rc = ensure_workspace(ix, nq, std::min(nprobe, ix->nlist), k);
-        if (!rc && any_width_eligible(ix, nq, nprobe, ix->cs)) (void)any_width_workspace(ix, nq, std::min(nprobe, ix->nlist), k, &rc);
+        if (!rc && any_width_eligible(ix, nq, nprobe, k, ix->cs)) (void)any_width_workspace(ix, nq, std::min(nprobe, ix->nlist), k, &rc);
         if (rc) { use_lane(ix, 0); return rc; }
     }
     use_lane(ix, 0);
@@ -1070,7 +1070,7 @@ extern "C" int ivf_search_device(ivf_index* ix, const float* q_dev, int32_t nq, 
     ix->lanes[lane].quiet = false;
     ix->next_lane = (ix->next_lane + 1) % ix->lanes.size();
     if (batched_eligible(ix, nq, nprobe)) rc = run_batched(ix, lane, q_dev, nq, nprobe, k, ids_dev, dists_dev, true);
-    else if (any_width_eligible(ix, nq, nprobe, ix->cs) && any_width_workspace(ix, nq, nprobe, k, &rc)) {
+    else if (any_width_eligible(ix, nq, nprobe, k, ix->cs) && any_width_workspace(ix, nq, nprobe, k, &rc)) {
         rc = enqueue_batched(ix, q_dev, nq, nprobe, k, ids_dev, dists_dev, true);
         if (rc == IVF_OK) rc = enqueue_redo(ix, q_dev, nq, nprobe, k, kprime_for(k), false, ids_dev, dists_dev);
     } else if (rc == IVF_OK) {
@@ -1201,7 +1201,7 @@ extern "C" int ivf_search(ivf_index* ix, const float* q_out, int32_t nq, int32_t
         }
         return IVF_OK;
     }
-    if (any_width_eligible(ix, nq, nprobe, ix->cs) && any_width_workspace(ix, nq, nprobe, k, &rc)) {
+    if (any_width_eligible(ix, nq, nprobe, k, ix->cs) && any_width_workspace(ix, nq, nprobe, k, &rc)) {
         if ((rc = enqueue_batched(ix, w.d_q, nq, nprobe, k, w.hd_out_ids, w.hd_out_dists, true))) return rc;
         if (stats) HIP_TRY(hipMemcpyAsync(w.h_probe, w.d_probe, (size_t)nq * nprobe * sizeof(int32_t), hipMemcpyDeviceToHost, ix->cs));
         HIP_TRY(hipStreamSynchronize(ix->cs));

@@ -1,8 +1,8 @@
 // Batched list scan for query batches that share probed clusters (TeleRAG Sec. 4.2 "Batching":
 // the GPU part of the search becomes a matrix-matrix product).  Each selected list is read from
 // HBM once per group of queries that probe it (up to 32 for fp16 / bf16 rows, up to 16 for fp32
-// rows); scores come from MFMA (v_mfma_f32_32x32x16 f16 / bf16 or v_mfma_f32_16x16x4 f32, fp32
-// accumulate) and are only used to FILTER rows: a row whose approximate score reaches the query's
+// rows); scores come from MFMA (v_mfma_f32_32x32x16 f16 / bf16, or v_mfma_f32_16x16x4 f32 for fp32 rows and
+// more than 8 queries; fp32 accumulate) or the vector units and are only used to FILTER rows: a row whose approximate score reaches the query's
 // threshold becomes a candidate, and the final ranking is done on fp64 re-scores with the fp32
 // query, exactly as in the single-query path.
 //
