@@ -1810,28 +1810,38 @@ constexpr int kRedoThreads = 256;
 constexpr int kRedoWaves = kRedoThreads / 64;
 static_assert(kRedoWaves == kRedoListsPerWg, "the list buffers are sized by kRedoListsPerWg");
 
-// The number of flagged queries, and the index of the one that workgroup `wg` serves.
-__device__ __forceinline__ uint32_t flagged_queries(const uint32_t* flag, int nq, uint32_t wg, uint32_t* s_count, int& qi) {
+// Workgroups of a call at most: four per compute unit of the largest part; each looks at every flag of the call, so one
+// per query makes the look quadratic (60,000 queries x 2 lists of 100 fp16 x 64, none flagged, whole call: 16.4 ms,
+// 3.5 with this bound; 16,384 queries 1.40, 0.97).
+constexpr uint32_t kRedoMaxWgs = 1024;
+
+// The number of flagged queries; `mine` of them are this thread's (tid, tid + 256, ...), numbers `before` and on.
+__device__ __forceinline__ uint32_t count_flagged(const uint32_t* flag, int nq, uint32_t* s_count, uint32_t& before, uint32_t& mine) {
     const int tid = threadIdx.x;
-    if (nq == 1) { qi = 0; return flag[0] != 0 ? 1u : 0u; }
-    uint32_t mine = 0;
-    const int per = (nq + kRedoThreads - 1) / kRedoThreads, i0 = min(tid * per, nq), i1 = min(i0 + per, nq);
-    for (int i = i0; i < i1; ++i) mine += flag[i] != 0 ? 1u : 0u;
+    before = 0;
+    mine = 0;
+    if (nq == 1) return flag[0] != 0 ? 1u : 0u;
+    for (int i = tid; i < nq; i += kRedoThreads) mine += flag[i] != 0 ? 1u : 0u;
     if (!__syncthreads_or(mine != 0)) return 0u;
     s_count[tid] = mine;
     __syncthreads();
-    uint32_t before = 0, total = 0;
+    uint32_t total = 0;
     for (int t = 0; t < kRedoThreads; ++t) { const uint32_t c = s_count[t]; before += t < tid ? c : 0u; total += c; }
     __syncthreads();
-    const uint32_t want = wg % total;
+    return total;
+}
+// the index of flagged query number `want`, by the workgroup together
+__device__ __forceinline__ int flagged_query(const uint32_t* flag, int nq, uint32_t want, uint32_t before, uint32_t mine, uint32_t* s_found) {
+    if (nq == 1) return 0;
     if (want >= before && want < before + mine) {
         uint32_t seen = before;
-        for (int i = i0; i < i1; ++i)
-            if (flag[i] != 0 && seen++ == want) s_count[0] = (uint32_t)i;
+        for (int i = threadIdx.x; i < nq; i += kRedoThreads)
+            if (flag[i] != 0 && seen++ == want) *s_found = (uint32_t)i;
     }
     __syncthreads();
-    qi = (int)s_count[0];
-    return total;
+    const int qi = (int)*s_found;
+    __syncthreads();
+    return qi;
 }
 
 __global__ __launch_bounds__(kRedoThreads) void exact_redo_kernel(RedoArgs a) {
@@ -1841,160 +1851,166 @@ __global__ __launch_bounds__(kRedoThreads) void exact_redo_kernel(RedoArgs a) {
     __shared__ unsigned long long w_key[kRedoWaves][IVF_MAX_K];     // ordered score; 0 = empty
     __shared__ long long w_id[kRedoWaves][IVF_MAX_K];
     const int tid = threadIdx.x, lane = lane_id(), wave = wave_id();
-    int qi = 0;
-    const uint32_t flagged = flagged_queries(a.redo_flag, a.nq, blockIdx.x, hist, qi);
+    uint32_t flags_before, flags_mine;
+    const uint32_t flagged = count_flagged(a.redo_flag, a.nq, hist, flags_before, flags_mine);
     if (flagged == 0) return;
-    // this workgroup is number `part` of the `parts` that serve query qi: first, first + flagged, ...
+    // this workgroup is number `part` of the `parts` that serve a query: first, first + flagged, ...; of more flagged
+    // queries than workgroups it serves several, one after the other and alone
     const uint32_t first = blockIdx.x % flagged, part = blockIdx.x / flagged, parts = (gridDim.x - first + flagged - 1) / flagged;
     const int np = a.nprobe, k = a.k;
-    const float* q = a.q + (size_t)qi * a.d;
-    const uint32_t* rp = a.slots.rprefix + (size_t)qi * (np + 1);
-    const int64_t* s_base = a.slots.base + (size_t)qi * np;
-    const uint32_t* s_grow = a.slots.grow + (size_t)qi * np;
-    const uint32_t R = rp[np];
-    const double thr = a.redo_thr[qi];
-    unsigned long long* mk = w_key[wave];
-    long long* mi = w_id[wave];
-    for (int i = lane; i < k; i += 64) { mk[i] = 0ull; mi[i] = 0; }
-    int count = 0;                                   // entries in this wavefront's list (uniform)
-    constexpr int lpc = kRescoreLanes;
-    constexpr int gpw = 64 / lpc;                    // rows a wavefront scores at a time
-    const int sub = lane % lpc;
-    const uint32_t my_group = (part * kRedoWaves + (uint32_t)wave) * gpw + (uint32_t)(lane / lpc);
-    const uint32_t ngroups = parts * kRedoWaves * gpw;
-    const uint32_t rounds = (R + ngroups - 1) / ngroups;
 #pragma unroll 1
-    for (uint32_t it = 0; it < rounds; ++it) {
-        const uint32_t r = it * ngroups + my_group;
-        double key = -INFINITY;
-        long long id = 0;
-        if (r < R) {
-            uint32_t lo = 0, hi = (uint32_t)np;            // rp[lo] <= r < rp[hi]
-            while (hi - lo > 1) {
-                const uint32_t mid = (lo + hi) >> 1;
-                if (rp[mid] <= r) lo = mid; else hi = mid;
+    for (uint32_t number = first; number < flagged; number += gridDim.x) {
+        const int qi = flagged_query(a.redo_flag, a.nq, number, flags_before, flags_mine, hist);
+        const float* q = a.q + (size_t)qi * a.d;
+        const uint32_t* rp = a.slots.rprefix + (size_t)qi * (np + 1);
+        const int64_t* s_base = a.slots.base + (size_t)qi * np;
+        const uint32_t* s_grow = a.slots.grow + (size_t)qi * np;
+        const uint32_t R = rp[np];
+        const double thr = a.redo_thr[qi];
+        unsigned long long* mk = w_key[wave];
+        long long* mi = w_id[wave];
+        for (int i = lane; i < k; i += 64) { mk[i] = 0ull; mi[i] = 0; }
+        int count = 0;                                   // entries in this wavefront's list (uniform)
+        constexpr int lpc = kRescoreLanes;
+        constexpr int gpw = 64 / lpc;                    // rows a wavefront scores at a time
+        const int sub = lane % lpc;
+        const uint32_t my_group = (part * kRedoWaves + (uint32_t)wave) * gpw + (uint32_t)(lane / lpc);
+        const uint32_t ngroups = parts * kRedoWaves * gpw;
+        const uint32_t rounds = (R + ngroups - 1) / ngroups;
+#pragma unroll 1
+        for (uint32_t it = 0; it < rounds; ++it) {
+            const uint32_t r = it * ngroups + my_group;
+            double key = -INFINITY;
+            long long id = 0;
+            if (r < R) {
+                uint32_t lo = 0, hi = (uint32_t)np;            // rp[lo] <= r < rp[hi]
+                while (hi - lo > 1) {
+                    const uint32_t mid = (lo + hi) >> 1;
+                    if (rp[mid] <= r) lo = mid; else hi = mid;
+                }
+                const uint32_t in_slot = r - rp[lo];
+                const size_t brow = (size_t)(s_base[lo] + (int64_t)in_slot);
+                const double s = rescore_row(a.buf, q, a.d, a.dtype, a.metric, brow, sub);
+                key = a.metric == 0 ? s : -s;
+                const uint32_t grow = s_grow[lo] + in_slot;
+                id = a.ids ? (long long)a.ids[grow] : (long long)grow;
             }
-            const uint32_t in_slot = r - rp[lo];
-            const size_t brow = (size_t)(s_base[lo] + (int64_t)in_slot);
-            const double s = rescore_row(a.buf, q, a.d, a.dtype, a.metric, brow, sub);
-            key = a.metric == 0 ? s : -s;
-            const uint32_t grow = s_grow[lo] + in_slot;
-            id = a.ids ? (long long)a.ids[grow] : (long long)grow;
-        }
-        // the rows of this round that reach the threshold, and the last entry of a full list, go into the
-        // list one after the other
-        const unsigned long long last_key = count == k ? mk[k - 1] : 0ull;
-        uint64_t want = __ballot(sub == 0 && r < R && key >= thr && (unsigned long long)ordered(key) >= last_key);
-        while (want) {
-            const int src = __ffsll((long long)want) - 1;
-            want &= want - 1;
-            const unsigned long long nk = ordered(__shfl(key, src));
-            const long long nid = __shfl(id, src);
-            // position: entries ahead of the new one (larger key, or equal key and smaller id)
-            int ahead = 0;
-            for (int i = lane; i < count; i += 64) ahead += (mk[i] > nk || (mk[i] == nk && mi[i] < nid)) ? 1 : 0;
+            // the rows of this round that reach the threshold, and the last entry of a full list, go into the
+            // list one after the other
+            const unsigned long long last_key = count == k ? mk[k - 1] : 0ull;
+            uint64_t want = __ballot(sub == 0 && r < R && key >= thr && (unsigned long long)ordered(key) >= last_key);
+            while (want) {
+                const int src = __ffsll((long long)want) - 1;
+                want &= want - 1;
+                const unsigned long long nk = ordered(__shfl(key, src));
+                const long long nid = __shfl(id, src);
+                // position: entries ahead of the new one (larger key, or equal key and smaller id)
+                int ahead = 0;
+                for (int i = lane; i < count; i += 64) ahead += (mk[i] > nk || (mk[i] == nk && mi[i] < nid)) ? 1 : 0;
 #pragma unroll
-            for (int m = 32; m >= 1; m >>= 1) ahead += __shfl_xor(ahead, m);
-            if (ahead >= k) continue;                      // the list is full of better rows
-            const int last = min(count, k - 1);            // entries ahead .. last-1 move down by one
-            for (int base = ((last - 1) / 64) * 64; base >= 0 && last > ahead; base -= 64) {
-                const int i = base + lane;
-                const bool mv = i >= ahead && i < last;
-                const unsigned long long tk = mv ? mk[i] : 0ull;
-                const long long ti = mv ? mi[i] : 0;
-                if (mv) { mk[i + 1] = tk; mi[i + 1] = ti; }    // a wavefront's LDS operations complete in order
+                for (int m = 32; m >= 1; m >>= 1) ahead += __shfl_xor(ahead, m);
+                if (ahead >= k) continue;                      // the list is full of better rows
+                const int last = min(count, k - 1);            // entries ahead .. last-1 move down by one
+                for (int base = ((last - 1) / 64) * 64; base >= 0 && last > ahead; base -= 64) {
+                    const int i = base + lane;
+                    const bool mv = i >= ahead && i < last;
+                    const unsigned long long tk = mv ? mk[i] : 0ull;
+                    const long long ti = mv ? mi[i] : 0;
+                    if (mv) { mk[i + 1] = tk; mi[i + 1] = ti; }    // a wavefront's LDS operations complete in order
+                }
+                if (lane == 0) { mk[ahead] = nk; mi[ahead] = nid; }
+                count = min(count + 1, k);
             }
-            if (lane == 0) { mk[ahead] = nk; mi[ahead] = nid; }
-            count = min(count + 1, k);
         }
-    }
-    // every wavefront leaves its k slots (0 = empty) in the list of its workgroup
-    {
-        const size_t o = ((size_t)blockIdx.x * kRedoWaves + wave) * (size_t)k;
-        for (int i = lane; i < k; i += 64) {
-            __hip_atomic_store(&a.list_key[o + i], i < count ? mk[i] : 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            __hip_atomic_store(&a.list_id[o + i], mi[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        }
-    }
-    __syncthreads();
-    if (tid == 0) {
-        __threadfence();
-        s_last = atomicAdd(&a.redo_ticket[qi], 1u) == parts - 1 ? 1u : 0u;
-    }
-    __syncthreads();
-    if (!s_last) return;
-    __threadfence();
-    // the last workgroup: the k best entries of all lists and of the host's candidates, by (score, id)
-    const uint32_t per_wg = kRedoWaves * (uint32_t)k, n = parts * per_wg;
-    const uint32_t nh = a.host_cand ? min((uint32_t)a.host_count[qi], (uint32_t)a.kprime) : 0u;
-    const uint32_t tot = n + nh;
-    auto place_of = [&](uint32_t j) -> size_t { return (size_t)(first + j / per_wg * flagged) * per_wg + j % per_wg; };
-    auto key_of = [&](uint32_t j) -> uint64_t {
-        if (j < n) return __hip_atomic_load(&a.list_key[place_of(j)], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        return ordered(a.host_cand[(size_t)qi * a.kprime + (j - n)].key);
-    };
-    auto id_of = [&](uint32_t j) -> long long {
-        if (j < n) return __hip_atomic_load(&a.list_id[place_of(j)], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        return (long long)a.host_cand[(size_t)qi * a.kprime + (j - n)].id;
-    };
-    // ascending = best first; the all-ones key marks an empty entry
-    auto up = [&](uint32_t j) -> uint64_t { return ~key_of(j); };
-    uint32_t mine = 0;
-    for (uint32_t j = tid; j < tot; j += kRedoThreads) mine += key_of(j) != 0 ? 1u : 0u;
-    if (tid == 0) s_n = 0;
-    __syncthreads();
-    if (mine) atomicAdd(&s_n, mine);
-    __syncthreads();
-    const uint32_t valid = s_n, kept = min(valid, (uint32_t)k);
-    uint64_t mask = 0, prefix = 0, id_edge = ~0ull;
-    uint32_t need = valid, group = valid;
-    if (valid > (uint32_t)k) {
-        block_radix_select<uint64_t>(up, tot, (uint32_t)k, hist, sh, mask, prefix, need, group);
-        if (need != group) {
-            // equal scores hold the k-th place: of those the `need` smallest ids
-            uint64_t im, ip;
-            uint32_t in, ig;
-            auto tied_id = [&](uint32_t j) -> uint64_t { const uint64_t u = up(j); return u != ~0ull && (u & mask) == prefix ? (uint64_t)id_of(j) : ~0ull; };
-            block_radix_select<uint64_t>(tied_id, tot, need, hist, sh, im, ip, in, ig);
-            id_edge = ip | ~im;
-        }
-    }
-    __syncthreads();
-    if (tid == 0) s_n = 0;
-    __syncthreads();
-    unsigned long long* o_key = w_key[0];
-    long long* o_id = w_id[0];
-    // those on the very edge last: with ids that occur more than once there may be more of them than places
-    for (int edge = 0; edge < 2; ++edge) {
-        for (uint32_t j = tid; j < tot; j += kRedoThreads) {
-            const uint64_t u = up(j);
-            if (u == ~0ull || (u & mask) > prefix) continue;
-            const long long id = id_of(j);
-            const bool tied = need != group && (u & mask) == prefix;
-            if ((tied && (uint64_t)id > id_edge) || (tied && (uint64_t)id == id_edge) != (edge == 1)) continue;
-            const uint32_t pos = atomicAdd(&s_n, 1u);
-            if (pos < kept) { o_key[pos] = ~u; o_id[pos] = id; }
+        // every wavefront leaves its k slots (0 = empty) in the list of its workgroup
+        {
+            const size_t o = ((size_t)blockIdx.x * kRedoWaves + wave) * (size_t)k;
+            for (int i = lane; i < k; i += 64) {
+                __hip_atomic_store(&a.list_key[o + i], i < count ? mk[i] : 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                __hip_atomic_store(&a.list_id[o + i], mi[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            }
         }
         __syncthreads();
-    }
-    for (uint32_t e = tid; e < kept; e += kRedoThreads) {
-        const unsigned long long ek = o_key[e];
-        const long long ei = o_id[e];
-        uint32_t rank = 0;
-        for (uint32_t j = 0; j < kept; ++j) rank += (uint32_t)(o_key[j] > ek || (o_key[j] == ek && (o_id[j] < ei || (o_id[j] == ei && j < e))));
-        const double key = unordered((uint64_t)ek);
-        a.out_ids[(size_t)qi * k + rank] = (int64_t)ei;
-        a.out_dists[(size_t)qi * k + rank] = (float)(a.metric == 0 ? key : -key);
-    }
-    for (uint32_t i = kept + tid; i < (uint32_t)k; i += kRedoThreads) {
-        a.out_ids[(size_t)qi * k + i] = -1;
-        a.out_dists[(size_t)qi * k + i] = a.metric == 0 ? -INFINITY : INFINITY;
+        if (tid == 0) {
+            __threadfence();
+            s_last = atomicAdd(&a.redo_ticket[qi], 1u) == parts - 1 ? 1u : 0u;
+        }
+        __syncthreads();
+        if (!s_last) return;                             // (parts > 1: there is no further query)
+        __threadfence();
+        // the last workgroup: the k best entries of all lists and of the host's candidates, by (score, id)
+        const uint32_t per_wg = kRedoWaves * (uint32_t)k, n = parts * per_wg;
+        const uint32_t nh = a.host_cand ? min((uint32_t)a.host_count[qi], (uint32_t)a.kprime) : 0u;
+        const uint32_t tot = n + nh;
+        auto place_of = [&](uint32_t j) -> size_t { return (size_t)(first + j / per_wg * flagged) * per_wg + j % per_wg; };
+        auto key_of = [&](uint32_t j) -> uint64_t {
+            if (j < n) return __hip_atomic_load(&a.list_key[place_of(j)], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            return ordered(a.host_cand[(size_t)qi * a.kprime + (j - n)].key);
+        };
+        auto id_of = [&](uint32_t j) -> long long {
+            if (j < n) return __hip_atomic_load(&a.list_id[place_of(j)], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            return (long long)a.host_cand[(size_t)qi * a.kprime + (j - n)].id;
+        };
+        // ascending = best first; the all-ones key marks an empty entry
+        auto up = [&](uint32_t j) -> uint64_t { return ~key_of(j); };
+        uint32_t mine = 0;
+        for (uint32_t j = tid; j < tot; j += kRedoThreads) mine += key_of(j) != 0 ? 1u : 0u;
+        if (tid == 0) s_n = 0;
+        __syncthreads();
+        if (mine) atomicAdd(&s_n, mine);
+        __syncthreads();
+        const uint32_t valid = s_n, kept = min(valid, (uint32_t)k);
+        uint64_t mask = 0, prefix = 0, id_edge = ~0ull;
+        uint32_t need = valid, group = valid;
+        if (valid > (uint32_t)k) {
+            block_radix_select<uint64_t>(up, tot, (uint32_t)k, hist, sh, mask, prefix, need, group);
+            if (need != group) {
+                // equal scores hold the k-th place: of those the `need` smallest ids
+                uint64_t im, ip;
+                uint32_t in, ig;
+                auto tied_id = [&](uint32_t j) -> uint64_t { const uint64_t u = up(j); return u != ~0ull && (u & mask) == prefix ? (uint64_t)id_of(j) : ~0ull; };
+                block_radix_select<uint64_t>(tied_id, tot, need, hist, sh, im, ip, in, ig);
+                id_edge = ip | ~im;
+            }
+        }
+        __syncthreads();
+        if (tid == 0) s_n = 0;
+        __syncthreads();
+        unsigned long long* o_key = w_key[0];
+        long long* o_id = w_id[0];
+        // those on the very edge last: with ids that occur more than once there may be more of them than places
+        for (int edge = 0; edge < 2; ++edge) {
+            for (uint32_t j = tid; j < tot; j += kRedoThreads) {
+                const uint64_t u = up(j);
+                if (u == ~0ull || (u & mask) > prefix) continue;
+                const long long id = id_of(j);
+                const bool tied = need != group && (u & mask) == prefix;
+                if ((tied && (uint64_t)id > id_edge) || (tied && (uint64_t)id == id_edge) != (edge == 1)) continue;
+                const uint32_t pos = atomicAdd(&s_n, 1u);
+                if (pos < kept) { o_key[pos] = ~u; o_id[pos] = id; }
+            }
+            __syncthreads();
+        }
+        for (uint32_t e = tid; e < kept; e += kRedoThreads) {
+            const unsigned long long ek = o_key[e];
+            const long long ei = o_id[e];
+            uint32_t rank = 0;
+            for (uint32_t j = 0; j < kept; ++j) rank += (uint32_t)(o_key[j] > ek || (o_key[j] == ek && (o_id[j] < ei || (o_id[j] == ei && j < e))));
+            const double key = unordered((uint64_t)ek);
+            a.out_ids[(size_t)qi * k + rank] = (int64_t)ei;
+            a.out_dists[(size_t)qi * k + rank] = (float)(a.metric == 0 ? key : -key);
+        }
+        for (uint32_t i = kept + tid; i < (uint32_t)k; i += kRedoThreads) {
+            a.out_ids[(size_t)qi * k + i] = -1;
+            a.out_dists[(size_t)qi * k + i] = a.metric == 0 ? -INFINITY : INFINITY;
+        }
+        __syncthreads();                                 // the lists in LDS are read until here
     }
 }
 
 hipError_t launch_redo(const RedoArgs& a, int grid, hipStream_t s) {
     if (a.k > IVF_MAX_K) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(exact_redo_kernel, dim3((unsigned)grid * (unsigned)a.nq), dim3(kRedoThreads), 0, s, a);
+    hipLaunchKernelGGL(exact_redo_kernel, dim3(std::min((uint32_t)grid * (uint32_t)a.nq, kRedoMaxWgs)), dim3(kRedoThreads), 0, s, a);
     return hipGetLastError();
 }
 

@@ -227,3 +227,57 @@ def test_flagged_queries_of_a_batch_share_the_second_pass(nq, every, k):
         oi, osc = O.search(rows[perm], O.F32, off, ids[perm], cent, q[b], nlist, k, O.IP)
         assert list(gi[b]) == list(oi)
     index.close()
+
+
+@pytest.mark.parametrize("nq,k", [(1023, 10), (1024, 3), (1025, 10), (2600, 40)])
+def test_more_flagged_queries_than_workgroups(nq, k):
+    """Every row sixty times: no first result can be proven, and with more than 1024 queries the workgroups of
+    the second pass serve several of them, one after the other."""
+    d, kinds, copies = 16, 40, 60
+    rng = np.random.default_rng(nq)
+    base = rng.standard_normal((kinds, d)).astype(np.float32)
+    rows = np.tile(base, (copies, 1))
+    assign = (np.arange(kinds * copies) % 3).astype(np.int32)
+    ids = rng.permutation(kinds * copies).astype(np.int64) * 3
+    cent = rng.standard_normal((3, d)).astype(np.float32)
+    q = rng.standard_normal((nq, d)).astype(np.float32)
+    index = P.ivf_build_layout(rows, "f32", cent, assign, ids=ids, metric=P.IVF_IP,
+                               compute_stream=torch.cuda.Stream(), copy_stream=torch.cuda.Stream())
+    index.ivf_set_batch_mode(1)
+    gi, gd, ss = index.ivf_search(q, 3, k, with_stats=True)
+    assert ss.n_exact_gpu == nq
+    best = np.argmax(q.astype(np.float64) @ base.astype(np.float64).T, axis=1)
+    of_kind = np.sort(ids.reshape(copies, kinds), axis=0)          # equal scores: smaller id first, and k is at most the copies
+    assert np.array_equal(gi, of_kind[:k, best].T)
+    index.close()
+
+
+def test_second_pass_of_many_proven_queries_costs_in_proportion():
+    """The workgroups of the second pass look for flagged queries; with one workgroup per query that look
+    grew with the square of the batch (16,384 queries 1.4 ms, 60,000 16.4 ms; in proportion: 3.7 times as long)."""
+    d, n, nlist, k = 16, 20000, 1000, 5
+    g = torch.Generator(device="cuda").manual_seed(1)
+    cent = torch.randn(nlist, d, generator=g, device="cuda")
+    rows = (cent.repeat_interleave(n // nlist, 0) + 0.3 * torch.randn(n, d, generator=g, device="cuda")).half()
+    torch.cuda.synchronize()
+    stream = torch.cuda.Stream()
+    index = P.ivf_adopt_layout(rows, "f16", np.arange(nlist + 1) * (n // nlist), cent.cpu().numpy(), metric=P.IVF_IP,
+                               compute_stream=stream, copy_stream=torch.cuda.Stream())
+    index.ivf_set_batch_mode(1)
+    took = {}
+    for nq in (60000, 15000):
+        q = torch.randn(nq, d, generator=g, device="cuda")
+        ids, dists = torch.empty(nq, k, dtype=torch.int64, device="cuda"), torch.empty(nq, k, device="cuda")
+        index.ivf_reserve(nq, 2, k)
+        torch.cuda.synchronize()
+        times = []
+        for _ in range(6):
+            e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            e0.record(stream)
+            index.ivf_search_device(q, 2, k, ids, dists)
+            e1.record(stream)
+            torch.cuda.synchronize()
+            times.append(e0.elapsed_time(e1))
+        took[nq] = min(times)
+    assert took[60000] < 6 * took[15000], took
+    index.close()
