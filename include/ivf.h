@@ -184,8 +184,17 @@ int ivf_search_device(ivf_index* index, const float* q_dev, int32_t nq, int32_t 
                       int32_t k, int64_t* ids_dev, float* dists_dev);
 
 /* Sizes the workspace for searches up to (nq, nprobe, k) so that later calls allocate nothing (a list-major
- * batch of rows whose d is a multiple of 64 sizes more of it in the first such call). */
+ * batch of rows whose d is a multiple of 64 sizes more of it in the first such call).  List-major batches need
+ * about 530 KB per query and lane beside what the rows themselves take; over rows of other widths, where they
+ * are searched in slices, for at most 4096 queries (2.2 GB), and only when a batch of up to these sizes may be
+ * searched so. */
 int ivf_reserve(ivf_index* index, int32_t nq, int32_t nprobe, int32_t k);
+
+/* Bounds the device memory that the list-major workspace of each lane may take (default: no bound) and gives
+ * back what it holds; waits for the device.  What does not fit: over rows whose d is a multiple of 64 a
+ * list-major batch fails with IVF_ENOMEM, as when the device has no more memory; over rows of other widths the
+ * batch is searched in smaller slices, or query by query when not even four queries fit. */
+int ivf_limit_batch_memory(ivf_index* index, size_t bytes);
 
 /*
  * ivf_search_device for callers that cannot allocate: code under HIP graph capture, tight serving

@@ -25,7 +25,7 @@ EXPORTS = [
     "ivf_search", "ivf_search_device", "ivf_search_device_noalloc", "ivf_reserve", "ivf_coarse_scores", "ivf_probe",
     "ivf_resident", "ivf_batched_scores", "ivf_get_layout", "ivf_profile_enable", "ivf_profile_read",
     "ivf_profile_reset", "ivf_set_host_threads", "ivf_set_pipeline_depth", "ivf_synchronize",
-    "ivf_set_batch_mode", "ivf_cache_configure", "ivf_cache_end_round", "ivf_cache_hotness",
+    "ivf_set_batch_mode", "ivf_limit_batch_memory", "ivf_cache_configure", "ivf_cache_end_round", "ivf_cache_hotness",
     "ivf_schedule", "ivf_host_scan", "ivf_host_scan_capacity", "ivf_prefetch_amount", "ivf_prefetch_plan", "ivf_cache_plan", "ivf_strerror", "ivf_last_error",
 ]
 
@@ -94,6 +94,7 @@ def load():
     L.ivf_set_pipeline_depth.argtypes = [vp, i32]
     L.ivf_synchronize.argtypes = [vp]
     L.ivf_set_batch_mode.argtypes = [vp, i32]
+    L.ivf_limit_batch_memory.argtypes = [vp, sz]
     L.ivf_cache_configure.argtypes = [vp, C.c_float, C.c_float, C.c_float, C.c_float]
     L.ivf_cache_end_round.argtypes = [vp, C.POINTER(CacheStats)]
     L.ivf_cache_hotness.argtypes = [vp, vp]
@@ -325,6 +326,9 @@ class Index:
 
     def ivf_set_batch_mode(self, mode):
         _check(load().ivf_set_batch_mode(self._h, mode))
+
+    def ivf_limit_batch_memory(self, limit):
+        _check(load().ivf_limit_batch_memory(self._h, limit))
 
 
 def ivf_build_layout(vectors, dtype, centroids, assign, ids=None, metric=IVF_IP,

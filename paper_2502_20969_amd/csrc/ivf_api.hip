@@ -102,6 +102,7 @@ struct Workspace {
     size_t h_scores_len = 0;
     // batched (list-major) search
     int b_nq = 0, b_nprobe = 0;
+    bool b_settled = false;       // any_width_workspace has sized it for what the rest is sized for
     void* d_q_store = nullptr;
     float* d_thr = nullptr;
     uint32_t* d_thr_part = nullptr;
@@ -180,7 +181,7 @@ struct ivf_index {
     std::vector<uint64_t> rows_desc_prefix;   // prefix sums of list sizes, largest first
     int resident_grid[2] = {0, 0};            // scan workgroups resident at once, for kprime <= 64 / > 64
     int batched_grid = 0;                     // resident workgroups of the batched scan kernel
-    bool any_width_off = false;               // no memory for the list-major workspace of any_width_eligible batches
+    size_t batch_memory = SIZE_MAX;           // bytes the list-major workspace of a lane may take (ivf_limit_batch_memory)
     int batch_mode = 0;                       // 0 auto, 1 always query by query, 2 list-major when eligible
     unsigned int* d_row_norm_max = nullptr;   // largest squared row norm (float bits); device placement
     float* d_row_norm = nullptr;              // squared norm of every row; device placement with squared L2
@@ -246,6 +247,17 @@ void free_sched(SchedSpace& s) {
     s = SchedSpace{};
 }
 
+void free_batched_workspace(Workspace& w) {
+    dfree(w.d_thr_part); dfree(w.d_cand_score); dfree(w.d_eps); dfree(w.d_qq);
+    dfree(w.d_q_store); dfree(w.d_thr); dfree(w.d_list_count); dfree(w.d_cursor); dfree(w.d_qstart);
+    dfree(w.d_tstart); dfree(w.d_qidx); dfree(w.d_tasks); dfree(w.d_cand_count); dfree(w.d_cand_row);
+    hfree(w.h_overflow);
+    w.d_thr_part = nullptr; w.d_cand_score = nullptr; w.d_eps = nullptr; w.d_qq = nullptr;
+    w.d_q_store = nullptr; w.d_thr = nullptr; w.d_list_count = w.d_cursor = w.d_qstart = w.d_tstart = w.d_qidx = nullptr;
+    w.d_tasks = nullptr; w.d_cand_count = w.d_cand_row = nullptr; w.h_overflow = w.hd_overflow = nullptr;
+    w.b_nq = w.b_nprobe = 0;
+}
+
 void free_workspace(Workspace& w) {
     dfree(w.d_q); dfree(w.d_scores); dfree(w.d_probe);
     dfree(w.slots.base); dfree(w.slots.grow); dfree(w.slots.nrows); dfree(w.slots.rprefix);
@@ -256,10 +268,7 @@ void free_workspace(Workspace& w) {
     dfree(w.d_redo_id); dfree(w.d_redo_key); hfree(w.h_flag);
     hfree(w.h_q); hfree(w.h_done); hfree(w.h_probe); hfree(w.h_out_ids); hfree(w.h_out_dists);
     hfree(w.h_cand); hfree(w.h_cand_count); hfree(w.h_scores);
-    dfree(w.d_thr_part); dfree(w.d_cand_score); dfree(w.d_eps); dfree(w.d_qq);
-    dfree(w.d_q_store); dfree(w.d_thr); dfree(w.d_list_count); dfree(w.d_cursor); dfree(w.d_qstart);
-    dfree(w.d_tstart); dfree(w.d_qidx); dfree(w.d_tasks); dfree(w.d_cand_count); dfree(w.d_cand_row);
-    hfree(w.h_overflow);
+    free_batched_workspace(w);
     w = Workspace{};
 }
 
@@ -526,8 +535,8 @@ int enqueue_merge(ivf_index* ix, const float* q_dev, int nq, int nprobe, int k, 
     return IVF_OK;
 }
 
-// The exact second pass for the queries whose merge could not prove its result; queries that were
-// proven cost one workgroup round that leaves at once.
+// The exact second pass for the queries whose merge could not prove its result: the workgroups of the call are
+// shared by those, and leave at once when there are none.
 int enqueue_redo(ivf_index* ix, const float* q_dev, int nq, int nprobe, int k, int kprime, bool with_host,
                  int64_t* out_ids, float* out_dists) {
     Workspace& w = *ix->cw;
@@ -586,62 +595,96 @@ bool worth_list_major(const ivf_index* ix, int nq, int nprobe, int k) {
     return scan_us(ix, (double)ix->n * picked) * (1.0 - once) >= (k > 56 ? 20.0 : 50.0);
 }
 
+// whether it holds for any batch of up to these sizes: it grows with all of them
+bool may_be_worth(const ivf_index* ix, int nq, int nprobe, int k) { return worth_list_major(ix, nq, nprobe, k); }
+
 // Batches of automatic mode over rows that are not whole blocks of 64 elements are searched list-major
 // too, completed on the stream by the exact pass (enqueue_any_width), so that they keep what the
 // query-by-query path promises them: outputs complete in stream order.  Not while the stream is
 // being captured, where their workspace could not be sized.
-bool any_width_eligible(const ivf_index* ix, int nq, int nprobe, int k, hipStream_t stream) {
-    if (ix->batch_mode != 0 || nq < 4 || ix->d % 64 == 0 || ix->any_width_off) return false;
-    if (ix->row_bytes < 16 || !has_list_major(ix) || !worth_list_major(ix, nq, nprobe, k)) return false;
-    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
-    return hipStreamIsCapturing(stream, &st) == hipSuccess && st == hipStreamCaptureStatusNone;
+bool any_width_index(const ivf_index* ix, int nq) {
+    return ix->batch_mode == 0 && nq >= 4 && ix->d % 64 != 0 && ix->row_bytes >= 16 && has_list_major(ix);
 }
 
+int alloc_batched_workspace(ivf_index* ix, Workspace& w, int nq, int nprobe) {
+    const size_t nqz = nq, nl = ix->nlist;
+    const uint64_t task_cap = batched_task_bound(ix->h_off.data(), ix->nlist, nq, ix->dtype);
+    size_t left = ix->batch_memory;
+    auto get = [&](auto** p, size_t bytes) -> int {
+        if (bytes > left) return fail(IVF_ENOMEM, "the list-major workspace of %d queries is above the limit of %zu bytes", nq, ix->batch_memory);
+        left -= bytes;
+        HIP_TRY(hipMalloc((void**)p, bytes));
+        return IVF_OK;
+    };
+    int rc;
+    if ((rc = get(&w.d_q_store, nqz * batched_query_stride(ix->d, ix->dtype) * (ix->dtype == IVF_F32 ? 4 : 2)))) return rc;
+    if ((rc = get(&w.d_qq, nqz * sizeof(float)))) return rc;
+    if ((rc = get(&w.d_thr, nqz * sizeof(float)))) return rc;
+    if ((rc = get(&w.d_thr_part, batched_sample_words(nq) * sizeof(uint32_t)))) return rc;
+    if ((rc = get(&w.d_list_count, (nl + 2) * sizeof(uint32_t)))) return rc;      // + a place past the end and the scan's task counter
+    if ((rc = get(&w.d_cursor, nl * sizeof(uint32_t)))) return rc;
+    if ((rc = get(&w.d_qstart, (nl + 1) * sizeof(uint32_t)))) return rc;
+    if ((rc = get(&w.d_tstart, (nl + 1) * sizeof(uint32_t)))) return rc;
+    if ((rc = get(&w.d_qidx, nqz * nprobe * sizeof(uint32_t)))) return rc;
+    if ((rc = get(&w.d_tasks, task_cap * sizeof(BatchTask)))) return rc;
+    if ((rc = get(&w.d_cand_count, nqz * kCountStride * sizeof(uint32_t)))) return rc;
+    if ((rc = get(&w.d_cand_row, nqz * kCandCap * sizeof(uint32_t)))) return rc;
+    if ((rc = get(&w.d_cand_score, nqz * kCandCap * sizeof(float)))) return rc;
+    if ((rc = get(&w.d_eps, nqz * sizeof(float)))) return rc;
+    // (the flags of a call that is searched slice by slice are kept side by side)
+    HIP_TRY(hipHostMalloc(&w.h_overflow, (size_t)std::max(nq, w.nq) * sizeof(int32_t)));
+    HIP_TRY(hipHostGetDevicePointer((void**)&w.hd_overflow, w.h_overflow, 0));
+    w.b_nq = nq; w.b_nprobe = nprobe;
+    return IVF_OK;
+}
+
+// All of it or, on a failure, nothing: what was obtained is given back.
 int ensure_batched_workspace(ivf_index* ix, int nq, int nprobe) {
     Workspace& w = *ix->cw;
     if (nq <= w.b_nq && nprobe <= w.b_nprobe) return IVF_OK;
     const int nq2 = std::max(nq, w.b_nq), np2 = std::max(nprobe, w.b_nprobe);
     HIP_TRY(hipDeviceSynchronize());
-    dfree(w.d_thr_part); dfree(w.d_cand_score); dfree(w.d_eps); dfree(w.d_qq);
-    dfree(w.d_q_store); dfree(w.d_thr); dfree(w.d_list_count); dfree(w.d_cursor); dfree(w.d_qstart);
-    dfree(w.d_tstart); dfree(w.d_qidx); dfree(w.d_tasks); dfree(w.d_cand_count); dfree(w.d_cand_row);
-    hfree(w.h_overflow);
-    w.d_thr_part = nullptr; w.d_cand_score = nullptr; w.d_eps = nullptr; w.d_qq = nullptr;
-    w.d_q_store = nullptr; w.d_thr = nullptr; w.d_list_count = w.d_cursor = w.d_qstart = w.d_tstart = w.d_qidx = nullptr;
-    w.d_tasks = nullptr; w.d_cand_count = w.d_cand_row = nullptr; w.h_overflow = w.hd_overflow = nullptr;
-    w.b_nq = w.b_nprobe = 0;
-    const size_t nqz = nq2, nl = ix->nlist;
-    const uint64_t task_cap = batched_task_bound(ix->h_off.data(), ix->nlist, nq2, ix->dtype);
-    HIP_TRY(hipMalloc(&w.d_q_store, nqz * batched_query_stride(ix->d, ix->dtype) * (ix->dtype == IVF_F32 ? 4 : 2)));
-    HIP_TRY(hipMalloc(&w.d_qq, nqz * sizeof(float)));
-    HIP_TRY(hipMalloc(&w.d_thr, nqz * sizeof(float)));
-    HIP_TRY(hipMalloc(&w.d_thr_part, batched_sample_words(nq2) * sizeof(uint32_t)));
-    HIP_TRY(hipMalloc(&w.d_list_count, (nl + 2) * sizeof(uint32_t)));      // + a place past the end and the scan's task counter
-    HIP_TRY(hipMalloc(&w.d_cursor, nl * sizeof(uint32_t)));
-    HIP_TRY(hipMalloc(&w.d_qstart, (nl + 1) * sizeof(uint32_t)));
-    HIP_TRY(hipMalloc(&w.d_tstart, (nl + 1) * sizeof(uint32_t)));
-    HIP_TRY(hipMalloc(&w.d_qidx, nqz * np2 * sizeof(uint32_t)));
-    HIP_TRY(hipMalloc(&w.d_tasks, task_cap * sizeof(BatchTask)));
-    HIP_TRY(hipMalloc(&w.d_cand_count, nqz * kCountStride * sizeof(uint32_t)));
-    HIP_TRY(hipMalloc(&w.d_cand_row, nqz * kCandCap * sizeof(uint32_t)));
-    HIP_TRY(hipMalloc(&w.d_cand_score, nqz * kCandCap * sizeof(float)));
-    HIP_TRY(hipMalloc(&w.d_eps, nqz * sizeof(float)));
-    HIP_TRY(hipHostMalloc(&w.h_overflow, nqz * sizeof(int32_t)));
-    HIP_TRY(hipHostGetDevicePointer((void**)&w.hd_overflow, w.h_overflow, 0));
-    w.b_nq = nq2; w.b_nprobe = np2;
-    return IVF_OK;
+    free_batched_workspace(w);
+    const int rc = alloc_batched_workspace(ix, w, nq2, np2);
+    if (rc) {
+        free_batched_workspace(w);
+        (void)hipGetLastError();
+    }
+    return rc;
 }
 
-// The workspaces of an any_width_eligible batch; false when there is no memory for the list-major one (the
-// batch is then searched query by query, and so are later ones).
-bool any_width_workspace(ivf_index* ix, int nq, int nprobe, int k, int* rc) {
-    if ((*rc = ensure_workspace(ix, nq, nprobe, k))) return false;
-    const int r = ensure_batched_workspace(ix, nq, nprobe);
-    if (r == IVF_OK) return true;
-    (void)hipGetLastError();
-    if (r == IVF_ENOMEM) ix->any_width_off = true;
-    else *rc = r;
-    return false;
+// Batches of an any_width_index are searched list-major in slices of up to this many queries, which bounds their
+// workspace: about 530 KB a query, 2.2 GB.
+constexpr int kAnyWidthSlice = 4096;
+
+// Sizes the workspaces for batches of up to (nq, nprobe, k) over an any_width_index: the list-major one when some batch
+// of up to the sizes of the ordinary one may use it, for as many queries as there is memory for.  That is settled
+// once for each size of the ordinary workspace, so that a call that fits it allocates nothing.
+int any_width_workspace(ivf_index* ix, int nq, int nprobe, int k) {
+    int rc = ensure_workspace(ix, nq, nprobe, k);
+    Workspace& w = *ix->cw;
+    if (rc || w.b_settled) return rc;
+    if (may_be_worth(ix, std::min(w.nq, kAnyWidthSlice), w.nprobe, w.k)) {
+        for (int m = std::min(w.nq, kAnyWidthSlice); m >= 4; m /= 2) {
+            rc = ensure_batched_workspace(ix, m, w.nprobe);
+            if (rc != IVF_ENOMEM) break;
+        }
+        if (rc && rc != IVF_ENOMEM) return rc;
+    }
+    w.b_settled = true;
+    return IVF_OK;
+}
+// queries per slice of a list-major search of such a batch; 0: it is searched query by query.  Both workspaces are sized.
+int any_width_slice(ivf_index* ix, int nq, int nprobe, int k, int* rc) {
+    *rc = IVF_OK;
+    if (!any_width_index(ix, nq)) return 0;
+    hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+    if (hipStreamIsCapturing(ix->cs, &st) != hipSuccess) { (void)hipGetLastError(); return 0; }
+    if (st != hipStreamCaptureStatusNone) return 0;
+    if ((*rc = any_width_workspace(ix, nq, nprobe, k))) return 0;
+    const Workspace& w = *ix->cw;
+    const int m = std::min(nq, w.b_nq);
+    return m >= 4 && nprobe <= w.b_nprobe && worth_list_major(ix, m, nprobe, k) ? m : 0;
 }
 
 // the parts of the batched scan's arguments that do not depend on the call
@@ -665,8 +708,9 @@ static void fill_batched_args(const ivf_index* ix, const Workspace& w, BatchedAr
 // coarse + select for the batch, then the list-major scan and the final ranking into (out_ids,
 // out_dists) (as the device addresses them); the overflow flags land in the workspace's pinned array
 // with_redo: the merge also marks the queries that overflowed for an exact pass on the device (enqueue_redo)
+// flags_at: where this call's overflow flags start
 int enqueue_batched(ivf_index* ix, const float* q_dev, int nq, int nprobe, int k, int64_t* out_ids, float* out_dists,
-                    bool with_redo = false) {
+                    bool with_redo = false, int flags_at = 0) {
     Workspace& w = *ix->cw;
     int rc;
     if ((rc = enqueue_probe(ix, q_dev, nq, nprobe, 1, false, true))) return rc;
@@ -674,6 +718,7 @@ int enqueue_batched(ivf_index* ix, const float* q_dev, int nq, int nprobe, int k
     BatchedArgs b{};
     fill_batched_args(ix, w, b);
     b.q = q_dev; b.out_ids = out_ids; b.out_dists = out_dists;
+    b.overflow = w.hd_overflow + flags_at;
     b.rows_counter = ix->profiling ? ix->d_prof_rows : nullptr;
     if (with_redo) { b.redo_flag = w.d_redo_flag; b.redo_thr = w.d_redo_thr; b.redo_ticket = w.d_redo_ticket; }
     b.nq = nq; b.nprobe = nprobe; b.k = k; b.kprime = kprime_for(k);
@@ -682,6 +727,25 @@ int enqueue_batched(ivf_index* ix, const float* q_dev, int nq, int nprobe, int k
     if ((rc = prof_events(ix, 3, &m0, &m1))) return rc;
     HIP_TRY(launch_batched(b, ix->batched_grid, ix->cs, e0, e1));
     if (m0) { HIP_TRY(hipEventRecord(m0, ix->cs)); HIP_TRY(hipEventRecord(m1, ix->cs)); }
+    return IVF_OK;
+}
+
+// A batch of an any_width_index, `slice` queries after the other: list-major, then the exact pass for the queries
+// that the merge could not settle (redo; without it they are left marked).  probe_host: room for the selected
+// clusters of all queries, or nullptr.
+int enqueue_any_width(ivf_index* ix, const float* q_dev, int nq, int nprobe, int k, int slice, bool redo, int64_t* out_ids,
+                      float* out_dists, int32_t* probe_host) {
+    int rc;
+    for (int at = 0; at < nq; at += slice) {
+        const int m = std::min(slice, nq - at);
+        const float* q = q_dev + (size_t)at * ix->d;
+        int64_t* ids = out_ids + (size_t)at * k;
+        float* dists = out_dists + (size_t)at * k;
+        if ((rc = enqueue_batched(ix, q, m, nprobe, k, ids, dists, true, at))) return rc;
+        if (probe_host)
+            HIP_TRY(hipMemcpyAsync(probe_host + (size_t)at * nprobe, ix->cw->d_probe, (size_t)m * nprobe * sizeof(int32_t), hipMemcpyDeviceToHost, ix->cs));
+        if (redo && (rc = enqueue_redo(ix, q, m, nprobe, k, kprime_for(k), false, ids, dists))) return rc;
+    }
     return IVF_OK;
 }
 
@@ -935,8 +999,8 @@ extern "C" int ivf_reserve(ivf_index* ix, int32_t nq, int32_t nprobe, int32_t k)
     }
     for (size_t i = 0; i < ix->lanes.size(); ++i) {
         use_lane(ix, i);
-        int rc = ensure_workspace(ix, nq, std::min(nprobe, ix->nlist), k);
-        if (!rc && any_width_eligible(ix, nq, nprobe, k, ix->cs)) (void)any_width_workspace(ix, nq, std::min(nprobe, ix->nlist), k, &rc);
+        const int np = std::min(nprobe, ix->nlist);
+        int rc = any_width_index(ix, nq) ? any_width_workspace(ix, nq, np, k) : ensure_workspace(ix, nq, np, k);
         if (rc) { use_lane(ix, 0); return rc; }
     }
     use_lane(ix, 0);
@@ -1053,6 +1117,21 @@ extern "C" int ivf_set_batch_mode(ivf_index* ix, int32_t mode) {
     return IVF_OK;
 }
 
+extern "C" int ivf_limit_batch_memory(ivf_index* ix, size_t bytes) {
+    if (!ix) return fail(IVF_EINVAL, "index is NULL");
+    for (size_t i = 0; i < ix->lanes.size(); ++i) {
+        int rc = settle_lane(ix, i);
+        if (rc) return rc;
+    }
+    HIP_TRY(hipDeviceSynchronize());
+    for (auto& l : ix->lanes) {
+        free_batched_workspace(l.ws);
+        l.ws.b_settled = false;
+    }
+    ix->batch_memory = bytes;
+    return IVF_OK;
+}
+
 extern "C" int ivf_search_device(ivf_index* ix, const float* q_dev, int32_t nq, int32_t nprobe,
                                  int32_t k, int64_t* ids_dev, float* dists_dev) {
     int rc = check_query_args(ix, q_dev, nq, nprobe);
@@ -1070,9 +1149,8 @@ extern "C" int ivf_search_device(ivf_index* ix, const float* q_dev, int32_t nq, 
     ix->lanes[lane].quiet = false;
     ix->next_lane = (ix->next_lane + 1) % ix->lanes.size();
     if (batched_eligible(ix, nq, nprobe)) rc = run_batched(ix, lane, q_dev, nq, nprobe, k, ids_dev, dists_dev, true);
-    else if (any_width_eligible(ix, nq, nprobe, k, ix->cs) && any_width_workspace(ix, nq, nprobe, k, &rc)) {
-        rc = enqueue_batched(ix, q_dev, nq, nprobe, k, ids_dev, dists_dev, true);
-        if (rc == IVF_OK) rc = enqueue_redo(ix, q_dev, nq, nprobe, k, kprime_for(k), false, ids_dev, dists_dev);
+    else if (const int slice = any_width_slice(ix, nq, nprobe, k, &rc)) {
+        rc = enqueue_any_width(ix, q_dev, nq, nprobe, k, slice, true, ids_dev, dists_dev, nullptr);
     } else if (rc == IVF_OK) {
         // one stream: the exact second pass follows every merge on the stream, outputs are complete in
         // stream order.  Several: it is decided when the lane is next needed or in ivf_synchronize.
@@ -1201,12 +1279,13 @@ extern "C" int ivf_search(ivf_index* ix, const float* q_out, int32_t nq, int32_t
         }
         return IVF_OK;
     }
-    if (any_width_eligible(ix, nq, nprobe, k, ix->cs) && any_width_workspace(ix, nq, nprobe, k, &rc)) {
-        if ((rc = enqueue_batched(ix, w.d_q, nq, nprobe, k, w.hd_out_ids, w.hd_out_dists, true))) return rc;
-        if (stats) HIP_TRY(hipMemcpyAsync(w.h_probe, w.d_probe, (size_t)nq * nprobe * sizeof(int32_t), hipMemcpyDeviceToHost, ix->cs));
+    if (const int slice = any_width_slice(ix, nq, nprobe, k, &rc)) {
+        // one slice: the exact pass is launched when there is something for it to do
+        const bool whole = slice == nq;
+        if ((rc = enqueue_any_width(ix, w.d_q, nq, nprobe, k, slice, !whole, w.hd_out_ids, w.hd_out_dists, stats ? w.h_probe : nullptr))) return rc;
         HIP_TRY(hipStreamSynchronize(ix->cs));
         for (int qi = 0; qi < nq; ++qi) st.n_exact_gpu += w.h_overflow[qi] != 0 ? 1 : 0;
-        if (st.n_exact_gpu) {
+        if (st.n_exact_gpu && whole) {
             if ((rc = enqueue_redo(ix, w.d_q, nq, nprobe, k, kprime, false, w.hd_out_ids, w.hd_out_dists))) return rc;
             HIP_TRY(hipStreamSynchronize(ix->cs));
         }

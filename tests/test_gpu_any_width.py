@@ -191,3 +191,81 @@ def test_small_batches_of_automatic_mode(dtype, d, nq, nprobe, k):
     assert np.array_equal(di.cpu().numpy(), mi) and np.array_equal(dd.cpu().numpy(), md)
     assert st.bytes_gpu == mst.bytes_gpu and st.n_probed == mst.n_probed and st.hit_rate == mst.hit_rate
     index.close()
+
+
+NO_LIMIT = (1 << 64) - 1
+
+
+def _device_search(index, q, nprobe, k):
+    """Complete in stream order, without ivf_synchronize."""
+    q_dev = torch.from_numpy(q).cuda()
+    ids, dists = torch.empty(q.shape[0], k, dtype=torch.int64, device="cuda"), torch.empty(q.shape[0], k, device="cuda")
+    torch.cuda.synchronize()
+    index.ivf_search_device(q_dev, nprobe, k, ids, dists)
+    torch.cuda.synchronize()
+    return ids.cpu().numpy(), dists.cpu().numpy()
+
+
+def test_batches_that_do_not_fit_their_memory():
+    """What the list-major workspace did get is given back when the rest of it is refused; the batch is searched
+    in slices, or query by query when nothing fits, and smaller batches stay list-major."""
+    n, d, nlist, nq, nprobe, k = 24000, 200, 8, 300, 5, 10
+    rows, off, cent, q = _problem(4, "f32", n, d, nlist, nq, 7)
+    index = _adopt(rows, "f32", off, cent, "ip")
+    index.ivf_set_batch_mode(1)
+    (wi, wd), each = _rows_scanned(index, q, nprobe, k)            # sizes the rest of the workspace
+    index.ivf_set_batch_mode(0)
+    torch.cuda.synchronize()
+    free = torch.cuda.mem_get_info()[0]
+    for limit, low, high in ((0, each, each), (1 << 20, each, each), (44 << 20, n + 1, each // 4), (NO_LIMIT, 1, n),
+                             (9 << 20, each, each)):        # room for nine queries, which share too little
+        index.ivf_limit_batch_memory(limit)
+        for _ in range(2):                                          # a refusal is not asked for again
+            (gi, gd), read = _rows_scanned(index, q, nprobe, k)
+            assert low <= read <= high, (limit, read)
+            assert np.array_equal(gi, wi) and np.array_equal(gd, wd)
+        di, dd = _device_search(index, q, nprobe, k)
+        assert np.array_equal(di, wi) and np.array_equal(dd, wd)
+        held = free - torch.cuda.mem_get_info()[0]
+        assert held <= min(limit, 300 * (600 << 10)) + (16 << 20), (limit, held)
+        if limit >= 44 << 20:                                       # a batch of which the slices hold all
+            (si, sd), read = _rows_scanned(index, q[:40], nprobe, k)
+            assert 0 < read <= n and np.array_equal(si, wi[:40]) and np.array_equal(sd, wd[:40])
+    index.close()
+
+
+def test_slices_finish_their_own_queries():
+    """Batches searched in slices: every slice's tied queries get the exact pass before the next slice takes the
+    workspace, on the stream, and are counted."""
+    n, d, nlist, nq, nprobe, k = 24000, 72, 4, 90, 3, 7
+    rng = np.random.default_rng(6)
+    rows_np = rng.standard_normal((n, d)).astype(np.float16)
+    rows_np[:18000] = np.float16(0.125)
+    off = np.arange(0, n + 1, n // nlist, dtype=np.int64)
+    cent = rng.standard_normal((nlist, d)).astype(np.float32)
+    cent[0], cent[1], cent[2] = 1.0, 0.9, 0.8
+    index = _adopt(torch.from_numpy(rows_np).cuda(), "f16", off, cent, "ip", rng.permutation(n).astype(np.int64))
+    q = np.abs(rng.standard_normal((nq, d))).astype(np.float32)
+    q[::3] *= -1.0                                                  # these select the list of different rows first
+    (oi, od, ost), (ti, td) = index.ivf_search(q, nprobe, k, with_stats=True), _device_search(index, q, nprobe, k)
+    index.ivf_limit_batch_memory(20 << 20)
+    (gi, gd, st), (di, dd) = index.ivf_search(q, nprobe, k, with_stats=True), _device_search(index, q, nprobe, k)
+    index.ivf_set_batch_mode(1)
+    pi, pd, pst = index.ivf_search(q, nprobe, k, with_stats=True)
+    for i, s in ((oi, od), (ti, td), (gi, gd), (di, dd)):
+        assert np.array_equal(i, pi) and np.array_equal(s, pd)
+    assert st.n_exact_gpu == ost.n_exact_gpu >= nq // 2
+    assert st.bytes_gpu == ost.bytes_gpu == pst.bytes_gpu and st.n_probed == pst.n_probed
+    index.close()
+
+
+def test_more_queries_than_a_slice_holds():
+    n, d, nlist, nq, nprobe, k = 24000, 60, 8, 4103, 5, 3
+    rows, off, cent, q = _problem(9, "f16", n, d, nlist, nq, 7)
+    index = _adopt(rows, "f16", off, cent, "l2")
+    (gi, gd), read = _rows_scanned(index, q, nprobe, k)
+    assert 0 < read <= 2 * n
+    index.ivf_set_batch_mode(1)
+    pi, pd = index.ivf_search(q, nprobe, k)
+    assert np.array_equal(gi, pi) and np.array_equal(gd, pd)
+    index.close()
