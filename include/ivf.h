@@ -237,7 +237,8 @@ int ivf_synchronize(ivf_index* index);
  *   0  automatic: batches of 4 or more queries on an index that has the list-major path are
  *      searched list-major (each selected cluster is read once per group of up to 32 queries,
  *      16 of fp32 rows, that probe it), unless they are so small that query by query is faster
- *      (bytes_gpu counts each cluster once all the same).  So are larger batches on a device-resident index whose d
+ *      (bytes_gpu counts each cluster once all the same, as the list-major search does that such a
+ *      batch may also get).  So are batches that are expected to gain by it on a device-resident index whose d
  *      is no multiple of 64, but these behave like a query-by-query call in every respect: outputs
  *      of ivf_search_device are complete in stream order, bytes_gpu counts every query's clusters,
  *      and a call under stream capture is enqueued query by query.  Anything else query by query

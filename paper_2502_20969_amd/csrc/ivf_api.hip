@@ -563,40 +563,66 @@ bool has_list_major(const ivf_index* ix) {
     return batched_scan_lds(ix->d, ix->dtype) <= ix->max_lds;              // a group's queries must fit LDS
 }
 
-// Time that query-by-query scans of `rows` rows take, us: about 4.8 TB/s and at most 10 rows a nanosecond.
-double scan_us(const ivf_index* ix, double rows) { return std::max(rows * (double)ix->row_bytes / 4.8e6, rows / 1e4); }
+// Query by query, 24 to 56 results of rows of up to 256 bytes: the merge's cut comes from 64 group maxima, and so close to
+// all of them it lets many candidates of narrow rows pass; the pool overflows often and the slower way behind it
+// takes 20 to 45 us more.  Whole calls, us, list-major / query by query: 10 queries x 6 clusters of 64 bf16, k 50 64 / 97,
+// 13 x 3 of 64 fp32, k 45 61 / 89, 17 x 7 of 64 fp16, k 31 60 / 82; wider rows, 5 x 9 of 504 fp16, k 44 60 / 44.
+bool merge_overflows(const ivf_index* ix, int k) { return k >= 24 && k <= 56 && ix->row_bytes <= 256; }
 
-// Automatic mode: batches so small that even the largest lists, scanned query by query, take less than the launches in
-// front of a list-major scan and what that loses by its few tasks.  Whole calls, us, list-major / query by query,
-// with that bound: 16 queries x 12 clusters of 384 fp16 (19) 63 / 45, 14 x 6 of 256 fp32 (28) 64 / 44, 4 x 144 of 64
-// bf16 (30) 68 / 58, 10 x 9 of 1024 bf16 (30) 66 / 49, 17 x 7 of 256 fp16 (38) 65 / 58, 5 x 123 of 512 fp16 (39) 75 / 68,
-// 11 x 23 of 768 bf16 (46) 70 / 50, 101 x 4 of 512 bf16 (86) 84 / 85.
-bool small_batch(const ivf_index* ix, int nq, int nprobe) { return scan_us(ix, (double)most_rows(ix, nprobe) * nq) < 60.0; }
+// Automatic mode, rows of whole blocks: batches so small that even the largest lists, scanned query by query at 4.8 TB/s
+// and at most 10 rows a nanosecond, take less than the launches in front of a list-major scan and what that
+// loses by its few tasks.  Whole calls, us, list-major / query by query, with that bound: 16 queries x 12 clusters of
+// 384 fp16 (19) 63 / 45, 14 x 6 of 256 fp32 (28) 64 / 44, 4 x 144 of 64 bf16 (30) 68 / 58, 10 x 9 of 1024 bf16 (30) 66 / 49,
+// 17 x 7 of 256 fp16 (38) 65 / 58, 5 x 123 of 512 fp16 (39) 75 / 68, 11 x 23 of 768 bf16 (46) 70 / 50, 101 x 4 of
+// 512 bf16 (86) 84 / 85.  Up to eight of them in flight the order is the same (16 x 12 of 384 fp16: 32 / 25 us a batch).
+bool small_batch(const ivf_index* ix, int nq, int nprobe, int k) {
+    const double rows = (double)most_rows(ix, nprobe) * nq;
+    return std::max(rows * (double)ix->row_bytes / 4.8e6, rows / 1e4) < 60.0 && !merge_overflows(ix, k);
+}
 
 // list-major by the batch mode and the number of queries (modes 0 and 2), for rows of whole blocks
 bool list_major_mode(const ivf_index* ix, int nq) {
     if (ix->batch_mode == 1 || nq < 2 || ix->d % 64 != 0) return false;
     return has_list_major(ix) && (ix->batch_mode == 2 || nq >= 4);
 }
-bool batched_eligible(const ivf_index* ix, int nq, int nprobe) {
-    return list_major_mode(ix, nq) && (ix->batch_mode == 2 || !small_batch(ix, nq, nprobe));
+bool batched_eligible(const ivf_index* ix, int nq, int nprobe, int k) {
+    return list_major_mode(ix, nq) && (ix->batch_mode == 2 || !small_batch(ix, nq, nprobe, k));
 }
 
-// Whether a batch over rows of any width shares enough for the launches in front of a list-major scan (sample, tasks:
-// 20 to 25 us) to pay: what query-by-query scans of clusters of mean size would take, less what one scan of
-// their union takes, were the queries independent.  From 50 us of that on (20 for more than 56 results, whose
-// query-by-query merge is the longer one) every batch measured is as fast or faster list-major; below it
-// either way may be, and the query-by-query one is kept.  Whole calls, us, list-major / query by query, with the estimate: 21 queries x 58 fp32 (1) 85 / 69, 12 x 47 fp32 (1) 92 / 115, 41 x 80 bf16 (8)
-// 92 / 72, 8 x 1022 bf16 (13) 114 / 86, 53 x 78 fp32 (30) 125 / 172, 48 x 100 fp32 (46) 114 to 120 / 113 to 118, 125 x 83 bf16 with k 93 (45) 175 / 759, 5 x 898 bf16 (58) 157 / 161,
-// 25 x 62 fp16 (86) 72 / 77, 36 x 230 fp32 (127) 88 / 152, 143 x 265 bf16 (200) 116 / 257.
+// Whether a batch over rows of any width is expected to be faster list-major.  Estimates, us, of what differs:
+//   - scanning the rows that the queries select together, query by query, and the union of those once, at 4.8 TB/s and
+//     at most 15 rows a nanosecond each; lists of mean size, queries independent of each other;
+//   - query by query a query has its share of four rounds of workgroups: the largest list that some query will
+//     select takes as long as they need for it, at 4 GB/s each (skewed lists; which queries meet is luck, so this
+//     has to come to more);
+//   - list-major 30 (80) for the launches in front of the scan (sample, tasks) and 0.2 per query (its sample and merge).
+// Fitted to whole calls of 4005 random batches (rows of 16 to 2060 bytes, 4 to 8192 queries, lists even and skewed): list-
+// major then is 15 % slower than query by query in 32 of them (1.44 times at most), and the choice 2.1 % slower
+// than the better way in the geometric mean.  (Every batch that shares rows worth 50 us at 4.8 TB/s: 126, 1.90, 4.3 %.)
+// Of 1459 further ones 4 are so slowed down, by 1.30 at most.
+// Some of them, us, list-major / query by query: 53 queries x 30 clusters of 78 fp32 (1000 lists, 500,000 rows) 73 / 72, 48 x 24 of 100 fp32 (1000,
+// 1 M) 97 / 99, 64 x 40 of 100 fp32 131 / 184, 25 x 200 of 62 fp16 (1000, 2 M) 112 / 298, 4726 x 4 of 50 fp16 (3552, 337,000) 793 / 433,
+// 1300 x 4 of 31 fp32 (8192, 4 M) 392 / 225, 64 x 4 of 888 fp32 (16, 2334) 104 / 67; lists by rank^-1.1: 61 x 26 of 302 bf16 (2540, 2.4 M)
+// 273 / 1126, 123 x 3 of 552 fp16 (586, 554,000) 168 / 644.
+double list_major_gain(const ivf_index* ix, int nq, int nprobe, bool at_most) {
+    const double share = std::min(1.0, (double)nprobe / ix->nlist), n = (double)ix->n;
+    const double per_row = std::max((double)ix->row_bytes / 4.8e6, 1.0 / 1.5e4);
+    const double once = per_row * n * (1.0 - std::pow(1.0 - share, nq)), each = per_row * n * share * nq;
+    const size_t rank = std::min<size_t>((size_t)std::ceil((double)ix->nlist / ((double)nq * nprobe)), ix->nlist);
+    const double wgs = std::max(1.0, std::ceil(4.0 * ix->n_cu * kScanMaxWgPerCu / nq));
+    const double list = (double)(ix->rows_desc_prefix[rank] - ix->rows_desc_prefix[rank - 1]) * (double)ix->row_bytes / (4e3 * wgs);
+    return std::max(each - once - 30.0, list - (at_most ? 0.0 : once) - 80.0) - 0.2 * nq;
+}
 bool worth_list_major(const ivf_index* ix, int nq, int nprobe, int k) {
-    const double share = std::min(1.0, (double)nprobe / ix->nlist), picked = share * nq;
-    const double once = (1.0 - std::pow(1.0 - share, nq)) / picked;        // union / sum of the queries' clusters
-    return scan_us(ix, (double)ix->n * picked) * (1.0 - once) >= (k > 56 ? 20.0 : 50.0);
+    return list_major_gain(ix, nq, nprobe, false) + (merge_overflows(ix, k) ? 30.0 : 0.0) > 0.0;
 }
-
-// whether it holds for any batch of up to these sizes: it grows with all of them
-bool may_be_worth(const ivf_index* ix, int nq, int nprobe, int k) { return worth_list_major(ix, nq, nprobe, k); }
+// whether worth_list_major holds for any batch of up to these sizes (or for none: an upper bound)
+bool may_be_worth(const ivf_index* ix, int nq, int nprobe, int k) {
+    const double merge = k >= 24 && merge_overflows(ix, 24) ? 30.0 : 0.0;
+    for (int m = 4; m <= nq; ++m)
+        if (list_major_gain(ix, m, nprobe, true) + merge > 0.0) return true;
+    return false;
+}
 
 // Batches of automatic mode over rows that are not whole blocks of 64 elements are searched list-major
 // too, completed on the stream by the exact pass (enqueue_any_width), so that they keep what the
@@ -1148,7 +1174,7 @@ extern "C" int ivf_search_device(ivf_index* ix, const float* q_dev, int32_t nq, 
     use_lane(ix, lane);
     ix->lanes[lane].quiet = false;
     ix->next_lane = (ix->next_lane + 1) % ix->lanes.size();
-    if (batched_eligible(ix, nq, nprobe)) rc = run_batched(ix, lane, q_dev, nq, nprobe, k, ids_dev, dists_dev, true);
+    if (batched_eligible(ix, nq, nprobe, k)) rc = run_batched(ix, lane, q_dev, nq, nprobe, k, ids_dev, dists_dev, true);
     else if (const int slice = any_width_slice(ix, nq, nprobe, k, &rc)) {
         rc = enqueue_any_width(ix, q_dev, nq, nprobe, k, slice, true, ids_dev, dists_dev, nullptr);
     } else if (rc == IVF_OK) {
@@ -1260,7 +1286,7 @@ extern "C" int ivf_search(ivf_index* ix, const float* q_out, int32_t nq, int32_t
     ivf_search_stats st{};
 
     if ((rc = stage_queries(ix, q_out, nq))) return rc;
-    if (batched_eligible(ix, nq, nprobe)) {
+    if (batched_eligible(ix, nq, nprobe, k)) {
         // list-major batched search: every selected cluster is read once per group of 32 queries
         // (the merge kernel stores the results in the pinned buffers itself: no copies to wait for)
         if ((rc = run_batched(ix, 0, w.d_q, nq, nprobe, k, w.hd_out_ids, w.hd_out_dists, false))) return rc;

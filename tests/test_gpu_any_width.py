@@ -193,6 +193,47 @@ def test_small_batches_of_automatic_mode(dtype, d, nq, nprobe, k):
     index.close()
 
 
+@pytest.mark.parametrize("dtype,d,n,nlist,nq,nprobe,k,list_major", [
+    ("f16", 20, 200000, 2000, 4096, 2, 5, False),         # a list-major call pays for its queries: 0.57 against 0.26 ms
+    ("f32", 109, 24600, 249, 2772, 3, 12, False),         # 0.35 / 0.18
+    ("f32", 100, 100000, 1000, 64, 200, 20, True),
+    ("f16", 300, 60000, 70, 512, 20, 10, True),
+    ("bf16", 64, 100000, 100, 10, 6, 50, True),           # the query-by-query merge overflows: 97 us against 64
+    ("f32", 64, 30000, 80, 13, 3, 45, True),
+    ("bf16", 64, 100000, 100, 10, 6, 10, False),
+    ("bf16", 256, 30000, 100, 10, 6, 50, False),
+])
+def test_the_faster_way_is_taken(dtype, d, n, nlist, nq, nprobe, k, list_major):
+    rows, off, cent, q = _problem(nq, dtype, n, d, nlist, nq, nlist)
+    index = _adopt(rows, dtype, off, cent, "ip")
+    (gi, gd), read = _rows_scanned(index, q, nprobe, k)
+    index.ivf_set_batch_mode(1)
+    (pi, pd), each = _rows_scanned(index, q, nprobe, k)
+    assert np.array_equal(gi, pi) and np.array_equal(gd, pd)
+    assert read < each if list_major else read == each
+    index.close()
+
+
+def test_a_reserved_size_covers_every_smaller_batch():
+    """A batch of the reserved size is searched query by query, smaller ones list-major: their workspace is there."""
+    n, d, nlist, nprobe, k = 120000, 40, 300, 30, 5
+    rows, off, cent, q = _problem(2, "f16", n, d, nlist, 3000, nlist)
+    index = _adopt(rows, "f16", off, cent, "ip")
+    index.ivf_reserve(3000, nprobe, k)
+    torch.cuda.synchronize()
+    free, routes = torch.cuda.mem_get_info()[0], set()
+    for nq in (3000, 1000, 300, 150, 60, 4):
+        (gi, gd), read = _rows_scanned(index, q[:nq], nprobe, k)
+        routes.add(read <= n)
+        index.ivf_set_batch_mode(1)
+        pi, pd = index.ivf_search(q[:nq], nprobe, k)
+        index.ivf_set_batch_mode(0)
+        assert np.array_equal(gi, pi) and np.array_equal(gd, pd)
+    assert routes == {True, False}
+    assert torch.cuda.mem_get_info()[0] == free
+    index.close()
+
+
 NO_LIMIT = (1 << 64) - 1
 
 
