@@ -275,6 +275,9 @@ int ivf_probe(ivf_index* index, const float* q, int32_t nq, int32_t nprobe, int3
  * 65536 rows.
  */
 int ivf_batched_scores(ivf_index* index, const float* q, int32_t nq, int32_t cluster, float* scores, float* eps);
+/* how the most recent ivf_prefetch copies its clusters: by_kernel of them with one kernel that reads the pinned lists,
+ * by_engine with one engine copy each (either may be NULL; empty clusters count for neither) */
+int ivf_prefetch_ways(const ivf_index* index, int32_t* by_kernel, int32_t* by_engine);
 /* resident clusters in ascending order; *n in: capacity of clusters, out: count */
 int ivf_resident(ivf_index* index, int32_t* clusters, int32_t* n);
 /* layout as built: offsets (host, nlist + 1) and/or ids (host, n); either may be NULL */

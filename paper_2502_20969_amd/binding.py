@@ -23,7 +23,7 @@ DTYPE_CODE = {"f32": IVF_F32, "f16": IVF_F16, "bf16": IVF_BF16}
 EXPORTS = [
     "ivf_build_layout", "ivf_adopt_layout", "ivf_free", "ivf_prefetch", "ivf_prefetch_wait",
     "ivf_search", "ivf_search_device", "ivf_search_device_noalloc", "ivf_reserve", "ivf_coarse_scores", "ivf_probe",
-    "ivf_resident", "ivf_batched_scores", "ivf_get_layout", "ivf_profile_enable", "ivf_profile_read",
+    "ivf_prefetch_ways", "ivf_resident", "ivf_batched_scores", "ivf_get_layout", "ivf_profile_enable", "ivf_profile_read",
     "ivf_profile_reset", "ivf_set_host_threads", "ivf_set_pipeline_depth", "ivf_synchronize",
     "ivf_set_batch_mode", "ivf_limit_batch_memory", "ivf_cache_configure", "ivf_cache_end_round", "ivf_cache_hotness",
     "ivf_schedule", "ivf_host_scan", "ivf_host_scan_capacity", "ivf_prefetch_amount", "ivf_prefetch_plan", "ivf_cache_plan", "ivf_strerror", "ivf_last_error",
@@ -78,6 +78,7 @@ def load():
     L.ivf_free.restype = None
     L.ivf_prefetch.argtypes = [vp, vp, i32, i32, sz, u32, C.POINTER(PrefetchStats)]
     L.ivf_prefetch_wait.argtypes = [vp, C.POINTER(C.c_float)]
+    L.ivf_prefetch_ways.argtypes = [vp, C.POINTER(i32), C.POINTER(i32)]
     L.ivf_search.argtypes = [vp, vp, i32, i32, i32, vp, vp, C.POINTER(SearchStats)]
     L.ivf_search_device.argtypes = [vp, vp, i32, i32, i32, vp, vp]
     L.ivf_search_device_noalloc.argtypes = [vp, vp, i32, i32, i32, vp, vp]
@@ -218,6 +219,11 @@ class Index:
         return ms.value
 
     # -- search ------------------------------------------------------------------------------
+    def ivf_prefetch_ways(self):
+        by_kernel, by_engine = C.c_int32(), C.c_int32()
+        _check(load().ivf_prefetch_ways(self._h, C.byref(by_kernel), C.byref(by_engine)))
+        return by_kernel.value, by_engine.value
+
     def ivf_search(self, q_out, nprobe, k, with_stats=False):
         q = _host(q_out, np.float32).reshape(-1, self.d)
         nq = q.shape[0]

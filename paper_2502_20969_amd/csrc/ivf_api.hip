@@ -174,6 +174,7 @@ struct ivf_index {
     MoveDesc* d_fetch = nullptr;
     hipEvent_t ev_fetch = nullptr;  // h_fetch has been staged
     bool fetch_recorded = false;
+    int fetched_by_kernel = 0, fetched_by_engine = 0;      // clusters of the most recent prefetch
     size_t buf_used = 0;
     hipEvent_t ev_pf_begin = nullptr, ev_pf_done = nullptr, ev_probe = nullptr, ev_pf_table = nullptr;
     bool pf_recorded = false;
@@ -1491,6 +1492,7 @@ extern "C" int ivf_prefetch(ivf_index* ix, const float* q_in, int32_t nq, int32_
             total += bytes;
             n_lists += bytes > 0 ? 1 : 0;
         }
+        ix->fetched_by_kernel = ix->fetched_by_engine = 0;
         const void* lists_dev = n_lists > 1 && total <= kFetchMeanBytes * (size_t)n_lists ? lists_on_device(ix) : nullptr;
         if (lists_dev) {
             if (ix->fetch_recorded) HIP_TRY(hipEventSynchronize(ix->ev_fetch));       // the previous plan has left h_fetch
@@ -1506,12 +1508,14 @@ extern "C" int ivf_prefetch(ivf_index* ix, const float* q_in, int32_t nq, int32_
             HIP_TRY(hipEventRecord(ix->ev_fetch, ix->copy));
             ix->fetch_recorded = true;
             HIP_TRY(launch_fetch_lists(lists_dev, ix->d_buf, ix->d_fetch, n_lists, chunks, ix->copy));
+            ix->fetched_by_kernel = n_lists;
         } else for (int32_t c : taken) {
             const size_t bytes = (size_t)(ix->h_off[c + 1] - ix->h_off[c]) * rb;
-            if (bytes > 0)
-                HIP_TRY(hipMemcpyAsync((char*)ix->d_buf + (size_t)res_off[c] * rb,
-                                       (const char*)ix->h_lists + (size_t)ix->h_off[c] * rb, bytes,
-                                       hipMemcpyHostToDevice, ix->copy));
+            if (bytes == 0) continue;
+            HIP_TRY(hipMemcpyAsync((char*)ix->d_buf + (size_t)res_off[c] * rb,
+                                   (const char*)ix->h_lists + (size_t)ix->h_off[c] * rb, bytes,
+                                   hipMemcpyHostToDevice, ix->copy));
+            ix->fetched_by_engine += 1;
         }
         // the residency table follows the data on the same stream; the pinned staging copy is reused,
         // so the previous upload from it must have finished
@@ -1542,6 +1546,13 @@ extern "C" int ivf_prefetch(ivf_index* ix, const float* q_in, int32_t nq, int32_
     ix->pf_recorded = true;
     st.buffer_used = ix->buf_used;
     if (stats) *stats = st;
+    return IVF_OK;
+}
+
+extern "C" int ivf_prefetch_ways(const ivf_index* ix, int32_t* by_kernel, int32_t* by_engine) {
+    if (!ix) return fail(IVF_EINVAL, "index is NULL");
+    if (by_kernel) *by_kernel = ix->fetched_by_kernel;
+    if (by_engine) *by_engine = ix->fetched_by_engine;
     return IVF_OK;
 }
 

@@ -288,7 +288,9 @@ def test_lists_fetched_by_a_kernel(monkeypatch, dtype, d, shift, pinned):
     index = P.ivf_adopt_layout(rows, dtype, off, cent, metric=P.IVF_L2, placement=P.IVF_PLACE_HOST,
                                device_buffer_bytes=n * d * rows.element_size() + 4096, **streams)
     for budget in (1 << 40, n * d * rows.element_size() // 3):
-        index.ivf_prefetch(q, nlist, budget, P.IVF_PREFETCH_RESET)
+        st = index.ivf_prefetch(q, nlist, budget, P.IVF_PREFETCH_RESET)
+        copied = st.n_taken - int(np.sum(sizes[index.ivf_resident()] == 0))
+        assert copied > 1 and index.ivf_prefetch_ways() == ((copied, 0) if pinned else (0, copied))
         index.ivf_prefetch(q[1:2], nlist, budget)           # a second plan while the first one may be on its way
         gi, gd, st = index.ivf_search(q, nlist, k, with_stats=True)
         pi, pd = plain.ivf_search(q, nlist, k)
