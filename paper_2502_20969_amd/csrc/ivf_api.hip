@@ -1447,10 +1447,15 @@ static const void* lists_on_device(const ivf_index* ix) {
     return dev;
 }
 
-// Lists of up to this mean size are fetched by a kernel (57 GB/s; the copy engine, one copy per list: 23 GB/s for
-// 0.39 MB each, 46 for 2.4, 54 for 4.7).  Larger ones keep the copy engine busy by themselves and leave every
-// compute unit to what runs beside the prefetch.
-constexpr size_t kFetchMeanBytes = (size_t)4 << 20;
+// Lists of up to this mean size are fetched by a kernel.  300 MB, ms, alone: engine 34.4 in lists of 0.1 MB, 12.6 of 0.4, 8.3
+// of 1.0, 6.6 of 2.4, 6.0 of 3.8 (57 GB/s and 10 us a copy), kernel 5.2 to 5.5 of any size.  But a prefetch is meant to run
+// beside generation, and there the engine disturbs nothing (16 ms of bf16 matrix products 8192^3 or matrix-vector
+// products 16384 x 8192 x 8 beside it take 0.1 longer), while the compute units that fetch hold up kernels that deal
+// their work out evenly: 15.3 becomes 18.2, 14.7 becomes 17.3, half of the kernel's time, with 8, 4 or 2 workgroups no
+// less.  So the kernel may cost half of its own time and the engine what it takes longer, whichever the
+// program around has: up to 1 MB the kernel's worst is the smaller one (2.9 of 300 MB against 7.3 for lists of 0.4 MB,
+// 3.0 of 1.0), above it the engine's (1.3 for 2.4 MB).
+constexpr size_t kFetchMeanBytes = (size_t)1 << 20;
 
 extern "C" int ivf_prefetch(ivf_index* ix, const float* q_in, int32_t nq, int32_t nprobe,
                             size_t budget_bytes, uint32_t flags, ivf_prefetch_stats* stats) {

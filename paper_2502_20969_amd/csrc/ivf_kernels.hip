@@ -2110,9 +2110,9 @@ hipError_t launch_gather_moves(void* buf, const MoveDesc* moves_dev, int n_moves
 // =============================================================================================
 // Prefetched clusters (Sec. 4.1 step 1): one launch reads all lists of a prefetch from pinned host memory and
 // writes them to their places in the device buffer, in the order of the plan.  Bound by the link to the
-// host: eight workgroups with 32 KB on its way each saturate it (57 GB/s, what the copy engine
-// reaches in one piece of 256 MB; 16 here cover the look-ups between chunks), so the other compute
-// units stay with the searches.  Rows may start at any element: 16-byte stores to aligned places, from
+// host: 16 workgroups with 32 KB on its way each reach 57 GB/s, what the copy engine reaches in one piece of 256 MB (8: 44
+// for lists of 0.1 MB, 50 for larger ones; 4: 28 to 35).  Kernels beside it that deal their work out evenly wait for
+// the units that fetch, with fewer of them no less.  Rows may start at any element: 16-byte stores to aligned places, from
 // loads at any address.  (One hipMemcpyAsync per list: 23 GB/s for lists of 390 KB, half of a list's time
 // passes before its first byte.)
 // =============================================================================================

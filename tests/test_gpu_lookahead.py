@@ -299,3 +299,24 @@ def test_lists_fetched_by_a_kernel(monkeypatch, dtype, d, shift, pinned):
             assert st.n_miss == 0
     index.close()
     plain.close()
+
+
+@pytest.mark.parametrize("rows_per_list,by_kernel", [(512, True), (513, False)])
+def test_lists_above_a_megabyte_leave_the_compute_units_alone(rows_per_list, by_kernel):
+    """Lists of up to 1 MB in the mean are fetched by the kernel, larger ones by the engine, which does not hold up
+    the generation that a prefetch runs beside."""
+    d, nlist, k = 512, 6, 5
+    rng = np.random.default_rng(rows_per_list)
+    off = np.arange(nlist + 1, dtype=np.int64) * rows_per_list
+    rows = torch.from_numpy(rng.standard_normal((nlist * rows_per_list, d)).astype(np.float32))
+    cent, q = rng.standard_normal((nlist, d)).astype(np.float32), rng.standard_normal((2, d)).astype(np.float32)
+    streams = dict(compute_stream=torch.cuda.Stream(), copy_stream=torch.cuda.Stream())
+    index = P.ivf_adopt_layout(rows.pin_memory(), "f32", off, cent, placement=P.IVF_PLACE_HOST, device_buffer_bytes=rows.numel() * 4, **streams)
+    plain = P.ivf_adopt_layout(rows.cuda(), "f32", off, cent, **streams)
+    index.ivf_prefetch(q, nlist, 1 << 40, P.IVF_PREFETCH_RESET)
+    assert index.ivf_prefetch_ways() == ((nlist, 0) if by_kernel else (0, nlist))
+    gi, gd = index.ivf_search(q, nlist, k)
+    pi, pd = plain.ivf_search(q, nlist, k)
+    assert np.array_equal(gi, pi) and np.array_equal(gd, pd)
+    index.close()
+    plain.close()
