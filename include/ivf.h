@@ -267,12 +267,13 @@ int ivf_probe(ivf_index* index, const float* q, int32_t nq, int32_t nprobe, int3
 /*
  * The scores the list-major scan filters with (Sec. 4.2 "Batching": the matrix-matrix product), for
  * every row of one cluster against nq <= 32 queries: scores (host, nq x rows of the cluster, in row
- * order) are the filter scores, larger is better: the MFMA accumulators (query rounded to the
+ * order) are the filter scores, larger is better: the products of the matrix cores, or of the vector units for up
+ * to 8 queries and fp32 rows (query rounded to the
  * storage type, fp32 accumulation) for the inner product, 2 <q, y> - |y|^2 - |q|^2 from the same
- * accumulators and the stored row norms for squared L2; eps (host, nq) is the bound the scan
+ * products and the stored row norms for squared L2; eps (host, nq) is the bound the scan
  * assumes for |score - exact value| (exact: <q, y>, or -|q - y|^2, with the fp32 query).
- * Only for an index that has the list-major path (see ivf_set_batch_mode), clusters of at most
- * 65536 rows.
+ * Only for an index that has the list-major path or that automatic mode searches list-major (see
+ * ivf_set_batch_mode), clusters of at most 65536 rows.
  */
 int ivf_batched_scores(ivf_index* index, const float* q, int32_t nq, int32_t cluster, float* scores, float* eps);
 /* how the most recent ivf_prefetch copies its clusters: by_kernel of them with one kernel that reads the pinned lists,

@@ -1816,11 +1816,8 @@ extern "C" int ivf_batched_scores(ivf_index* ix, const float* q, int32_t nq, int
     if (!scores || !eps) return fail(IVF_EINVAL, "scores or eps is NULL");
     if (cluster < 0 || cluster >= ix->nlist) return fail(IVF_EINVAL, "cluster %d is outside [0, %d)", cluster, ix->nlist);
     if (nq > 32) return fail(IVF_ELIMIT, "at most 32 queries (one group of the list-major scan)");
-    const int saved_mode = ix->batch_mode;
-    ix->batch_mode = 2;
-    const bool ok = list_major_mode(ix, 2);
-    ix->batch_mode = saved_mode;
-    if (!ok) return fail(IVF_ESTATE, "this index has no list-major scan (needs all rows in HBM, fewer than 2^32 of them, and d a multiple of 64 that fits LDS)");
+    if (!has_list_major(ix) || ix->row_bytes < 16)
+        return fail(IVF_ESTATE, "this index has no list-major scan (needs all rows in HBM, fewer than 2^32 of them, of 16 bytes or more, and a group of queries in LDS)");
     const int64_t n_c = ix->h_off[cluster + 1] - ix->h_off[cluster];
     if (n_c > kCandCap) return fail(IVF_ELIMIT, "the cluster has %lld rows, at most %d can be returned", (long long)n_c, kCandCap);
     if ((rc = settle_on_lane0(ix))) return rc;
