@@ -45,7 +45,8 @@ static int coarse_rows_queries(const CoarseArgs& a) {
 constexpr int64_t kPairsMin = 12288;
 constexpr int kPairTile = 4;
 constexpr int64_t kCoarsePairWgs = 2048;         // workgroups of that kernel; more pairs make their walks longer
-static bool coarse_in_pairs(const CoarseArgs& a) { return a.d >= 4 && a.nq >= 3 && (int64_t)a.nq * a.nlist >= kPairsMin; }
+// (inner products that come here are at most 4 queries of 2048 centroids)
+static bool coarse_in_pairs(const CoarseArgs& a) { return a.metric != 0 && a.d >= 4 && a.nq >= 3 && (int64_t)a.nq * a.nlist >= kPairsMin; }
 constexpr int kSelectWaveSortMax = 4096;   // select: register sorting path up to this many clusters
 
 // RAGGED: d is no multiple of 4, rows start at any element.
@@ -101,7 +102,7 @@ __global__ __launch_bounds__(256) void coarse_rows_kernel(CoarseArgs a, int per)
     }
 }
 
-// The same sums, four centroids by four queries to a wavefront: for batches, where one pair at a time is bound by
+// The same sums for squared L2, four centroids by four queries to a wavefront: for batches, where one pair at a time is bound by
 // the rows' way from the caches (two rows per pair; here half a row) and by the wavefront's sum.  A
 // pair's products are added in the order of the row kernel and the lanes' sums by the same
 // butterfly, which hands the halves of the sixteen values on as it goes: bit for bit the same scores.
@@ -145,8 +146,8 @@ __global__ __launch_bounds__(256) void coarse_pairs_kernel(CoarseArgs a, int per
                 for (int i = 0; i < T; ++i)
 #pragma unroll
                     for (int j = 0; j < T; ++j) {
-                        if (a.metric == 0) acc[i * T + j] = fma(x[j], y[i], acc[i * T + j]);
-                        else { const double df = x[j] - y[i]; acc[i * T + j] = fma(df, df, acc[i * T + j]); }
+                        const double df = x[j] - y[i];
+                        acc[i * T + j] = fma(df, df, acc[i * T + j]);
                     }
             }
         }
