@@ -177,8 +177,8 @@ int ivf_search(ivf_index* index, const float* q_out, int32_t nq, int32_t nprobe,
  * this point (with a pipeline depth above 1: see ivf_set_pipeline_depth; searched list-major:
  * see ivf_set_batch_mode, after ivf_synchronize()).  q_dev must be 16-byte aligned; q_dev, ids_dev
  * and dists_dev must stay valid until the outputs are complete.  IVF_PLACE_DEVICE only.  nq, nprobe and k must not exceed what
- * ivf_reserve() or an earlier search has sized the workspace for, else the call sizes it
- * itself, which synchronises the device.
+ * ivf_reserve() or an earlier search (in the same batch mode) has sized the workspace for, else the call
+ * sizes it itself, which synchronises the device.
  */
 int ivf_search_device(ivf_index* index, const float* q_dev, int32_t nq, int32_t nprobe,
                       int32_t k, int64_t* ids_dev, float* dists_dev);
@@ -244,10 +244,11 @@ int ivf_synchronize(ivf_index* index);
  *      and a call under stream capture is enqueued query by query.  Anything else query by query
  *   1  always query by query
  *   2  list-major from 2 queries on; IVF_ESTATE (and the mode stays) when the index has no
- *      list-major path
+ *      list-major path, rows whose d is no multiple of 64 among them
  * An index has the list-major path when all its rows are in HBM (IVF_PLACE_DEVICE), there are
  * fewer than 2^32 of them, and d is a multiple of 64 whose group of queries (32 of fp16 / bf16, 16
- * of fp32) fits LDS; any storage type, both metrics.
+ * of fp32) fits LDS; any storage type, both metrics.  (The scan itself reads rows of any width from 16
+ * bytes on; batches of those are completed in another way and belong to mode 0.)
  * The results are the same in every mode (the MFMA scores only filter rows; the ranking uses
  * fp64 re-scores with the fp32 query).  A list-major batch may leave a few queries to be
  * searched again one by one (their candidate lists overflowed): ivf_search does that before it

@@ -1138,7 +1138,8 @@ extern "C" int ivf_set_batch_mode(ivf_index* ix, int32_t mode) {
         ix->batch_mode = 2;
         const bool ok = list_major_mode(ix, 2);
         ix->batch_mode = saved;
-        if (!ok) return fail(IVF_ESTATE, "this index has no list-major scan (needs all rows in HBM, fewer than 2^32 of them, and d a multiple of 64 that fits LDS)");
+        if (!ok) return fail(IVF_ESTATE, "mode 2 needs all rows in HBM, fewer than 2^32 of them, and d a multiple of 64 of which a group of queries fits LDS (d = %d); "
+                              "rows of other widths are searched list-major by mode 0", ix->d);
     }
     ix->batch_mode = mode;
     return IVF_OK;
