@@ -247,12 +247,13 @@ def _device_search(index, q, nprobe, k):
     return ids.cpu().numpy(), dists.cpu().numpy()
 
 
-def test_batches_that_do_not_fit_their_memory():
+@pytest.mark.parametrize("dtype,d", [("f32", 200), ("f32", 201), ("f16", 301), ("bf16", 75)])       # slices start at any element
+def test_batches_that_do_not_fit_their_memory(dtype, d):
     """What the list-major workspace did get is given back when the rest of it is refused; the batch is searched
     in slices, or query by query when nothing fits, and smaller batches stay list-major."""
-    n, d, nlist, nq, nprobe, k = 24000, 200, 8, 300, 5, 10
-    rows, off, cent, q = _problem(4, "f32", n, d, nlist, nq, 7)
-    index = _adopt(rows, "f32", off, cent, "ip")
+    n, nlist, nq, nprobe, k = 24000, 8, 300, 5, 10
+    rows, off, cent, q = _problem(4, dtype, n, d, nlist, nq, 7)
+    index = _adopt(rows, dtype, off, cent, "ip")
     index.ivf_set_batch_mode(1)
     (wi, wd), each = _rows_scanned(index, q, nprobe, k)            # sizes the rest of the workspace
     index.ivf_set_batch_mode(0)
