@@ -301,11 +301,11 @@ def test_lists_fetched_by_a_kernel(monkeypatch, dtype, d, shift, pinned):
     plain.close()
 
 
-@pytest.mark.parametrize("rows_per_list,by_kernel", [(512, True), (513, False)])
-def test_lists_above_a_megabyte_leave_the_compute_units_alone(rows_per_list, by_kernel):
+@pytest.mark.parametrize("nlist,rows_per_list,by_kernel", [(6, 512, True), (6, 513, False), (1, 512, False), (2, 8, False), (2, 9, True), (3, 1, True)])
+def test_lists_are_fetched_the_cheaper_way(nlist, rows_per_list, by_kernel):
     """Lists of up to 1 MB in the mean are fetched by the kernel, larger ones by the engine, which does not hold up
-    the generation that a prefetch runs beside."""
-    d, nlist, k = 512, 6, 5
+    the generation that a prefetch runs beside; a single list and two of 16 KB go by the engine too."""
+    d, k = 512, 5
     rng = np.random.default_rng(rows_per_list)
     off = np.arange(nlist + 1, dtype=np.int64) * rows_per_list
     rows = torch.from_numpy(rng.standard_normal((nlist * rows_per_list, d)).astype(np.float32))
