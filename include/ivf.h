@@ -193,7 +193,8 @@ int ivf_reserve(ivf_index* index, int32_t nq, int32_t nprobe, int32_t k);
 /* Bounds the device memory that the list-major workspace of each lane may take (default: no bound) and gives
  * back what it holds; waits for the device.  What does not fit: over rows whose d is a multiple of 64 a
  * list-major batch fails with IVF_ENOMEM, as when the device has no more memory; over rows of other widths the
- * batch is searched in smaller slices, or query by query when not even four queries fit. */
+ * batch is searched in smaller slices, or query by query when not even four queries fit.  Like every call that
+ * sizes the workspace anew it leaves list-major calls that were captured into a graph without theirs. */
 int ivf_limit_batch_memory(ivf_index* index, size_t bytes);
 
 /*
