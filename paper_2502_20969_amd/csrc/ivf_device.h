@@ -95,9 +95,42 @@ __device__ __forceinline__ void store_stream16(void* p, const uint4& v) {
     __builtin_nontemporal_store(t, (u4_t*)p);
 }
 
+// Value held by lane (lane ^ STRIDE), with register-to-register moves only: DPP quad
+// permutes (1, 2), row shifts (4), a row rotate (8), and the 16- and 32-lane swaps of gfx950.
+template <int STRIDE>
+__device__ __forceinline__ uint32_t xor_lane_u32(uint32_t v) {
+    const int lane = lane_id();
+    if (STRIDE == 1) return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0xB1, 0xF, 0xF, true);
+    if (STRIDE == 2) return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x4E, 0xF, 0xF, true);
+    if (STRIDE == 4) {
+        int up = __builtin_amdgcn_update_dpp(0, (int)v, 0x104, 0xF, 0xF, true);   // row_shl:4 = lane + 4
+        int dn = __builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xF, 0xF, true);   // row_shr:4 = lane - 4
+        return (uint32_t)((lane & 4) ? dn : up);
+    }
+    if (STRIDE == 8) return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x128, 0xF, 0xF, true);  // row_ror:8
+    if (STRIDE == 16) {
+        auto r = __builtin_amdgcn_permlane16_swap(v, v, false, false);   // [0] = rows 0,0,2,2  [1] = rows 1,1,3,3
+        return (lane & 16) ? r[0] : r[1];
+    }
+    auto r = __builtin_amdgcn_permlane32_swap(v, v, false, false);       // [0] = low half twice, [1] = high half twice
+    return (lane & 32) ? r[0] : r[1];
+}
+template <int STRIDE>
+__device__ __forceinline__ double xor_lane(double v) {
+    const uint64_t u = (uint64_t)__double_as_longlong(v);
+    return __longlong_as_double((long long)(((uint64_t)xor_lane_u32<STRIDE>((uint32_t)(u >> 32)) << 32) | xor_lane_u32<STRIDE>((uint32_t)u)));
+}
+
+// Sums of doubles by a butterfly over the lane distances 32 .. 1, and over 1 .. 16 (each aligned group of 32 lanes),
+// the values moved between registers.
 __device__ __forceinline__ double wave_sum(double v) {
-#pragma unroll
-    for (int m = 32; m >= 1; m >>= 1) v += __shfl_xor(v, m);
+    v += xor_lane<32>(v); v += xor_lane<16>(v); v += xor_lane<8>(v);
+    v += xor_lane<4>(v); v += xor_lane<2>(v); v += xor_lane<1>(v);
+    return v;
+}
+__device__ __forceinline__ double group32_sum(double v) {
+    v += xor_lane<1>(v); v += xor_lane<2>(v); v += xor_lane<4>(v);
+    v += xor_lane<8>(v); v += xor_lane<16>(v);
     return v;
 }
 
@@ -109,9 +142,21 @@ __device__ __forceinline__ uint32_t read_lane(uint32_t v, int lane) {
 }
 
 // ---- stored element types -------------------------------------------------------------------
-struct F32 { static constexpr int kBytes = 4; static constexpr int kPerLoad = 4; };
-struct F16 { static constexpr int kBytes = 2; static constexpr int kPerLoad = 8; };
-struct BF16 { static constexpr int kBytes = 2; static constexpr int kPerLoad = 8; };
+struct F32 {
+    static constexpr int kBytes = 4, kPerLoad = 4;
+    typedef float raw;
+    __device__ static __forceinline__ float value(raw v) { return v; }
+};
+struct F16 {
+    static constexpr int kBytes = 2, kPerLoad = 8;
+    typedef uint16_t raw;
+    __device__ static __forceinline__ float value(raw v) { return (float)__builtin_bit_cast(_Float16, v); }
+};
+struct BF16 {
+    static constexpr int kBytes = 2, kPerLoad = 8;
+    typedef uint16_t raw;
+    __device__ static __forceinline__ float value(raw v) { return __uint_as_float((uint32_t)v << 16); }
+};
 
 typedef _Float16 half2_t __attribute__((ext_vector_type(2)));
 
@@ -160,7 +205,7 @@ __device__ __forceinline__ double widen(const void* base, int dtype, size_t idx)
 // (elements in memory order, one fused multiply-add each); the accumulators are added by a
 // butterfly over the lane distances 1, 2, 4, 8, 16.  Rows that are not whole 16-byte chunks use
 // the same scheme over single elements.
-constexpr int kRescoreLanes = 32;
+constexpr int kRescoreLanes = 32;          // group32_sum adds them
 
 // Partial fp64 scores of R stored rows over the 16-byte chunks sub, sub + lpc, ... (lane `sub`
 // of a group of `lpc` lanes); several loads are in flight at a time, those of all rows together.
@@ -203,91 +248,66 @@ __device__ __forceinline__ void rescore_partial(const unsigned char* const (&row
     }
 }
 
-// fp64 score of the stored row `brow` of the buffer for the query q, computed by a group of
-// kRescoreLanes lanes (sub = lane in the group); every lane of the group gets the sum.  One fixed
-// order of operations (rescore_partial, then a butterfly over the lane distances 1 .. 16).
-__device__ __forceinline__ double rescore_row(const void* buf, const float* q, int d, int dtype, int metric,
-                                              size_t brow, int sub) {
+// The same over single elements, for rows that are not whole 16-byte chunks; U elements of a lane and row are requested
+// together and added in order.
+template <typename T, int R, int U>
+__device__ __forceinline__ void rescore_elements(const unsigned char* const (&row)[R], const float* q, int d, int metric, int sub, double (&s)[R]) {
     constexpr int lpc = kRescoreLanes;
-    const size_t row_bytes = (size_t)d * (dtype == 0 ? 4 : 2);
-    const unsigned char* rp = (const unsigned char*)buf + brow * row_bytes;
-    double s = 0.0;
-    if (row_bytes % 16 == 0) {
-        const unsigned char* const one[1] = {rp};
-        double acc[1];
-        if (dtype == 0) rescore_partial<F32, 1>(one, q, d, metric, sub, lpc, acc);
-        else if (dtype == 1) rescore_partial<F16, 1>(one, q, d, metric, sub, lpc, acc);
-        else rescore_partial<BF16, 1>(one, q, d, metric, sub, lpc, acc);
-        s = acc[0];
-    } else {
-        const size_t e0 = brow * (size_t)d;
-        // eight elements of a lane are requested together and added in order
+#pragma unroll
+    for (int r = 0; r < R; ++r) s[r] = 0.0;
 #pragma unroll 1
-        for (int t0 = sub; t0 < d; t0 += 8 * lpc) {
-            double x[8], y[8];
+    for (int t0 = sub; t0 < d; t0 += U * lpc) {
+        float x[U];
+        typename T::raw y[R][U];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                const int t = min(t0 + u * lpc, d - 1);
-                x[u] = (double)q[t]; y[u] = widen(buf, dtype, e0 + t);
-            }
+        for (int u = 0; u < U; ++u) {
+            const int t = min(t0 + u * lpc, d - 1);
+            x[u] = q[t];
 #pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                if (t0 + u * lpc < d) {
-                    if (metric == 0) s = fma(x[u], y[u], s);
-                    else { const double df = x[u] - y[u]; s = fma(df, df, s); }
+            for (int r = 0; r < R; ++r) y[r][u] = ((const typename T::raw*)row[r])[t];
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            if (t0 + u * lpc < d) {
+                const double qd = (double)x[u];
+#pragma unroll
+                for (int r = 0; r < R; ++r) {
+                    const double yd = (double)T::value(y[r][u]);
+                    if (metric == 0) s[r] = fma(qd, yd, s[r]);
+                    else { const double df = qd - yd; s[r] = fma(df, df, s[r]); }
                 }
             }
         }
     }
-#pragma unroll 1
-    for (int o = 1; o < lpc; o <<= 1) s += __shfl_xor(s, o);
-    return s;
 }
 
-// The same for R rows at once: their loads overlap, every row's order of operations is that of rescore_row.
-template <int R>
+template <typename T, int R>
+__device__ __forceinline__ void rescore_typed(const unsigned char* const (&row)[R], const float* q, int d, int metric, int sub, double (&s)[R]) {
+    if (d % T::kPerLoad == 0) rescore_partial<T, R>(row, q, d, metric, sub, kRescoreLanes, s);
+    else rescore_elements<T, R, R == 1 ? 16 : 8>(row, q, d, metric, sub, s);
+}
+
+// fp64 scores of R stored rows of the buffer for the query q, computed by a group of kRescoreLanes lanes (sub = lane in
+// the group); every lane of the group gets the sums.  One fixed order of operations (rescore_partial or
+// rescore_elements, then a butterfly over the lane distances 1 .. 16), whatever R is; the rows' loads overlap.
+template <int R, typename Row>
 __device__ __forceinline__ void rescore_rows(const void* buf, const float* q, int d, int dtype, int metric,
-                                             const uint32_t (&brow)[R], int sub, double (&s)[R]) {
-    constexpr int lpc = kRescoreLanes;
+                                             const Row (&brow)[R], int sub, double (&s)[R]) {
     const size_t row_bytes = (size_t)d * (dtype == 0 ? 4 : 2);
-    if (row_bytes % 16 == 0) {
-        const unsigned char* rp[R];
+    const unsigned char* rp[R];
 #pragma unroll
-        for (int r = 0; r < R; ++r) rp[r] = (const unsigned char*)buf + brow[r] * row_bytes;
-        if (dtype == 0) rescore_partial<F32, R>(rp, q, d, metric, sub, lpc, s);
-        else if (dtype == 1) rescore_partial<F16, R>(rp, q, d, metric, sub, lpc, s);
-        else rescore_partial<BF16, R>(rp, q, d, metric, sub, lpc, s);
-    } else {
-        constexpr int U = 4;
+    for (int r = 0; r < R; ++r) rp[r] = (const unsigned char*)buf + brow[r] * row_bytes;
+    if (dtype == 0) rescore_typed<F32, R>(rp, q, d, metric, sub, s);
+    else if (dtype == 1) rescore_typed<F16, R>(rp, q, d, metric, sub, s);
+    else rescore_typed<BF16, R>(rp, q, d, metric, sub, s);
 #pragma unroll
-        for (int r = 0; r < R; ++r) s[r] = 0.0;
-#pragma unroll 1
-        for (int t0 = sub; t0 < d; t0 += U * lpc) {
-            double x[U], y[R][U];
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const int t = min(t0 + u * lpc, d - 1);
-                x[u] = (double)q[t];
-#pragma unroll
-                for (int r = 0; r < R; ++r) y[r][u] = widen(buf, dtype, (size_t)brow[r] * d + t);
-            }
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                if (t0 + u * lpc < d) {
-#pragma unroll
-                    for (int r = 0; r < R; ++r) {
-                        if (metric == 0) s[r] = fma(x[u], y[r][u], s[r]);
-                        else { const double df = x[u] - y[r][u]; s[r] = fma(df, df, s[r]); }
-                    }
-                }
-            }
-        }
-    }
-#pragma unroll 1
-    for (int o = 1; o < lpc; o <<= 1) {
-#pragma unroll
-        for (int r = 0; r < R; ++r) s[r] += __shfl_xor(s[r], o);
-    }
+    for (int r = 0; r < R; ++r) s[r] = group32_sum(s[r]);
+}
+__device__ __forceinline__ double rescore_row(const void* buf, const float* q, int d, int dtype, int metric, size_t brow, int sub) {
+    const size_t one[1] = {brow};
+    double s[1];
+    rescore_rows<1>(buf, q, d, dtype, metric, one, sub, s);
+    return s[0];
 }
 
 // ---- order-preserving integer keys ------------------------------------------------------------
@@ -601,26 +621,6 @@ __device__ __forceinline__ Cand read_lane(Cand v, int lane) {
 }
 
 // ---- sorting networks over the 64 lanes of a wavefront --------------------------------------------
-// Value held by lane (lane ^ STRIDE), with register-to-register moves only: DPP quad
-// permutes (1, 2), row shifts (4), a row rotate (8), and the 16- and 32-lane swaps of gfx950.
-template <int STRIDE>
-__device__ __forceinline__ uint32_t xor_lane_u32(uint32_t v) {
-    const int lane = lane_id();
-    if (STRIDE == 1) return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0xB1, 0xF, 0xF, true);
-    if (STRIDE == 2) return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x4E, 0xF, 0xF, true);
-    if (STRIDE == 4) {
-        int up = __builtin_amdgcn_update_dpp(0, (int)v, 0x104, 0xF, 0xF, true);   // row_shl:4 = lane + 4
-        int dn = __builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xF, 0xF, true);   // row_shr:4 = lane - 4
-        return (uint32_t)((lane & 4) ? dn : up);
-    }
-    if (STRIDE == 8) return (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x128, 0xF, 0xF, true);  // row_ror:8
-    if (STRIDE == 16) {
-        auto r = __builtin_amdgcn_permlane16_swap(v, v, false, false);   // [0] = rows 0,0,2,2  [1] = rows 1,1,3,3
-        return (lane & 16) ? r[0] : r[1];
-    }
-    auto r = __builtin_amdgcn_permlane32_swap(v, v, false, false);       // [0] = low half twice, [1] = high half twice
-    return (lane & 32) ? r[0] : r[1];
-}
 // Value held by lane 63 - lane.
 __device__ __forceinline__ uint32_t mirror_lane_u32(uint32_t v) {
     uint32_t m = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x140, 0xF, 0xF, true);   // row_mirror = lane ^ 15

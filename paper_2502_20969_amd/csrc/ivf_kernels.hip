@@ -1336,139 +1336,403 @@ hipError_t launch_scan(const ScanArgs& a, hipStream_t s, hipEvent_t e0, hipEvent
 // all workgroup lists, re-scores those rows in fp64 from the stored rows, adds the host's
 // candidates (already fp64), orders everything by (score, id) and writes the k nearest.
 // =============================================================================================
-constexpr int kMergeCandCap = 4096;    // candidates the fast path can pool
-constexpr int kMergeQlistCap = 1024;   // lists the fast path can visit
-constexpr int kMergeFastThreads = 1024;
+constexpr int kMergeCandCap = 4096;    // candidates that can be pooled
+constexpr int kMergeThreads = 1024;    // kprime up to 64
+constexpr int kMergeWideThreads = 1024;
 
 struct MergeLds {
-    uint32_t gmax[kMergeFastThreads];      // fast path: the largest head key of every thread's share
-    uint32_t hist[256];                    // general path: digit counts of the radix select
+    uint32_t red[96];                      // the groups' maxima; scratch of the bucket cut
+    uint32_t hist[256];                    // bucket cut, radix select
     uint32_t sh[8];
+    uint32_t f_last;                       // key image of the last candidate that counts as kept
     Cand c_cand[kMaxKPrime];
-    double f_key[2 * kMaxKPrime];
+    uint64_t f_key[2 * kMaxKPrime];        // ordered fp64 scores: larger is nearer
     int64_t f_id[2 * kMaxKPrime];
+    double q_part[kMergeWideThreads / 64]; // |q|^2, by wavefronts
 };
 
-// The kprime best of `cnt` pooled candidates (cnt above 64) into L.c_cand, their number into
-// L.sh[4].  The usual search pools fewer than 64 and never comes here.
-__device__ __forceinline__ void rank_pool(Cand* pool, uint32_t cnt, int kp, MergeLds& L) {
-    const int tid = threadIdx.x, nt = blockDim.x, lane = lane_id(), wave = wave_id(), nw = nt >> 6;
-    if (cnt <= (uint32_t)nt) {
-        // eight lanes per candidate count those ahead of it, and the first kprime take their places
-#pragma unroll 1
-        for (uint32_t t = (uint32_t)tid / 8; t < cnt; t += (uint32_t)nt / 8) {
-            const Cand me = pool[t];
-            uint32_t rank, equal;
-            count_above(pool, cnt, me, (uint32_t)tid & 7u, rank, equal);
-            if ((tid & 7) == 0 && rank < (uint32_t)kp) L.c_cand[rank] = me;
+// Last resort: radix select over all entries of all lists (candidates are distinct, so the
+// selection ends with exactly kprime of them).  Returns their number.
+__device__ __forceinline__ int gather_radix(const MergeArgs& a, const Cand* part, MergeLds& L) {
+    const int tid = threadIdx.x, nt = blockDim.x, lane = lane_id();
+    const uint32_t n = (uint32_t)a.nparts * (uint32_t)a.list_len, kp = a.kprime;
+    auto key_at = [&](uint32_t i) { return ~part[i]; };      // ascending = best first; all ones = empty
+    uint32_t my_valid = 0;
+    for (uint32_t i = tid; i < n; i += nt) my_valid += part[i] != 0;
+    if (tid == 0) { L.sh[4] = 0; L.sh[5] = 0; L.f_last = 0xFFFFFFFFu; }
+    __syncthreads();
+#pragma unroll
+    for (int m2 = 32; m2 >= 1; m2 >>= 1) my_valid += __shfl_xor(my_valid, m2);
+    if (lane == 0) atomicAdd(&L.sh[5], my_valid);
+    __syncthreads();
+    const uint32_t n_valid = L.sh[5];
+    uint64_t mask = 0, prefix = 0; uint32_t need, group;      // all valid ones: those below the all-ones key
+    if (n_valid > kp) block_radix_select<uint64_t>(key_at, n, kp, L.hist, L.sh, mask, prefix, need, group);
+    // need == group here: distinct keys leave a boundary group of one
+    for (uint32_t i = tid; i < n; i += nt) {
+        const uint64_t key = key_at(i);
+        if (key != ~0ull && (key & mask) <= prefix) {
+            uint32_t p = atomicAdd(&L.sh[4], 1u);
+            if (p < (uint32_t)kMaxKPrime) L.c_cand[p] = part[i];
+            atomicMin(&L.f_last, (uint32_t)(part[i] >> 32));
         }
-        __syncthreads();
-        if (tid == 0) L.sh[4] = min(cnt, (uint32_t)kp);
-        __syncthreads();
-        return;
-    }
-    // many: sort the pooled candidates in chunks of 64, merge the chunks
-    const int nchunks = (int)((cnt + 63) / 64);
-#pragma unroll 1
-    for (int c = wave; c < nchunks; c += nw) {
-        const uint32_t e = c * 64 + lane;
-        pool[e] = bitonic_sort64<true>(e < cnt ? pool[e] : (Cand)0);
     }
     __syncthreads();
-    if (wave == 0) {
-        Cand top = pool[lane];
-#pragma unroll 1
-        for (int c = 1; c < nchunks; ++c) top = merge_best64<true>(top, pool[c * 64 + lane]);
-        const bool ok = lane < kp && top != 0;          // valid entries form a prefix
-        if (ok) L.c_cand[lane] = top;
-        const uint32_t m = (uint32_t)__popcll(__ballot(ok));
-        if (lane == 0) L.sh[4] = m;
-    }
-    __syncthreads();
+    return (int)min(L.sh[4], (uint32_t)kMaxKPrime);
 }
 
-// Fast path (kprime <= 64).  The scan left one unordered list of `slots` candidates per wavefront
-// and each list's best entry in `heads` (0: empty list).  Candidates are distinct.  The heads are
-// dealt to 64 groups (a thread's heads go to the group of its lane); the kprime-th largest group
-// maximum T is not above the kprime-th largest head, so at least kprime candidates reach T and the
+// Can a row that the scan or the gathering dropped still belong to the k nearest?  Everything
+// dropped anywhere has an fp32 key of at most f_last, the key of the last candidate kept, so its
+// exact score is at most f_last + E, E bounding the rounding of the fp32 accumulation:
+//   inner product   |fl(sum) - sum| <= g |q| |y|        squared distance   |fl(sum) - sum| <= g sum
+// with g = err_coef (a little above (terms + 2) 2^-24 for sums whose terms pass through at most
+// `terms` roundings).  The k-th best exact score found, s_k, is a lower bound of the true one;
+// the result is exact when s_k > f_last + E.
+__device__ __forceinline__ bool result_is_safe(double s_k, float f_last, const MergeArgs& a, double qq) {
+    // single precision is enough for the bound itself: it is rounded upwards
+    const float e = a.metric == 0 ? a.err_coef * (sqrtf((float)qq) * 1.0001f) * a.row_norm_max * 1.0001f
+                                  : a.err_coef * fabsf(f_last) * 1.0001f;
+    return s_k > (double)f_last + (double)e;
+}
+// The verdict on query qi: redo_flag and, for the second pass, the k-th best score found.
+__device__ __forceinline__ void conclude(const MergeArgs& a, int qi, bool unsafe, double kth) {
+    if (a.redo_flag) {
+        a.redo_flag[qi] = unsafe ? 1u : 0u;
+        if (unsafe) {
+            a.redo_thr[qi] = kth;
+            a.redo_ticket[qi] = 0u;
+        }
+    }
+    if (a.host_flag) a.host_flag[qi] = unsafe ? 1u : 0u;       // pinned: stored before the completion word
+}
+// The completion word, behind everything that the workgroup has stored.
+__device__ __forceinline__ void signal_done(const MergeArgs& a) {
+    if (!a.done) return;
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        __threadfence_system();
+        __hip_atomic_store(a.done, a.done_value, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+    }
+}
+
+// Places in the buffer of R rows (global row numbers) of query qi, by a group of kRescoreLanes lanes: the slots whose
+// range of global rows holds them.  false: none does.
+template <int R>
+__device__ __forceinline__ void find_rows(const MergeArgs& a, int qi, int sub, const uint32_t (&row)[R], size_t (&brow)[R], bool (&found)[R]) {
+    const int np = a.nprobe;
+    const int64_t* s_base = a.slots.base + (size_t)qi * np;
+    const uint32_t* s_grow = a.slots.grow + (size_t)qi * np;
+    const uint32_t* s_n = a.slots.nrows + (size_t)qi * np;
+    int at[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) at[r] = -1;
+#pragma unroll 1
+    for (int s = sub; s < np; s += kRescoreLanes) {
+        const uint32_t g = s_grow[s], n = s_n[s];
+#pragma unroll
+        for (int r = 0; r < R; ++r) if (row[r] >= g && row[r] - g < n) at[r] = s;
+    }
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+#pragma unroll 1
+        for (int o = 1; o < kRescoreLanes; o <<= 1) at[r] = max(at[r], __shfl_xor(at[r], o));
+        found[r] = at[r] >= 0;
+        brow[r] = found[r] ? (size_t)(s_base[at[r]] + (int64_t)(row[r] - s_grow[at[r]])) : 0;
+    }
+}
+// Candidates c0, c0 + step, ... (R of them, below m) of query qi re-scored by a group of kRescoreLanes lanes.  The order of
+// operations is fixed (see rescore_rows), so a row has the same fp64 score whichever kernel, or the host,
+// computes it.
+template <int R>
+__device__ __forceinline__ void score_candidates(const MergeArgs& a, int qi, MergeLds& L, const Cand* cands, uint32_t c0, uint32_t step, uint32_t m, int sub) {
+    uint32_t row[R];
+    int64_t id[R];
+    size_t brow[R];
+    bool found[R];
+    double s[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        row[r] = cand_tie(cands[min(c0 + step * r, m - 1)]);
+        id[r] = a.ids ? a.ids[row[r]] : (int64_t)row[r];
+        brow[r] = row[r]; found[r] = true;
+    }
+    if (!a.identity) find_rows<R>(a, qi, sub, row, brow, found);
+    rescore_rows<R>(a.buf, a.q + (size_t)qi * a.d, a.d, a.dtype, a.metric, brow, sub, s);
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const uint32_t c = c0 + step * r;
+        if (sub == 0 && c < m) {
+            L.f_key[c] = ordered(!found[r] ? -INFINITY : (a.metric == 0 ? s[r] : -s[r]));
+            L.f_id[c] = id[r];
+        }
+    }
+}
+// The host's candidates behind the m that were re-scored; returns their number.
+__device__ __forceinline__ uint32_t add_host_candidates(const MergeArgs& a, int qi, MergeLds& L, uint32_t m) {
+    if (!a.host_cand) return 0;
+    const uint32_t kp = (uint32_t)a.kprime, nh = min((uint32_t)a.host_count[qi], kp);
+    for (uint32_t i = threadIdx.x; i < nh; i += blockDim.x) {
+        L.f_key[m + i] = ordered(a.host_cand[(size_t)qi * kp + i].key);
+        L.f_id[m + i] = a.host_cand[(size_t)qi * kp + i].id;
+    }
+    return nh;
+}
+__device__ __forceinline__ void pad_results(const MergeArgs& a, int qi, uint32_t have) {
+    for (uint32_t i = have + threadIdx.x; i < (uint32_t)a.k; i += blockDim.x) {
+        a.out_ids[(size_t)qi * a.k + i] = -1;
+        a.out_dists[(size_t)qi * a.k + i] = a.metric == 0 ? -INFINITY : INFINITY;
+    }
+}
+
+// ---- kprime up to 64 -----------------------------------------------------------------------------
+// The scan left one unordered list of 64 candidates per wavefront and each list's best entry in `heads` (0: empty
+// list).  Candidates are distinct.  The heads are dealt to 64 groups (list l to group l % 64); the kprime-th largest
+// group maximum T is not above the kprime-th largest head, so at least kprime candidates reach T and the
 // kprime best overall are among those that do, in lists whose head does.  With heads spread at
-// random over the groups, about kprime (1 + kprime / 128) heads reach T.  The passing entries of
-// those lists are pooled; up to 64 are ordered by one sort of wavefront 0, more by rank_pool.
-// Returns false (for the whole workgroup) when they did not fit `pool` (kMergeCandCap) or the
-// lists did not fit `qlist` (kMergeQlistCap).
-__device__ __forceinline__ bool gather_fast(const MergeArgs& a, const Cand* part, const Cand* heads, MergeLds& L,
-                                            Cand* pool, uint32_t* qlist) {
-    const int tid = threadIdx.x, nt = blockDim.x, lane = lane_id(), wave = wave_id(), nw = nt >> 6;
-    const int kp = a.kprime, np = a.nparts, slots = a.list_len;
-    // 1. the cut, from the list heads (the first two heads of a thread stay in registers)
-    if (tid == 0) { L.sh[4] = 0; L.sh[5] = 0; }
-    const Cand h0 = tid < np ? heads[tid] : (Cand)0;
-    const Cand h1 = tid + nt < np ? heads[tid + nt] : (Cand)0;
-    auto head_at = [&](uint32_t l) -> Cand { return l == (uint32_t)tid ? h0 : (l == (uint32_t)(tid + nt) ? h1 : heads[l]); };
-    uint32_t best = max((uint32_t)(h0 >> 32), (uint32_t)(h1 >> 32));
+// random over the groups, about kprime (1 + kprime / 128) heads reach T.  A wavefront pools the passing entries of
+// the lists whose heads it holds.  Up to 32 are all re-scored, up to 512 are ranked first, more are cut
+// again (the pool dealt anew).  The result is exact when nothing that was dropped can matter: result_is_safe.
+//
+// What bounds it: a chain of four trips to memory (heads, lists, rows, results; what the scan wrote comes from other
+// XCDs, 0.8 us a trip) and the steps between them, whose instructions sixteen wavefronts issue in turn, four to a SIMD.  So: ranks
+// by ballots (every lane holds one of 64 values, a value's rank is the number of lanes above it) dealt to the
+// wavefronts, where a sorting network is one wavefront's chain of 21 exchanges; groups of sixteen lanes, so that one LDS
+// read brings all maxima; no division by the list length; |q|^2 by a wavefront beside the others; no barrier behind the
+// stores of the results (it waits for them).  Whole kernel, us, before / now: 2500 rows of 128 fp32 7.8 / 6.5, 30,000 of
+// 768 fp32 8.4 / 6.9, 34,000 of 300 fp16 in squared L2 10.2 / 8.1.  Eight wavefronts with two rows of a group of lanes in flight:
+// 7.5, 8.6, 8.6; four with four rows: 8.6, 9.4, 10.0; four lists always requested together: 7.0, 7.4, 8.5.
+constexpr int kMergeHeads = 2048 / kMergeThreads;         // heads of a thread that stay in registers: all of one query's lists
+constexpr int kMergeRows = 1024 / kMergeThreads;          // rows of a group of lanes in flight: 32 candidates in one go
+constexpr int kNormLds = 1024;                            // elements of the query that go through LDS to the wavefront that sums |q|^2
+constexpr int kMergeRanked = 512;                         // pooled candidates that are ranked as they are
+
+__global__ __launch_bounds__(kMergeThreads) __attribute__((amdgpu_waves_per_eu(5))) void merge_kernel(MergeArgs a) {
+    extern __shared__ __align__(16) unsigned char m_dyn[];
+    __shared__ MergeLds L;
+    __shared__ float s_q[kNormLds];
+    constexpr int nt = kMergeThreads, nw = nt / 64, slots = 64, H = kMergeHeads, G = nt / 64;     // G lanes hold a group's heads
+    Cand* pool = (Cand*)m_dyn;
+    const int tid = threadIdx.x, lane = lane_id(), wave = wave_id();
+    const int qi = blockIdx.x, np = a.nparts, kp = a.kprime;
+    const Cand* part = a.part + (size_t)qi * (size_t)np * slots;
+    const Cand* heads = a.heads + (size_t)qi * np;
+    const float* q = a.q + (size_t)qi * a.d;
+    const uint64_t below = (1ull << lane) - 1ull;
+    // head i of a thread: G consecutive lanes take the lists g, g + 64, g + 128, ... of group g
+    auto list_of = [&](int t, int i) __attribute__((always_inline)) { return (i * G + (t & (G - 1))) * 64 + t / G; };
+    auto head_at = [&](int i) __attribute__((always_inline)) -> Cand {
+        const int l = list_of(tid, i);
+        const Cand c = heads[min(l, np - 1)];
+        return l < np ? c : (Cand)0;
+    };
+    Cand h[H];
+#pragma unroll
+    for (int i = 0; i < H; ++i) h[i] = head_at(i);
+    float x[kNormLds / nt];
+#pragma unroll
+    for (int u = 0; u < kNormLds / nt; ++u) x[u] = q[min(tid + u * nt, a.d - 1)];
+    if (tid == 0) { L.sh[4] = 0; L.sh[6] = 0; }
+
+    // 1. the cut: T is the largest of the 64 maxima that at least kprime of them reach (0: fewer than kprime groups hold
+    //    anything, all pass).  A wavefront tries an equal share of the 64, each by one ballot.
+    auto group_max = [&](uint32_t v) __attribute__((always_inline)) {
+        v = max(v, xor_lane_u32<1>(v));
+        v = max(v, xor_lane_u32<2>(v));
+        if (G > 4) v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x141, 0xF, 0xF, true));      // row_half_mirror
+        if (G > 8) v = max(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x140, 0xF, 0xF, true));      // row_mirror
+        if ((lane & (G - 1)) == 0) L.red[tid / G] = v;
+    };
+    auto cut_of_groups = [&]() __attribute__((always_inline)) -> uint32_t {
+        __syncthreads();
+        const uint32_t g = L.red[lane];
+        uint32_t best = 0;
+#pragma unroll
+        for (int i = 0; i < 64 / nw; ++i) {
+            const uint32_t v = read_lane(g, wave * (64 / nw) + i);
+            best = __popcll(__ballot(g >= v)) >= kp ? max(best, v) : best;
+        }
+        if (lane == 0 && best) atomicMax(&L.sh[6], best);
+        __syncthreads();
+        return L.sh[6];
+    };
+    {
+        uint32_t best = 0;
+#pragma unroll
+        for (int i = 0; i < H; ++i) best = max(best, (uint32_t)(h[i] >> 32));
 #pragma unroll 1
-    for (int l = tid + 2 * nt; l < np; l += nt) best = max(best, (uint32_t)(heads[l] >> 32));
-    L.gmax[wave * 64 + lane] = best;
-    __syncthreads();
-    if (wave == 0) {
-        uint32_t g = 0;
-#pragma unroll 4
-        for (int w = 0; w < nw; ++w) g = max(g, L.gmax[w * 64 + lane]);
-        const Cand sorted = bitonic_sort64<true>((Cand)g << 32);          // largest first
-        if (lane == kp - 1) L.sh[6] = (uint32_t)(sorted >> 32);            // 0: fewer than kprime groups hold anything, all pass
+        for (int i = H; i * nt < np; ++i) best = max(best, (uint32_t)(head_at(i) >> 32));
+        group_max(best);
+#pragma unroll
+        for (int u = 0; u < kNormLds / nt; ++u) s_q[tid + u * nt] = tid + u * nt < a.d ? x[u] : 0.f;
+    }
+    const uint32_t cut = cut_of_groups();
+
+    // 2. the entries that pass, of the lists whose heads do (mostly one or two of a wavefront's)
+    constexpr int C = 4;
+    Cand c[C];
+    auto offer = [&](uint32_t at_least) __attribute__((always_inline)) {
+        uint64_t b[C];
+        uint32_t n = 0;
+#pragma unroll
+        for (int u = 0; u < C; ++u) { b[u] = __ballot(c[u] != 0 && (uint32_t)(c[u] >> 32) >= at_least); n += (uint32_t)__popcll(b[u]); }
+        if (n == 0) return;
+        uint32_t base = 0;
+        if (lane == 0) base = atomicAdd(&L.sh[4], n);
+        base = read_lane(base, 0);
+#pragma unroll
+        for (int u = 0; u < C; ++u) {
+            const uint32_t pos = base + __popcll(b[u] & below);
+            if (((b[u] >> lane) & 1u) && pos < (uint32_t)kMergeCandCap) pool[pos] = c[u];
+            base += (uint32_t)__popcll(b[u]);
+        }
+    };
+    auto pool_lists = [&](Cand head, int i) __attribute__((always_inline)) {
+        uint64_t lists = __ballot(head != 0 && (uint32_t)(head >> 32) >= cut);
+#pragma unroll 1
+        while (lists) {
+#pragma unroll
+            for (int u = 0; u < C; ++u) {
+                c[u] = 0;
+                if (lists) {
+                    c[u] = part[(size_t)list_of(wave * 64 + __builtin_ctzll(lists), i) * slots + lane];
+                    lists &= lists - 1;
+                }
+            }
+            offer(cut);
+        }
+    };
+#pragma unroll
+    for (int i = 0; i < H; ++i) pool_lists(h[i], i);
+#pragma unroll 1
+    for (int i = H; i * nt < np; ++i) pool_lists(head_at(i), i);
+    if (wave == nw - 1) {
+        // |q|^2 for the error bound
+        double s = 0.0;
+#pragma unroll
+        for (int u = 0; u < kNormLds / 64; ++u) { const double y = (double)s_q[u * 64 + lane]; s = fma(y, y, s); }
+#pragma unroll 1
+        for (int t = lane + kNormLds; t < a.d; t += 64) { const double y = (double)q[t]; s = fma(y, y, s); }
+        s = wave_sum(s);
+        if (lane == 0) L.q_part[0] = s;
     }
     __syncthreads();
-    const uint32_t cut = L.sh[6];
-    // 2. the lists whose head passes ...
+    int cnt = (int)L.sh[4];
+    const Cand* cands = pool;
+    uint32_t m = 0;
 #pragma unroll 1
-    for (int l = tid; l < np; l += nt) {
-        const Cand h = head_at((uint32_t)l);
-        if (h != 0 && (uint32_t)(h >> 32) >= cut) {
-            const uint32_t pos = atomicAdd(&L.sh[5], 1u);
-            if (pos < (uint32_t)kMergeQlistCap) qlist[pos] = (uint32_t)l;
+    for (int round = 0; __builtin_expect(cnt > kMergeRanked && cnt <= kMergeCandCap && round < 3, 0); ++round) {
+        // many (rows that are all alike, a few lists that hold them all): another cut, the pool dealt anew
+        constexpr int R = kMergeCandCap / nt;
+        Cand v[R];
+        uint32_t best = 0;
+#pragma unroll
+        for (int u = 0; u < R; ++u) {
+            v[u] = u * nt + tid < cnt ? pool[u * nt + tid] : (Cand)0;
+            best = max(best, (uint32_t)(v[u] >> 32));
         }
+        group_max(best);
+        if (tid == 0) L.sh[6] = 0;
+        const uint32_t tighter = cut_of_groups();      // (behind its barrier everyone has read the pool and its size)
+        if (tid == 0) L.sh[4] = 0;
+        __syncthreads();
+#pragma unroll
+        for (int u0 = 0; u0 < R; u0 += C) {
+#pragma unroll
+            for (int u = 0; u < C; ++u) c[u] = u0 + u < R ? v[u0 + u] : (Cand)0;
+            offer(tighter);
+        }
+        __syncthreads();
+        cnt = (int)L.sh[4];
     }
-    __syncthreads();
-    const int nql = (int)L.sh[5];
-    if (nql > kMergeQlistCap) return false;
-    // ... and their entries that pass: four entries per thread and pass, all requested before
-    // the first is looked at
-    const int total = nql * slots;
-#pragma unroll 1
-    for (int e0 = 0; e0 < total; e0 += 4 * nt) {
-        Cand c[4];
+    if (cnt <= 32) {
+        m = (uint32_t)cnt;
+        const Cand other = lane < cnt ? pool[lane] : (Cand)0;
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const int e = e0 + u * nt + tid;
-            c[u] = e < total ? part[(size_t)qlist[e / slots] * slots + e % slots] : (Cand)0;
+        for (int i = 0; i < 32 / nw; ++i) {
+            const Cand v = read_lane(other, wave * (32 / nw) + i);
+            if (v != 0 && __popcll(__ballot(other > v)) == kp - 1 && lane == 0) L.f_last = (uint32_t)(v >> 32);
         }
+    } else if (cnt <= kMergeRanked) {
+        // the first kprime take their places.  Up to 64: a value's rank is the number of lanes above it; more:
+        // eight lanes per candidate count those ahead of it
+        auto place = [&](Cand v, uint32_t rank) __attribute__((always_inline)) {
+            if (rank < (uint32_t)kp) L.c_cand[rank] = v;
+            if (rank == (uint32_t)kp - 1) L.f_last = (uint32_t)(v >> 32);
+        };
+        if (cnt <= 64) {
+            const Cand other = lane < cnt ? pool[lane] : (Cand)0;
 #pragma unroll
-        for (int u = 0; u < 4; ++u) {
-            const bool ok = c[u] != 0 && (uint32_t)(c[u] >> 32) >= cut;
-            const uint64_t b = __ballot(ok);
-            if (b) {
-                uint32_t base = 0;
-                if (lane == 0) base = atomicAdd(&L.sh[4], (uint32_t)__popcll(b));
-                base = read_lane(base, 0);
-                const uint32_t pos = base + __popcll(b & ((1ull << lane) - 1ull));
-                if (ok && pos < (uint32_t)kMergeCandCap) pool[pos] = c[u];
+            for (int i = 0; i < 64 / nw; ++i) {
+                const Cand v = read_lane(other, wave * (64 / nw) + i);
+                const uint32_t rank = (uint32_t)__popcll(__ballot(other > v));
+                if (lane == 0 && v != 0) place(v, rank);
+            }
+        } else {
+#pragma unroll 1
+            for (int t = tid / 8; t < cnt; t += nt / 8) {
+                const Cand me = pool[t];
+                uint32_t rank, equal;
+                count_above(pool, (uint32_t)cnt, me, (uint32_t)tid & 7u, rank, equal);
+                if ((tid & 7) == 0) place(me, rank);
             }
         }
+        __syncthreads();
+        m = (uint32_t)min(cnt, kp);
+        cands = L.c_cand;
+    } else {
+        m = (uint32_t)gather_radix(a, part, L);
+        cands = L.c_cand;
     }
+
+    // 3. fp64 re-score
+    constexpr uint32_t groups = nt / kRescoreLanes;
+#pragma unroll 1
+    for (uint32_t c0 = (uint32_t)(tid / kRescoreLanes); c0 < m; c0 += kMergeRows * groups)
+        score_candidates<kMergeRows>(a, qi, L, cands, c0, groups, m, tid % kRescoreLanes);
+    const uint32_t tot = m + add_host_candidates(a, qi, L, m);
     __syncthreads();
-    const uint32_t cnt = L.sh[4];
-    if (cnt > (uint32_t)kMergeCandCap) return false;
-    if (__builtin_expect(cnt > 64, 0)) { rank_pool(pool, cnt, kp, L); return true; }
-    // 3. at most 64 candidates: one sort
-    if (wave == 0) {
-        const Cand sorted = bitonic_sort64<true>((uint32_t)lane < cnt ? pool[lane] : (Cand)0);
-        if ((uint32_t)lane < cnt && lane < kp) L.c_cand[lane] = sorted;
-        if (lane == 0) L.sh[4] = min(cnt, (uint32_t)kp);
+    // 4. ranked by ballots, every wavefront an equal share of the results against all: nearest first, ties by smaller
+    //    id (and, with an id that occurs more than once, by place); the lane whose result is the k-th proves it
+    const int k = a.k;
+#pragma unroll 1
+    for (uint32_t t0 = 0; t0 < tot; t0 += 64) {
+        const uint32_t at = min(t0 + (uint32_t)lane, tot - 1), last = min(tot - t0, 64u);
+        const uint64_t mk = L.f_key[at];
+        const int64_t mi = L.f_id[at];
+        uint32_t rank = 0;                           // of result t0 + lane, for lanes of this wavefront's share
+#pragma unroll 1
+        for (uint32_t j0 = 0; j0 < tot; j0 += 64) {
+            const uint32_t j = j0 + (uint32_t)lane;
+            const bool in = j < tot;
+            const uint64_t ok = t0 == j0 ? mk : L.f_key[min(j, tot - 1)];
+            const int64_t oi = t0 == j0 ? mi : L.f_id[min(j, tot - 1)];
+#pragma unroll 1
+            for (uint32_t t = (uint32_t)wave; t < last; t += nw) {
+                const uint64_t v = read_lane(mk, (int)t);
+                uint64_t ahead = __ballot(in && ok > v);
+                const uint64_t tie = __ballot(in && ok == v);
+                if (__builtin_expect((tie & (tie - 1)) != 0 || t0 != j0, 0)) {
+                    const int64_t vi = (int64_t)read_lane((uint64_t)mi, (int)t);
+                    ahead |= __ballot(in && ok == v && (oi < vi || (oi == vi && j < t0 + t)));
+                }
+                if (lane == (int)t) rank += (uint32_t)__popcll(ahead);
+            }
+        }
+        if (lane % nw == wave && t0 + (uint32_t)lane < tot && rank < (uint32_t)k) {
+            const double key = unordered(mk);
+            a.out_ids[(size_t)qi * k + rank] = mi;
+            a.out_dists[(size_t)qi * k + rank] = (float)(a.metric == 0 ? key : -key);
+            // Rows were dropped only if kprime candidates were kept (a wavefront of the scan drops nothing before
+            // it holds kprime, the gathering nothing before it has kprime).
+            if (rank == (uint32_t)k - 1 && m >= (uint32_t)kp) conclude(a, qi, !result_is_safe(key, unordered(L.f_last), a, L.q_part[0]), key);
+        }
     }
-    __syncthreads();
-    return true;
+    if (tid == 0 && m < (uint32_t)kp) conclude(a, qi, false, 0.0);
+    pad_results(a, qi, tot);
+    signal_done(a);
 }
 
+// ---- kprime above 64 -----------------------------------------------------------------------------
 // Wide path (kprime above 64: every list holds 128 entries, best first).  A first cut is taken from
 // the heads (block_bucket_cut: at least kprime of them pass, so at least kprime candidates do), the
 // lists whose head passes are walked 16 entries at a time while their last entry read still passes,
@@ -1479,16 +1743,17 @@ __device__ __forceinline__ bool gather_fast(const MergeArgs& a, const Cand* part
 // What bounds it: one workgroup, a handful of dependent L2 reads and barriers.  (The radix select
 // over all entries reads 2 MB up to ten times from one compute unit: 494 us at 2048 lists against
 // 27 us here, k 100 on 4 M x 768 fp16 rows.)
-// Returns false (for the whole workgroup) when the lists do not fit or masses of equal keys keep
-// overflowing the pool.
+// Returns the number of candidates in L.c_cand, with the key of the kprime-th in L.f_last; -1 (for the whole
+// workgroup) when the lists do not fit or masses of equal keys keep overflowing the pool.
 constexpr int kWideLists = 2048;           // lists the wide path can visit: all of one query's scan wavefronts
 constexpr int kWideRounds = 4;             // cuts tried before the radix select takes over
-__device__ __forceinline__ bool gather_wide(const MergeArgs& a, const Cand* part, const Cand* heads, MergeLds& L,
+__device__ __forceinline__ int gather_wide(const MergeArgs& a, const Cand* part, const Cand* heads, MergeLds& L,
                                             Cand* pool, uint16_t* alive) {
-    const int tid = threadIdx.x, nt = blockDim.x, lane = lane_id();
+    constexpr int nt = kMergeWideThreads;
+    const int tid = threadIdx.x, lane = lane_id();
     const int np = a.nparts, slots = a.list_len;
     const uint32_t kp = (uint32_t)a.kprime;
-    if (np > kWideLists) return false;
+    if (np > kWideLists) return -1;
     const Cand h0 = tid < np ? heads[tid] : (Cand)0;
     const Cand h1 = tid + nt < np ? heads[tid + nt] : (Cand)0;
     auto head_key = [&](uint32_t l) -> uint32_t { return (uint32_t)((l == (uint32_t)tid ? h0 : l == (uint32_t)(tid + nt) ? h1 : heads[l]) >> 32); };
@@ -1503,7 +1768,7 @@ __device__ __forceinline__ bool gather_wide(const MergeArgs& a, const Cand* part
         const uint32_t pos = base + __popcll(b & ((1ull << lane) - 1ull));
         if (ok && pos < (uint32_t)kMergeCandCap) pool[pos] = c;
     };
-    BucketCut bc = block_bucket_cut(head_key, (uint32_t)np, kp, L.hist, L.gmax);
+    BucketCut bc = block_bucket_cut(head_key, (uint32_t)np, kp, L.hist, L.red);
     uint32_t cnt = 0;
 #pragma unroll 1
     for (int round = 0;; ++round) {
@@ -1548,20 +1813,20 @@ __device__ __forceinline__ bool gather_wide(const MergeArgs& a, const Cand* part
         __syncthreads();
         cnt = L.sh[4];
         if (cnt <= (uint32_t)kMergeCandCap) break;
-        if (round == kWideRounds - 1) return false;
-        bc = block_bucket_cut(pool_key, (uint32_t)kMergeCandCap, kp, L.hist, L.gmax);
+        if (round == kWideRounds - 1) return -1;
+        bc = block_bucket_cut(pool_key, (uint32_t)kMergeCandCap, kp, L.hist, L.red);
     }
     if (cnt > 512) {
-        // kMergeCandCap / kMergeFastThreads entries per thread stay in registers while the pool is rebuilt
-        bc = block_bucket_cut(pool_key, cnt, kp, L.hist, L.gmax);
-        Cand mine[kMergeCandCap / kMergeFastThreads];
+        // kMergeCandCap / kMergeWideThreads entries per thread stay in registers while the pool is rebuilt
+        bc = block_bucket_cut(pool_key, cnt, kp, L.hist, L.red);
+        Cand mine[kMergeCandCap / kMergeWideThreads];
 #pragma unroll
-        for (int u = 0; u < kMergeCandCap / kMergeFastThreads; ++u) mine[u] = (uint32_t)(tid + u * nt) < cnt ? pool[tid + u * nt] : (Cand)0;
+        for (int u = 0; u < kMergeCandCap / kMergeWideThreads; ++u) mine[u] = (uint32_t)(tid + u * nt) < cnt ? pool[tid + u * nt] : (Cand)0;
         __syncthreads();
         if (tid == 0) L.sh[4] = 0;
         __syncthreads();
 #pragma unroll
-        for (int u = 0; u < kMergeCandCap / kMergeFastThreads; ++u) append(mine[u], mine[u] != 0 && bc.pass((uint32_t)(mine[u] >> 32)));
+        for (int u = 0; u < kMergeCandCap / kMergeWideThreads; ++u) append(mine[u], mine[u] != 0 && bc.pass((uint32_t)(mine[u] >> 32)));
         __syncthreads();
         cnt = L.sh[4];
     }
@@ -1572,74 +1837,20 @@ __device__ __forceinline__ bool gather_wide(const MergeArgs& a, const Cand* part
         uint32_t rank, equal;
         count_above(pool, cnt, me, (uint32_t)tid & 7u, rank, equal);
         if ((tid & 7) == 0 && rank < kp) L.c_cand[rank] = me;
+        if ((tid & 7) == 0 && rank == kp - 1) L.f_last = (uint32_t)(me >> 32);
     }
     __syncthreads();
-    if (tid == 0) L.sh[4] = min(cnt, kp);
-    __syncthreads();
-    return true;
+    return (int)min(cnt, kp);
 }
 
-// Last resort: radix select over all entries of all lists (candidates are distinct, so the
-// selection ends with exactly kprime of them).
-__device__ __forceinline__ void gather_radix(const MergeArgs& a, const Cand* part, MergeLds& L) {
-    const int tid = threadIdx.x, nt = blockDim.x, lane = lane_id();
-    const uint32_t n = (uint32_t)a.nparts * (uint32_t)a.list_len, kp = a.kprime;
-    auto key_at = [&](uint32_t i) { return ~part[i]; };      // ascending = best first; all ones = empty
-    uint32_t my_valid = 0;
-    for (uint32_t i = tid; i < n; i += nt) my_valid += part[i] != 0;
-    if (tid == 0) { L.sh[4] = 0; L.sh[5] = 0; }
-    __syncthreads();
-#pragma unroll
-    for (int m2 = 32; m2 >= 1; m2 >>= 1) my_valid += __shfl_xor(my_valid, m2);
-    if (lane == 0) atomicAdd(&L.sh[5], my_valid);
-    __syncthreads();
-    const uint32_t n_valid = L.sh[5];
-    if (n_valid <= kp) {
-        for (uint32_t i = tid; i < n; i += nt)
-            if (part[i] != 0) L.c_cand[atomicAdd(&L.sh[4], 1u)] = part[i];
-        __syncthreads();
-        return;
-    }
-    uint64_t mask, prefix; uint32_t need, group;
-    block_radix_select<uint64_t>(key_at, n, kp, L.hist, L.sh, mask, prefix, need, group);
-    // need == group here: distinct keys leave a boundary group of one
-    for (uint32_t i = tid; i < n; i += nt) {
-        const uint64_t key = key_at(i);
-        if (key != ~0ull && (key & mask) <= prefix) {
-            uint32_t p = atomicAdd(&L.sh[4], 1u);
-            if (p < (uint32_t)kMaxKPrime) L.c_cand[p] = part[i];
-        }
-    }
-    __syncthreads();
-}
-
-// Can a row that the scan or the gathering dropped still belong to the k nearest?  Everything
-// dropped anywhere has an fp32 key of at most f_last, the key of the last candidate kept, so its
-// exact score is at most f_last + E, E bounding the rounding of the fp32 accumulation:
-//   inner product   |fl(sum) - sum| <= g |q| |y|        squared distance   |fl(sum) - sum| <= g sum
-// with g = err_coef (a little above (terms + 2) 2^-24 for sums whose terms pass through at most
-// `terms` roundings).  The k-th best exact score found, s_k, is a lower bound of the true one;
-// the result is exact when s_k > f_last + E.
-__device__ __forceinline__ bool result_is_safe(double s_k, float f_last, const MergeArgs& a, double qq) {
-    // single precision is enough for the bound itself: it is rounded upwards
-    const float e = a.metric == 0 ? a.err_coef * (sqrtf((float)qq) * 1.0001f) * a.row_norm_max * 1.0001f
-                                  : a.err_coef * fabsf(f_last) * 1.0001f;
-    return s_k > (double)f_last + (double)e;
-}
-
-// WIDE: kprime above 64 (see gather_wide), else gather_fast; two kernels, so that neither carries
-// the code of the other (a workgroup that runs alone pays for the code it fetches).
-template <bool WIDE>
-__global__ __launch_bounds__(kMergeFastThreads) void merge_kernel(MergeArgs a) {
+__global__ __launch_bounds__(kMergeWideThreads) void merge_wide_kernel(MergeArgs a) {
     extern __shared__ __align__(16) unsigned char m_dyn[];
     __shared__ MergeLds L;
-    __shared__ double q_part[kSelectThreads / 64];
-    __shared__ double s_kth;
-    __shared__ uint32_t f_min;
-    const int tid = threadIdx.x, nt = blockDim.x;
+    constexpr int nt = kMergeWideThreads;
+    const int tid = threadIdx.x;
     const int qi = blockIdx.x;
-    const uint32_t n = (uint32_t)a.nparts * (uint32_t)a.list_len;
-    const Cand* part = a.part + (size_t)qi * n;
+    const Cand* part = a.part + (size_t)qi * (size_t)a.nparts * (size_t)a.list_len;
+    const Cand* heads = a.heads + (size_t)qi * a.nparts;
     const uint32_t kp = a.kprime;
     const float* q = a.q + (size_t)qi * a.d;
 
@@ -1648,105 +1859,37 @@ __global__ __launch_bounds__(kMergeFastThreads) void merge_kernel(MergeArgs a) {
         double s = 0.0;
         for (int t = tid; t < a.d; t += nt) { const double x = (double)q[t]; s = fma(x, x, s); }
         s = wave_sum(s);
-        if (lane_id() == 0) q_part[wave_id()] = s;
-        if (tid == 0) { f_min = 0xFFFFFFFFu; s_kth = -INFINITY; }
+        if (lane_id() == 0) L.q_part[wave_id()] = s;
     }
-
     // 1. the kprime best fp32 candidates
     Cand* pool = (Cand*)m_dyn;
-    const Cand* heads = a.heads + (size_t)qi * a.nparts;
-    const bool gathered = WIDE ? gather_wide(a, part, heads, L, pool, (uint16_t*)(pool + kMergeCandCap))
-                               : gather_fast(a, part, heads, L, pool, (uint32_t*)(pool + kMergeCandCap));
-    if (__builtin_expect(!gathered, 0)) {
+    int got = gather_wide(a, part, heads, L, pool, (uint16_t*)(pool + kMergeCandCap));
+    if (__builtin_expect(got < 0, 0)) {
         __syncthreads();
-        gather_radix(a, part, L);
+        got = gather_radix(a, part, L);
     }
-    const uint32_t m = min(L.sh[4], (uint32_t)kMaxKPrime);
-
-    // 2. fp64 re-score: a group of kRescoreLanes lanes per candidate, nt / kRescoreLanes
-    //    candidates at once.  The order of operations is fixed (see rescore_row), so a row has
-    //    the same fp64 score whichever kernel, or the host, computes it.
-    const int np = a.nprobe;
-    constexpr int lpc = kRescoreLanes;
-    const int sub = tid % lpc;
-    // More than one round of them (WIDE), rows found without a search and whole 16-byte chunks: two
-    // candidates per group are in flight (112 of 1.5 KB: 29.4 -> 27.0 us for the whole kernel).
-    const bool paired = WIDE && a.identity && ((size_t)a.d * (a.dtype == 0 ? 4 : 2)) % 16 == 0;
-    if (paired) {
-        const uint32_t groups = (uint32_t)(nt / lpc);
+    const uint32_t m = (uint32_t)got;
+    // 2. fp64 re-score, two candidates of a group of lanes in flight (112 of 1.5 KB: 29.4 -> 27.0 us for the whole kernel)
+    {
+        constexpr uint32_t groups = nt / kRescoreLanes;
 #pragma unroll 1
-        for (uint32_t c = (uint32_t)(tid / lpc); c < m; c += 2 * groups) {
-            uint32_t row[2];
-            int64_t id[2];
-            double s[2];
-#pragma unroll
-            for (int r = 0; r < 2; ++r) {
-                row[r] = cand_tie(L.c_cand[min(c + groups * r, m - 1)]);
-                id[r] = a.ids ? a.ids[row[r]] : (int64_t)row[r];
-            }
-            rescore_rows<2>(a.buf, q, a.d, a.dtype, a.metric, row, sub, s);
-#pragma unroll
-            for (int r = 0; r < 2; ++r) {
-                const uint32_t e = c + groups * r;
-                if (sub == 0 && e < m) {
-                    L.f_key[e] = a.metric == 0 ? s[r] : -s[r];
-                    L.f_id[e] = id[r];
-                    atomicMin(&f_min, (uint32_t)(L.c_cand[e] >> 32));
-                }
-            }
-        }
-    }
-#pragma unroll 1
-    for (uint32_t c = paired ? m : (uint32_t)(tid / lpc); c < m; c += (uint32_t)(nt / lpc)) {
-        const Cand cand = L.c_cand[c];
-        const uint32_t row = cand_tie(cand);
-        const int64_t id = a.ids ? a.ids[row] : (int64_t)row;
-        size_t brow = row;
-        bool found_row = true;
-        if (!a.identity) {
-            // the slot whose global row range holds the row
-            const int64_t* s_base = a.slots.base + (size_t)qi * np;
-            const uint32_t* s_grow = a.slots.grow + (size_t)qi * np;
-            const uint32_t* s_n = a.slots.nrows + (size_t)qi * np;
-            int found = -1;
-#pragma unroll 1
-            for (int s = sub; s < np; s += lpc)
-                if (row >= s_grow[s] && row - s_grow[s] < s_n[s]) found = s;
-#pragma unroll 1
-            for (int o = 1; o < lpc; o <<= 1) found = max(found, __shfl_xor(found, o));
-            found_row = found >= 0;
-            brow = found_row ? (size_t)(s_base[found] + (int64_t)(row - s_grow[found])) : 0;
-        }
-        const double s = rescore_row(a.buf, q, a.d, a.dtype, a.metric, brow, sub);
-        if (sub == 0) {
-            L.f_key[c] = !found_row ? -INFINITY : (a.metric == 0 ? s : -s);
-            L.f_id[c] = id;
-            atomicMin(&f_min, (uint32_t)(cand >> 32));        // key image of the last candidate kept
-        }
+        for (uint32_t c = (uint32_t)(tid / kRescoreLanes); c < m; c += 2 * groups)
+            score_candidates<2>(a, qi, L, L.c_cand, c, groups, m, tid % kRescoreLanes);
     }
     // 3. host candidates
-    uint32_t nh = 0;
-    if (a.host_cand) {
-        nh = min((uint32_t)a.host_count[qi], kp);
-        for (uint32_t i = tid; i < nh; i += nt) {
-            L.f_key[m + i] = a.host_cand[(size_t)qi * kp + i].key;
-            L.f_id[m + i] = a.host_cand[(size_t)qi * kp + i].id;
-        }
-    }
+    const uint32_t tot = m + add_host_candidates(a, qi, L, m);
     __syncthreads();
-    // 4. rank by counting; nearest first, ties by smaller id
-    const uint32_t tot = m + nh;
+    // 4. rank by counting, eight lanes per candidate; nearest first, ties by smaller id
     const int k = a.k;
-    // eight lanes per candidate
     for (uint32_t t = (uint32_t)tid / 8; t < tot; t += (uint32_t)nt / 8) {
-        const double mk = L.f_key[t];
+        const uint64_t mk = L.f_key[t];
         const int64_t mi = L.f_id[t];
         uint32_t rank = 0;
         // four others per lane and pass, all read before any is compared, and no branches: a compare that
         // waits for its own LDS read every time costs more than the whole pass
 #pragma unroll 1
         for (uint32_t j0 = (uint32_t)tid & 7u; j0 < tot; j0 += 32) {
-            double ok[4]; int64_t oi[4];
+            uint64_t ok[4]; int64_t oi[4];
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
                 const uint32_t j = min(j0 + 8u * u, tot - 1);
@@ -1754,44 +1897,27 @@ __global__ __launch_bounds__(kMergeFastThreads) void merge_kernel(MergeArgs a) {
             }
 #pragma unroll
             for (int u = 0; u < 4; ++u) {
-                const bool ahead = (ok[u] > mk) | ((ok[u] == mk) & (oi[u] < mi));
-                rank += (uint32_t)(ahead & (j0 + 8u * u < tot));
+                const uint32_t j = j0 + 8u * u;
+                const bool ahead = (ok[u] > mk) | ((ok[u] == mk) & ((oi[u] < mi) | ((oi[u] == mi) & (j < t))));
+                rank += (uint32_t)(ahead & (j < tot));
             }
         }
         rank = sum_of_8(rank);
         if ((tid & 7) == 0 && rank < (uint32_t)k) {
+            const double key = unordered(mk);
             a.out_ids[(size_t)qi * k + rank] = mi;
-            a.out_dists[(size_t)qi * k + rank] = (float)(a.metric == 0 ? mk : -mk);
-        }
-        if ((tid & 7) == 0 && rank == (uint32_t)k - 1) s_kth = mk;
-    }
-    for (uint32_t i = tot + tid; i < (uint32_t)k; i += nt) {
-        a.out_ids[(size_t)qi * k + i] = -1;
-        a.out_dists[(size_t)qi * k + i] = a.metric == 0 ? -INFINITY : INFINITY;
-    }
-    __syncthreads();
-    // 5. is the result proven?  Rows were dropped only if kprime candidates were kept (a wavefront
-    //    drops nothing before it holds kprime, the gathering nothing before it has kprime).
-    if (tid == 0) {
-        uint32_t unsafe = 0;
-        if (m == kp) {
-            double qq = 0.0;
-            for (int w = 0; w < nt / 64; ++w) qq += q_part[w];
-            unsafe = result_is_safe(s_kth, unordered(f_min), a, qq) ? 0u : 1u;
-        }
-        if (a.redo_flag) {
-            a.redo_flag[qi] = unsafe;
-            if (unsafe) {
-                a.redo_thr[qi] = s_kth;
-                a.redo_ticket[qi] = 0u;
+            a.out_dists[(size_t)qi * k + rank] = (float)(a.metric == 0 ? key : -key);
+            if (rank == (uint32_t)k - 1 && m >= kp) {
+                double qq = 0.0;
+#pragma unroll
+                for (int w = 0; w < nt / 64; ++w) qq += L.q_part[w];
+                conclude(a, qi, !result_is_safe(key, unordered(L.f_last), a, qq), key);
             }
         }
-        if (a.host_flag) a.host_flag[qi] = unsafe;       // pinned: stored before the completion word below
-        if (a.done) {
-            __threadfence_system();
-            __hip_atomic_store(a.done, a.done_value, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
-        }
     }
+    if (tid == 0 && m < kp) conclude(a, qi, false, 0.0);
+    pad_results(a, qi, tot);
+    signal_done(a);
 }
 
 // =============================================================================================
@@ -2018,8 +2144,8 @@ hipError_t launch_redo(const RedoArgs& a, int grid, hipStream_t s) {
 hipError_t launch_merge(const MergeArgs& a, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
     if (a.done && a.nq != 1) return hipErrorInvalidValue;
     const size_t pool = (size_t)kMergeCandCap * sizeof(uint64_t);
-    if (a.kprime > 64) IVF_LAUNCH(merge_kernel<true>, dim3(a.nq), dim3(kMergeFastThreads), pool + 2 * kWideLists * sizeof(uint16_t), s, e0, e1, a);
-    else IVF_LAUNCH(merge_kernel<false>, dim3(a.nq), dim3(kMergeFastThreads), pool + kMergeQlistCap * sizeof(uint32_t), s, e0, e1, a);
+    if (a.kprime > 64) IVF_LAUNCH(merge_wide_kernel, dim3(a.nq), dim3(kMergeWideThreads), pool + 2 * kWideLists * sizeof(uint16_t), s, e0, e1, a);
+    else IVF_LAUNCH(merge_kernel, dim3(a.nq), dim3(kMergeThreads), pool, s, e0, e1, a);
     return hipGetLastError();
 }
 
