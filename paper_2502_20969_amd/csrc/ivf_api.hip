@@ -473,8 +473,9 @@ static int stage_queries(ivf_index* ix, const float* q_host, int nq) {
 
 // coarse scoring + selection for nq queries already in d_q (device); leaves the probe lists
 // and slot tables in the workspace
+// in_scan: the scan selects (select_in_scan)
 int enqueue_probe(ivf_index* ix, const float* q_dev, int nq, int nprobe, int grid, bool count_rows = true,
-                  bool is_search = false) {
+                  bool is_search = false, bool in_scan = false) {
     Workspace& w = *ix->cw;
     int rc;
     // the per-workgroup tables of the workspace were sized for w.wg_cap workgroups and w.nq queries
@@ -484,6 +485,7 @@ int enqueue_probe(ivf_index* ix, const float* q_dev, int nq, int nprobe, int gri
     if ((rc = prof_events(ix, 0, &e0, &e1))) return rc;
     CoarseArgs ca{ix->d_centroids, q_dev, w.d_scores, ix->nlist, ix->d, nq, ix->metric};
     HIP_TRY(launch_coarse(ca, ix->cs, e0, e1));
+    if (in_scan) return IVF_OK;
     if ((rc = prof_events(ix, 1, &e0, &e1))) return rc;
     SelectArgs sa{};
     sa.scores = w.d_scores; sa.probe = w.d_probe; sa.off = ix->d_off; sa.res_off = ix->d_res_off;
@@ -497,9 +499,20 @@ int enqueue_probe(ivf_index* ix, const float* q_dev, int nq, int nprobe, int gri
     return IVF_OK;
 }
 
-int enqueue_scan(ivf_index* ix, const float* q_dev, int nq, int nprobe, int kprime, int grid, const ScanShape& shape) {
+// Whether the scan of a search selects the clusters itself: when all its workgroups are resident at once, so that they do it
+// side by side.  Not while kernels are timed one by one.
+bool select_in_scan(const ivf_index* ix, int nq, int nprobe, int kprime, int grid, const ScanShape& shape) {
+    return !ix->profiling && scan_selects(shape, ix->nlist, nprobe) && (int64_t)nq * grid <= ix->resident_grid[kprime > 64 ? 1 : 0];
+}
+
+int enqueue_scan(ivf_index* ix, const float* q_dev, int nq, int nprobe, int kprime, int grid, const ScanShape& shape, bool in_scan = false) {
     Workspace& w = *ix->cw;
     ScanArgs sc{};
+    if (in_scan) {
+        sc.scores = w.d_scores; sc.off = ix->d_off; sc.res_off = ix->d_res_off; sc.nlist = ix->nlist;
+        sc.probe = w.d_probe;
+        sc.used = ix->cache_on ? ix->d_used : nullptr;
+    }
     sc.buf = ix->d_buf; sc.q = q_dev; sc.slots = w.slots;
     sc.part = w.d_part; sc.heads = w.d_heads;
     sc.desc = w.d_desc;
@@ -1108,8 +1121,9 @@ static int enqueue_per_query(ivf_index* ix, const float* q_dev, int nq, int npro
     const int kprime = kprime_for(k);
     const ScanShape shape = shape_for(ix, nprobe, kprime, nq);
     const int grid = scan_grid_for(ix, nprobe, kprime, nq, shape);
-    if ((r = enqueue_probe(ix, q_dev, nq, nprobe, grid, true, true))) return r;
-    if ((r = enqueue_scan(ix, q_dev, nq, nprobe, kprime, grid, shape))) return r;
+    const bool in_scan = select_in_scan(ix, nq, nprobe, kprime, grid, shape);
+    if ((r = enqueue_probe(ix, q_dev, nq, nprobe, grid, true, true, in_scan))) return r;
+    if ((r = enqueue_scan(ix, q_dev, nq, nprobe, kprime, grid, shape, in_scan))) return r;
     if ((r = enqueue_merge(ix, q_dev, nq, nprobe, k, kprime, grid, false, ids_dev, dists_dev, lazy && nq == 1, lazy))) return r;
     if (lazy) return IVF_OK;
     return enqueue_redo(ix, q_dev, nq, nprobe, k, kprime, false, ids_dev, dists_dev);
@@ -1260,8 +1274,9 @@ extern "C" int ivf_search_device_noalloc(ivf_index* ix, const float* q_dev, int3
     // nothing in the area has to start at zero
     hipStream_t cs = ix->cs; Workspace* cw = ix->cw;
     ix->cs = ix->compute; ix->cw = &w;
-    rc = enqueue_probe(ix, q_dev, nq, nprobe, grid, true, true);
-    if (!rc) rc = enqueue_scan(ix, q_dev, nq, nprobe, kprime, grid, ix->shape);
+    const bool in_scan = select_in_scan(ix, nq, nprobe, kprime, grid, ix->shape);
+    rc = enqueue_probe(ix, q_dev, nq, nprobe, grid, true, true, in_scan);
+    if (!rc) rc = enqueue_scan(ix, q_dev, nq, nprobe, kprime, grid, ix->shape, in_scan);
     if (!rc) rc = enqueue_merge(ix, q_dev, nq, nprobe, k, kprime, grid, false, ids_dev, dists_dev);
     if (!rc) rc = enqueue_redo(ix, q_dev, nq, nprobe, k, kprime, false, ids_dev, dists_dev);
     ix->cs = cs; ix->cw = cw;
@@ -1330,13 +1345,14 @@ extern "C" int ivf_search(ivf_index* ix, const float* q_out, int32_t nq, int32_t
     }
     if (rc) return rc;
     if (hybrid && ix->pf_recorded) HIP_TRY(hipStreamWaitEvent(ix->cs, ix->ev_pf_done, 0));
-    if ((rc = enqueue_probe(ix, w.d_q, nq, nprobe, grid, true, true))) return rc;
     const bool want_probe = hybrid || stats;
+    const bool in_scan = !want_probe && select_in_scan(ix, nq, nprobe, kprime, grid, shape);
+    if ((rc = enqueue_probe(ix, w.d_q, nq, nprobe, grid, true, true, in_scan))) return rc;
     if (want_probe) {
         HIP_TRY(hipMemcpyAsync(w.h_probe, w.d_probe, (size_t)nq * nprobe * sizeof(int32_t), hipMemcpyDeviceToHost, ix->cs));
         HIP_TRY(hipEventRecord(ix->ev_probe, ix->cs));
     }
-    if ((rc = enqueue_scan(ix, w.d_q, nq, nprobe, kprime, grid, shape))) return rc;
+    if ((rc = enqueue_scan(ix, w.d_q, nq, nprobe, kprime, grid, shape, in_scan))) return rc;
 
     if (want_probe) {
         HIP_TRY(hipEventSynchronize(ix->ev_probe));

@@ -95,7 +95,15 @@ struct ScanArgs {
     uint64_t* heads;         // [nq x (grid x kScanWaves)] out: the best entry of every list, packed densely for the merge
     int d, dtype, metric, nprobe, nq, kprime, grid;
     ScanShape shape;
+    // Nullable: coarse scores [nq x nlist].  The scan then selects the clusters itself (scan_selects), and its first workgroup
+    // of a query writes what the select kernel would have (slots, probe, used, rows_counter).
+    const double* scores;
+    const int64_t* off; const int64_t* res_off;
+    int32_t* probe; uint32_t* used; unsigned long long* rows_counter;
+    int nlist;
 };
+// whether the scan of this shape can select the clusters itself
+bool scan_selects(const ScanShape& shape, int nlist, int nprobe);
 hipError_t launch_scan(const ScanArgs& a, hipStream_t s, hipEvent_t start = nullptr, hipEvent_t stop = nullptr);
 // workgroups of the scan kernel for (shape, dtype, metric, kprime) that are resident at once
 int scan_resident_grid(const ScanShape& shape, int dtype, int metric, int kprime, int d, int n_cu);

@@ -47,7 +47,6 @@ constexpr int kPairTile = 4;
 constexpr int64_t kCoarsePairWgs = 2048;         // workgroups of that kernel; more pairs make their walks longer
 // (inner products that come here are at most 4 queries of 2048 centroids)
 static bool coarse_in_pairs(const CoarseArgs& a) { return a.metric != 0 && a.d >= 4 && a.nq >= 3 && (int64_t)a.nq * a.nlist >= kPairsMin; }
-constexpr int kSelectWaveSortMax = 4096;   // select: register sorting path up to this many clusters
 
 // RAGGED: d is no multiple of 4, rows start at any element.
 // A wavefront takes one centroid for `per` queries, one after the other: as few as still make no more
@@ -439,6 +438,233 @@ __device__ __forceinline__ void select_sorted(const SelectArgs& a, const double*
     block_bitonic_sort(keys, idx, pad);
 }
 
+// ---- up to 64 clusters of up to four per thread -----------------------------------------------------
+// The order is (key, index) with key = the order-preserving image of the 64-bit score, larger = nearer, equal keys by smaller
+// index.  Clusters are dealt to 64 groups by their numbers (128 when more than 32 are wanted); T, the largest of the
+// maxima's high words that at least nprobe of them reach, lets at least nprobe candidates pass and, with groups
+// unrelated to the scores, about nprobe (1 + nprobe / 128) of them.  Those are pooled, and each finds its rank by
+// ballots over the pool: exact, whatever ties there are.
+// What bounds it: two trips to memory and the instructions of one workgroup.  Ranks by ballots are dealt to the
+// wavefronts, where a sorting network is one wavefront's chain (a kernel of its own, us, before / now: 8 of 64 clusters
+// 5.4 / 4.2, 32 of 1024 5.9 / 4.9; a search that selects 64 of 4096 whose best are all in one of eight groups 60 / 26).
+constexpr int kFewPerThread = 4;
+constexpr int kFewThreads = 256;         // up to 1024 clusters; more: kSelectThreads
+struct FewLds {
+    uint32_t red[128];
+    uint32_t n, cut, above, pad;
+    uint32_t pick[64];           // the selected clusters, nearest first
+    // behind it: uint64_t key[NT * kFewPerThread], uint32_t idx[NT * kFewPerThread]
+};
+static size_t few_lds(int threads) { return sizeof(FewLds) + (size_t)threads * kFewPerThread * 12; }
+
+// Leaves the clusters in L.pick[0 .. nprobe - 1]; all threads of the workgroup (NT) call it, nprobe <= min(64, nlist) and
+// nlist <= NT * kFewPerThread.
+template <int NT>
+__device__ __forceinline__ void select_few(const double* sc, int nlist, int nprobe, int metric, FewLds& L) {
+    constexpr int C = kFewPerThread, NW = NT / 64, G = NT / 128;       // G lanes hold one of 128 groups
+    uint64_t* pkey = (uint64_t*)(&L + 1);
+    uint32_t* pidx = (uint32_t*)(pkey + NT * C);
+    const int tid = threadIdx.x, lane = lane_id(), wave = wave_id();
+    // cluster c belongs to group c % 128: scores that rise or fall with the number, or come in runs, spread over the groups
+    const int first = (tid & (G - 1)) * 128 + tid / G;
+    double v[C];
+#pragma unroll
+    for (int j = 0; j < C; ++j) v[j] = sc[min(first + j * NT, nlist - 1)];
+    if (tid == 0) { L.n = 0; L.cut = 0; L.above = 0; }
+    uint64_t key[C];
+    uint32_t idx[C];
+#pragma unroll
+    for (int j = 0; j < C; ++j) { key[j] = ~coarse_key(v[j], metric); idx[j] = (uint32_t)(first + j * NT); }
+    // T for the words of those in `active` (bit j: candidate j of the thread) and `want` of them
+    auto cut_of = [&](const uint32_t (&word)[C], uint32_t active, int want) __attribute__((always_inline)) -> uint32_t {
+        uint32_t best = 0;
+#pragma unroll
+        for (int j = 0; j < C; ++j) if ((active >> j) & 1u) best = max(best, word[j]);
+        if (G >= 2) best = max(best, xor_lane_u32<1>(best));
+        if (G >= 4) best = max(best, xor_lane_u32<2>(best));
+        if (G >= 8) best = max(best, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)best, 0x141, 0xF, 0xF, true));      // row_half_mirror
+        if ((lane & (G - 1)) == 0) L.red[tid / G] = best;
+        __syncthreads();
+        uint32_t g0 = L.red[2 * lane], g1 = L.red[2 * lane + 1];
+        const bool fine = want > 32;                 // all 128 groups; else two of them together
+        if (!fine) { g0 = max(g0, g1); g1 = 0; }
+        uint32_t t = 0;
+#pragma unroll
+        for (int i = 0; i < 64 / NW; ++i) {
+            const uint32_t u = read_lane(g0, wave * (64 / NW) + i);
+            int reach = __popcll(__ballot(g0 >= u));
+            if (fine) {
+                const uint32_t w = read_lane(g1, wave * (64 / NW) + i);
+                reach += __popcll(__ballot(g1 >= u));
+                const int reach1 = __popcll(__ballot(g0 >= w)) + __popcll(__ballot(g1 >= w));
+                t = reach1 >= want ? max(t, w) : t;
+            }
+            t = reach >= want ? max(t, u) : t;
+        }
+        if (lane == 0 && t) atomicMax(&L.cut, t);
+        __syncthreads();
+        return L.cut;                                // 0: fewer than `want` groups hold anything, all pass
+    };
+    auto pool = [&](uint32_t which) __attribute__((always_inline)) {
+        uint64_t b[C];
+        uint32_t n = 0;
+#pragma unroll
+        for (int j = 0; j < C; ++j) { b[j] = __ballot((which >> j) & 1u); n += (uint32_t)__popcll(b[j]); }
+        if (n) {
+            uint32_t base = 0;
+            if (lane == 0) base = atomicAdd(&L.n, n);
+            base = read_lane(base, 0);
+            const uint64_t below = (1ull << lane) - 1ull;
+#pragma unroll
+            for (int j = 0; j < C; ++j) {
+                const uint32_t pos = base + __popcll(b[j] & below);
+                if ((b[j] >> lane) & 1u) { pkey[pos] = key[j]; pidx[pos] = idx[j]; }
+                base += (uint32_t)__popcll(b[j]);
+            }
+        }
+        __syncthreads();
+        return (int)L.n;
+    };
+    uint32_t active = 0, taken = 0;
+    uint32_t word[C];
+#pragma unroll
+    for (int j = 0; j < C; ++j) { word[j] = (uint32_t)(key[j] >> 32); active |= first + j * NT < nlist ? 1u << j : 0u; }
+    int want = nprobe;
+    uint32_t cut = cut_of(word, active, want);
+    auto passing = [&]() __attribute__((always_inline)) {
+        uint32_t m = 0;
+#pragma unroll
+        for (int j = 0; j < C; ++j) m |= word[j] >= cut ? 1u << j : 0u;
+        return (m & active) | taken;
+    };
+    int cnt = pool(passing());                       // at least nprobe
+#pragma unroll 1
+    for (int round = 0, level = 0; __builtin_expect(cnt > 128 && round < 5, 0); ++round) {
+        // Many.  Those above the cut word are in, when they are fewer than wanted (masses of scores with the same high
+        // word, as of a query of zeros); of those with the cut word the low words decide, then the numbers of the clusters.
+        // Else only those above it matter (scores that run with the groups): they are dealt anew, in the order of the pool.
+        uint32_t over = 0, same = 0;
+#pragma unroll
+        for (int j = 0; j < C; ++j) {
+            if ((active >> j) & 1u) { over |= word[j] > cut ? 1u << j : 0u; same |= word[j] == cut ? 1u << j : 0u; }
+        }
+        const uint32_t mine = (uint32_t)__popc(over);
+        if (mine) atomicAdd(&L.above, mine);
+        __syncthreads();
+        const int above = (int)L.above;
+        __syncthreads();
+        if (tid == 0) { L.n = 0; L.cut = 0; L.above = 0; }
+        __syncthreads();
+        if (above >= want) {
+            cnt = pool(over | taken);
+            active = 0;
+#pragma unroll
+            for (int j = 0; j < C; ++j) {
+                const int at = first + j * NT;
+                if (at < cnt) { key[j] = pkey[at]; idx[j] = pidx[at]; active |= 1u << j; }
+            }
+            taken = 0; want = nprobe; level = 0;
+            __syncthreads();
+            if (tid == 0) L.n = 0;
+        } else {
+            want -= above;
+            taken |= over;
+            active = same;
+            ++level;
+        }
+#pragma unroll
+        for (int j = 0; j < C; ++j) word[j] = level == 0 ? (uint32_t)(key[j] >> 32) : level == 1 ? (uint32_t)key[j] : ~idx[j];
+        cut = cut_of(word, active, want);
+        cnt = pool(passing());
+    }
+    if (__builtin_expect(cnt <= 128, 1)) {
+        // (places past the end: below every score, behind every index)
+        const uint64_t k0 = lane < cnt ? pkey[lane] : 0, k1 = lane + 64 < cnt ? pkey[lane + 64] : 0;
+        const uint32_t i0 = lane < cnt ? pidx[lane] : ~0u, i1 = lane + 64 < cnt ? pidx[lane + 64] : ~0u;
+        auto rank_of = [&](uint64_t k, uint32_t i) __attribute__((always_inline)) {
+            int rank = __popcll(__ballot(k0 > k));
+            uint64_t e0 = __ballot(k0 == k), e1 = 0;
+            if (cnt > 64) { rank += __popcll(__ballot(k1 > k)); e1 = __ballot(k1 == k); }
+            if (__builtin_expect(__popcll(e0) + __popcll(e1) > 1, 0)) rank += __popcll(__ballot(k0 == k && i0 < i)) + __popcll(__ballot(k1 == k && i1 < i));
+            if (rank < nprobe && lane == 0) L.pick[rank] = i;
+        };
+#pragma unroll 1
+        for (int j = wave; j < min(cnt, 64); j += NW) rank_of(read_lane(k0, j), read_lane(i0, j));
+#pragma unroll 1
+        for (int j = 64 + wave; j < cnt; j += NW) rank_of(read_lane(k1, j - 64), read_lane(i1, j - 64));
+    } else {
+        // (scores that five cuts did not thin out)
+#pragma unroll 1
+        for (int t = tid; t < cnt; t += NT) {
+            const uint64_t k = pkey[t];
+            const uint32_t i = pidx[t];
+            int rank = 0;
+#pragma unroll 1
+            for (int j0 = 0; j0 < cnt && rank < nprobe; j0 += 8) {
+                uint64_t o[8];
+                uint32_t w[8];
+#pragma unroll
+                for (int u = 0; u < 8; ++u) { o[u] = pkey[min(j0 + u, cnt - 1)]; w[u] = pidx[min(j0 + u, cnt - 1)]; }
+#pragma unroll
+                for (int u = 0; u < 8; ++u) rank += (int)((j0 + u < cnt) & ((o[u] > k) | ((o[u] == k) & (w[u] < i))));
+            }
+            if (rank < nprobe) L.pick[rank] = i;
+        }
+    }
+    __syncthreads();
+}
+
+// Inclusive sum over the lanes of a wavefront.
+__device__ __forceinline__ uint32_t wave_prefix(uint32_t v) {
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xF, 0xF, true);        // row_shr:1, 2, 4, 8
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xF, 0xF, true);
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xF, 0xF, true);
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xF, 0xF, true);
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xA, 0xF, false);       // row_bcast:15 into rows 1 and 3
+    v += (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xC, 0xF, false);       // row_bcast:31 into rows 2 and 3
+    return v;
+}
+
+// The slot table of a query that selected up to 64 clusters, one slot per lane (L.pick), by one wavefront.
+struct LaneSlot { uint32_t cluster, grow, nrows, end; int64_t base; };     // end: rows of the resident slots up to and with this one
+__device__ __forceinline__ LaneSlot slot_of_lane(const FewLds& L, int nprobe, const int64_t* off, const int64_t* res_off) {
+    LaneSlot s;
+    const int lane = lane_id();
+    s.cluster = L.pick[min(lane, nprobe - 1)];
+    const int64_t lo = off[s.cluster], hi = off[s.cluster + 1];
+    s.base = res_off[s.cluster];
+    s.grow = (uint32_t)lo;
+    s.nrows = (uint32_t)(hi - lo);
+    s.end = wave_prefix(lane < nprobe && s.base >= 0 ? s.nrows : 0u);
+    return s;
+}
+// ... written where the merge, the second pass and the caller look for it.
+__device__ __forceinline__ void store_slots(const LaneSlot& s, int nprobe, int qi, const SlotTables& slots, int32_t* probe, uint32_t* used,
+                                            unsigned long long* rows_counter) {
+    const int lane = lane_id();
+    if (lane < nprobe) {
+        const size_t o = (size_t)qi * nprobe + lane;
+        probe[o] = (int32_t)s.cluster;
+        slots.base[o] = s.base;
+        slots.grow[o] = s.grow;
+        slots.nrows[o] = s.nrows;
+        slots.rprefix[o + qi + 1] = s.end;
+        if (used && s.base >= 0) used[s.cluster] = 1u;            // cache bookkeeping: resident and selected
+    }
+    if (lane == 0) slots.rprefix[(size_t)qi * (nprobe + 1)] = 0u;
+    if (rows_counter && lane == 63) atomicAdd(rows_counter, (unsigned long long)s.end);
+}
+
+template <int NT>
+__global__ __launch_bounds__(NT) void select_few_kernel(SelectArgs a) {
+    extern __shared__ __align__(16) unsigned char smem_raw[];
+    FewLds& L = *(FewLds*)smem_raw;
+    select_few<NT>(a.scores + (size_t)blockIdx.x * a.nlist, a.nlist, a.nprobe, a.metric, L);
+    if (wave_id() == 0) store_slots(slot_of_lane(L, a.nprobe, a.off, a.res_off), a.nprobe, (int)blockIdx.x, a.slots, a.probe, a.used, a.rows_counter);
+}
+// up to 64 of up to 4096 clusters
+static bool selects_few(int nlist, int nprobe) { return nprobe <= 64 && nlist <= kSelectThreads * kFewPerThread; }
+
 // The nprobe nearest by packed candidates (top 40 bits of the descending key image, complement of
 // the cluster index: larger = nearer).  The candidates are dealt to the threads; a bucket cut over
 // the threads' best lets at least nprobe of those pass, so at least nprobe candidates do, and, with
@@ -611,133 +837,7 @@ __global__ __launch_bounds__(kSelectThreads) void select_kernel(SelectArgs a, ui
     const uint32_t nprobe = a.nprobe;
     const size_t sort_bytes = in_lds ? (size_t)pad * 12 : 0;
     uint32_t* idx;
-    if (in_lds && nprobe <= 64 && a.nlist <= kSelectWaveSortMax) {
-        // Few clusters wanted from a small index.  Each score is cut down to a packed candidate:
-        // the top 40 bits of its descending key image, then the complement of the cluster index
-        // (larger = nearer; equal prefixes by smaller index).  The candidates are dealt to 64 or
-        // 128 groups (a thread's go to the group of its lane); the nprobe-th largest group maximum
-        // is not above the nprobe-th largest candidate, so the nprobe nearest are among the
-        // candidates that reach its prefix: about nprobe (1 + nprobe / 128) of them when the
-        // groups are unrelated to the scores.  Those are pooled; up to 64 are ordered by one
-        // sort of wavefront 0, more by counting.  The order of the prefixes is the order of the
-        // scores wherever prefixes differ, so the result is exact unless two prefixes tie among
-        // the selected clusters or across the cut; then the exact general path below redoes the
-        // selection, as it does when the pool overflows.
-        uint64_t* keys = (uint64_t*)smem_raw;
-        idx = (uint32_t*)(smem_raw + sizeof(uint64_t) * pad);
-        const int lane = lane_id(), wave = wave_id(), nw = nt >> 6;
-        Cand* pool = (Cand*)(((uintptr_t)(smem_raw + sort_bytes + (size_t)(nprobe + 1) * 4) + 15) & ~(uintptr_t)15);   // [nt]
-        Cand* sel = pool + nt;                                  // [65] the nprobe best and the one after, when counted
-        uint32_t* gmax = (uint32_t*)(sel + 66);                 // [2 * nt] halves of every thread's best candidate
-        if (tid == 0) { sh[4] = 0; sh[6] = 0; }
-        if (tid < 65) sel[tid] = 0;
-        auto packed = [&](int i, double s) {
-            return (~coarse_key(s, a.metric) & ~0xFFFFFFull) | (uint64_t)(0xFFFFFFu - (uint32_t)i);
-        };
-        // the first four scores of a thread are requested together and stay in registers
-        Cand c4[4];
-        {
-            double s4[4];
-#pragma unroll
-            for (int j = 0; j < 4; ++j) { const int i = tid + j * nt; s4[j] = i < a.nlist ? sc[i] : 0.0; }
-#pragma unroll
-            for (int j = 0; j < 4; ++j) { const int i = tid + j * nt; c4[j] = i < a.nlist ? packed(i, s4[j]) : (Cand)0; }
-        }
-        Cand mine = max(max(c4[0], c4[1]), max(c4[2], c4[3]));
-#pragma unroll 1
-        for (int i = tid + 4 * nt; i < a.nlist; i += nt) mine = max(mine, packed(i, sc[i]));
-        gmax[2 * tid] = (uint32_t)mine; gmax[2 * tid + 1] = (uint32_t)(mine >> 32);
-        __syncthreads();
-        // more than 32 wanted: 128 groups, sorted by two wavefronts, keep the pool small
-        const int gw = nprobe > 32 ? 2 : 1;
-        Cand sorted = 0;
-        if (wave < gw) {
-            Cand g = 0;
-#pragma unroll 4
-            for (int w = wave; w < nw; w += gw) {
-                const Cand o = ((Cand)gmax[2 * (w * 64 + lane) + 1] << 32) | gmax[2 * (w * 64 + lane)];
-                g = max(g, o);
-            }
-            sorted = bitonic_sort64<true>(g);                                  // largest first
-            if (wave == 1) pool[lane] = sorted;
-        }
-        if (gw == 2) {
-            __syncthreads();
-            if (wave == 0) sorted = merge_best64<true>(sorted, pool[lane]);
-        }
-        if (wave == 0 && lane == (int)nprobe - 1) { gmax[0] = (uint32_t)(sorted >> 24); gmax[1] = (uint32_t)(sorted >> 56); }   // 0: all pass
-        __syncthreads();
-        const uint64_t cut = ((uint64_t)gmax[1] << 32) | gmax[0];              // 40-bit prefix
-        {
-            auto offer = [&](Cand c) {
-                const bool ok = c != 0 && (c >> 24) >= cut;
-                const uint64_t bal = __ballot(ok);
-                if (bal) {
-                    uint32_t base = 0;
-                    if (lane == 0) base = atomicAdd(&sh[4], (uint32_t)__popcll(bal));
-                    base = read_lane(base, 0);
-                    const uint32_t pos = base + __popcll(bal & ((1ull << lane) - 1ull));
-                    if (ok && pos < (uint32_t)nt) pool[pos] = c;
-                }
-            };
-#pragma unroll
-            for (int j = 0; j < 4; ++j) offer(c4[j]);
-#pragma unroll 1
-            for (int i0 = 4 * nt; i0 < a.nlist; i0 += nt) { const int i = i0 + tid; offer(i < a.nlist ? packed(i, sc[i]) : (Cand)0); }
-        }
-        __syncthreads();
-        const uint32_t cnt = sh[4];
-        Cand half = 0;                       // 65 .. 128 pooled: the sorted half of wavefronts 0 and 1
-        Cand* run2 = (Cand*)gmax;            // the cut has been read: the area is free
-        if (__builtin_expect(cnt > (uint32_t)nt, 0)) {
-            if (tid == 0) sh[6] = 1;                                            // pool overflow: masses of equal prefixes
-        } else if (__builtin_expect(cnt > 128, 0)) {
-            // each pooled candidate counts those ahead of it; the first nprobe + 1 take their places
-            const Cand me = (uint32_t)tid < cnt ? pool[tid] : (Cand)0;
-            uint32_t rank = 0;
-#pragma unroll 1
-            for (uint32_t j0 = 0; j0 < cnt; j0 += 8) {
-                Cand o[8];
-#pragma unroll
-                for (int u = 0; u < 8; ++u) o[u] = pool[min(j0 + u, cnt - 1)];
-#pragma unroll
-                for (int u = 0; u < 8; ++u) rank += (uint32_t)((o[u] > me) & (j0 + u < cnt));
-            }
-            if ((uint32_t)tid < cnt && rank <= nprobe) sel[rank] = me;
-        } else if (cnt > 64) {
-            if (wave < 2) {
-                half = bitonic_sort64<true>((uint32_t)tid < cnt ? pool[tid] : (Cand)0);
-                if (wave == 1) run2[lane] = half;
-            }
-        }
-        __syncthreads();
-        if (wave == 0 && sh[6] == 0) {
-            Cand best, after;
-            if (cnt <= 64) {
-                const Cand sorted = bitonic_sort64<true>((uint32_t)lane < cnt ? pool[lane] : (Cand)0);
-                after = nprobe < 64 ? read_lane(sorted, (int)(nprobe & 63)) : (Cand)0;
-                best = lane < (int)nprobe ? sorted : (Cand)0;
-            } else if (cnt <= 128) {
-                Cand dropped;
-                const Cand merged = merge_best64<true>(half, run2[lane], dropped);
-                after = nprobe < 64 ? read_lane(merged, (int)(nprobe & 63)) : wave_max(dropped);
-                best = lane < (int)nprobe ? merged : (Cand)0;
-            } else {
-                best = lane < (int)nprobe ? sel[lane] : (Cand)0;
-                after = sel[nprobe];
-            }
-            const int ns = __popcll(__ballot(best != 0));                     // a prefix of the lanes
-            const uint64_t next = ((uint64_t)(uint32_t)__shfl_down((int)(uint32_t)(best >> 32), 1) << 32) |
-                                  (uint32_t)__shfl_down((int)(uint32_t)best, 1);
-            const bool adjacent = lane + 1 < ns && (best >> 24) == (next >> 24);
-            const bool cut_tie = ns > 0 && after != 0 && (after >> 24) == (read_lane(best, max(ns - 1, 0)) >> 24);
-            const bool redo = __ballot(adjacent) != 0 || cut_tie;
-            if (lane == 0) sh[6] = redo;
-            if (!redo && lane < (int)pad) idx[lane] = best != 0 ? 0xFFFFFFu - (uint32_t)(best & 0xFFFFFFull) : 0xFFFFFFFFu;
-        }
-        __syncthreads();
-        if (__builtin_expect(sh[6] != 0, 0)) select_sorted(a, sc, keys, idx, pad, hist, sh);
-    } else if (in_lds) {
+    if (in_lds) {
         uint64_t* keys = (uint64_t*)smem_raw;
         idx = (uint32_t*)(smem_raw + sizeof(uint64_t) * pad);
         bool done = false;
@@ -872,18 +972,19 @@ uint32_t select_sort_pad(int nlist, int nprobe) {
 }
 
 hipError_t launch_select(const SelectArgs& a, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
+    if (selects_few(a.nlist, a.nprobe)) {
+        if (a.nlist <= kFewThreads * kFewPerThread) IVF_LAUNCH(select_few_kernel<kFewThreads>, dim3(a.nq), dim3(kFewThreads), few_lds(kFewThreads), s, e0, e1, a);
+        else IVF_LAUNCH(select_few_kernel<kSelectThreads>, dim3(a.nq), dim3(kSelectThreads), few_lds(kSelectThreads), s, e0, e1, a);
+        return hipGetLastError();
+    }
     uint32_t pad = select_sort_pad(a.nlist, a.nprobe);
     int in_lds = pad <= (uint32_t)kSortLdsCap;
     int prefix_in_lds = a.nprobe <= kPrefixLdsCap;
-    // a workgroup with one wavefront per SIMD issues fastest when there is little work per thread (up
-    // to 64 clusters wanted; more are ranked by all wavefronts: 256 of 1000 lists 23 us with 4, 12 with 16)
-    const int threads = a.nlist <= 1024 && a.grid <= 1024 && a.nprobe <= 64 ? 256 : kSelectThreads;
+    const int threads = kSelectThreads;
     size_t lds = (in_lds ? (size_t)pad * 12 : 0) + (prefix_in_lds ? (size_t)(a.nprobe + 1) * 4 : 0);
-    const bool wave_sort = in_lds && a.nprobe <= 64 && a.nlist <= kSelectWaveSortMax;
     // the pool holds what passes the cut for up to 512 of any number of clusters, and all of 1024 (for
     // 1000 of 2048 lists it would rank 2048: 50 us against 32 of the sorting network below)
-    const int pooled = in_lds && !wave_sort && a.nlist <= 0xFFFFFF && (a.nprobe <= 512 || a.nlist <= 1024);
-    if (wave_sort) lds += 16 + (size_t)threads * 8 + 66 * 8 + (size_t)threads * 8;      // pool, the ranked few, the threads' best
+    const int pooled = in_lds && a.nlist <= 0xFFFFFF && (a.nprobe <= 512 || a.nlist <= 1024);
     if (pooled) lds += 16 + (size_t)kSelectPoolCap * 16;           // the pool, as it came and in order
     IVF_LAUNCH(select_kernel, dim3(a.nq), dim3(threads), lds, s, e0, e1, a, pad, in_lds, prefix_in_lds, pooled);
     return hipGetLastError();
@@ -942,6 +1043,20 @@ struct LaneTable {
             grow = p.slots.grow[o];
             base = p.slots.base[o];
         }
+    }
+    // Every workgroup selects the clusters for itself, from the coarse scores; the first of a query also leaves the tables.
+    // For calls whose workgroups are all resident at once: selecting side by side takes as long as once, and the
+    // launch in between and the way of the tables through memory go (whole search, us, select kernel / here: 8 of 64
+    // clusters, 2500 rows of 128 19.0 / 15.4; 32 of 1024, 30,000 rows of 768 33.4 / 32.0).
+    __device__ __forceinline__ void select(const ScanArgs& p, int qi) {
+        extern __shared__ __align__(16) unsigned char smem_raw[];
+        FewLds& L = *(FewLds*)smem_raw;
+        select_few<kScanThreads>(p.scores + (size_t)qi * p.nlist, p.nlist, p.nprobe, p.metric, L);
+        const LaneSlot s = slot_of_lane(L, p.nprobe, p.off, p.res_off);
+        on = true;
+        nprobe = p.nprobe;
+        end = s.end; grow = s.grow; base = s.base;
+        if (blockIdx.x == 0 && wave_id() == 0) store_slots(s, p.nprobe, qi, p.slots, p.probe, p.used, p.rows_counter);
     }
     __device__ __forceinline__ uint32_t total() const { return read_lane(end, nprobe - 1); }
     // points the cursor at the slot that holds row c.r (c.r below the total)
@@ -1090,8 +1205,13 @@ __global__ __launch_bounds__(kScanThreads) void scan_kernel(ScanArgs p) {
     };
 
     LaneTable tab;
-    tab.load(p, qi);
-    load_query();
+    if (p.scores) {
+        load_query();                 // (behind the selection: 0.4 us longer, and 8 registers more)
+        tab.select(p, qi);
+    } else {
+        tab.load(p, qi);
+        load_query();
+    }
     Cursor cur = start_cursor(p, qi, tab, RPB);
 
     WaveTopK<KL, false> top;
@@ -1298,6 +1418,10 @@ static size_t scan_lds_bytes(const ScanShape& sh, int d) {
     return sh.lanes_per_row == 0 ? (size_t)d * 4 : 0;      // only the fallback kernel stages the query
 }
 
+bool scan_selects(const ScanShape& shape, int nlist, int nprobe) {
+    return shape.lanes_per_row != 0 && nprobe <= kLaneTableSlots && nlist <= kScanThreads * kFewPerThread;
+}
+
 float scan_error_coef(const ScanShape& shape, int d, int dtype, int metric) {
     // roundings on the longest path of one row's sum: the fused multiply-adds of a lane, then the tree over the lanes
     int terms;
@@ -1326,7 +1450,7 @@ hipError_t launch_scan(const ScanArgs& a, hipStream_t s, hipEvent_t e0, hipEvent
     ScanFn fn = scan_fn(a.shape, a.dtype, a.metric, a.kprime);
     if (!fn) return hipErrorInvalidValue;
     dim3 grid(a.grid, a.nq);
-    IVF_LAUNCH(fn, grid, dim3(kScanThreads), scan_lds_bytes(a.shape, a.d), s, e0, e1, a);
+    IVF_LAUNCH(fn, grid, dim3(kScanThreads), a.scores ? few_lds(kScanThreads) : scan_lds_bytes(a.shape, a.d), s, e0, e1, a);
     return hipGetLastError();
 }
 
@@ -1337,7 +1461,7 @@ hipError_t launch_scan(const ScanArgs& a, hipStream_t s, hipEvent_t e0, hipEvent
 // candidates (already fp64), orders everything by (score, id) and writes the k nearest.
 // =============================================================================================
 constexpr int kMergeCandCap = 4096;    // candidates that can be pooled
-constexpr int kMergeThreads = 1024;    // kprime up to 64
+constexpr int kMergeThreads = 1024;    // kprime up to 64, one search at a time
 constexpr int kMergeWideThreads = 1024;
 
 struct MergeLds {
@@ -1491,7 +1615,7 @@ __device__ __forceinline__ void pad_results(const MergeArgs& a, int qi, uint32_t
 // kprime best overall are among those that do, in lists whose head does.  With heads spread at
 // random over the groups, about kprime (1 + kprime / 128) heads reach T.  A wavefront pools the passing entries of
 // the lists whose heads it holds.  Up to 32 are all re-scored, up to 512 are ranked first, more are cut
-// again (the pool dealt anew).  The result is exact when nothing that was dropped can matter: result_is_safe.
+// again (the pool dealt anew) while that thins them out.  The result is exact when nothing that was dropped can matter: result_is_safe.
 //
 // What bounds it: a chain of four trips to memory (heads, lists, rows, results; what the scan wrote comes from other
 // XCDs, 0.8 us a trip) and the steps between them, whose instructions sixteen wavefronts issue in turn, four to a SIMD.  So: ranks
@@ -1501,16 +1625,19 @@ __device__ __forceinline__ void pad_results(const MergeArgs& a, int qi, uint32_t
 // stores of the results (it waits for them).  Whole kernel, us, before / now: 2500 rows of 128 fp32 7.8 / 6.5, 30,000 of
 // 768 fp32 8.4 / 6.9, 34,000 of 300 fp16 in squared L2 10.2 / 8.1.  Eight wavefronts with two rows of a group of lanes in flight:
 // 7.5, 8.6, 8.6; four with four rows: 8.6, 9.4, 10.0; four lists always requested together: 7.0, 7.4, 8.5.
-constexpr int kMergeHeads = 2048 / kMergeThreads;         // heads of a thread that stay in registers: all of one query's lists
-constexpr int kMergeRows = 1024 / kMergeThreads;          // rows of a group of lanes in flight: 32 candidates in one go
 constexpr int kNormLds = 1024;                            // elements of the query that go through LDS to the wavefront that sums |q|^2
-constexpr int kMergeRanked = 512;                         // pooled candidates that are ranked as they are
+constexpr int kMergeCut = 512;                            // pooled candidates above which another cut is tried
+constexpr int kMergeRanked = 1024;                        // ... up to which they are ranked
 
-__global__ __launch_bounds__(kMergeThreads) __attribute__((amdgpu_waves_per_eu(5))) void merge_kernel(MergeArgs a) {
+template <int NT>
+__global__ __launch_bounds__(NT) void merge_kernel(MergeArgs a) {
     extern __shared__ __align__(16) unsigned char m_dyn[];
     __shared__ MergeLds L;
     __shared__ float s_q[kNormLds];
-    constexpr int nt = kMergeThreads, nw = nt / 64, slots = 64, H = kMergeHeads, G = nt / 64;     // G lanes hold a group's heads
+    constexpr int nt = NT, nw = nt / 64, slots = 64;
+    constexpr int H = 2048 / nt;                  // heads of a thread that stay in registers: all of one query's lists
+    constexpr int G = nt / 64;                    // lanes that hold a group's heads
+    constexpr int kRows = 1024 / nt;              // rows of a group of lanes in flight: 32 candidates in one go
     Cand* pool = (Cand*)m_dyn;
     const int tid = threadIdx.x, lane = lane_id(), wave = wave_id();
     const int qi = blockIdx.x, np = a.nparts, kp = a.kprime;
@@ -1620,7 +1747,8 @@ __global__ __launch_bounds__(kMergeThreads) __attribute__((amdgpu_waves_per_eu(5
     const Cand* cands = pool;
     uint32_t m = 0;
 #pragma unroll 1
-    for (int round = 0; __builtin_expect(cnt > kMergeRanked && cnt <= kMergeCandCap && round < 3, 0); ++round) {
+    for (int before = kMergeCandCap + 1; __builtin_expect(cnt > kMergeCut && cnt < before, 0);) {
+        before = cnt;
         // many (rows that are all alike, a few lists that hold them all): another cut, the pool dealt anew
         constexpr int R = kMergeCandCap / nt;
         Cand v[R];
@@ -1687,8 +1815,8 @@ __global__ __launch_bounds__(kMergeThreads) __attribute__((amdgpu_waves_per_eu(5
     // 3. fp64 re-score
     constexpr uint32_t groups = nt / kRescoreLanes;
 #pragma unroll 1
-    for (uint32_t c0 = (uint32_t)(tid / kRescoreLanes); c0 < m; c0 += kMergeRows * groups)
-        score_candidates<kMergeRows>(a, qi, L, cands, c0, groups, m, tid % kRescoreLanes);
+    for (uint32_t c0 = (uint32_t)(tid / kRescoreLanes); c0 < m; c0 += kRows * groups)
+        score_candidates<kRows>(a, qi, L, cands, c0, groups, m, tid % kRescoreLanes);
     const uint32_t tot = m + add_host_candidates(a, qi, L, m);
     __syncthreads();
     // 4. ranked by ballots, every wavefront an equal share of the results against all: nearest first, ties by smaller
@@ -2145,7 +2273,7 @@ hipError_t launch_merge(const MergeArgs& a, hipStream_t s, hipEvent_t e0, hipEve
     if (a.done && a.nq != 1) return hipErrorInvalidValue;
     const size_t pool = (size_t)kMergeCandCap * sizeof(uint64_t);
     if (a.kprime > 64) IVF_LAUNCH(merge_wide_kernel, dim3(a.nq), dim3(kMergeWideThreads), pool + 2 * kWideLists * sizeof(uint16_t), s, e0, e1, a);
-    else IVF_LAUNCH(merge_kernel, dim3(a.nq), dim3(kMergeThreads), pool, s, e0, e1, a);
+    else IVF_LAUNCH(merge_kernel<kMergeThreads>, dim3(a.nq), dim3(kMergeThreads), pool, s, e0, e1, a);
     return hipGetLastError();
 }
 
