@@ -541,6 +541,7 @@ int enqueue_merge(ivf_index* ix, const float* q_dev, int nq, int nprobe, int k, 
     ma.d = ix->d; ma.dtype = ix->dtype; ma.metric = ix->metric; ma.nprobe = nprobe; ma.nq = nq;
     ma.k = k; ma.kprime = kprime; ma.nparts = grid * kScanWaves; ma.list_len = cand_slots(kprime);
     ma.identity = ix->placement == IVF_PLACE_DEVICE;
+    ma.beside = ix->lanes.size() > 1;
     if (signal_done) { ma.done = w.hd_done; ma.done_value = ++w.done_seq; }
     hipEvent_t e0, e1;
     int rc = prof_events(ix, 3, &e0, &e1);

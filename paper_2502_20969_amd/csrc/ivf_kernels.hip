@@ -1462,6 +1462,7 @@ hipError_t launch_scan(const ScanArgs& a, hipStream_t s, hipEvent_t e0, hipEvent
 // =============================================================================================
 constexpr int kMergeCandCap = 4096;    // candidates that can be pooled
 constexpr int kMergeThreads = 1024;    // kprime up to 64, one search at a time
+constexpr int kMergeBesideThreads = 512;       // ... with other searches in flight
 constexpr int kMergeWideThreads = 1024;
 
 struct MergeLds {
@@ -1629,6 +1630,9 @@ constexpr int kNormLds = 1024;                            // elements of the que
 constexpr int kMergeCut = 512;                            // pooled candidates above which another cut is tried
 constexpr int kMergeRanked = 1024;                        // ... up to which they are ranked
 
+// NT threads.  With other searches in flight half of them: a workgroup of sixteen wavefronts finds no room on a compute unit
+// beside two workgroups of a scan (four wavefronts of 96 registers and two of 72 on a SIMD of 512) and waits
+// for a scan to end (64 queries of 1 M x 768 fp32, 16 in flight: 1320 us, 1240 with eight wavefronts).
 template <int NT>
 __global__ __launch_bounds__(NT) void merge_kernel(MergeArgs a) {
     extern __shared__ __align__(16) unsigned char m_dyn[];
@@ -2273,6 +2277,7 @@ hipError_t launch_merge(const MergeArgs& a, hipStream_t s, hipEvent_t e0, hipEve
     if (a.done && a.nq != 1) return hipErrorInvalidValue;
     const size_t pool = (size_t)kMergeCandCap * sizeof(uint64_t);
     if (a.kprime > 64) IVF_LAUNCH(merge_wide_kernel, dim3(a.nq), dim3(kMergeWideThreads), pool + 2 * kWideLists * sizeof(uint16_t), s, e0, e1, a);
+    else if (a.beside) IVF_LAUNCH(merge_kernel<kMergeBesideThreads>, dim3(a.nq), dim3(kMergeBesideThreads), pool, s, e0, e1, a);
     else IVF_LAUNCH(merge_kernel<kMergeThreads>, dim3(a.nq), dim3(kMergeThreads), pool, s, e0, e1, a);
     return hipGetLastError();
 }
