@@ -515,7 +515,7 @@ int enqueue_probe(ivf_index* ix, const float* q_dev, int nq, int nprobe, int gri
 // Whether the scan of a search selects the clusters itself: when all its workgroups are resident at once, so that they do it
 // side by side.  Not while kernels are timed one by one.
 bool select_in_scan(const ivf_index* ix, int nq, int nprobe, int kprime, int grid, const ScanShape& shape) {
-    return !ix->profiling && scan_selects(shape, ix->nlist, nprobe) && (int64_t)nq * grid <= ix->resident_grid[kprime > 64 ? 1 : 0];
+    return !ix->profiling && scan_selects(shape, ix->nlist, nprobe, kprime) && (int64_t)nq * grid <= ix->resident_grid[0];
 }
 
 int enqueue_scan(ivf_index* ix, const float* q_dev, int nq, int nprobe, int kprime, int grid, const ScanShape& shape, bool in_scan = false) {

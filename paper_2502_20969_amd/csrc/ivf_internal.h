@@ -103,7 +103,7 @@ struct ScanArgs {
     int nlist;
 };
 // whether the scan of this shape can select the clusters itself
-bool scan_selects(const ScanShape& shape, int nlist, int nprobe);
+bool scan_selects(const ScanShape& shape, int nlist, int nprobe, int kprime);
 hipError_t launch_scan(const ScanArgs& a, hipStream_t s, hipEvent_t start = nullptr, hipEvent_t stop = nullptr);
 // workgroups of the scan kernel for (shape, dtype, metric, kprime) that are resident at once
 int scan_resident_grid(const ScanShape& shape, int dtype, int metric, int kprime, int d, int n_cu);

@@ -1155,7 +1155,9 @@ __device__ __forceinline__ void write_wave_list(WaveTopK<KL, false>& top, const 
 // that the lane before it has already, in its slice of the query and in every chunk it loads: no
 // load leaves the row.  (One element per lane and row at a time, 34,500 rows of 300 fp16: 30.1 us;
 // this: 12.4.)
-template <typename T, int LPR, int SEG, int U, int METRIC, int KL, bool TAIL>
+// SEL: the scan selects the clusters itself.  A kernel of its own: with both ways in one the scan of given tables lost 4
+// to 14 per cent (269 of 6988 clusters of 1024 bf16 32.1 -> 36.5 us).
+template <typename T, int LPR, int SEG, int U, int METRIC, int KL, bool TAIL, bool SEL>
 __global__ __launch_bounds__(kScanThreads) void scan_kernel(ScanArgs p) {
     constexpr int EPL = T::kPerLoad;
     constexpr int RPI = 64 / LPR;
@@ -1205,7 +1207,7 @@ __global__ __launch_bounds__(kScanThreads) void scan_kernel(ScanArgs p) {
     };
 
     LaneTable tab;
-    if (p.scores) {
+    if (SEL) {
         load_query();                 // (behind the selection: 0.4 us longer, and 8 registers more)
         tab.select(p, qi);
     } else {
@@ -1380,46 +1382,50 @@ ScanShape scan_shape_for_rows(const ScanShape& shape, uint64_t rows, int kprime,
 typedef void (*ScanFn)(ScanArgs);
 
 template <typename T, int LPR, int SEG, int U, bool TAIL>
-static ScanFn scan_fn_shape(int metric, bool big) {
-    if (metric == 0) return big ? (ScanFn)scan_kernel<T, LPR, SEG, U, 0, 2, TAIL> : (ScanFn)scan_kernel<T, LPR, SEG, U, 0, 1, TAIL>;
-    return big ? (ScanFn)scan_kernel<T, LPR, SEG, U, 1, 2, TAIL> : (ScanFn)scan_kernel<T, LPR, SEG, U, 1, 1, TAIL>;
+static ScanFn scan_fn_shape(int metric, bool big, bool sel) {
+    if (sel) return metric == 0 ? (ScanFn)scan_kernel<T, LPR, SEG, U, 0, 1, TAIL, true> : (ScanFn)scan_kernel<T, LPR, SEG, U, 1, 1, TAIL, true>;
+    if (metric == 0) return big ? (ScanFn)scan_kernel<T, LPR, SEG, U, 0, 2, TAIL, false> : (ScanFn)scan_kernel<T, LPR, SEG, U, 0, 1, TAIL, false>;
+    return big ? (ScanFn)scan_kernel<T, LPR, SEG, U, 1, 2, TAIL, false> : (ScanFn)scan_kernel<T, LPR, SEG, U, 1, 1, TAIL, false>;
 }
 
 template <typename T, int LPR, bool TAIL>
-static ScanFn scan_fn_few(int metric) {
-    return metric == 0 ? (ScanFn)scan_kernel<T, LPR, 1, kFewGroups, 0, 1, TAIL> : (ScanFn)scan_kernel<T, LPR, 1, kFewGroups, 1, 1, TAIL>;
+static ScanFn scan_fn_few(int metric, bool sel) {
+    if (sel) return metric == 0 ? (ScanFn)scan_kernel<T, LPR, 1, kFewGroups, 0, 1, TAIL, true> : (ScanFn)scan_kernel<T, LPR, 1, kFewGroups, 1, 1, TAIL, true>;
+    return metric == 0 ? (ScanFn)scan_kernel<T, LPR, 1, kFewGroups, 0, 1, TAIL, false> : (ScanFn)scan_kernel<T, LPR, 1, kFewGroups, 1, 1, TAIL, false>;
 }
 
+// sel: the variant that selects the clusters itself (kprime up to 64)
 template <typename T>
-static ScanFn scan_fn_dtype(const ScanShape& sh, int metric, bool big) {
+static ScanFn scan_fn_dtype(const ScanShape& sh, int metric, bool big, bool sel) {
     const int l = sh.lanes_per_row, g = sh.segments;
-#define IVF_FEW(L) if (l == L && g == 1 && !big && sh.unroll == kFewGroups) return sh.tail ? scan_fn_few<T, L, true>(metric) : scan_fn_few<T, L, false>(metric);
+#define IVF_FEW(L) if (l == L && g == 1 && !big && sh.unroll == kFewGroups) return sh.tail ? scan_fn_few<T, L, true>(metric, sel) : scan_fn_few<T, L, false>(metric, sel);
     IVF_FEW(16) IVF_FEW(32) IVF_FEW(64)
 #undef IVF_FEW
-#define IVF_SHAPE(L, G, UU) if (l == L && g == G) return sh.tail ? scan_fn_shape<T, L, G, UU, true>(metric, big) : scan_fn_shape<T, L, G, UU, false>(metric, big);
+#define IVF_SHAPE(L, G, UU) if (l == L && g == G) return sh.tail ? scan_fn_shape<T, L, G, UU, true>(metric, big, sel) : scan_fn_shape<T, L, G, UU, false>(metric, big, sel);
     IVF_SHAPE(16, 1, 6) IVF_SHAPE(32, 1, 6) IVF_SHAPE(64, 1, 6) IVF_SHAPE(32, 3, 2)
     IVF_SHAPE(64, 2, 3) IVF_SHAPE(64, 3, 2) IVF_SHAPE(64, 4, 2) IVF_SHAPE(64, 8, 1)
 #undef IVF_SHAPE
     return nullptr;
 }
 
-static ScanFn scan_fn(const ScanShape& sh, int dtype, int metric, int kprime) {
+static ScanFn scan_fn(const ScanShape& sh, int dtype, int metric, int kprime, bool sel = false) {
     const bool big = kprime > 64;
+    if (sel && (big || sh.lanes_per_row == 0)) return nullptr;
     if (sh.lanes_per_row == 0) {
         if (metric == 0) return big ? (ScanFn)scan_generic_kernel<0, 2> : (ScanFn)scan_generic_kernel<0, 1>;
         return big ? (ScanFn)scan_generic_kernel<1, 2> : (ScanFn)scan_generic_kernel<1, 1>;
     }
-    if (dtype == 0) return scan_fn_dtype<F32>(sh, metric, big);
-    if (dtype == 1) return scan_fn_dtype<F16>(sh, metric, big);
-    return scan_fn_dtype<BF16>(sh, metric, big);
+    if (dtype == 0) return scan_fn_dtype<F32>(sh, metric, big, sel);
+    if (dtype == 1) return scan_fn_dtype<F16>(sh, metric, big, sel);
+    return scan_fn_dtype<BF16>(sh, metric, big, sel);
 }
 
 static size_t scan_lds_bytes(const ScanShape& sh, int d) {
     return sh.lanes_per_row == 0 ? (size_t)d * 4 : 0;      // only the fallback kernel stages the query
 }
 
-bool scan_selects(const ScanShape& shape, int nlist, int nprobe) {
-    return shape.lanes_per_row != 0 && nprobe <= kLaneTableSlots && nlist <= kScanThreads * kFewPerThread;
+bool scan_selects(const ScanShape& shape, int nlist, int nprobe, int kprime) {
+    return shape.lanes_per_row != 0 && kprime <= 64 && nprobe <= kLaneTableSlots && nlist <= kScanThreads * kFewPerThread;
 }
 
 float scan_error_coef(const ScanShape& shape, int d, int dtype, int metric) {
@@ -1447,7 +1453,7 @@ int scan_resident_grid(const ScanShape& shape, int dtype, int metric, int kprime
 }
 
 hipError_t launch_scan(const ScanArgs& a, hipStream_t s, hipEvent_t e0, hipEvent_t e1) {
-    ScanFn fn = scan_fn(a.shape, a.dtype, a.metric, a.kprime);
+    ScanFn fn = scan_fn(a.shape, a.dtype, a.metric, a.kprime, a.scores != nullptr);
     if (!fn) return hipErrorInvalidValue;
     dim3 grid(a.grid, a.nq);
     IVF_LAUNCH(fn, grid, dim3(kScanThreads), a.scores ? few_lds(kScanThreads) : scan_lds_bytes(a.shape, a.d), s, e0, e1, a);
@@ -1719,15 +1725,28 @@ __global__ __launch_bounds__(NT) void merge_kernel(MergeArgs a) {
     };
     auto pool_lists = [&](Cand head, int i) __attribute__((always_inline)) {
         uint64_t lists = __ballot(head != 0 && (uint32_t)(head >> 32) >= cut);
+        auto entry = [&](int l) __attribute__((always_inline)) { return part[(size_t)list_of(wave * 64 + l, i) * slots + lane]; };
 #pragma unroll 1
         while (lists) {
+            if ((lists & (lists - 1)) == 0) {
+                c[0] = entry(__builtin_ctzll(lists));
 #pragma unroll
-            for (int u = 0; u < C; ++u) {
-                c[u] = 0;
-                if (lists) {
-                    c[u] = part[(size_t)list_of(wave * 64 + __builtin_ctzll(lists), i) * slots + lane];
+                for (int u = 1; u < C; ++u) c[u] = 0;
+                lists = 0;
+            } else {
+                // several: all requested before the first is looked at, the last one again where there are fewer (a load
+                // behind a branch of its own is waited for where the branch ends)
+                bool own[C];
+                int l = 0;
+#pragma unroll
+                for (int u = 0; u < C; ++u) {
+                    own[u] = lists != 0;
+                    l = own[u] ? __builtin_ctzll(lists) : l;
                     lists &= lists - 1;
+                    c[u] = entry(l);
                 }
+#pragma unroll
+                for (int u = 0; u < C; ++u) c[u] = own[u] ? c[u] : (Cand)0;
             }
             offer(cut);
         }
