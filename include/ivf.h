@@ -362,7 +362,8 @@ int ivf_host_scan(const void* lists, const int64_t* offsets, const int64_t* ids,
 int32_t ivf_host_scan_capacity(int32_t k);
 
 /* Kernel timing with HIP events on compute_stream around each kernel of every search while
- * enabled (adds event records to the stream; leave off when timing throughput). */
+ * enabled (adds event records to the stream; leave off when timing throughput).  While it is enabled the
+ * clusters are selected by a kernel of their own also in single searches whose scan otherwise does it. */
 int ivf_profile_enable(ivf_index* index, int on);
 int ivf_profile_read(ivf_index* index, ivf_profile* out); /* synchronises compute_stream */
 int ivf_profile_reset(ivf_index* index);
