@@ -1778,7 +1778,8 @@ __global__ __launch_bounds__(NT) void merge_kernel(MergeArgs a) {
         uint32_t best = 0;
 #pragma unroll
         for (int u = 0; u < R; ++u) {
-            v[u] = u * nt + tid < cnt ? pool[u * nt + tid] : (Cand)0;
+            const int at = u * nt + (tid & (G - 1)) * 64 + tid / G;       // (a sorted list's entries stand side by side)
+            v[u] = at < cnt ? pool[at] : (Cand)0;
             best = max(best, (uint32_t)(v[u] >> 32));
         }
         group_max(best);
