@@ -141,6 +141,10 @@ __device__ __forceinline__ uint32_t read_lane(uint32_t v, int lane) {
     return (uint32_t)__builtin_amdgcn_readlane((int)v, lane);
 }
 
+// Waits until everything this wavefront has stored is behind its L2.  For threads whose stores another thread of the workgroup
+// publishes: __syncthreads() waits for LDS only, and a fence for the stores of the wavefront that executes it.
+__device__ __forceinline__ void wait_for_stores() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
+
 // ---- stored element types -------------------------------------------------------------------
 struct F32 {
     static constexpr int kBytes = 4, kPerLoad = 4;

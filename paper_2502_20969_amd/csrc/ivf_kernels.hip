@@ -1534,11 +1534,12 @@ __device__ __forceinline__ void conclude(const MergeArgs& a, int qi, bool unsafe
             a.redo_ticket[qi] = 0u;
         }
     }
-    if (a.host_flag) a.host_flag[qi] = unsafe ? 1u : 0u;       // pinned: stored before the completion word
+    if (a.host_flag) a.host_flag[qi] = unsafe ? 1u : 0u;       // pinned: read behind the completion word or the end of the kernel
 }
-// The completion word, behind everything that the workgroup has stored.
+// The completion word, behind everything that the workgroup has stored: results and verdict come from several wavefronts.
 __device__ __forceinline__ void signal_done(const MergeArgs& a) {
     if (!a.done) return;
+    wait_for_stores();
     __syncthreads();
     if (threadIdx.x == 0) {
         __threadfence_system();
@@ -1628,8 +1629,8 @@ __device__ __forceinline__ void pad_results(const MergeArgs& a, int qi, uint32_t
 // XCDs, 0.8 us a trip) and the steps between them, whose instructions sixteen wavefronts issue in turn, four to a SIMD.  So: ranks
 // by ballots (every lane holds one of 64 values, a value's rank is the number of lanes above it) dealt to the
 // wavefronts, where a sorting network is one wavefront's chain of 21 exchanges; groups of sixteen lanes, so that one LDS
-// read brings all maxima; no division by the list length; |q|^2 by a wavefront beside the others; no barrier behind the
-// stores of the results (it waits for them).  Whole kernel, us, before / now: 2500 rows of 128 fp32 7.8 / 6.5, 30,000 of
+// read brings all maxima; no division by the list length; |q|^2 by a wavefront beside the others; the verdict by the lane
+// that holds the k-th result, which needs no barrier behind the ranks.  Whole kernel, us, before / now: 2500 rows of 128 fp32 7.8 / 6.5, 30,000 of
 // 768 fp32 8.4 / 6.9, 34,000 of 300 fp16 in squared L2 10.2 / 8.1.  Eight wavefronts with two rows of a group of lanes in flight:
 // 7.5, 8.6, 8.6; four with four rows: 8.6, 9.4, 10.0; four lists always requested together: 7.0, 7.4, 8.5.
 constexpr int kNormLds = 1024;                            // elements of the query that go through LDS to the wavefront that sums |q|^2
