@@ -1488,6 +1488,7 @@ __device__ __forceinline__ int gather_radix(const MergeArgs& a, const Cand* part
     const int tid = threadIdx.x, nt = blockDim.x, lane = lane_id();
     const uint32_t n = (uint32_t)a.nparts * (uint32_t)a.list_len, kp = a.kprime;
     auto key_at = [&](uint32_t i) { return ~part[i]; };      // ascending = best first; all ones = empty
+    __syncthreads();                       // everyone has read the words of L.sh that brought them here
     uint32_t my_valid = 0;
     for (uint32_t i = tid; i < n; i += nt) my_valid += part[i] != 0;
     if (tid == 0) { L.sh[4] = 0; L.sh[5] = 0; L.f_last = 0xFFFFFFFFu; }
@@ -2017,10 +2018,7 @@ __global__ __launch_bounds__(kMergeWideThreads) void merge_wide_kernel(MergeArgs
     // 1. the kprime best fp32 candidates
     Cand* pool = (Cand*)m_dyn;
     int got = gather_wide(a, part, heads, L, pool, (uint16_t*)(pool + kMergeCandCap));
-    if (__builtin_expect(got < 0, 0)) {
-        __syncthreads();
-        got = gather_radix(a, part, L);
-    }
+    if (__builtin_expect(got < 0, 0)) got = gather_radix(a, part, L);
     const uint32_t m = (uint32_t)got;
     // 2. fp64 re-score, two candidates of a group of lanes in flight (112 of 1.5 KB: 29.4 -> 27.0 us for the whole kernel)
     {
