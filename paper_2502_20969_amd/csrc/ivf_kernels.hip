@@ -2208,6 +2208,7 @@ __global__ __launch_bounds__(kRedoThreads) void exact_redo_kernel(RedoArgs a) {
                 __hip_atomic_store(&a.list_id[o + i], mi[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             }
         }
+        wait_for_stores();                               // the lists are in memory before the ticket says so
         __syncthreads();
         if (tid == 0) {
             __threadfence();

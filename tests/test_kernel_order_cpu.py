@@ -13,6 +13,7 @@ import paper_2502_20969_amd.build as B
 OBJDUMP = "/opt/rocm/llvm/bin/llvm-objdump"
 MERGES = ["_ZN3ivf12merge_kernelILi512EEEvNS_9MergeArgsE", "_ZN3ivf12merge_kernelILi1024EEEvNS_9MergeArgsE",
           "_ZN3ivf17merge_wide_kernelENS_9MergeArgsE"]
+REDO = "_ZN3ivf17exact_redo_kernelENS_8RedoArgsE"
 
 
 @pytest.fixture(scope="module")
@@ -23,7 +24,7 @@ def code(tmp_path_factory):
     subprocess.run([OBJDUMP, "--offloading", "libivf.so"], cwd=at, check=True, capture_output=True)
     found = {}
     for f in sorted(p for p in os.listdir(at) if "gfx950" in p):
-        r = subprocess.run([OBJDUMP, "-d", "--no-show-raw-insn", "--disassemble-symbols=" + ",".join(MERGES), f], cwd=at,
+        r = subprocess.run([OBJDUMP, "-d", "--no-show-raw-insn", "--disassemble-symbols=" + ",".join(MERGES + [REDO]), f], cwd=at,
                            check=True, capture_output=True, text=True)
         for line in r.stdout.splitlines():
             head = re.match(r"[0-9a-f]+ <(\S+)>:", line)
@@ -55,6 +56,14 @@ def test_completion_word_is_stored_behind_everyones_results(code, kernel):
     word = [i for i, (_, t, _) in enumerate(body) if t.startswith("global_store_dwordx2") and t.endswith("sc0 sc1")]
     assert len(word) == 1
     assert _waits_for_stores(body, word[0])
+
+
+def test_ticket_of_the_exact_pass_is_drawn_behind_everyones_lists(code):
+    """The workgroup that draws the last ticket reads the lists of the others, which may have run beside another L2."""
+    body = code[REDO]
+    ticket = [i for i, (_, t, _) in enumerate(body) if t.startswith("global_atomic_add")]
+    assert len(ticket) == 1
+    assert _waits_for_stores(body, ticket[0])
 
 
 @pytest.mark.parametrize("kernel", MERGES)
