@@ -1624,7 +1624,7 @@ __device__ __forceinline__ void pad_results(const MergeArgs& a, int qi, uint32_t
 // kprime best overall are among those that do, in lists whose head does.  With heads spread at
 // random over the groups, about kprime (1 + kprime / 128) heads reach T.  A wavefront pools the passing entries of
 // the lists whose heads it holds.  Up to 32 are all re-scored, up to 512 are ranked first, more are cut
-// again (the pool dealt anew) while that thins them out.  The result is exact when nothing that was dropped can matter: result_is_safe.
+// again (the pool dealt anew) while that thins them out; what does not fit the pool is left to gather_radix.  The result is exact when nothing that was dropped can matter: result_is_safe.
 //
 // What bounds it: a chain of four trips to memory (heads, lists, rows, results; what the scan wrote comes from other
 // XCDs, 0.8 us a trip) and the steps between them, whose instructions sixteen wavefronts issue in turn, four to a SIMD.  So: ranks
@@ -1636,7 +1636,9 @@ __device__ __forceinline__ void pad_results(const MergeArgs& a, int qi, uint32_t
 // 7.5, 8.6, 8.6; four with four rows: 8.6, 9.4, 10.0; four lists always requested together: 7.0, 7.4, 8.5.
 constexpr int kNormLds = 1024;                            // elements of the query that go through LDS to the wavefront that sums |q|^2
 constexpr int kMergeCut = 512;                            // pooled candidates above which another cut is tried
-constexpr int kMergeRanked = 1024;                        // ... up to which they are ranked
+// ... up to which they are ranked by counting; more are sorted.  Whole searches with that many copies of the best row among 400,000 of
+// 128 fp32, k 10, us (400 of them the exact pass), counted / sorted: 150 415 / 420, 250 421 / 423, 400 436 / 433, 900 475 / 440.
+constexpr int kMergeRanked = 384;
 
 // NT threads.  With other searches in flight half of them: a workgroup of sixteen wavefronts finds no room on a compute unit
 // beside two workgroups of a scan (four wavefronts of 96 registers and two of 72 on a SIMD of 512) and waits
@@ -1806,9 +1808,9 @@ __global__ __launch_bounds__(NT) void merge_kernel(MergeArgs a) {
             const Cand v = read_lane(other, wave * (32 / nw) + i);
             if (v != 0 && __popcll(__ballot(other > v)) == kp - 1 && lane == 0) L.f_last = (uint32_t)(v >> 32);
         }
-    } else if (cnt <= kMergeRanked) {
-        // the first kprime take their places.  Up to 64: a value's rank is the number of lanes above it; more:
-        // eight lanes per candidate count those ahead of it
+    } else if (cnt <= kMergeCandCap) {
+        // the first kprime take their places.  Up to 64: a value's rank is the number of lanes above it; up to
+        // kMergeRanked: eight lanes per candidate count those ahead of it
         auto place = [&](Cand v, uint32_t rank) __attribute__((always_inline)) {
             if (rank < (uint32_t)kp) L.c_cand[rank] = v;
             if (rank == (uint32_t)kp - 1) L.f_last = (uint32_t)(v >> 32);
@@ -1821,13 +1823,28 @@ __global__ __launch_bounds__(NT) void merge_kernel(MergeArgs a) {
                 const uint32_t rank = (uint32_t)__popcll(__ballot(other > v));
                 if (lane == 0 && v != 0) place(v, rank);
             }
-        } else {
+        } else if (cnt <= kMergeRanked) {
 #pragma unroll 1
             for (int t = tid / 8; t < cnt; t += nt / 8) {
                 const Cand me = pool[t];
                 uint32_t rank, equal;
                 count_above(pool, (uint32_t)cnt, me, (uint32_t)tid & 7u, rank, equal);
                 if ((tid & 7) == 0) place(me, rank);
+            }
+        } else {
+            // more, which no cut thins out: every wavefront sorts and merges its runs of 64, then wavefront 0 what the
+            // wavefronts have (1500 and 3000 copies as above: 443 and 453 us, by the radix select over all lists 830 and 841)
+            auto run = [&](int c) __attribute__((always_inline)) { return bitonic_sort64<true>(c * 64 + lane < cnt ? pool[c * 64 + lane] : (Cand)0); };
+            Cand best = run(wave);
+#pragma unroll 1
+            for (int c = wave + nw; c * 64 < cnt; c += nw) best = merge_best64<true>(best, run(c));
+            __syncthreads();
+            pool[tid] = best;
+            __syncthreads();
+            if (wave == 0) {
+#pragma unroll 1
+                for (int w = 1; w < nw; ++w) best = merge_best64<true>(best, pool[w * 64 + lane]);
+                place(best, (uint32_t)lane);
             }
         }
         __syncthreads();
