@@ -538,6 +538,22 @@ int enqueue_scan(ivf_index* ix, const float* q_dev, int nq, int nprobe, int kpri
     return IVF_OK;
 }
 
+// Bytes of lists that nq queries select in the mean.
+static double mean_list_bytes(const ivf_index* ix, int nq, int nprobe) {
+    return (double)nq * nprobe / ix->nlist * (double)ix->n * (double)ix->row_bytes;
+}
+
+// Whether the merge of a search takes half the wavefronts, which find room beside resident scans: with other searches in flight, for
+// up to 48 candidates and, as the merges of a batch wait for each other's scans only, one query or a scan of 50 us.  us a
+// search or batch, 512 / 1024 threads.  64 of 1000 lists, 96,000 rows of 1024 bf16, depth 2 / 4 / 16: k 10 42.0 39.0 33.7 / 43.4 39.9
+// 35.0; k 56 54.3 51.4 39.0 / 52.2 49.6 39.9, one at a time 94 / 86.  32 of 1024, 31,000 of 768 fp32: k 10 28.3 23.9 19.4 / 29.8 25.7
+// 20.8, k 40 30.5 26.1 20.5 / 31.3 27.5 21.8, k 56 35.6 30.7 23.1 / 34.9 31.2 23.7.  Batches, k 10, depth 2 / 4 / 16: 4 of 50 MB
+// 31.3 34.2 26.9 / 30.6 33.9 26.7, 32 of 0.8 MB 30.4 31.8 24.2 / 29.5 31.5 24.1; 32 of 20 MB 108.9 112.1 106.8 / 110.8 112.7 107.9, 32 of 200 MB
+// 919 931 920 / 934 933 926.
+static bool merge_beside(const ivf_index* ix, int nq, int nprobe, int kprime) {
+    return ix->lanes.size() > 1 && kprime <= 48 && (nq == 1 || mean_list_bytes(ix, nq, nprobe) >= 256e6);
+}
+
 // host_flags: the proof flags also go to the pinned array (searches whose caller waits on the host)
 int enqueue_merge(ivf_index* ix, const float* q_dev, int nq, int nprobe, int k, int kprime, int grid,
                   bool with_host, int64_t* out_ids, float* out_dists, bool signal_done = false, bool host_flags = false) {
@@ -554,7 +570,7 @@ int enqueue_merge(ivf_index* ix, const float* q_dev, int nq, int nprobe, int k, 
     ma.d = ix->d; ma.dtype = ix->dtype; ma.metric = ix->metric; ma.nprobe = nprobe; ma.nq = nq;
     ma.k = k; ma.kprime = kprime; ma.nparts = grid * kScanWaves; ma.list_len = cand_slots(kprime);
     ma.identity = ix->placement == IVF_PLACE_DEVICE;
-    ma.beside = ix->lanes.size() > 1;
+    ma.beside = merge_beside(ix, nq, nprobe, kprime);
     if (signal_done) { ma.done = w.hd_done; ma.done_value = ++w.done_seq; }
     hipEvent_t e0, e1;
     int rc = prof_events(ix, 3, &e0, &e1);

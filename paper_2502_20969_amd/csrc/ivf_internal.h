@@ -119,7 +119,7 @@ struct MergeArgs {
     int64_t* out_ids; float* out_dists;   // [nq x k]
     int d, dtype, metric, nprobe, nq, k, kprime, nparts, list_len;   // list_len: entries per list
     int identity;            // 1: buffer row == global row (device placement)
-    int beside;              // 1: other searches are in flight beside this one
+    int beside;              // 1: half the wavefronts, which find room beside the scans of other searches
     // Completion word in pinned host memory (device address) or nullptr: set to done_value after
     // the results are visible to the host.  Only for nq == 1 (one workgroup writes it).
     unsigned long long* done; unsigned long long done_value;

@@ -1468,7 +1468,7 @@ hipError_t launch_scan(const ScanArgs& a, hipStream_t s, hipEvent_t e0, hipEvent
 // =============================================================================================
 constexpr int kMergeCandCap = 4096;    // candidates that can be pooled
 constexpr int kMergeThreads = 1024;    // kprime up to 64, one search at a time
-constexpr int kMergeBesideThreads = 512;       // ... with other searches in flight
+constexpr int kMergeBesideThreads = 512;       // ... with other searches in flight, up to 48 candidates
 constexpr int kMergeWideThreads = 1024;
 
 struct MergeLds {
@@ -1640,9 +1640,9 @@ constexpr int kMergeCut = 512;                            // pooled candidates a
 // 128 fp32, k 10, us (400 of them the exact pass), counted / sorted: 150 415 / 420, 250 421 / 423, 400 436 / 433, 900 475 / 440.
 constexpr int kMergeRanked = 384;
 
-// NT threads.  With other searches in flight half of them: a workgroup of sixteen wavefronts finds no room on a compute unit
-// beside two workgroups of a scan (four wavefronts of 96 registers and two of 72 on a SIMD of 512) and waits
-// for a scan to end (64 queries of 1 M x 768 fp32, 16 in flight: 1320 us, 1240 with eight wavefronts).
+// NT threads.  With other searches in flight half of them (a.beside): a workgroup of sixteen wavefronts finds no room on a
+// compute unit beside two workgroups of a scan (four wavefronts of 96 registers and two of 72 on a SIMD of 512) and waits
+// for a scan to end.  (Re-scored 32 at a time either way, so that more than 48 candidates make it too long by itself.)
 template <int NT>
 __global__ __launch_bounds__(NT) void merge_kernel(MergeArgs a) {
     extern __shared__ __align__(16) unsigned char m_dyn[];
