@@ -289,8 +289,9 @@ def run_single_query(args):
         "roofline": {"bound": "hbm", "achieved": round(prof["scan_gbs"], 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                      "frac": round(prof["scan_gbs"] / HBM_PEAK_GBS, 4),
                      "traffic": C2_SCAN_TRAFFIC_BYTES if (args.n == 1_000_000 and args.nprobe == 32 and args.metric == "ip") else None,
-                     "kernel": "scan_kernel", "us_per_launch": round(prof["us_scan"], 2),
-                     "bytes_per_launch": round(prof["scan_bytes_per_call"], 1)},
+                     # (up to 1024 clusters the scan of a single query selects them, too)
+                     "kernel": "scan_kernel" if prof["us_select"] > 0 else "scan_kernel with the selection",
+                     "us_per_launch": round(prof["us_scan"], 2), "bytes_per_launch": round(prof["scan_bytes_per_call"], 1)},
         "kernels_us": {k_: round(prof[k_], 2) for k_ in ("us_coarse", "us_select", "us_scan", "us_merge")},
         "nprobe_sweep": sweep,
         "setup": info,

@@ -100,8 +100,8 @@ typedef struct ivf_search_stats {
 typedef struct ivf_profile {
     uint64_t calls;        /* searches measured since ivf_profile_reset() */
     double ms_coarse;      /* summed HIP-event time of the coarse-scoring kernel */
-    double ms_select;      /* ... of the top-nprobe selection kernel */
-    double ms_scan;        /* ... of the list-scan kernel */
+    double ms_select;      /* ... of the top-nprobe selection kernels; none where the scan selects the clusters itself */
+    double ms_scan;        /* ... of the list-scan kernel, with the selection where it does that */
     double ms_merge;       /* ... of the merge / re-score kernel */
     uint64_t scan_bytes;   /* summed list bytes the scan kernels covered */
     uint64_t scan_rows;    /* summed rows the scan kernels covered */
@@ -362,8 +362,8 @@ int ivf_host_scan(const void* lists, const int64_t* offsets, const int64_t* ids,
 int32_t ivf_host_scan_capacity(int32_t k);
 
 /* Kernel timing with HIP events on compute_stream around each kernel of every search while
- * enabled (adds event records to the stream; leave off when timing throughput).  While it is enabled the
- * clusters are selected by a kernel of their own also in single searches whose scan otherwise does it. */
+ * enabled (adds event records to the stream; leave off when timing throughput).  The kernels are those that a
+ * search launches otherwise, too. */
 int ivf_profile_enable(ivf_index* index, int on);
 int ivf_profile_read(ivf_index* index, ivf_profile* out); /* synchronises compute_stream */
 int ivf_profile_reset(ivf_index* index);

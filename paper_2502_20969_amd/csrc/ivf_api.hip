@@ -127,7 +127,8 @@ struct SchedAnswer {
     hipEvent_t e0 = nullptr, e1 = nullptr;
 };
 
-struct ProfSet { hipEvent_t e[8]; };   // begin/end of the coarse, select, scan and merge kernels
+// begin/end of the coarse, select, scan and merge kernels and of a second select kernel; select kernels the search launched
+struct ProfSet { hipEvent_t e[10]; int selects = 0; };
 
 }  // namespace
 
@@ -429,10 +430,13 @@ int drain_profile(ivf_index* ix) {
     if (ix->prof_used == 0) return IVF_OK;
     for (auto& l : ix->lanes) HIP_TRY(hipStreamSynchronize(l.stream));
     for (size_t i = 0; i < ix->prof_used; ++i) {
-        float ms[4];
-        for (int j = 0; j < 4; ++j)
-            HIP_TRY(hipEventElapsedTime(&ms[j], ix->prof_sets[i].e[2 * j], ix->prof_sets[i].e[2 * j + 1]));
-        ix->prof.ms_coarse += ms[0]; ix->prof.ms_select += ms[1];
+        const ProfSet& set = ix->prof_sets[i];
+        float ms[5] = {};
+        for (int j = 0; j < 5; ++j) {
+            if ((j == 1 && set.selects < 1) || (j == 4 && set.selects < 2)) continue;
+            HIP_TRY(hipEventElapsedTime(&ms[j], set.e[2 * j], set.e[2 * j + 1]));
+        }
+        ix->prof.ms_coarse += ms[0]; ix->prof.ms_select += ms[1] + ms[4];
         ix->prof.ms_scan += ms[2]; ix->prof.ms_merge += ms[3];
         ix->prof.calls += 1;
     }
@@ -452,8 +456,11 @@ int prof_events(ivf_index* ix, int which, hipEvent_t* e0, hipEvent_t* e1) {
         int rc = drain_profile(ix);
         if (rc) return rc;
     }
-    *e0 = ix->prof_sets[ix->prof_used].e[2 * which];
-    *e1 = ix->prof_sets[ix->prof_used].e[2 * which + 1];
+    ProfSet& set = ix->prof_sets[ix->prof_used];
+    if (which == 0) set.selects = 0;
+    const int pair = which == 1 && set.selects++ > 0 ? 4 : which;
+    *e0 = set.e[2 * pair];
+    *e1 = set.e[2 * pair + 1];
     if (which == 3) ix->prof_used += 1;
     return IVF_OK;
 }
@@ -482,14 +489,14 @@ int enqueue_coarse(ivf_index* ix, const float* q_dev, int nq) {
 }
 
 // selection from the coarse scores: the probe lists and slot tables in the workspace.  res_off: where the lists are.
-int enqueue_select(ivf_index* ix, int nq, int nprobe, int grid, const int64_t* res_off, unsigned long long* rows_counter, uint32_t* used, bool timed) {
+int enqueue_select(ivf_index* ix, int nq, int nprobe, int grid, const int64_t* res_off, unsigned long long* rows_counter, uint32_t* used) {
     Workspace& w = *ix->cw;
     // the per-workgroup tables of the workspace were sized for w.wg_cap workgroups and w.nq queries
     if ((size_t)grid * nq > w.wg_cap || nq > w.nq)
         return fail(IVF_ESTATE, "workspace holds %zu scan workgroups and %d queries, asked for %d x %d", w.wg_cap, w.nq, grid, nq);
-    hipEvent_t e0 = nullptr, e1 = nullptr;
-    int rc;
-    if (timed && (rc = prof_events(ix, 1, &e0, &e1))) return rc;
+    hipEvent_t e0, e1;
+    int rc = prof_events(ix, 1, &e0, &e1);
+    if (rc) return rc;
     SelectArgs sa{};
     sa.scores = w.d_scores; sa.probe = w.d_probe; sa.off = ix->d_off; sa.res_off = res_off;
     sa.slots = w.slots; sa.sort_keys = w.d_sort_keys; sa.sort_idx = w.d_sort_idx;
@@ -509,13 +516,13 @@ int enqueue_probe(ivf_index* ix, const float* q_dev, int nq, int nprobe, int gri
     int rc = enqueue_coarse(ix, q_dev, nq);
     if (rc || in_scan) return rc;
     return enqueue_select(ix, nq, nprobe, grid, ix->d_res_off, ix->profiling && count_rows ? ix->d_prof_rows : nullptr,
-                          is_search && ix->cache_on ? ix->d_used : nullptr, true);
+                          is_search && ix->cache_on ? ix->d_used : nullptr);
 }
 
 // Whether the scan of a search selects the clusters itself: when all its workgroups are resident at once, so that they do it
-// side by side.  Not while kernels are timed one by one.
+// side by side.
 bool select_in_scan(const ivf_index* ix, int nq, int nprobe, int kprime, int grid, const ScanShape& shape) {
-    return !ix->profiling && scan_selects(shape, ix->nlist, nprobe, kprime) && (int64_t)nq * grid <= ix->resident_grid[0];
+    return scan_selects(shape, ix->nlist, nprobe, kprime) && (int64_t)nq * grid <= ix->resident_grid[0];
 }
 
 int enqueue_scan(ivf_index* ix, const float* q_dev, int nq, int nprobe, int kprime, int grid, const ScanShape& shape, bool in_scan = false) {
@@ -525,6 +532,7 @@ int enqueue_scan(ivf_index* ix, const float* q_dev, int nq, int nprobe, int kpri
         sc.scores = w.d_scores; sc.off = ix->d_off; sc.res_off = ix->d_res_off; sc.nlist = ix->nlist;
         sc.probe = w.d_probe;
         sc.used = ix->cache_on ? ix->d_used : nullptr;
+        sc.rows_counter = ix->profiling ? ix->d_prof_rows : nullptr;
     }
     sc.buf = ix->d_buf; sc.q = q_dev; sc.slots = w.slots;
     sc.part = w.d_part; sc.heads = w.d_heads;
@@ -1388,10 +1396,10 @@ extern "C" int ivf_search(ivf_index* ix, const float* q_out, int32_t nq, int32_t
         // selection takes the places of the lists from the offsets: the table is being replaced.  (Two rounds of four
         // queries x 128 of 1600 lists, 118 MB fetched in the first: 4.62 -> 3.90 ms a pass.)
         if ((rc = enqueue_coarse(ix, w.d_q, nq))) return rc;
-        if ((rc = enqueue_select(ix, nq, nprobe, grid, ix->d_off, nullptr, nullptr, false))) return rc;
+        if ((rc = enqueue_select(ix, nq, nprobe, grid, ix->d_off, nullptr, nullptr))) return rc;
         if ((rc = probe_to_host())) return rc;
         HIP_TRY(hipStreamWaitEvent(ix->cs, ix->ev_pf_done, 0));
-        if ((rc = enqueue_select(ix, nq, nprobe, grid, ix->d_res_off, ix->profiling ? ix->d_prof_rows : nullptr, ix->cache_on ? ix->d_used : nullptr, true))) return rc;
+        if ((rc = enqueue_select(ix, nq, nprobe, grid, ix->d_res_off, ix->profiling ? ix->d_prof_rows : nullptr, ix->cache_on ? ix->d_used : nullptr))) return rc;
     } else {
         if (hybrid && ix->pf_recorded) HIP_TRY(hipStreamWaitEvent(ix->cs, ix->ev_pf_done, 0));
         in_scan = !want_probe && select_in_scan(ix, nq, nprobe, kprime, grid, shape);

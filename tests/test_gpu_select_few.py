@@ -60,3 +60,30 @@ def test_clusters_and_results(nlist, kind, metric):
             assert list(ids[0]) == list(oi) == list(other[0]), (nprobe, b)
             np.testing.assert_array_equal(dists, again)
     index.close()
+
+
+@pytest.mark.parametrize("nlist", [64, 1024, 1025])
+def test_profile_times_the_kernels_that_a_search_launches(nlist):
+    """With up to 1024 clusters the scan of a single query selects, and the time of its selection is the scan's."""
+    rng = np.random.default_rng(nlist)
+    d, per, k, nprobe = 32, 20, 5, 16
+    cent = rng.standard_normal((nlist, d)).astype(np.float32)
+    rows = rng.standard_normal((nlist * per, d)).astype(np.float32)
+    off = np.arange(0, nlist * per + 1, per).astype(np.int64)
+    index = P.ivf_adopt_layout(torch.from_numpy(rows).cuda(), "f32", off, cent, metric=P.IVF_IP, compute_stream=torch.cuda.Stream(),
+                               copy_stream=torch.cuda.Stream())
+    q = torch.from_numpy(rng.standard_normal((1, d)).astype(np.float32)).cuda()
+    ids, dists = torch.empty(1, k, dtype=torch.int64, device="cuda"), torch.empty(1, k, device="cuda")
+    torch.cuda.synchronize()
+    index.ivf_profile_enable(True)
+    index.ivf_profile_reset()
+    for _ in range(3):
+        index.ivf_search_device(q, nprobe, k, ids, dists)
+    p = index.ivf_profile_read()
+    index.ivf_profile_enable(False)
+    assert p.calls == 3 and p.scan_rows == 3 * nprobe * per
+    assert (p.ms_select > 0) == (nlist > 1024)
+    assert min(p.ms_coarse, p.ms_scan, p.ms_merge) > 0
+    oi, _ = O.search(rows, O.F32, off, np.arange(nlist * per, dtype=np.int64), cent, q[0].cpu().numpy(), nprobe, k, O.IP)
+    assert list(ids[0].cpu().numpy()) == list(oi)
+    index.close()
