@@ -519,8 +519,10 @@ int enqueue_probe(ivf_index* ix, const float* q_dev, int nq, int nprobe, int gri
                           is_search && ix->cache_on ? ix->d_used : nullptr);
 }
 
-// Whether the scan of a search selects the clusters itself: when all its workgroups are resident at once, so that they do it
-// side by side.
+// Whether the scan of a search selects the clusters itself: when no more workgroups than are resident at once do it, side by side
+// if the GPU is theirs.  With others in flight they may wait for places; us a search at depths 2 / 4 / 16, in the scan / by a kernel:
+// 25 MB of rows of 512 fp16 (50 of 1000 lists) 21.9 16.3 12.5 / 24.0 18.5 16.2, 32 of 1024 lists, 94 MB of 768 fp32 28.3 23.9 19.4 / 29.3 24.7
+// 20.7, 64 of 1000, 197 MB of 1024 bf16 42.0 39.0 33.7 / 41.5 38.2 33.5: a launch less for the host, 2 % lost where the scan is long.
 bool select_in_scan(const ivf_index* ix, int nq, int nprobe, int kprime, int grid, const ScanShape& shape) {
     return scan_selects(shape, ix->nlist, nprobe, kprime) && (int64_t)nq * grid <= ix->resident_grid[0];
 }
@@ -531,7 +533,6 @@ int enqueue_scan(ivf_index* ix, const float* q_dev, int nq, int nprobe, int kpri
     if (in_scan) {
         sc.scores = w.d_scores; sc.off = ix->d_off; sc.res_off = ix->d_res_off; sc.nlist = ix->nlist;
         sc.probe = w.d_probe;
-        sc.used = ix->cache_on ? ix->d_used : nullptr;
         sc.rows_counter = ix->profiling ? ix->d_prof_rows : nullptr;
     }
     sc.buf = ix->d_buf; sc.q = q_dev; sc.slots = w.slots;

@@ -96,10 +96,10 @@ struct ScanArgs {
     int d, dtype, metric, nprobe, nq, kprime, grid;
     ScanShape shape;
     // Nullable: coarse scores [nq x nlist].  The scan then selects the clusters itself (scan_selects), and its first workgroup
-    // of a query writes what the select kernel would have (slots, probe, used, rows_counter).
+    // of a query writes what the select kernel would have (slots, probe, rows_counter).
     const double* scores;
     const int64_t* off; const int64_t* res_off;
-    int32_t* probe; uint32_t* used; unsigned long long* rows_counter;
+    int32_t* probe; unsigned long long* rows_counter;
     int nlist;
 };
 // whether the scan of this shape can select the clusters itself

@@ -1045,7 +1045,7 @@ struct LaneTable {
         }
     }
     // Every workgroup selects the clusters for itself, from the coarse scores; the first of a query also leaves the tables.
-    // For calls whose workgroups are all resident at once: selecting side by side takes as long as once, and the
+    // When they are all resident at once, selecting side by side takes as long as once, and the
     // launch in between and the way of the tables through memory go (whole search, us, select kernel / here: 8 of 64
     // clusters, 2500 rows of 128 19.0 / 15.4; 32 of 1024, 30,000 rows of 768 33.4 / 32.0).
     __device__ __forceinline__ void select(const ScanArgs& p, int qi) {
@@ -1056,7 +1056,7 @@ struct LaneTable {
         on = true;
         nprobe = p.nprobe;
         end = s.end; grow = s.grow; base = s.base;
-        if (blockIdx.x == 0 && wave_id() == 0) store_slots(s, p.nprobe, qi, p.slots, p.probe, p.used, p.rows_counter);
+        if (blockIdx.x == 0 && wave_id() == 0) store_slots(s, p.nprobe, qi, p.slots, p.probe, nullptr, p.rows_counter);
     }
     __device__ __forceinline__ uint32_t total() const { return read_lane(end, nprobe - 1); }
     // points the cursor at the slot that holds row c.r (c.r below the total)
