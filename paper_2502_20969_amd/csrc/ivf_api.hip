@@ -519,11 +519,20 @@ int enqueue_probe(ivf_index* ix, const float* q_dev, int nq, int nprobe, int gri
                           is_search && ix->cache_on ? ix->d_used : nullptr);
 }
 
+// Bytes of lists that nq queries select in the mean.
+static double mean_list_bytes(const ivf_index* ix, int nq, int nprobe) {
+    return (double)nq * nprobe / ix->nlist * (double)ix->n * (double)ix->row_bytes;
+}
+
 // Whether the scan of a search selects the clusters itself: when no more workgroups than are resident at once do it, side by side
-// if the GPU is theirs.  With others in flight they may wait for places; us a search at depths 2 / 4 / 16, in the scan / by a kernel:
-// 25 MB of rows of 512 fp16 (50 of 1000 lists) 21.9 16.3 12.5 / 24.0 18.5 16.2, 32 of 1024 lists, 94 MB of 768 fp32 28.3 23.9 19.4 / 29.3 24.7
-// 20.7, 64 of 1000, 197 MB of 1024 bf16 42.0 39.0 33.7 / 41.5 38.2 33.5: a launch less for the host, 2 % lost where the scan is long.
+// if the GPU is theirs.  With others in flight their time for it is taken from the other scans, and pays where the launch that it spares
+// the host is what the rate depends on: up to 112 MB of lists, 56 where the merge needs sixteen wavefronts and waits for them.
+// us a search at depths 4 / 6 / 16, in the scan / by a kernel.  Rows of 768 fp32, k 10: 47 MB 17.7 15.2 13.8 / 20.2 17.6 16.3, 94 MB
+// 24.0 20.7 19.4 / 24.8 22.2 20.4, 141 MB 31.6 27.3 26.0 / 30.6 27.1 25.8, 188 MB 38.1 34.2 32.6 / 37.1 33.3 32.2; k 56: 47 MB 22.8 18.7
+// 17.1 / 24.3 20.1 18.1, 94 MB 31.0 25.1 23.6 / 29.8 25.1 23.0, 188 MB 45.2 39.4 37.1 / 41.7 35.8 34.8.  1024 bf16, k 10: 98 MB
+// 24.4 21.2 20.1 / 25.2 22.4 20.8, 147 MB 32.7 28.1 26.9 / 31.8 28.2 26.8.  768 fp16, k 56: 71 MB 29.4 22.8 21.6 / 27.9 22.7 21.0.
 bool select_in_scan(const ivf_index* ix, int nq, int nprobe, int kprime, int grid, const ScanShape& shape) {
+    if (ix->lanes.size() > 1 && mean_list_bytes(ix, nq, nprobe) > (kprime <= 48 ? 112e6 : 56e6)) return false;
     return scan_selects(shape, ix->nlist, nprobe, kprime) && (int64_t)nq * grid <= ix->resident_grid[0];
 }
 
@@ -545,11 +554,6 @@ int enqueue_scan(ivf_index* ix, const float* q_dev, int nq, int nprobe, int kpri
     if (rc) return rc;
     HIP_TRY(launch_scan(sc, ix->cs, e0, e1));
     return IVF_OK;
-}
-
-// Bytes of lists that nq queries select in the mean.
-static double mean_list_bytes(const ivf_index* ix, int nq, int nprobe) {
-    return (double)nq * nprobe / ix->nlist * (double)ix->n * (double)ix->row_bytes;
 }
 
 // Whether the merge of a search takes half the wavefronts, which find room beside resident scans: with other searches in flight, for

@@ -68,3 +68,32 @@ def test_batch_of_large_scans_beside_others():
     s = q.double().cpu() @ rows.double().cpu().T
     s[:, ::40] = s[:, 7:8]                               # the same score, whatever the order of the sums
     assert torch.equal(results[0][0], (-s).argsort(dim=1, stable=True)[:, :k])
+
+
+@pytest.mark.parametrize("k,nprobe", [(10, 28), (10, 64), (56, 8), (56, 28)])
+def test_selection_beside_others(k, nprobe):
+    """Single queries over 22 to 178 MB of lists: with others in flight the scan selects the clusters up to 112 MB (56 for more than 40
+    results), and a kernel of its own above."""
+    nlist, per, d = 64, 1450, 480
+    gen = torch.Generator(device="cuda").manual_seed(nprobe)
+    rows = torch.randn(nlist * per, d, generator=gen, device="cuda")
+    cent = torch.randn(nlist, d, generator=gen, device="cuda")
+    q = torch.randn(9, d, generator=gen, device="cuda")
+    index = P.ivf_adopt_layout(rows, "f32", np.arange(nlist + 1) * per, cent.cpu().numpy(), metric=P.IVF_IP, compute_stream=torch.cuda.Stream(),
+                               copy_stream=torch.cuda.Stream())
+    results = []
+    for depth in (1, 3):
+        index.ivf_set_pipeline_depth(depth)
+        ids, dists = torch.empty(9, k, dtype=torch.int64, device="cuda"), torch.empty(9, k, device="cuda")
+        torch.cuda.synchronize()
+        for b in range(9):
+            index.ivf_search_device(q[b:b + 1], nprobe, k, ids[b:b + 1], dists[b:b + 1])
+        index.ivf_synchronize()
+        results.append((ids.cpu(), dists.cpu()))
+    index.close()
+    assert torch.equal(results[0][0], results[1][0]) and torch.equal(results[0][1], results[1][1])
+    picked = (q.double() @ cent.double().T).topk(nprobe, dim=1).indices
+    for b in range(9):
+        at = (picked[b][:, None] * per + torch.arange(per, device="cuda")).flatten()
+        best = (rows[at].double() @ q[b].double()).topk(k)
+        assert torch.equal(results[0][0][b], at[best.indices].cpu())
