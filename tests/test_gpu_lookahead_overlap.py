@@ -64,6 +64,8 @@ def test_clusters_are_selected_while_the_fetch_waits(nq, cache):
     index.ivf_search(q, nprobe, k)                       # the host's threads are there
     torch.cuda.synchronize()
     gid = np.arange(n, dtype=np.int64)
+    index.ivf_profile_enable(True)
+    index.ivf_profile_reset()
     for turn in range(2):              # a part of what the queries want; then more of it, beside what is there
         with torch.cuda.stream(copy):
             for _ in range(60):                          # 130 GFLOP each
@@ -79,4 +81,6 @@ def test_clusters_are_selected_while_the_fetch_waits(nq, cache):
         if cache:
             index.ivf_cache_end_round()
             torch.cuda.synchronize()
+    p = index.ivf_profile_read()
+    assert p.calls == 2 and min(p.ms_coarse, p.ms_select, p.ms_scan, p.ms_merge) > 0
     index.close()
