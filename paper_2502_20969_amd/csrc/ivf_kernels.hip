@@ -1047,7 +1047,7 @@ struct LaneTable {
     // Every workgroup selects the clusters for itself, from the coarse scores; the first of a query also leaves the tables.
     // When they are all resident at once, selecting side by side takes as long as once, and the
     // launch in between and the way of the tables through memory go (whole search, us, select kernel / here: 8 of 64
-    // clusters, 2500 rows of 128 19.0 / 15.4; 32 of 1024, 30,000 rows of 768 33.4 / 32.0).
+    // clusters, 2500 rows of 128 18.0 / 15.6; 48 of 700, 41,000 of 300 fp16 43.1 / 42.0; 32 of 1024, 30,000 of 768 33.3 / 33.0).
     __device__ __forceinline__ void select(const ScanArgs& p, int qi) {
         extern __shared__ __align__(16) unsigned char smem_raw[];
         FewLds& L = *(FewLds*)smem_raw;
