@@ -1,6 +1,6 @@
 """Compiles the CPU oracle (plain C, gcc) into oracle/liboracle.so.
 
-Test infrastructure: building the checker is not using it."""
+Test infrastructure: building the oracle is not using it."""
 import os
 import subprocess
 

@@ -141,8 +141,9 @@ __device__ __forceinline__ uint32_t read_lane(uint32_t v, int lane) {
     return (uint32_t)__builtin_amdgcn_readlane((int)v, lane);
 }
 
-// Waits until everything this wavefront has stored is behind its L2.  For threads whose stores another thread of the workgroup
-// publishes: __syncthreads() waits for LDS only, and a fence for the stores of the wavefront that executes it.
+// Waits until everything this wavefront has stored is in its L2 (atomic stores of agent or system scope: behind it).  For threads whose
+// stores another thread of the workgroup publishes: __syncthreads() waits for LDS only; the publisher's fence writes the L2 back, but
+// waits for the stores of the wavefront that executes it alone.
 __device__ __forceinline__ void wait_for_stores() { asm volatile("s_waitcnt vmcnt(0)" ::: "memory"); }
 
 // ---- stored element types -------------------------------------------------------------------
